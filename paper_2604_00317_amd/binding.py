@@ -37,6 +37,7 @@ EXPORTS = [
     "nimble_plan_solve_static", "nimble_static_scratch_bytes", "nimble_debug_barrier_probe",
     "nimble_topo_reserve_batch", "nimble_debug_fail_allocation",
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
+    "nimble_host_patch_check",
 ]
 
 _lib = None
@@ -124,6 +125,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
                                                vp]
     lib.nimble_plan_quantize.restype = ctypes.c_int
     lib.nimble_plan_quantize.argtypes = [vp, vp, vp, i32, ctypes.c_int64, ctypes.c_double, vp, vp]
+    lib.nimble_host_patch_check.restype = ctypes.c_int
+    lib.nimble_host_patch_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, vp]
     lib.nimble_host_layout_stats.restype = ctypes.c_int
     lib.nimble_host_layout_stats.argtypes = [i32, i32, vp, i32, vp, vp, vp]
     for name in ("nimble_host_build_reverse", "nimble_host_build_reverse_streaming"):
@@ -423,6 +426,23 @@ def nimble_host_layout_stats(n_links, n_comm, comm_path_ptr, n_paths, path_link_
             "pieces_uniform", "strip_items", "strip_rows", "records_lane_major", "records_dict",
             "record_bodies", "group_blocks", "group_block_max_slots", "group_block_max_tasks",
             "record_bodies_product"]
+    return dict(zip(keys, (int(v) for v in out)))
+
+
+def nimble_host_patch_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_ptr, path_links,
+                            strips, lanes=0):
+    """Host-only: builds and checks the patch layout of a strips x strips grid; dict of its sizes
+    (see include/nimble_plan_debug.h), `failed` is the number of the check that failed."""
+    cp = _host(comm_path_ptr, np.int32)
+    lp = _host(path_link_ptr, np.int32)
+    pl = _host(path_links, np.int32)
+    out = np.zeros(12, dtype=np.int64)
+    st = load_library().nimble_host_patch_check(n_links, n_comm, _hp(cp), n_paths, _hp(lp), _hp(pl),
+                                                strips, lanes, _hp(out))
+    if st != NIMBLE_OK:
+        raise NimbleError(st, "invalid CSR")
+    keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "rounds", "threads",
+            "max_local", "max_groups", "max_users", "max_parts", "parts"]
     return dict(zip(keys, (int(v) for v in out)))
 
 

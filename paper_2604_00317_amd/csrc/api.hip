@@ -128,6 +128,7 @@ struct nimble_topo {
     bool ad_ready = false;
     int64_t ad_sigma_rows = 0;
     void *sync_words = nullptr; // barrier counter and reductions of the persistent kernel
+    std::vector<nimble::DevicePatches> patches;   // layouts of the patch kernels (may be none)
     // per-plan state: state_plans blocks of d.state_stride bytes in one allocation; the state
     // pointers of `d` are those of block 0
     unsigned char *state = nullptr;
@@ -293,6 +294,125 @@ hipError_t ensure_state_plans(nimble_topo *t, int32_t plans)
     return hipSuccess;
 }
 
+// ---- patch layouts --------------------------------------------------------------------------
+
+hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::DevicePatches &p)
+{
+    p.shape = l.shape;
+    p.n_comm_slots = l.n_comm_slots;
+    p.max_local = l.max_local;
+    p.max_groups = l.max_groups;
+    p.max_parts = l.max_parts;
+    p.n_parts = l.n_parts;
+    p.max_teams = 1 << 30;
+    p.parts = nullptr;
+    p.maxima = nullptr;
+    p.abort_word = nullptr;
+    p.iteration_us = nimble::patch_scan_us(l.shape) +
+                     nimble::patch_exchange_us(l.n_patches, l.max_parts);
+    hipError_t e = upload(t, l.desc.data(), l.desc.size(), &p.desc);
+    if (e == hipSuccess) e = upload(t, l.loc_link.data(), l.loc_link.size(), &p.loc_link);
+    if (e == hipSuccess) e = upload(t, l.comm.data(), l.comm.size(), &p.comm);
+    if (e == hipSuccess) e = upload(t, l.group.data(), l.group.size(), &p.group);
+    if (e == hipSuccess) e = upload(t, l.words.data(), l.words.size(), &p.words);
+    if (e == hipSuccess) e = upload(t, l.first.data(), l.first.size(), &p.first);
+    if (e == hipSuccess && l.n_patches > 1) {
+        p.max_teams = t->n_cu / l.n_patches;
+        e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_parts, &p.parts);
+        if (e == hipSuccess)
+            e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_patches, &p.maxima);
+        if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
+    }
+    p.n_patches = e == hipSuccess ? l.n_patches : 0;
+    return e;
+}
+
+// Builds the patch layouts of a fabric: the one with the fewest patches, which solves the most
+// plans side by side, and the one whose estimate is lowest for a single plan, if that is another.
+hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, const int32_t *pl)
+{
+    const nimble::DeviceTopo &d = t->d;
+    const char *env = std::getenv("NIMBLE_TUNE_PATCH_STRIPS");
+    const char *env_lanes = std::getenv("NIMBLE_TUNE_PATCH_LANES");
+    const int32_t forced = env ? std::atoi(env) : -1, lanes = env_lanes ? std::atoi(env_lanes) : 0;
+    if (forced == 0 || d.resident_generic) return hipSuccess;
+    nimble::PatchScan scan;
+    nimble::scan_patches(d.E, d.K, cp, lp, pl, scan);
+    if (!scan.fits) return hipSuccess;
+    nimble::PatchLayout built[2];
+    int32_t n_built = 0, best_strips = 0;
+    double best_us = 0.0;
+    int32_t parts = 0;            // of the layout with the fewest patches: about the same for all
+    for (int32_t strips = 1; strips * strips <= t->n_cu; ++strips) {
+        if (forced > 0 && strips != forced) continue;
+        // (a lane holds at most four commodities: most grids are ruled out by their size alone)
+        if (d.K > static_cast<int64_t>(strips) * strips * nimble::kPatchThreads * 4) continue;
+        nimble::PatchCut cut;
+        nimble::PatchShape shape;
+        nimble::cut_patches(d.K, scan, strips, cut);
+        if (!nimble::patch_shape(scan, cut.most, lanes, shape)) continue;
+        if (n_built == 0) {
+            if (!nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, shape, built[0])) continue;
+            n_built = 1;
+            parts = built[0].max_parts;
+        }
+        const int64_t n = strips == 1 ? 1 : static_cast<int64_t>(strips) * strips;
+        const double us = nimble::patch_scan_us(shape) + nimble::patch_exchange_us(n, parts);
+        if (best_strips == 0 || us < best_us) {
+            best_us = us;
+            best_strips = strips;
+        }
+    }
+    if (n_built == 0) return hipSuccess;
+    {
+        nimble::PatchCut cut;
+        nimble::PatchShape shape;
+        nimble::cut_patches(d.K, scan, best_strips, cut);
+        if (static_cast<int32_t>(cut.members.size()) != built[0].n_patches &&
+            nimble::patch_shape(scan, cut.most, lanes, shape) &&
+            nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, shape, built[1]))
+            n_built = 2;
+    }
+    for (int32_t i = n_built - 1; i >= 0; --i) {
+        nimble::DevicePatches p;
+        const hipError_t e = upload_patches(t, built[i], p);
+        if (e != hipSuccess) return e;
+        if (nimble::patch_blocks_per_cu(p, d.cost_max) >= 1) t->patches.push_back(p);
+    }
+    return hipSuccess;
+}
+
+// The layout for `plans` plans on stream `s`, or null: no layout fits the fabric, more
+// iterations than the kernels count, or a stream under capture (a cooperative launch cannot be
+// recorded everywhere; the streaming regime can).
+const nimble::DevicePatches *pick_patches(const nimble_topo *t, int32_t plans, int32_t iters,
+                                          hipStream_t s, bool single_only = false)
+{
+    if (iters > nimble::kPatchMaxIters) return nullptr;
+    const nimble::DevicePatches *best = nullptr;
+    double best_us = 0.0;
+    for (const nimble::DevicePatches &p : t->patches) {
+        if (single_only && p.n_patches > 1) continue;
+        const int32_t at_once = p.n_patches > 1 ? p.max_teams : t->n_cu;
+        const double us = p.iteration_us * ((plans + at_once - 1) / at_once);
+        if (best == nullptr || us < best_us) {
+            best = &p;
+            best_us = us;
+        }
+    }
+    if (best != nullptr && best->n_patches > 1) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+        if (cap != hipStreamCaptureStatusNone) return nullptr;
+    }
+    return best;
+}
+
+// Solves with the patch kernels when regime and fabric allow it; `done` says whether it did.
+nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_traffic, double eps,
+                              int32_t iters, double *d_len, double *d_splits, double *d_lambda,
+                              hipStream_t s, bool &done);
+
 nimble_status_t check_solve_args(const nimble_topo *topo, const double *d_traffic, double eps,
                                  int32_t iters, const double *d_splits, const double *d_lambda)
 {
@@ -376,6 +496,27 @@ uint8_t *own_log(const nimble_topo *topo, int32_t iters, int32_t plans = 1)
 {
     return (!topo->no_choice_log &&
             topo->log_rows >= static_cast<int64_t>(iters) * plans) ? topo->choice_log : nullptr;
+}
+
+nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_traffic, double eps,
+                              int32_t iters, double *d_len, double *d_splits, double *d_lambda,
+                              hipStream_t s, bool &done)
+{
+    done = false;
+    if (topo->forced_regime != NIMBLE_REGIME_AUTO && topo->forced_regime != NIMBLE_REGIME_RESIDENT)
+        return NIMBLE_OK;
+    // (lists of a single node: a thread per commodity and link with everything in registers)
+    if (d_len == nullptr && nimble::resident_in_registers(topo->d)) return NIMBLE_OK;
+    const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s,
+                                                  topo->forced_regime == NIMBLE_REGIME_RESIDENT);
+    if (p == nullptr) return NIMBLE_OK;
+    const hipError_t e =
+        nimble::launch_patches(topo->d, *p, plans, d_traffic, d_len, d_len, eps, iters,
+                               topo->spin_limit, d_splits, d_lambda, s);
+    if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
+    topo->last_regime = p->n_patches > 1 ? NIMBLE_REGIME_PERSISTENT : NIMBLE_REGIME_RESIDENT;
+    done = true;
+    return NIMBLE_OK;
 }
 
 nimble_status_t solve_persistent(nimble_topo *topo, const double *d_traffic, double eps,
@@ -644,6 +785,7 @@ nimble_status_t nimble_topo_create(int32_t n_links, const double *cap, int32_t n
                    "record bodies");
     }
 
+    NIMBLE_TRY(make_patches(t, comm_path_ptr, path_link_ptr, path_links), "patch layouts");
     {
         // the address of the static scratch on this device (nimble_plan_solve_static)
         unsigned char *sp = nullptr;
@@ -769,6 +911,9 @@ nimble_status_t nimble_plan_solve(nimble_topo_t *topo, const double *d_traffic, 
     st = check_device(topo);
     if (st != NIMBLE_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    bool done = false;
+    st = solve_patches(topo, 1, d_traffic, eps, iters, nullptr, d_splits, d_lambda, s, done);
+    if (st != NIMBLE_OK || done) return st;
     const int32_t regime = pick_regime(topo, 1);
     topo->last_regime = regime;
     if (regime == NIMBLE_REGIME_RESIDENT) {
@@ -794,6 +939,9 @@ nimble_status_t nimble_plan_solve_batch(nimble_topo_t *topo, int32_t batch,
     st = check_device(topo);
     if (st != NIMBLE_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    bool done = false;
+    st = solve_patches(topo, batch, d_traffic, eps, iters, nullptr, d_splits, d_lambda, s, done);
+    if (st != NIMBLE_OK || done) return st;
     const int32_t regime = pick_regime(topo, batch);
     topo->last_regime = regime;
     if (regime == NIMBLE_REGIME_RESIDENT) {
@@ -953,9 +1101,12 @@ nimble_status_t nimble_plan_solve_warm(nimble_topo_t *topo, const double *d_traf
     if (!d_len) return fail(NIMBLE_ERR_INVALID, "the length pointer must not be NULL");
     st = check_device(topo);
     if (st != NIMBLE_OK) return st;
-    topo->last_regime = NIMBLE_REGIME_STREAM;
-    return solve_stream(topo, d_traffic, eps, iters, d_splits, d_lambda,
-                        static_cast<hipStream_t>(hip_stream), own_log(topo, iters),
+    hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    bool done = false;
+    st = solve_patches(topo, 1, d_traffic, eps, iters, d_len, d_splits, d_lambda, s, done);
+    topo->last_regime = NIMBLE_REGIME_STREAM;      // (what a warm start reports, whatever ran)
+    if (st != NIMBLE_OK || done) return st;
+    return solve_stream(topo, d_traffic, eps, iters, d_splits, d_lambda, s, own_log(topo, iters),
                         topo->log_stride, d_len);
 }
 

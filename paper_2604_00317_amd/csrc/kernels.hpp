@@ -4,7 +4,42 @@
 
 #include <cstdint>
 
+#include "host_patch.hpp"
+
 namespace nimble {
+
+// One patch layout on the device (host_patch.hpp) with the exchange buffers of its teams, and
+// the arguments of a launch of the patch kernels (patch_kernel.hpp).
+struct DevicePatches {
+    PatchShape shape;
+    int32_t n_patches = 0;       // 0: no such layout
+    int32_t n_comm_slots, max_local, max_groups, max_parts;
+    int64_t n_parts;
+    int32_t max_teams;           // plans whose patches are resident at once
+    const int32_t *desc, *loc_link, *comm, *group;
+    const uint32_t *words, *first;
+    double *parts;               // [max_teams][2][n_parts]
+    double *maxima;              // [max_teams][2][n_patches]
+    uint32_t *abort_word;
+    double iteration_us;         // estimate of one iteration of max_teams plans
+};
+
+struct PatchArgs {
+    const int32_t *desc, *loc_link, *comm, *group;
+    const uint32_t *words, *first;
+    const int32_t *comm_ptr;
+    const double *invcap;        // by link id
+    const double *demand;        // [plans * K]
+    const double *len_in;        // lengths to start from, by link id (null: all 1)
+    double *len_out;             // receives the lengths by link id (null: nobody wants them)
+    double *splits, *lambda;
+    double *parts, *maxima;
+    uint32_t *abort_word;
+    int64_t n_parts;
+    int32_t K, P, n_patches, n_comm_slots, plans, teams, iters;
+    uint32_t spin_limit;
+    double eps;
+};
 
 // Device-side view of one topology plus the workspace of one solve.
 // One step of the adaptive solve (sigma = 1 / max u; S += sigma u; len *= 1 + eps sigma u; the
@@ -187,6 +222,16 @@ int resident_kernel_kind(const DeviceTopo &t, int batch);
 double resident_iteration_us(const DeviceTopo &t, int batch);
 hipError_t launch_resident(const DeviceTopo &t, int32_t batch, const double *demand, double eps,
                            int32_t iters, double *splits, double *lambda, hipStream_t s);
+
+// ---- patch kernels: one kernel per solve, a workgroup per patch of the fabric -----------------
+size_t patch_lds_bytes(const DevicePatches &p);      // of the largest patch
+// workgroups of the kernel a compute unit holds at once (0: it cannot run)
+int patch_blocks_per_cu(const DevicePatches &p, bool cost_max);
+constexpr int32_t kPatchMaxIters = 65535;      // choices are counted in 16 bits
+hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t plans,
+                          const double *demand, const double *len_in, double *len_out, double eps,
+                          int32_t iters, uint32_t spin_limit, double *splits, double *lambda,
+                          hipStream_t s);
 
 // ---- persistent regime: one kernel per solve, grid barriers between the phases -------------
 // `sync_words` is device memory of persistent_sync_bytes() bytes owned by the topology.

@@ -1,0 +1,121 @@
+"""The patch layout (commodities cut into patches, one workgroup each) and its kernels: the layout
+reads back to the CSR on the CPU, and on the GPU every shape -- slots of either form, one to four
+lanes per commodity, one patch and several -- gives the oracle's plans."""
+import numpy as np
+import pytest
+
+from paper_2604_00317_amd import binding as B
+from paper_2604_00317_amd import workloads as W
+
+
+def fabric(nodes, gpus, rails):
+    if nodes == 1:
+        return W.build_fabric(1, gpus)
+    if rails == "pair":
+        return W.build_fabric(nodes, gpus, gpus // 2, W.pair_access(gpus // 2))
+    if rails == "xor":
+        return W.build_fabric(nodes, gpus, gpus, W.xor_access(gpus))
+    return W.build_fabric(nodes, gpus, gpus, [[r] for r in range(gpus)])
+
+
+FABRICS = [(1, 4, "none"), (2, 8, "pair"), (2, 5, "own"), (3, 4, "xor"), (7, 6, "pair"),
+           (4, 8, "own"), (3, 8, "xor")]
+RANDOM = [(1, 7, 3, 4, 3), (2, 40, 130, 9, 5), (3, 64, 65, 30, 4), (4, 1, 5, 1, 1),
+          (5, 500, 1500, 12, 2)]
+
+
+def _random(seed, E, K, pm, lm):
+    return W.random_topology(np.random.default_rng(seed), E, K, pm, lm)
+
+
+@pytest.mark.parametrize("lanes", [0, 1, 2, 4])
+@pytest.mark.parametrize("strips", [1, 2, 3])
+def test_layout_reads_back(strips, lanes):
+    built = 0
+    for t in [fabric(*f) for f in FABRICS] + [_random(*r) for r in RANDOM]:
+        s = B.nimble_host_patch_check(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths,
+                                      t.path_link_ptr, t.path_links, strips, lanes)
+        assert s["failed"] == 0, (t.n_comm, s)
+        built += s["patches"] > 0
+    assert built >= 6
+    # more candidates than slots hold, and paths of more than five links
+    for t in (_random(6, 50, 40, 127, 2), _random(7, 60, 40, 5, 9)):
+        assert np.diff(t.comm_path_ptr).max() > 32 or np.diff(t.path_link_ptr).max() > 5
+        assert B.nimble_host_patch_check(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths,
+                                         t.path_link_ptr, t.path_links, 1)["patches"] == 0
+
+
+def _solve(t, d, eps, iters, flags):
+    h = B.nimble_topo_create(*t.csr(), flags=flags)
+    try:
+        out = B.plan(h, d, eps, iters)
+        return out[0], out[1], h.regime
+    finally:
+        h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("strips,lanes", [(1, 1), (1, 2), (1, 4), (2, 1), (2, 4), (3, 0), (3, 2)])
+def test_patch_kernels_match_the_oracle(monkeypatch, strips, lanes, flags):
+    """Byte counts: the same bits as the oracle, whatever the cut; more iterations than 8-bit
+    counters hold; a batch with a plan of no traffic."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_LANES", str(lanes))
+    cases = [(f, fabric(*f)) for f in FABRICS[1:]] + [(r, _random(*r)) for r in RANDOM]
+    for name, t in cases:
+        rng = np.random.default_rng(5)
+        d = np.floor(rng.pareto(1.1, (3, t.n_comm)) * 1e6)
+        d[:, rng.integers(0, t.n_comm, 3)] = 0.0
+        d[2] = 0.0
+        print(f"[patch] {name} strips={strips} lanes={lanes} flags={flags}", flush=True)
+        iters = 300 if t.n_comm < 300 else 40
+        splits, lam, _ = _solve(t, d, 0.05, iters, flags)
+        for b in range(3):
+            ref = oracle.solve(*t.csr(), d[b], 0.05, iters, flags=flags)
+            assert np.array_equal(splits[b], ref["splits"]), (name, b)
+            assert lam[b] == ref["lam"], (name, b)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("strips", [1, 3])
+def test_fractional_demands_are_deterministic(monkeypatch, strips):
+    """Demands on no common grid: the loads are summed as integers (one rounding at the end), so
+    two runs agree bit for bit; the oracle's sequential sums differ from them by at most one
+    rounding per addition, K * 2^-53 relative, which may turn a tie but moves lambda by less than
+    a commodity's choice in one of the iterations does."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    for f in FABRICS[1:5]:
+        t = fabric(*f)
+        rng = np.random.default_rng(8)
+        d = np.floor(rng.pareto(1.1, t.n_comm) * 1e6) * (1.0 + rng.random(t.n_comm))
+        print(f"[patch] fractional {f} strips={strips}", flush=True)
+        a = _solve(t, d, 0.05, 60, 0)
+        b = _solve(t, d, 0.05, 60, 0)
+        assert np.array_equal(a[0], b[0]) and a[1] == b[1]
+        ref = oracle.solve(*t.csr(), d, 0.05, 60)
+        assert abs(a[1] - ref["lam"]) <= 1e-6 * ref["lam"]
+        assert np.mean(a[0] != ref["splits"]) < 0.05
+
+
+@pytest.mark.gpu
+def test_a_team_that_cannot_meet_gives_up(monkeypatch):
+    """A poll limit of zero: patches that have to wait for each other abandon the solve, lambda is
+    NaN (or right, where nobody had to wait), and the topology works again afterwards."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "3")
+    t = fabric(7, 6, "pair")
+    d = np.floor(np.random.default_rng(9).pareto(1.1, t.n_comm) * 1e6)
+    ref = oracle.solve(*t.csr(), d, 0.05, 30)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        B.nimble_debug_set_spin_limit(h, 0)
+        _, lam = B.plan(h, d, 0.05, 30)
+        assert np.isnan(lam) or lam == ref["lam"]
+        B.nimble_debug_set_spin_limit(h, 1 << 22)
+        splits, lam = B.plan(h, d, 0.05, 30)
+        assert lam == ref["lam"] and np.array_equal(splits, ref["splits"])
+    finally:
+        h.close()
