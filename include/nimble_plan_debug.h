@@ -183,10 +183,10 @@ nimble_status_t nimble_host_resident_kernel(int32_t n_links, int32_t n_comm,
  * Host-only helper (no device call): builds the patch layout of a grid of strips x strips patches
  * (1..64), with `lanes` lanes per commodity (0: the library's choice), and checks it: every candidate reads back from the slots link by link,
  * every part of the exchange has one writer, every link in use one patch that reports it.
- * out[12]: patches (0: the fabric or the grid does not suit the patch kernels), the number of
+ * out[11]: patches (0: the fabric or the grid does not suit the patch kernels), the number of
  * the check that failed (0: none), 1 for product slots, lanes per commodity, slots per lane,
- * rounds, threads, most local links of a patch, most groups, most users of a group, most parts a
- * patch reads / 8, doubles of one exchange buffer.
+ * threads, most local links of a patch, most groups, most users of a group, most parts (eight
+ * doubles each) a patch reads, doubles of one exchange buffer.
  */
 nimble_status_t nimble_host_patch_check(int32_t n_links, int32_t n_comm,
                                         const int32_t *comm_path_ptr, int32_t n_paths,

@@ -441,7 +441,7 @@ def nimble_host_patch_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_p
                                                 strips, lanes, _hp(out))
     if st != NIMBLE_OK:
         raise NimbleError(st, "invalid CSR")
-    keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "rounds", "threads",
+    keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "threads",
             "max_local", "max_groups", "max_users", "max_parts", "parts"]
     return dict(zip(keys, (int(v) for v in out)))
 

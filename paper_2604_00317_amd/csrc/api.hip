@@ -299,7 +299,7 @@ hipError_t ensure_state_plans(nimble_topo *t, int32_t plans)
 hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::DevicePatches &p)
 {
     p.shape = l.shape;
-    p.n_comm_slots = l.n_comm_slots;
+    p.max_comm = l.max_comm;
     p.max_local = l.max_local;
     p.max_groups = l.max_groups;
     p.max_parts = l.max_parts;
@@ -345,8 +345,8 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
     int32_t parts = 0;            // of the layout with the fewest patches: about the same for all
     for (int32_t strips = 1; strips * strips <= t->n_cu; ++strips) {
         if (forced > 0 && strips != forced) continue;
-        // (a lane holds at most four commodities: most grids are ruled out by their size alone)
-        if (d.K > static_cast<int64_t>(strips) * strips * nimble::kPatchThreads * 4) continue;
+        // (most grids are ruled out by their size alone)
+        if (d.K > static_cast<int64_t>(strips) * strips * nimble::kPatchThreads) continue;
         nimble::PatchCut cut;
         nimble::PatchShape shape;
         nimble::cut_patches(d.K, scan, strips, cut);

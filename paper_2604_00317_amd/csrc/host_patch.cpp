@@ -162,6 +162,9 @@ int32_t slots_of(int32_t n_cand, int32_t p0, const int32_t *path_link_ptr,
     return n;
 }
 
+// the parts of a group are read eight users at a time
+int32_t padded_parts(int32_t users) { return (users + 7) / 8 * 8; }
+
 template <typename F>
 void parallel_ranges(int64_t n, F f, int64_t grain = 1)
 {
@@ -198,11 +201,11 @@ void scan_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int3
         int32_t m[2] = {0, 0};
         for (int64_t k = k0; k < k1; ++k) {
             const int32_t n = cp[k + 1] - cp[k];
-            const int32_t a = slots_of(n, cp[k], lp, pl, true, tmp), b = (n + 3) / 4;
-            s[0] += a;
-            s[1] += b;
-            m[0] = std::max(m[0], a);
-            m[1] = std::max(m[1], b);
+            const int32_t ns[2] = {slots_of(n, cp[k], lp, pl, true, tmp), (n + 3) / 4};
+            for (int32_t form = 0; form < 2; ++form) {
+                s[form] += ns[form];
+                m[form] = std::max(m[form], ns[form]);
+            }
             int32_t first = INT32_MAX, last = INT32_MAX;
             for (int32_t p = cp[k]; p < cp[k + 1]; ++p) {
                 first = std::min(first, pl[lp[p]]);
@@ -320,10 +323,9 @@ double patch_scan_us(const PatchShape &s)
     // cycles the LDS is busy (four per price read of a wave, more per atomic the more lanes add)
     // and cycles of vector issue; a wave's own chain of reads and additions on top
     const double waves = s.threads / 64.0;
-    const double reads = s.quads * (s.product ? 36.0 : 80.0);
-    const double lds = s.rounds * waves * (reads + (s.lanes == 1 ? 130.0 : s.lanes == 2 ? 95.0 : 70.0));
-    const double valu = s.rounds * waves * (s.quads * (s.product ? 36.0 : 50.0) + (s.lanes > 1 ? 60.0 : 40.0));
-    return 0.3 + 0.06 * s.quads * s.rounds + std::max(lds, valu) / 2400.0;
+    const double lds = waves * (s.quads * (s.product ? 36.0 : 80.0) + 50.0 + 80.0 / s.lanes);
+    const double valu = waves * (s.quads * (s.product ? 28.0 : 50.0) + (s.lanes > 1 ? 85.0 : 70.0));
+    return 0.3 + 0.06 * s.quads + std::max(lds, valu) / 2400.0;
 }
 
 double patch_exchange_us(int64_t patches, int32_t parts)
@@ -338,31 +340,26 @@ bool patch_shape(const PatchScan &scan, int64_t most, int32_t lanes, PatchShape 
 {
     out = PatchShape();
     double best = 0.0;
-    auto offer = [&](int32_t product, int32_t L, int32_t QL, int32_t R) {
+    auto offer = [&](int32_t product, int32_t L, int32_t QL) {
         if (product != scan.product || (lanes > 0 && L != lanes)) return;
         if (L * QL < scan.slots || (L > 1 && L * (QL - 1) >= scan.slots)) return;
-        const int64_t per = (most + R - 1) / R;
-        if (per * L > kPatchThreads) return;
+        if (most * L > kPatchThreads) return;
         PatchShape s;
         s.product = product;
         s.lanes = L;
         s.quads = QL;
-        s.rounds = R;
-        s.threads = static_cast<int32_t>((per * L + 63) / 64 * 64);
+        s.threads = static_cast<int32_t>((most * L + 63) / 64 * 64);
         const double us = patch_scan_us(s);
         if (out.threads == 0 || us < best) {
             best = us;
             out = s;
         }
     };
-#define NIMBLE_PATCH_OFFER(PR, LL, QQ, RR) offer(PR, LL, QQ, RR);
+#define NIMBLE_PATCH_OFFER(PR, LL, QQ) offer(PR, LL, QQ);
     NIMBLE_PATCH_SHAPES(NIMBLE_PATCH_OFFER)
 #undef NIMBLE_PATCH_OFFER
     return out.threads > 0;
 }
-
-// the parts of a group are read eight users at a time
-static int32_t padded_parts(int32_t users) { return (users + 7) / 8 * 8; }
 
 bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int32_t *lp,
                    const int32_t *pl, const PatchScan &scan, PatchCut &cut,
@@ -371,12 +368,11 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
     out = PatchLayout();
     out.shape = shape;
     const bool product = shape.product != 0;
-    const int32_t L = shape.lanes, QL = shape.quads, R = shape.rounds, NT = shape.threads;
-    const int32_t QT = R * QL;
+    const int32_t L = shape.lanes, QL = shape.quads, NT = shape.threads;
     const int32_t NW = product ? kPatchWordsProduct : kPatchWordsPlain;
     std::vector<std::vector<int32_t>> &members = cut.members;
     const int32_t B = static_cast<int32_t>(members.size());
-    out.n_comm_slots = R * (NT / L);
+    if (cut.most * L > NT) return false;
     // Lanes that work side by side should hold commodities of different sources and different
     // destinations: their loads then fall on different links.  So a patch's commodities are taken
     // diagonal by diagonal of its source x destination table.
@@ -453,6 +449,7 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
     // local numbering: the groups (padded), then the private links
     out.desc.assign(static_cast<size_t>(kPatchDescInts) * B, 0);
     std::vector<int32_t> first_local(B + 1, 0), first_group(B + 1, 0);
+    std::vector<int32_t> first_comm(B + 1, 0);
     for (int32_t b = 0; b < B; ++b) {
         int32_t n_private = 0, parts = 0;
         for (int32_t e : links[b]) n_private += users[e].size() == 1 ? 1 : 0;
@@ -471,13 +468,16 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
         d[2] = ng * kPatchGroup;
         d[3] = first_group[b];
         d[4] = ng;
-        d[5] = static_cast<int32_t>(members[b].size());
+        d[5] = first_comm[b];
+        d[6] = static_cast<int32_t>(members[b].size());
+        first_comm[b + 1] = first_comm[b] + d[6];
+        out.max_comm = std::max(out.max_comm, d[6]);
     }
     out.loc_link.assign(first_local[B], -1);
     out.group.assign(static_cast<size_t>(4) * first_group[B], 0);
-    out.comm.assign(static_cast<size_t>(B) * out.n_comm_slots, -1);
-    out.words.assign(static_cast<size_t>(B) * QT * NW * NT, 0u);
-    out.first.assign(static_cast<size_t>(B) * QT * NT, 0u);
+    out.comm.assign(n_comm, -1);
+    out.words.assign(static_cast<size_t>(B) * QL * NW * NT, 0u);
+    out.first.assign(static_cast<size_t>(B) * QL * NT, 0u);
     parallel_ranges(B, [&](int64_t b0, int64_t b1) {
         std::vector<int32_t> local(n_links, 0), seen(n_links, -1);
         Slot slot[32];
@@ -507,59 +507,54 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
             auto offset = [&](int32_t e) -> uint32_t {
                 return e == kZero ? zero : e == kInf ? inf : 8u * static_cast<uint32_t>(local[e]);
             };
-            const int32_t group_lanes = NT / L;
-            uint32_t *words = &out.words[static_cast<size_t>(b) * QT * NW * NT];
-            uint32_t *first = &out.first[static_cast<size_t>(b) * QT * NT];
-            for (int32_t r = 0; r < R; ++r)
-                for (int32_t g = 0; g < group_lanes; ++g) {
-                    const size_t ci = static_cast<size_t>(r) * group_lanes + g;
-                    const int32_t k = ci < members[b].size() ? members[b][ci] : -1;
-                    out.comm[static_cast<size_t>(b) * out.n_comm_slots + ci] = k;
-                    const int32_t n =
-                        k < 0 ? 0 : slots_of(cp[k + 1] - cp[k], cp[k], lp, pl, product, slot);
-                    // lane j of the commodity scans the slots j, j + L: candidates ascend
-                    for (int32_t q = 0; q < QL; ++q)
-                        for (int32_t j = 0; j < L; ++j) {
-                            const int32_t si = q * L + j;
-                            const size_t t = static_cast<size_t>(g) * L + j;
-                            const size_t sl = static_cast<size_t>(r) * QL + q;
-                            uint32_t o[20];
-                            uint32_t meta = 0u, once = 0u;
-                            const int32_t n_off = product ? 9 : 20;
-                            if (si < n) {
-                                const Slot &s = slot[si];
-                                meta = static_cast<uint32_t>(s.base | s.shift << 7 | s.n << 9);
-                                for (int32_t x = 0; x < n_off; ++x) {
-                                    o[x] = offset(s.at[x]);
-                                    if (s.at[x] >= 0 && seen[s.at[x]] != k) {
-                                        seen[s.at[x]] = k;
-                                        once |= 1u << x;
-                                    }
+            uint32_t *words = &out.words[static_cast<size_t>(b) * QL * NW * NT];
+            uint32_t *first = &out.first[static_cast<size_t>(b) * QL * NT];
+            std::copy(members[b].begin(), members[b].end(), out.comm.begin() + first_comm[b]);
+            for (int32_t g = 0; g < NT / L; ++g) {
+                const int32_t k =
+                    g < static_cast<int32_t>(members[b].size()) ? members[b][g] : -1;
+                const int32_t n =
+                    k < 0 ? 0 : slots_of(cp[k + 1] - cp[k], cp[k], lp, pl, product, slot);
+                // lane j scans the slots j, j + L, ...: candidates ascend
+                for (int32_t q = 0; q < QL; ++q)
+                    for (int32_t j = 0; j < L; ++j) {
+                        const int32_t si = q * L + j;
+                        const size_t t = static_cast<size_t>(g) * L + j;
+                        uint32_t o[20], meta = 0u, once = 0u;
+                        const int32_t n_off = product ? 9 : 20;
+                        for (int32_t x = 0; x < n_off; ++x) o[x] = inf;
+                        if (si < n) {
+                            const Slot &s = slot[si];
+                            meta = static_cast<uint32_t>(s.base | s.shift << 7 | s.n << 9);
+                            for (int32_t x = 0; x < n_off; ++x) {
+                                o[x] = offset(s.at[x]);
+                                if (s.at[x] >= 0 && seen[s.at[x]] != k) {
+                                    seen[s.at[x]] = k;
+                                    once |= 1u << x;
                                 }
-                            } else {
-                                for (int32_t x = 0; x < n_off; ++x) o[x] = inf;
                             }
-                            uint32_t w[kPatchWordsPlain];
-                            if (product) {
-                                w[0] = o[A0] | o[A2] << 16;
-                                w[1] = o[B0] | o[B2] << 16;
-                                w[2] = o[C] | meta << 16;
-                                w[3] = o[D0] | o[D1] << 16;
-                                w[4] = o[E0] | o[E1] << 16;
-                            } else {
-                                for (int32_t c = 0; c < 4; ++c) {
-                                    w[2 * c] = o[5 * c] | o[5 * c + 1] << 16;
-                                    w[2 * c + 1] = o[5 * c + 2] | o[5 * c + 3] << 16;
-                                }
-                                w[8] = o[4] | o[9] << 16;
-                                w[9] = o[14] | o[19] << 16;
-                                w[10] = meta << 16;
-                            }
-                            for (int32_t x = 0; x < NW; ++x)
-                                words[(sl * NW + x) * NT + t] = w[x];
-                            first[sl * NT + t] = once;
                         }
-                }
+                        uint32_t w[kPatchWordsPlain];
+                        if (product) {
+                            w[0] = o[A0] | o[A2] << 16;
+                            w[1] = o[B0] | o[B2] << 16;
+                            w[2] = o[C] | meta << 16;
+                            w[3] = o[D0] | o[D1] << 16;
+                            w[4] = o[E0] | o[E1] << 16;
+                        } else {
+                            for (int32_t c = 0; c < 4; ++c) {
+                                w[2 * c] = o[5 * c] | o[5 * c + 1] << 16;
+                                w[2 * c + 1] = o[5 * c + 2] | o[5 * c + 3] << 16;
+                            }
+                            w[8] = o[4] | o[9] << 16;
+                            w[9] = o[14] | o[19] << 16;
+                            w[10] = meta << 16;
+                        }
+                        for (int32_t x = 0; x < NW; ++x)
+                            words[(static_cast<size_t>(q) * NW + x) * NT + t] = w[x];
+                        first[static_cast<size_t>(q) * NT + t] = once;
+                    }
+            }
         }
     });
     out.n_patches = B;
@@ -569,8 +564,9 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
 int check_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int32_t *lp,
                   const int32_t *pl, const PatchLayout &t)
 {
-    const int32_t L = t.shape.lanes, QL = t.shape.quads, R = t.shape.rounds, NT = t.shape.threads;
-    const int32_t QT = R * QL, NW = t.shape.product ? kPatchWordsProduct : kPatchWordsPlain;
+    const int32_t L = t.shape.lanes, QL = t.shape.quads, NT = t.shape.threads;
+    const bool product = t.shape.product != 0;
+    const int32_t NW = product ? kPatchWordsProduct : kPatchWordsPlain;
     if (NT < 64 || NT > kPatchThreads || NT % 64 || t.max_local > kPatchMaxLocal) return 1;
     std::vector<int32_t> comm_seen(n_comm, 0), exported(n_links, 0);
     std::vector<uint8_t> part_owner(static_cast<size_t>(t.n_parts / kPatchGroup), 0);
@@ -605,22 +601,21 @@ int check_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int3
             if (ref.empty()) ref = mine;
             else if (ref != mine) return 7;
         }
-        for (int32_t ci = 0; ci < t.n_comm_slots; ++ci) {
-            const int32_t k = t.comm[static_cast<size_t>(b) * t.n_comm_slots + ci];
-            const int32_t r = ci / (NT / L), g = ci % (NT / L);
+        if (d[6] > NT / L) return 18;
+        for (int32_t g = 0; g < NT / L; ++g) {
+            const int32_t k = g < d[6] ? t.comm[d[5] + g] : -1;
             std::vector<int32_t> used;
             int32_t next = 0;
             for (int32_t q = 0; q < QL; ++q)
                 for (int32_t j = 0; j < L; ++j) {
-                    const size_t sl = static_cast<size_t>(r) * QL + q;
                     const size_t th = static_cast<size_t>(g) * L + j;
                     auto word = [&](int32_t x) {
-                        return t.words[((static_cast<size_t>(b) * QT + sl) * NW + x) * NT + th];
+                        return t.words[((static_cast<size_t>(b) * QL + q) * NW + x) * NT + th];
                     };
-                    const uint32_t once = t.first[(static_cast<size_t>(b) * QT + sl) * NT + th];
+                    const uint32_t once = t.first[(static_cast<size_t>(b) * QL + q) * NT + th];
                     uint32_t o[20], meta;
-                    const int32_t n_off = t.shape.product ? 9 : 20;
-                    if (t.shape.product) {
+                    const int32_t n_off = product ? 9 : 20;
+                    if (product) {
                         const uint32_t w[5] = {word(0), word(1), word(2), word(3), word(4)};
                         o[A0] = w[0] & 0xFFFFu, o[A2] = w[0] >> 16;
                         o[B0] = w[1] & 0xFFFFu, o[B2] = w[1] >> 16;
@@ -640,7 +635,9 @@ int check_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int3
                     const uint32_t zero = 8u * n_local, inf = zero + 8u;
                     for (int32_t x = 0; x < n_off; ++x)
                         if (o[x] % 8 || o[x] > inf) return 8;
-                    const int32_t base = meta & 127, shift = (meta >> 7) & 3, n = (meta >> 9) & 7;
+                    const int32_t base = meta & 127, shift = (meta >> 7) & 3;
+                    const int32_t n = (meta >> 9) & 7;
+                    if (k < 0 && (n != 0 || once != 0u)) return 20;
                     for (int32_t x = 0; x < n_off; ++x)
                         if ((once >> x) & 1u) {
                             if (o[x] >= zero) return 9;
@@ -657,7 +654,7 @@ int check_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int3
                             return off != inf;
                         };
                         bool ok = true;
-                        if (t.shape.product) {
+                        if (product) {
                             const int32_t h = pos >> 1, l = pos & 1;
                             for (int32_t x : {A0 + h, B0 + h, int32_t(C), D0 + l, E0 + l})
                                 ok = add(o[x]) && ok;
@@ -673,7 +670,7 @@ int check_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int3
                     for (int32_t pos = 0; pos < 4; ++pos) {
                         if ((pos & ((1 << shift) - 1)) == 0 && (pos >> shift) < n) continue;
                         bool absent = false;
-                        if (t.shape.product) {
+                        if (product) {
                             const int32_t h = pos >> 1, l = pos & 1;
                             for (int32_t x : {A0 + h, B0 + h, int32_t(C), D0 + l, E0 + l})
                                 absent = absent || o[x] == inf;
@@ -733,12 +730,11 @@ extern "C" nimble_status_t nimble_host_patch_check(int32_t n_links, int32_t n_co
     out[2] = t.shape.product;
     out[3] = t.shape.lanes;
     out[4] = t.shape.quads;
-    out[5] = t.shape.rounds;
-    out[6] = t.shape.threads;
-    out[7] = t.max_local;
-    out[8] = t.max_groups;
-    out[9] = t.max_users;
-    out[10] = t.max_parts;
-    out[11] = t.n_parts;
+    out[5] = t.shape.threads;
+    out[6] = t.max_local;
+    out[7] = t.max_groups;
+    out[8] = t.max_users;
+    out[9] = t.max_parts;
+    out[10] = t.n_parts;
     return NIMBLE_OK;
 }

@@ -12,10 +12,10 @@
 // in every patch.  Shared links with the same users are bundled into groups of up to
 // kPatchGroup links, so that the parts of a group are contiguous for writer and reader.
 //
-// The candidates of a commodity are stored in SLOTS, what one lane scans: byte offsets of local
-// links in the price array (16 bits each), padded with the offset of a slot that holds +0.0
-// (adding +0.0 is exact wherever it happens in the left-to-right sum of a path) and, where a
-// candidate is absent, of one that holds +inf.  Two forms, one per layout:
+// The candidates of a commodity are stored in SLOTS of up to four: byte offsets of local links in
+// the price array (16 bits each), padded with the offset of a place that holds +0.0 (adding +0.0
+// is exact wherever it happens in the left-to-right sum of a path) and, where a candidate is
+// absent, of one that holds +inf.  Two forms, one per layout:
 //   product  nine offsets a0 a2 b0 b2 c d0 d1 e0 e1; candidate (h, l) of the slot, h and l from
 //            {0, 1}, is the path  a_h b_h c d_l e_l.  Four consecutive candidates of a product
 //            rule (egress x ingress of one rail) fill a slot; any two paths that differ in at
@@ -35,46 +35,42 @@ namespace nimble {
 
 constexpr int32_t kPatchGroup = 8;
 constexpr int32_t kPatchThreads = 1024;
-constexpr int32_t kPatchWordsProduct = 5;
-constexpr int32_t kPatchWordsPlain = 11;
 constexpr int32_t kPatchMaxLocal = 2900;      // local links whose state fits the LDS
 constexpr int32_t kPatchExport = 1 << 30;     // in loc_link: this patch writes the link's results
 constexpr int32_t kPatchDescInts = 8;
+constexpr int32_t kPatchWordsProduct = 5;
+constexpr int32_t kPatchWordsPlain = 11;
 
 struct PatchShape {              // what one kernel instantiation is made for
     int32_t product = 0;         // 1: product slots, 0: plain slots
     int32_t lanes = 0;           // lanes per commodity: 1, 2 or 4
-    int32_t quads = 0;           // slots per lane and commodity
-    int32_t rounds = 0;          // commodities per group of lanes
+    int32_t quads = 0;           // slots per lane
     int32_t threads = 0;         // workgroup size
 };
-// The shapes there are kernels for: X(product, lanes, quads, rounds).  A lane keeps at most eight
-// product slots or four plain slots in registers.
+// The shapes there are kernels for: X(product, lanes, quads).
 #define NIMBLE_PATCH_SHAPES(X)                                                                  \
-    X(1, 1, 1, 1) X(1, 1, 2, 1) X(1, 1, 2, 2) X(1, 1, 2, 4) X(1, 1, 3, 1) X(1, 1, 3, 2)         \
-    X(1, 1, 4, 1) X(1, 1, 4, 2) X(1, 1, 6, 1) X(1, 1, 8, 1)                                     \
-    X(1, 2, 1, 1) X(1, 2, 1, 2) X(1, 2, 2, 1) X(1, 2, 2, 2) X(1, 2, 3, 1) X(1, 2, 4, 1)         \
-    X(1, 4, 1, 1) X(1, 4, 1, 2) X(1, 4, 2, 1)                                                   \
-    X(0, 1, 1, 1) X(0, 1, 1, 2) X(0, 1, 1, 4) X(0, 1, 2, 1) X(0, 1, 2, 2) X(0, 1, 4, 1)         \
-    X(0, 2, 1, 1) X(0, 2, 1, 2) X(0, 2, 2, 1) X(0, 2, 4, 1)                                     \
-    X(0, 4, 1, 1) X(0, 4, 2, 1)
+    X(1, 1, 1) X(1, 1, 2) X(1, 1, 3) X(1, 1, 4) X(1, 1, 6) X(1, 1, 8)                           \
+    X(1, 2, 1) X(1, 2, 2) X(1, 2, 3) X(1, 2, 4) X(1, 4, 1) X(1, 4, 2)                           \
+    X(0, 1, 1) X(0, 1, 2) X(0, 1, 4) X(0, 2, 1) X(0, 2, 2) X(0, 2, 4) X(0, 4, 1) X(0, 4, 2)
 
 struct PatchLayout {
     PatchShape shape;
     int32_t n_patches = 0;       // 0: the fabric does not fit
-    int32_t n_comm_slots = 0;    // per patch: rounds * threads / lanes
+    int32_t max_comm = 0;        // most commodities of a patch
     int32_t max_local = 0;       // most local links (groups padded) of a patch
     int32_t max_groups = 0;      // most groups of a patch
     int32_t max_users = 0;       // most users of a group
     int32_t max_parts = 0;       // most parts (summed over its groups) of a patch
     int64_t n_parts = 0;         // doubles of one exchange buffer
     std::vector<int32_t> desc;      // [kPatchDescInts * n_patches] first local link, local links,
-                                    // links in groups (padded), first group, groups, commodities
+                                    // links in groups (padded), first group, groups, first
+                                    // commodity (in comm), commodities
     std::vector<int32_t> loc_link;  // link id | kPatchExport; -1: padding of a group
-    std::vector<int32_t> comm;      // [n_patches * n_comm_slots] commodity, -1: none
+    std::vector<int32_t> comm;      // [n_comm] commodities, patch after patch
     std::vector<uint32_t> words;    // [patch][slot][word][thread]
     std::vector<uint32_t> first;    // [patch][slot][thread] bit i: offset i of the slot is the
-                                    // commodity's first use of that link (width)
+                                    // commodity's first use of that link (width); offsets in the
+                                    // order a0 a2 b0 b2 c d0 d1 e0 e1, or candidate by candidate
     std::vector<int32_t> group;     // [4 * groups] first part, parts (users rounded up to eight),
                                     // own number among the users, users
 };
@@ -95,8 +91,8 @@ void scan_patches(int32_t n_links, int32_t n_comm, const int32_t *comm_path_ptr,
 // The cut of a fabric into a grid of `strips` x `strips` patches (1: one patch).
 struct PatchCut {
     int32_t strips = 0;
-    std::vector<std::vector<int32_t>> members;   // commodities of every patch
     int64_t most = 0;                            // most commodities of a patch
+    std::vector<std::vector<int32_t>> members;   // commodities of every patch
 };
 void cut_patches(int32_t n_comm, const PatchScan &scan, int32_t strips, PatchCut &out);
 

@@ -13,7 +13,7 @@ namespace nimble {
 struct DevicePatches {
     PatchShape shape;
     int32_t n_patches = 0;       // 0: no such layout
-    int32_t n_comm_slots, max_local, max_groups, max_parts;
+    int32_t max_comm, max_local, max_groups, max_parts;
     int64_t n_parts;
     int32_t max_teams;           // plans whose patches are resident at once
     const int32_t *desc, *loc_link, *comm, *group;
@@ -36,7 +36,7 @@ struct PatchArgs {
     double *parts, *maxima;
     uint32_t *abort_word;
     int64_t n_parts;
-    int32_t K, P, n_patches, n_comm_slots, plans, teams, iters;
+    int32_t K, P, n_patches, plans, teams, iters;
     uint32_t spin_limit;
     double eps;
 };

@@ -36,8 +36,8 @@ PatchKernel kernel_of(const DevicePatches &p, bool cost_max)
 
 size_t patch_lds_bytes(const DevicePatches &p)
 {
-    return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups,
-                                                 p.shape.rounds * p.shape.quads, p.shape.threads)
+    return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups, p.max_comm,
+                                                 p.shape.lanes * p.shape.quads)
                                    .bytes);
 }
 
@@ -85,7 +85,6 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     a.K = t.K;
     a.P = t.P;
     a.n_patches = p.n_patches;
-    a.n_comm_slots = p.n_comm_slots;
     a.plans = plans;
     a.teams = plans < p.max_teams ? plans : p.max_teams;
     a.iters = iters;

@@ -20,10 +20,12 @@
 // their writers published after reading n: nobody misses a word.  Every wait is bounded; when one
 // expires the team gives up and lambda becomes NaN.
 //
-// Sums of loads do not depend on the order of the atomics.  Where the demands of a patch lie on
-// a power-of-two grid with a total below 2^53 units (byte counts) binary64 additions are exact;
-// elsewhere a demand is split into two 64-bit integers, units of 2^-61 and 2^-105 of the patch's
-// total, and integer additions are (the sum is rounded once at the end).
+// Sums of loads do not depend on the order of the atomics: they are sums of integers.  Where the
+// demands of a patch lie on a power-of-two grid with a total below 2^53 units (byte counts) those
+// are the units, and the sum is what exact additions give; elsewhere a demand is split into
+// 2^-61 of the patch's total and 2^-105 of it, and the sum is rounded once at the end.  (64-bit
+// integer additions also take the LDS 6.2 cycles a wave where binary64 ones take 8.2, and 2
+// instead of 3 for every lane that meets another on the same link.)
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -39,29 +41,31 @@ constexpr unsigned long long kSign = 1ull << 63;
 constexpr int kNone = 0x7FFFFFFF;
 constexpr int kSumBits = 61, kLowBits = 44;
 
-// LDS of a patch, byte offsets.  The prices come first: a slot's offsets are LDS addresses.
+// LDS of a patch, byte offsets.  The prices come first: a slot's offsets are LDS addresses.  The
+// state of a link is one record; the choices of a candidate are counted in 16 bits, those of slot
+// s (of all the lanes' slots) of the patch's commodity c at count + (c * slots + s) * 8.
+struct LinkState {
+    unsigned long long load, low;      // load so far, see Grid
+    double len, S, invcap;
+};
 struct Lds {
-    int acc, low, len, S, invcap, group, count, red, bytes;
+    int link, red, group, count, bytes;
 };
 
-__host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int slots, int threads)
+__host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int n_comm, int slots)
 {
     Lds l;
     int o = 8 * (n_local + 2);                  // [n_local] +0.0, [n_local + 1] +inf
-    l.acc = o;     o += 8 * (n_local + 2);
-    l.low = o;     o += 8 * (n_local + 2);
-    l.len = o;     o += 8 * n_local;
-    l.S = o;       o += 8 * n_local;
-    l.invcap = o;  o += 8 * n_local;
+    l.link = o;    o += static_cast<int>(sizeof(LinkState)) * n_local;
     l.red = o;     o += 8 * 40;
+    o = (o + 15) & ~15;
     l.group = o;   o += 16 * n_groups;
-    l.count = o;   o += 8 * slots * threads;   // 16 bits per candidate of a slot
+    l.count = o;   o += 8 * n_comm * slots;
     l.bytes = o;
     return l;
 }
 
-// The largest of the dynamic LDS arrays has to start at LDS address 0 for the offsets to be
-// addresses, so this kernel has no static LDS.
+// The dynamic LDS starts at LDS address 0 (there is no other), so a slot's offsets are addresses.
 extern __shared__ __align__(16) unsigned char s_lds[];
 
 __device__ __forceinline__ double lds_f64(uint32_t off)
@@ -72,6 +76,8 @@ __device__ __forceinline__ double *lds_ptr(uint32_t off)
 {
     return reinterpret_cast<double *>(s_lds + off);
 }
+__device__ __forceinline__ double lds_lo(uint32_t w) { return lds_f64(w & 0xFFFFu); }
+__device__ __forceinline__ double lds_hi(uint32_t w) { return lds_f64(w >> 16); }
 
 template <bool MAXC>
 __device__ __forceinline__ double join(double acc, double p)
@@ -80,116 +86,75 @@ __device__ __forceinline__ double join(double acc, double p)
     else return acc + p;
 }
 
-// lowest cost of a slot and the position (0..3) that holds it, lowest first
-template <bool PRODUCT, bool MAXC>
-__device__ __forceinline__ void scan_slot(const uint32_t *w, double &m, int &pos)
+__device__ __forceinline__ int select(bool c, int a, int b)
 {
-    double c[4];
-    if constexpr (PRODUCT) {
-        const double a0 = lds_f64(w[0] & 0xFFFFu), a2 = lds_f64(w[0] >> 16);
-        const double b0 = lds_f64(w[1] & 0xFFFFu), b2 = lds_f64(w[1] >> 16);
-        const double mid = lds_f64(w[2] & 0xFFFFu);
-        const double d0 = lds_f64(w[3] & 0xFFFFu), d1 = lds_f64(w[3] >> 16);
-        const double e0 = lds_f64(w[4] & 0xFFFFu), e1 = lds_f64(w[4] >> 16);
-        const double t0 = join<MAXC>(join<MAXC>(a0, b0), mid);
-        const double t2 = join<MAXC>(join<MAXC>(a2, b2), mid);
-        c[0] = join<MAXC>(join<MAXC>(t0, d0), e0);
-        c[1] = join<MAXC>(join<MAXC>(t0, d1), e1);
-        c[2] = join<MAXC>(join<MAXC>(t2, d0), e0);
-        c[3] = join<MAXC>(join<MAXC>(t2, d1), e1);
-    } else {
-        double p[4][5];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            p[q][0] = lds_f64(w[2 * q] & 0xFFFFu);
-            p[q][1] = lds_f64(w[2 * q] >> 16);
-            p[q][2] = lds_f64(w[2 * q + 1] & 0xFFFFu);
-            p[q][3] = lds_f64(w[2 * q + 1] >> 16);
-            p[q][4] = lds_f64((w[8 + q / 2] >> (16 * (q & 1))) & 0xFFFFu);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            c[q] = p[q][0];
-#pragma unroll
-            for (int i = 1; i < 5; ++i) c[q] = join<MAXC>(c[q], p[q][i]);
-        }
-    }
-    m = fast_min_f64(fast_min_f64(c[0], c[1]), fast_min_f64(c[2], c[3]));
-    pos = c[0] == m ? 0 : (c[1] == m ? 1 : (c[2] == m ? 2 : 3));
+    int r;
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(c);
+    asm("v_cndmask_b32 %0, %1, %2, %3" : "=v"(r) : "v"(b), "v"(a), "s"(m));
+    return r;
 }
-
-template <bool PRODUCT>
-__device__ __forceinline__ uint32_t meta_of(const uint32_t *w)
+__device__ __forceinline__ uint32_t select(bool c, uint32_t a, uint32_t b)
 {
-    return (PRODUCT ? w[2] : w[10]) >> 16;
+    return static_cast<uint32_t>(select(c, static_cast<int>(a), static_cast<int>(b)));
 }
-
-// offsets of the five links of the candidate at position `pos` of a slot
-template <bool PRODUCT>
-__device__ __forceinline__ void links_of(const uint32_t *w, int pos, uint32_t (&off)[5])
-{
-    if constexpr (PRODUCT) {
-        const int h = (pos & 2) << 3, l = (pos & 1) << 4;
-        off[0] = (w[0] >> h) & 0xFFFFu;
-        off[1] = (w[1] >> h) & 0xFFFFu;
-        off[2] = w[2] & 0xFFFFu;
-        off[3] = (w[3] >> l) & 0xFFFFu;
-        off[4] = (w[4] >> l) & 0xFFFFu;
-    } else {
-        const bool hi = pos & 2, odd = pos & 1;
-        const uint32_t u0 = odd ? w[2] : w[0], u1 = odd ? w[3] : w[1];
-        const uint32_t v0 = odd ? w[6] : w[4], v1 = odd ? w[7] : w[5];
-        const uint32_t x = hi ? v0 : u0, y = hi ? v1 : u1, z = hi ? w[9] : w[8];
-        off[0] = x & 0xFFFFu;
-        off[1] = x >> 16;
-        off[2] = y & 0xFFFFu;
-        off[3] = y >> 16;
-        off[4] = (z >> (odd ? 16 : 0)) & 0xFFFFu;
-    }
-}
-
-// How the loads of a patch are summed: exact in binary64, or as two integers.
-struct Grid {
-    bool exact;
-    int scale;          // the patch's total is below 2^scale
-};
 
 // What is derived from these values is worked out where it is used: taken out of the loop over
 // the iterations (they never change) it would fill more registers than there are.
 __device__ __forceinline__ void keep_in_loop(uint32_t &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void keep_in_loop(double &v) { asm volatile("" : "+v"(v)); }
 
-__device__ __forceinline__ void add_load(uint32_t acc, uint32_t low, const Grid &gr, double d)
+// How the loads of a patch are summed: as whole numbers of units of 2^unit, and where the demands
+// are no such whole numbers also of 2^(unit - kLowBits).
+struct Grid {
+    bool exact;
+    int unit;
+};
+struct Demand {
+    unsigned long long units, low;
+};
+
+__device__ __forceinline__ Demand on_grid(double d, const Grid &gr)
 {
-    if (gr.exact) {
-        (void)__builtin_amdgcn_ds_atomic_fadd_f64(
-            (__attribute__((address_space(3))) double *)(lds_ptr(acc)), d);
-        return;
-    }
-    keep_in_loop(d);
-    const double h = trunc(ldexp(d, kSumBits - gr.scale));
-    const double r = d - ldexp(h, gr.scale - kSumBits);
-    const double l = trunc(ldexp(r, kSumBits + kLowBits - gr.scale));
-    (void)__hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(lds_ptr(acc)),
-                                 static_cast<unsigned long long>(static_cast<long long>(h)),
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    (void)__hip_atomic_fetch_add(reinterpret_cast<unsigned long long *>(lds_ptr(low)),
-                                 static_cast<unsigned long long>(static_cast<long long>(l)),
-                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const double h = trunc(ldexp(d, -gr.unit));
+    const double r = d - ldexp(h, gr.unit);
+    Demand n;
+    n.units = static_cast<unsigned long long>(static_cast<long long>(h));
+    n.low = static_cast<unsigned long long>(
+        static_cast<long long>(trunc(ldexp(r, kLowBits - gr.unit))));
+    return n;
 }
 
-// the load of local link i, which starts at zero again
-__device__ __forceinline__ double take_load(const Lds &l, int i, const Grid &gr)
+__device__ __forceinline__ void lds_add(unsigned long long *p, unsigned long long v)
 {
-    double *a = lds_ptr(l.acc) + i;
-    const double v = *a;
-    *a = 0.0;
-    if (gr.exact) return v;
-    double *b = lds_ptr(l.low) + i;
-    const double hi = static_cast<double>(__double_as_longlong(v));
-    const double lo = static_cast<double>(__double_as_longlong(*b));
-    *b = 0.0;
-    return ldexp(hi, gr.scale - kSumBits) + ldexp(lo, gr.scale - kSumBits - kLowBits);
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// adds d to the loads of the links at off[0..N-1] (offsets from `pad` on are no links)
+template <int N>
+__device__ __forceinline__ void add_loads(LinkState *links, uint32_t pad, const uint32_t (&off)[N],
+                                          const Grid &gr, const Demand &d)
+{
+    static_assert(sizeof(LinkState) == 40, "five times the 8 bytes of a price");
+    unsigned char *base = reinterpret_cast<unsigned char *>(links);
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        if (off[x] < pad)
+            lds_add(&reinterpret_cast<LinkState *>(base + off[x] * 5u)->load, d.units);
+    if (gr.exact) return;                                               // wave-uniform
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        if (off[x] < pad) lds_add(&reinterpret_cast<LinkState *>(base + off[x] * 5u)->low, d.low);
+}
+
+// the load of a link, which starts at zero again
+__device__ __forceinline__ double take_load(LinkState &s, const Grid &gr)
+{
+    const double hi = ldexp(static_cast<double>(static_cast<long long>(s.load)), gr.unit);
+    s.load = 0ull;
+    if (gr.exact) return hi;
+    const double lo = ldexp(static_cast<double>(static_cast<long long>(s.low)), gr.unit - kLowBits);
+    s.low = 0ull;
+    return hi + lo;
 }
 
 __device__ __forceinline__ void put_word(double *p, double v, unsigned phase)
@@ -245,33 +210,42 @@ __device__ __forceinline__ double add_across32(double v)
 // (q < kGroupsAtOnce).  `at` and `users`: first part and users of the groups (0 users: none).
 constexpr int kGroupsAtOnce = 4;
 constexpr int kPartsAtOnce = 4;
-__device__ __forceinline__ double group_loads(const double *parts, const int (&at)[kGroupsAtOnce],
-                                              const int (&users)[kGroupsAtOnce], unsigned phase,
-                                              unsigned limit, unsigned *abort_word, bool &dead,
+// first part and parts of some groups, the same in all lanes (0 parts: no group)
+struct Bundle {
+    int at[kGroupsAtOnce], parts[kGroupsAtOnce];
+};
+__device__ __forceinline__ double group_loads(const double *parts, const Bundle &bu, unsigned phase,
+                                              unsigned limit, unsigned *abort_word, int &dead,
                                               int lane)
 {
-    const int j = lane >> 3;
     double sum[kGroupsAtOnce];
     int most = 0;
 #pragma unroll
     for (int q = 0; q < kGroupsAtOnce; ++q) {
         sum[q] = 0.0;
-        most = most > users[q] ? most : users[q];
+        most = most > bu.parts[q] ? most : bu.parts[q];
     }
-    for (int c0 = 0; c0 < most; c0 += 8 * kPartsAtOnce) {           // wave-uniform
+    for (int c0 = 0; c0 < most; c0 += 8 * kPartsAtOnce) {           // wave-uniform, as all below
         unsigned long long v[kGroupsAtOnce][kPartsAtOnce];
         unsigned polls = 0;
         for (;;) {
             unsigned any = 0u, all = ~0u;
 #pragma unroll
             for (int q = 0; q < kGroupsAtOnce; ++q) {
-                const double *src = parts + at[q] + c0 * kPatchGroup;         // wave-uniform
+                const double *src = parts + (bu.at[q] + c0 * kPatchGroup);
+                const int n = bu.parts[q] - c0;
 #pragma unroll
-                for (int x = 0; x < kPartsAtOnce; ++x) {
+                for (int x = 0; x < kPartsAtOnce; ++x)
                     v[q][x] = static_cast<unsigned long long>(phase) << 63;
-                    if (c0 + 8 * x < users[q])                                // wave-uniform
-                        v[q][x] = get_word(src + static_cast<unsigned>(lane) +
-                                           x * (8 * kPatchGroup));
+                if (n > 0) {
+                    v[q][0] = get_word(src + static_cast<unsigned>(lane));
+                    if (n > 8) {
+                        v[q][1] = get_word(src + static_cast<unsigned>(lane) + 64);
+                        if (n > 16) {
+                            v[q][2] = get_word(src + static_cast<unsigned>(lane) + 128);
+                            if (n > 24) v[q][3] = get_word(src + static_cast<unsigned>(lane) + 192);
+                        }
+                    }
                 }
             }
 #pragma unroll
@@ -281,9 +255,18 @@ __device__ __forceinline__ double group_loads(const double *parts, const int (&a
                     any |= static_cast<unsigned>(v[q][x] >> 32);
                     all &= static_cast<unsigned>(v[q][x] >> 32);
                 }
-            const bool ok = phase ? (all >> 31) != 0u : (any >> 31) == 0u;
-            if (__all(ok) || dead) break;
-            if (!keep_waiting(polls, limit, abort_word)) dead = true;
+            const unsigned long long wrong =
+                phase ? __builtin_amdgcn_ballot_w64((all >> 31) == 0u)
+                      : __builtin_amdgcn_ballot_w64((any >> 31) != 0u);
+            if (wrong == 0ull || dead) break;
+            ++polls;
+            if (polls > limit) {
+                __hip_atomic_store(abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                dead = 1;
+            } else if ((polls & 63u) == 0u) {
+                dead = __builtin_amdgcn_readfirstlane(static_cast<int>(__hip_atomic_load(
+                    abort_word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+            }
         }
 #pragma unroll
         for (int q = 0; q < kGroupsAtOnce; ++q)
@@ -296,7 +279,7 @@ __device__ __forceinline__ double group_loads(const double *parts, const int (&a
         double t = sum[q] + dpp_f64<0x128>(sum[q]);     // row_ror:8, lane ^ 8
         t = add_across16(t);
         t = add_across32(t);
-        mine = j == q ? t : mine;
+        mine = (lane >> 3) == q ? t : mine;
     }
     return mine;
 }
@@ -312,42 +295,51 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-template <bool PRODUCT, int L, int QL, int R, bool MAXC, bool MULTI>
+// keep, or the words of slot q where `better`
+template <int NW>
+__device__ __forceinline__ void take_words(uint32_t (&keep)[NW], const uint32_t (&w)[NW], bool better)
+{
+#pragma unroll
+    for (int x = 0; x < NW; ++x) keep[x] = select(better, w[x], keep[x]);
+}
+
+template <bool PRODUCT, int L, int QL, bool MAXC, bool MULTI>
 __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
 {
-    constexpr int QT = QL * R;
     constexpr int NW = PRODUCT ? kPatchWordsProduct : kPatchWordsPlain;
     const int t = threadIdx.x, NT = blockDim.x;
-    const int lane = t & (kWave - 1), wave = t >> 6, n_waves = NT >> 6;
+    const int lane = t & (kWave - 1), n_waves = NT >> 6;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int team = MULTI ? blockIdx.x / a.n_patches : blockIdx.x;
     const int p = MULTI ? blockIdx.x - team * a.n_patches : 0;
     const int32_t *dsc = a.desc + kPatchDescInts * p;
     const int n_local = dsc[1], n_shared = MULTI ? dsc[2] : 0, n_groups = MULTI ? dsc[4] : 0;
-    const int n_comm = dsc[5];
+    const int n_comm = dsc[6];
+    const int32_t *comm = a.comm + dsc[5];
     const int32_t *loc_link = a.loc_link + dsc[0];
-    const Lds l = lds_layout(n_local, n_groups, QT, NT);
-    double *price = lds_ptr(0), *len = lds_ptr(l.len), *S = lds_ptr(l.S);
-    double *invcap = lds_ptr(l.invcap), *red = lds_ptr(l.red);
+    const Lds l = lds_layout(n_local, n_groups, n_comm, L * QL);
+    const uint32_t pad = 8u * static_cast<uint32_t>(n_local);
+    double *price = lds_ptr(0), *red = lds_ptr(l.red);
+    LinkState *links = reinterpret_cast<LinkState *>(lds_ptr(l.link));
     int *s_flag = reinterpret_cast<int *>(red + 39);
     int4 *groups = reinterpret_cast<int4 *>(s_lds + l.group);
-    // choices of slot s, candidate position pos: half pos & 1 of word (2 s + (pos >> 1)) * NT + t
-    uint32_t *tally = reinterpret_cast<uint32_t *>(s_lds + l.count) + t;
 
     // this lane's share of the lists, for the whole solve
-    uint32_t w[QT][NW];
+    const int j = t % L, g = t / L;
+    uint32_t w[QL][NW];
 #pragma unroll
-    for (int s = 0; s < QT; ++s)
+    for (int q = 0; q < QL; ++q)
 #pragma unroll
         for (int x = 0; x < NW; ++x)
-            w[s][x] = a.words[((static_cast<size_t>(p) * QT + s) * NW + x) * NT + t];
-    const int per = NT / L, g = t / L, j = t % L;
+            w[q][x] = a.words[((static_cast<size_t>(p) * QL + q) * NW + x) * NT + t];
+    const bool busy = (wave * kWave) / L < n_comm;         // this wave has commodities
     if constexpr (MULTI)
         for (int q = t; q < n_groups; q += NT)
             groups[q] = reinterpret_cast<const int4 *>(a.group)[dsc[3] + q];
 
     unsigned exchange = 0u;          // exchanges made so far, the same in all patches of a team
     unsigned meeting = 0u;           // maxima folded over all patches so far
-    bool dead = false;
+    int dead = 0;                    // this wave has given up waiting
     double *parts_of_team = nullptr, *maxima_of_team = nullptr;
     if constexpr (MULTI) {
         parts_of_team = a.parts + static_cast<size_t>(team) * 2 * a.n_parts;
@@ -357,26 +349,20 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
     for (int plan = team; plan < a.plans; plan += MULTI ? a.teams : a.plans) {
         const double *demand = a.demand + static_cast<size_t>(plan) * a.K;
         double *splits = a.splits + static_cast<size_t>(plan) * a.P;
-        double d[R];
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const int k = a.comm[static_cast<size_t>(p) * a.n_comm_slots + r * per + g];
-            d[r] = k >= 0 ? demand[k] : 0.0;
-        }
-#pragma unroll
-        for (int s = 0; s < 2 * QT; ++s) tally[s * NT] = 0u;
+        const double d = g < n_comm ? demand[comm[g]] : 0.0;
         __syncthreads();                 // (the plan before is done with LDS)
         for (int i = t; i < n_local; i += NT) {
             const int e = loc_link[i];
             const double ic = e >= 0 ? a.invcap[e & ~kPatchExport] : 0.0;
             const double l0 = a.len_in && e >= 0 ? a.len_in[e & ~kPatchExport] : 1.0;
-            invcap[i] = ic;
-            len[i] = l0;
+            links[i].load = 0ull;
+            links[i].low = 0ull;
+            links[i].len = l0;
+            links[i].S = 0.0;
+            links[i].invcap = ic;
             price[i] = MAXC ? l0 : l0 * ic;
-            S[i] = 0.0;
-            lds_ptr(l.acc)[i] = 0.0;
-            lds_ptr(l.low)[i] = 0.0;
         }
+        for (int i = t; i < n_comm * L * QL; i += NT) lds_ptr(l.count)[i] = 0.0;
         if (t == 0) {
             price[n_local] = 0.0;
             price[n_local + 1] = __builtin_inf();
@@ -385,18 +371,15 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         // total and finest grid of the patch's demands
         Grid gr;
         {
-            double sum = 0.0;
+            double sum = j == 0 ? d : 0.0;
             int fine = 4096;
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                if (j != 0 || d[r] == 0.0) continue;
-                sum = sum + d[r];
+            if (d != 0.0) {
                 const unsigned long long b =
-                    static_cast<unsigned long long>(__double_as_longlong(d[r]));
+                    static_cast<unsigned long long>(__double_as_longlong(d));
                 const int ex = static_cast<int>((b >> 52) & 2047u);
                 const unsigned long long man =
                     (b & ((1ull << 52) - 1ull)) | (ex ? 1ull << 52 : 0ull);
-                fine = min(fine, (ex ? ex : 1) - 1075 + __ffsll(static_cast<long long>(man)) - 1);
+                fine = (ex ? ex : 1) - 1075 + __ffsll(static_cast<long long>(man)) - 1;
             }
             sum = wave_sum(sum);
             for (int o = 32; o > 0; o >>= 1) fine = min(fine, __shfl_xor(fine, o, kWave));
@@ -410,30 +393,30 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 total = total + red[q];
                 fine = min(fine, reinterpret_cast<const int *>(red + 16)[q]);
             }
-            gr.exact = !(total > 0.0) || !(total < __builtin_inf());
-            gr.scale = gr.exact ? 0 : ilogb(total) + 1;
-            gr.exact = gr.exact || gr.scale - fine <= 53;
-            gr.exact = __builtin_amdgcn_readfirstlane(gr.exact ? 1 : 0) != 0;
-            gr.scale = __builtin_amdgcn_readfirstlane(gr.scale);
+            const bool some = total > 0.0 && total < __builtin_inf();
+            const int top = some ? ilogb(total) + 1 : 0;            // the total is below 2^top
+            gr.exact = __builtin_amdgcn_readfirstlane(!some || top - fine <= 53 ? 1 : 0) != 0;
+            gr.unit = __builtin_amdgcn_readfirstlane(
+                !some ? 0 : gr.exact ? fine : top - kSumBits);
         }
+        const Demand units = on_grid(d, gr);
         // width rho: every commodity that can reach a link counts once
 #pragma unroll
-        for (int s = 0; s < QT; ++s) {
-            const uint32_t once = a.first[(static_cast<size_t>(p) * QT + s) * NT + t];
+        for (int q = 0; q < QL; ++q) {
+            const uint32_t once = a.first[(static_cast<size_t>(p) * QL + q) * NT + t];
             constexpr int n_off = PRODUCT ? 9 : 20;
+            uint32_t off[n_off];
 #pragma unroll
             for (int x = 0; x < n_off; ++x) {
                 // where offset x of a slot is kept (see host_patch.hpp)
-                const uint32_t word =
-                    PRODUCT ? w[s][x < 4 ? x / 2 : x == 4 ? 2 : (x + 1) / 2]
-                            : w[s][x % 5 == 4 ? 8 + x / 10 : 2 * (x / 5) + (x % 5) / 2];
-                const bool high = PRODUCT ? (x < 4 ? x & 1 : x == 4 ? false : !(x & 1))
+                const uint32_t word = PRODUCT ? w[q][x < 4 ? x / 2 : x == 4 ? 2 : (x + 1) / 2]
+                                              : w[q][x % 5 == 4 ? 8 + x / 10 : 2 * (x / 5) + (x % 5) / 2];
+                const bool high = PRODUCT ? (x < 4 ? x & 1 : x != 4 && !(x & 1))
                                           : (x % 5 == 4 ? (x / 5) & 1 : (x % 5) & 1);
-                if ((once >> x) & 1u) {
-                    const uint32_t off = high ? word >> 16 : word & 0xFFFFu;
-                    add_load(l.acc + off, l.low + off, gr, d[s / QL]);
-                }
+                off[x] = high ? word >> 16 : word & 0xFFFFu;
+                if (!((once >> x) & 1u)) off[x] = pad;
             }
+            add_loads<n_off>(links, pad, off, gr, units);
         }
         __syncthreads();
         double wmax = 0.0;
@@ -444,30 +427,34 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 put_word(dst + c * kPatchGroup, c == gd.z ? v : 0.0, (exchange >> 1) & 1u);
         };
         for (int i = t; i < n_local; i += NT) {
-            const double reach = take_load(l, i, gr);
+            const double reach = take_load(links[i], gr);
             if (MULTI && i < n_shared) publish(reach, i);
-            else wmax = fmax(wmax, reach * invcap[i]);
+            else wmax = fmax(wmax, reach * links[i].invcap);
         }
         // f(local link, load) for the shared links, a lane each; the groups of a patch are dealt
         // to its waves in bundles
+        auto bundle_of = [&](int q0) {
+            Bundle bu;
+#pragma unroll
+            for (int q = 0; q < kGroupsAtOnce; ++q) {
+                const int4 gd = groups[q0 + q < n_groups ? q0 + q : 0];
+                bu.at[q] = __builtin_amdgcn_readfirstlane(gd.x);
+                bu.parts[q] = q0 + q < n_groups ? __builtin_amdgcn_readfirstlane(gd.y) : 0;
+            }
+            return bu;
+        };
         auto for_shared = [&](auto f) {
             for (int q0 = wave * kGroupsAtOnce; q0 < n_groups; q0 += n_waves * kGroupsAtOnce) {
-                int at[kGroupsAtOnce], users[kGroupsAtOnce];
-#pragma unroll
-                for (int q = 0; q < kGroupsAtOnce; ++q) {
-                    const int4 gd = groups[q0 + q < n_groups ? q0 + q : q0];
-                    at[q] = __builtin_amdgcn_readfirstlane(gd.x);
-                    users[q] = __builtin_amdgcn_readfirstlane(q0 + q < n_groups ? gd.y : 0);
-                }
+                const Bundle bu = bundle_of(q0);
                 const double load =
-                    group_loads(parts_of_team + (exchange & 1u) * a.n_parts, at, users,
+                    group_loads(parts_of_team + (exchange & 1u) * a.n_parts, bu,
                                 (exchange >> 1) & 1u, a.spin_limit, a.abort_word, dead, lane);
                 if (lane < kGroupsAtOnce * kPatchGroup && q0 + (lane >> 3) < n_groups)
                     f(q0 * kPatchGroup + lane, load);
             }
         };
         if constexpr (MULTI) {
-            for_shared([&](int i, double reach) { wmax = fmax(wmax, reach * invcap[i]); });
+            for_shared([&](int i, double reach) { wmax = fmax(wmax, reach * links[i].invcap); });
             exchange += 1u;
         }
         wmax = wave_max(wmax);
@@ -486,11 +473,12 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 for (;;) {
                     v = get_word(mx + b);
                     if (static_cast<unsigned>(v >> 63) == phase || dead) break;
-                    if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = true;
+                    if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
                 }
                 wmax = fmax(wmax, word_value(v));
             }
             meeting += 1u;
+            dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
             wmax = wave_max(wmax);
             __syncthreads();
             if (lane == 0) red[wave] = wmax;
@@ -501,98 +489,158 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         const double invrho = wmax > 0.0 ? 1.0 / wmax : 0.0;
 
         auto update = [&](int i, double load) {
-            const double ic = invcap[i];
+            LinkState &s = links[i];
+            const double ic = s.invcap;
             const double u = load * ic;
-            S[i] = S[i] + u;
+            s.S = s.S + u;
             const double gn = u * invrho;
             const double t1 = a.eps * gn;
             const double t2 = 1.0 + t1;
-            const double ln = len[i] * t2;
-            len[i] = ln;
+            const double ln = s.len * t2;
+            s.len = ln;
             price[i] = MAXC ? ln : ln * ic;
         };
-        for (int it = 0; it < a.iters; ++it) {
+        // Scan and scatter of an iteration.
+        auto pass = [&]() {
+            double best = 0.0;
+            uint32_t wb[NW];             // the slot that holds the best candidate so far
+            int sb = 0, pos = 0;
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                // (a wave without commodities in this round has nothing to scan)
-                if (r * per + (wave * kWave) / L >= n_comm) break;           // wave-uniform
-                double best = __builtin_inf();
-                int pos = 0;
-                uint32_t wb[NW];            // the slot that holds the best candidate so far
-                int sb = r * QL;
+            for (int q = 0; q < QL; ++q) {
+                if constexpr (QL > 1 || !PRODUCT)
 #pragma unroll
-                for (int q = 0; q < QL; ++q) {
-                    uint32_t *ws = w[r * QL + q];
-                    if constexpr (QT > 1 || !PRODUCT)
+                    for (int x = 0; x < NW; ++x) keep_in_loop(w[q][x]);
+                const uint32_t *ws = w[q];
+                double m;
+                int at = 0;
+                if constexpr (PRODUCT) {
+                    // Of the two ways to reach the middle link the cheaper one is the cheaper
+                    // one for every way on: rounded additions keep the order.  (Which of equally
+                    // cheap candidates comes first is settled below.)
+                    const double mid = lds_lo(ws[2]);
+                    const double t0 = join<MAXC>(join<MAXC>(lds_lo(ws[0]), lds_lo(ws[1])), mid);
+                    const double t2 = join<MAXC>(join<MAXC>(lds_hi(ws[0]), lds_hi(ws[1])), mid);
+                    const double tm = fast_min_f64(t0, t2);
+                    m = fast_min_f64(join<MAXC>(join<MAXC>(tm, lds_lo(ws[3])), lds_lo(ws[4])),
+                                     join<MAXC>(join<MAXC>(tm, lds_hi(ws[3])), lds_hi(ws[4])));
+                } else {
+                    double c[4];
 #pragma unroll
-                        for (int x = 0; x < NW; ++x) keep_in_loop(ws[x]);
-                    double m;
-                    int at;
-                    scan_slot<PRODUCT, MAXC>(ws, m, at);
-                    // the strict `<` of a scan in candidate order; a commodity whose candidates
-                    // all cost +inf resolves to its first
-                    const bool better = q == 0 || m < best;
-                    best = better ? m : best;
-                    pos = better ? at : pos;
-                    sb = better ? r * QL + q : sb;
-#pragma unroll
-                    for (int x = 0; x < NW; ++x) wb[x] = better ? ws[x] : wb[x];
+                    for (int x = 0; x < 4; ++x) {
+                        c[x] = join<MAXC>(
+                            join<MAXC>(join<MAXC>(lds_lo(ws[2 * x]), lds_hi(ws[2 * x])),
+                                       lds_lo(ws[2 * x + 1])),
+                            lds_hi(ws[2 * x + 1]));
+                        c[x] = join<MAXC>(c[x], x & 1 ? lds_hi(ws[8 + x / 2])
+                                                      : lds_lo(ws[8 + x / 2]));
+                    }
+                    m = fast_min_f64(fast_min_f64(c[0], c[1]), fast_min_f64(c[2], c[3]));
+                    at = select(c[2] == m, 2, 3);
+                    at = select(c[1] == m, 1, at);
+                    at = select(c[0] == m, 0, at);
                 }
-                const uint32_t meta = meta_of<PRODUCT>(wb);
-                bool mine = (meta >> 9) != 0u;
-                if constexpr (L > 1) {
-                    const int cand = mine ? static_cast<int>(meta & 127u) +
-                                                (pos >> ((meta >> 7) & 3u))
-                                          : kNone;
-                    const int chosen = group_argmin_two_pass<L>(best, cand);   // (all lanes)
-                    mine = mine && chosen == cand;
-                }
-                if (mine) {
-                    uint32_t off[5];
-                    links_of<PRODUCT>(wb, pos, off);
-                    const uint32_t pad = 8u * static_cast<uint32_t>(n_local);
+                if (q == 0) {
+                    best = m;
+                    pos = at;
 #pragma unroll
-                    for (int x = 0; x < 5; ++x)
-                        if (off[x] < pad) add_load(l.acc + off[x], l.low + off[x], gr, d[r]);
-                    (void)__hip_atomic_fetch_add(tally + (2 * sb + (pos >> 1)) * NT,
-                                                 1u << (16 * (pos & 1)), __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_WORKGROUP);
+                    for (int x = 0; x < NW; ++x) wb[x] = ws[x];
+                } else {
+                    // the strict `<` of a scan in candidate order
+                    const bool better = m < best;
+                    best = fast_min_f64(best, m);
+                    sb = select(better, q, sb);
+                    if constexpr (!PRODUCT) pos = select(better, at, pos);
+                    take_words<NW>(wb, w[q], better);
                 }
             }
+            uint32_t off[5];
+            if constexpr (PRODUCT) {
+                // the candidates of the best slot, exactly: the first that costs `best`
+                const double mid = lds_lo(wb[2]);
+                const double t0 = join<MAXC>(join<MAXC>(lds_lo(wb[0]), lds_lo(wb[1])), mid);
+                const double t2 = join<MAXC>(join<MAXC>(lds_hi(wb[0]), lds_hi(wb[1])), mid);
+                const double d0 = lds_lo(wb[3]), d1 = lds_hi(wb[3]);
+                const double e0 = lds_lo(wb[4]), e1 = lds_hi(wb[4]);
+                pos = select(join<MAXC>(join<MAXC>(t2, d0), e0) == best, 2, 3);
+                pos = select(join<MAXC>(join<MAXC>(t0, d1), e1) == best, 1, pos);
+                pos = select(join<MAXC>(join<MAXC>(t0, d0), e0) == best, 0, pos);
+            }
+            // (a commodity whose candidates all cost +inf resolves to its first)
+            pos = select(best < __builtin_inf(), pos, 0);
+            const uint32_t meta = (PRODUCT ? wb[2] : wb[NW - 1]) >> 16;
+            bool mine = (meta >> 9) != 0u;
+            if constexpr (L > 1) {
+                const int cand = select(
+                    mine, static_cast<int>(meta & 127u) + (pos >> ((meta >> 7) & 3u)), kNone);
+                mine = group_argmin_two_pass<L>(best, cand) == cand && mine;
+            }
+            if constexpr (PRODUCT) {
+                const int hs = (pos & 2) << 3, ls = (pos & 1) << 4;
+                off[0] = (wb[0] >> hs) & 0xFFFFu;
+                off[1] = (wb[1] >> hs) & 0xFFFFu;
+                off[2] = wb[2] & 0xFFFFu;
+                off[3] = (wb[3] >> ls) & 0xFFFFu;
+                off[4] = (wb[4] >> ls) & 0xFFFFu;
+            } else {
+                const bool hi = pos & 2, odd = pos & 1;
+                const uint32_t x = select(hi, select(odd, wb[6], wb[4]), select(odd, wb[2], wb[0]));
+                const uint32_t y = select(hi, select(odd, wb[7], wb[5]), select(odd, wb[3], wb[1]));
+                const uint32_t z = select(hi, wb[9], wb[8]);
+                off[0] = x & 0xFFFFu;
+                off[1] = x >> 16;
+                off[2] = y & 0xFFFFu;
+                off[3] = y >> 16;
+                off[4] = (z >> (odd ? 16 : 0)) & 0xFFFFu;
+            }
+            if (mine) {
+                add_loads<5>(links, pad, off, gr, units);
+                uint32_t *n = reinterpret_cast<uint32_t *>(
+                    lds_ptr(l.count + 8 * (g * (L * QL) + sb * L + j) + 4 * (pos >> 1)));
+                (void)__hip_atomic_fetch_add(n, 1u << (16 * (pos & 1)), __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+            }
+        };
+
+        for (int it = 0; it < a.iters; ++it) {
+            if (busy) pass();                                                // wave-uniform
             __syncthreads();
             if constexpr (MULTI) {
-                for (int i = t; i < n_shared; i += NT) publish(take_load(l, i, gr), i);
-                for (int i = n_shared + t; i < n_local; i += NT) update(i, take_load(l, i, gr));
+                for (int i = t; i < n_shared; i += NT) publish(take_load(links[i], gr), i);
+                for (int i = n_shared + t; i < n_local; i += NT) update(i, take_load(links[i], gr));
                 for_shared(update);
                 exchange += 1u;
                 if (dead) *s_flag = 1;
             } else {
-                for (int i = t; i < n_local; i += NT) update(i, take_load(l, i, gr));
+                for (int i = t; i < n_local; i += NT) update(i, take_load(links[i], gr));
             }
             __syncthreads();
             if constexpr (MULTI)
-                if (*s_flag != 0) break;                         // workgroup-uniform
+                if (__builtin_amdgcn_readfirstlane(*s_flag) != 0) break;     // workgroup-uniform
         }
         const double T = static_cast<double>(a.iters);
+        if (g < n_comm) {
+            double *out0 = splits + a.comm_ptr[comm[g]];
 #pragma unroll
-        for (int s = 0; s < QT; ++s) {
-            const int k = a.comm[static_cast<size_t>(p) * a.n_comm_slots + (s / QL) * per + g];
-            const uint32_t meta = meta_of<PRODUCT>(w[s]);
-            const int n = static_cast<int>(meta >> 9), shift = static_cast<int>((meta >> 7) & 3u);
-            if (k < 0 || n == 0) continue;
-            double *out = splits + a.comm_ptr[k] + (meta & 127u);
-            const uint32_t c0 = tally[2 * s * NT], c1 = tally[(2 * s + 1) * NT];
-            const uint32_t n4[4] = {c0 & 0xFFFFu, c0 >> 16, c1 & 0xFFFFu, c1 >> 16};
+            for (int q = 0; q < QL; ++q) {
+                const uint32_t meta = (PRODUCT ? w[q][2] : w[q][NW - 1]) >> 16;
+                const int n = static_cast<int>(meta >> 9);
+                const int shift = static_cast<int>((meta >> 7) & 3u);
+                if (n == 0) continue;
+                double *out = out0 + (meta & 127u);
+                const uint2 c = *reinterpret_cast<const uint2 *>(
+                    lds_ptr(l.count + 8 * (g * (L * QL) + q * L + j)));
+                const uint32_t n4[4] = {c.x & 0xFFFFu, c.x >> 16, c.y & 0xFFFFu, c.y >> 16};
 #pragma unroll
-            for (int pos = 0; pos < 4; ++pos)
-                if ((pos & ((1 << shift) - 1)) == 0 && (pos >> shift) < n)
-                    out[pos >> shift] = static_cast<double>(n4[pos]) / T;
+                for (int pos = 0; pos < 4; ++pos)
+                    if ((pos & ((1 << shift) - 1)) == 0 && (pos >> shift) < n)
+                        out[pos >> shift] = static_cast<double>(n4[pos]) / T;
+            }
         }
         double smax = 0.0;
         for (int i = t; i < n_local; i += NT) {
-            smax = fmax(smax, S[i]);
+            smax = fmax(smax, links[i].S);
             if (a.len_out != nullptr && (loc_link[i] & kPatchExport) && loc_link[i] >= 0)
-                a.len_out[loc_link[i] & ~kPatchExport] = len[i];
+                a.len_out[loc_link[i] & ~kPatchExport] = links[i].len;
         }
         smax = wave_max(smax);
         __syncthreads();
@@ -632,9 +680,9 @@ using PatchKernel = void (*)(PatchArgs);
 template <bool MAXC, bool MULTI>
 PatchKernel kernel_for(const PatchShape &s)
 {
-#define NIMBLE_PATCH(PR, LL, QQ, RR)                                                           \
-    if (s.product == PR && s.lanes == LL && s.quads == QQ && s.rounds == RR)                   \
-        return k_patch<PR != 0, LL, QQ, RR, MAXC, MULTI>;
+#define NIMBLE_PATCH(PR, LL, QQ)                                                               \
+    if (s.product == PR && s.lanes == LL && s.quads == QQ)                                     \
+        return k_patch<PR != 0, LL, QQ, MAXC, MULTI>;
     NIMBLE_PATCH_SHAPES(NIMBLE_PATCH)
 #undef NIMBLE_PATCH
     return nullptr;
