@@ -220,7 +220,7 @@ nimble_status_t nimble_alg1_solve_batch(nimble_topo_t *topo, int32_t batch,
  *           everywhere is the cold start).  Lengths grow by at most (1 + eps) per iteration:
  *           the caller rescales them (e.g. by a power of two, which changes nothing else)
  *           before they can overflow.
- * The other arguments as for nimble_plan_solve.  Always runs the streaming regime; like
+ * The other arguments as for nimble_plan_solve.  Reported as the streaming regime; like
  * nimble_plan_solve it only enqueues work.
  */
 nimble_status_t nimble_plan_solve_warm(nimble_topo_t *topo, const double *d_traffic, double eps,
@@ -247,12 +247,14 @@ nimble_status_t nimble_plan_solve_warm(nimble_topo_t *topo, const double *d_traf
  *   iters_done   host out: iterations made (0 for all-zero traffic: every pair then stays on
  *                its first candidate)
  *   lower_bound  host out: best LB seen (0 if no check was made)
- * The stop decision is taken on the device; the host enqueues ahead and follows the device's
- * progress through two words of pinned memory, so the stream is never synchronised during the
- * solve (kernels enqueued after the stop return at once).  Unlike nimble_plan_solve the call
+ * The stop decision is taken on the device.  Fabrics that fit the patch kernels are solved in one
+ * launch; on others the host enqueues ahead and follows the device's progress through two words
+ * of pinned memory, so the stream is never synchronised during the solve (kernels enqueued after
+ * the stop return at once).  Unlike nimble_plan_solve the call
  * waits for the stream before it returns, because iters_done and lower_bound are host outputs,
- * and it cannot be captured into a graph.  Always runs the streaming regime; needs the per-iteration choice log of
- * max_iters rows and grows it when it is shorter (NIMBLE_ERR_ALLOC if it cannot be allocated,
+ * and it cannot be captured into a graph.  Reported as the streaming regime; needs the
+ * per-iteration choice log of max_iters rows and grows it when it is shorter (NIMBLE_ERR_ALLOC if
+ * it cannot be allocated,
  * NIMBLE_ERR_RANGE beyond 1 GiB), as well as a workspace of its own on the first call.
  * Bit-identical to the plain CPU definition for integer-valued demands.
  */

@@ -14,8 +14,8 @@
 extern "C" {
 #endif
 
-/* 1 if nimble_plan_solve_adaptive applies the step of an iteration inside the record kernel of
- * the next one on this topology (two launches per iteration; the prices of the scan are formed
+/* 1 if nimble_plan_solve_adaptive, where it is not solved in one launch, applies the step of an
+ * iteration inside the record kernel of the next one on this topology (two launches per iteration; the prices of the scan are formed
  * from the lengths before the step, the loads and the step, with the operations of the step
  * itself), 0 if in a launch of its own (three), -1 for a NULL handle.  Both give the same
  * bits. */

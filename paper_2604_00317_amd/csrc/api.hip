@@ -129,6 +129,9 @@ struct nimble_topo {
     int64_t ad_sigma_rows = 0;
     void *sync_words = nullptr; // barrier counter and reductions of the persistent kernel
     std::vector<nimble::DevicePatches> patches;   // layouts of the patch kernels (may be none)
+    const int32_t *idle = nullptr;                // links no candidate uses
+    int32_t n_idle = 0;
+    bool ad_fold_forced = false;                  // a switch asks for the launched adaptive solve
     // per-plan state: state_plans blocks of d.state_stride bytes in one allocation; the state
     // pointers of `d` are those of block 0
     unsigned char *state = nullptr;
@@ -320,7 +323,8 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
         p.max_teams = t->n_cu / l.n_patches;
         e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_parts, &p.parts);
         if (e == hipSuccess)
-            e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_patches, &p.maxima);
+            e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * nimble::kPatchCopies * l.n_patches,
+                         &p.maxima);
         if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
     }
     p.n_patches = e == hipSuccess ? l.n_patches : 0;
@@ -377,8 +381,15 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
         nimble::DevicePatches p;
         const hipError_t e = upload_patches(t, built[i], p);
         if (e != hipSuccess) return e;
-        if (nimble::patch_blocks_per_cu(p, d.cost_max) >= 1) t->patches.push_back(p);
+        p.adaptive = !d.cost_max && nimble::patch_blocks_per_cu(p, false, true) >= 1;
+        if (nimble::patch_blocks_per_cu(p, d.cost_max, false) >= 1) t->patches.push_back(p);
     }
+    std::vector<int32_t> idle(static_cast<size_t>(d.E));
+    for (int32_t e = 0; e < d.E; ++e) idle[static_cast<size_t>(e)] = e;
+    for (int64_t i = 0; i < lp[cp[d.K]]; ++i) idle[static_cast<size_t>(pl[i])] = -1;
+    idle.erase(std::remove(idle.begin(), idle.end(), -1), idle.end());
+    t->n_idle = static_cast<int32_t>(idle.size());
+    if (t->n_idle > 0) return upload(t, idle.data(), idle.size(), &t->idle);
     return hipSuccess;
 }
 
@@ -533,6 +544,37 @@ nimble_status_t solve_persistent(nimble_topo *topo, const double *d_traffic, dou
 }  // namespace
 
 // whether nimble_plan_solve_adaptive applies a step inside the next iteration's record kernel
+// The layout the adaptive solve runs on in one launch, or null: it is then launched kernel by
+// kernel.  (Every iteration is a trip from patch to patch longer than the fixed step's; the
+// limit on the iterations keeps one launch to a few seconds.)
+static const nimble::DevicePatches *adaptive_patches(const nimble_topo_t *t, int32_t max_iters)
+{
+    if (t->d.cost_max || t->ad_fold_forced || max_iters > 1 << 20 ||
+        t->forced_regime != NIMBLE_REGIME_AUTO)
+        return nullptr;
+    const nimble::DevicePatches *best = nullptr;
+    for (const nimble::DevicePatches &p : t->patches)
+        if (p.adaptive && (best == nullptr || p.iteration_us < best->iteration_us)) best = &p;
+    return best;
+}
+
+// Waits for an adaptive solve and hands its host outputs over.
+static nimble_status_t adaptive_results(nimble_topo_t *t, int32_t *iters_done, double *lower_bound,
+                                        hipStream_t s)
+{
+    int32_t flags[2] = {0, 0};
+    double ascal[4] = {0, 0, 0, 0};
+    hipError_t e = hipMemcpyAsync(flags, t->ad.flags, sizeof(flags), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess)
+        e = hipMemcpyAsync(ascal, t->ad.ascal, sizeof(ascal), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail_hip(e, "adaptive solve (results)");
+    if (flags[0] == 2) return fail(NIMBLE_ERR_HIP, "adaptive solve: a wait between patches expired");
+    *iters_done = flags[1];
+    *lower_bound = ascal[2];
+    return NIMBLE_OK;
+}
+
 static bool adaptive_folds(const nimble_topo_t *t)
 {
     if (t->ad_fold == 0 || (t->d.n_blocks <= 0 && t->d.n_gblocks <= 0)) return false;
@@ -600,7 +642,10 @@ nimble_status_t nimble_topo_create(int32_t n_links, const double *cap, int32_t n
     d.rev_row_max = 0;
     for (int32_t len : h.rev_rowlen) d.rev_row_max = std::max(d.rev_row_max, len);
     t->no_choice_log = std::getenv("NIMBLE_TUNE_NO_CHOICE_LOG") != nullptr;
-    if (const char *v = std::getenv("NIMBLE_TUNE_ADAPTIVE_FOLD")) t->ad_fold = std::atoi(v) != 0;
+    if (const char *v = std::getenv("NIMBLE_TUNE_ADAPTIVE_FOLD")) {
+        t->ad_fold = std::atoi(v) != 0;
+        t->ad_fold_forced = true;
+    }
     d.resident_generic = std::getenv("NIMBLE_TUNE_RESIDENT_GENERIC") ? 1 : 0;
     d.alg1_thread_per_problem = std::getenv("NIMBLE_TUNE_ALG1_THREAD_PER_PROBLEM") ? 1 : 0;
     d.n_records = h.n_records;
@@ -1145,6 +1190,9 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
                                          static_cast<size_t>(4) * static_cast<size_t>(d.n_blocks),
                                          static_cast<size_t>(16) * static_cast<size_t>(d.n_gblocks)}),
                          &a.block_max_u);
+        if (e == hipSuccess && !topo->patches.empty())
+            e = allocate(topo, static_cast<size_t>(nimble::patch_adaptive_words(d.K, d.E)), &a.terms);
+        if (e == hipSuccess && !topo->patches.empty()) e = allocate(topo, 1, &a.patch_abort);
         if (e == hipSuccess && !a.host_words_host) {
             // two words of pinned host memory the device writes and the host polls
             void *hp = nullptr;
@@ -1186,6 +1234,21 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
     st = grow_choice_log(topo, max_iters);
     if (st != NIMBLE_OK) return st;
     topo->last_regime = NIMBLE_REGIME_STREAM;
+    if (const nimble::DevicePatches *p = adaptive_patches(topo, max_iters)) {
+        // the whole solve in one launch
+        nimble::PatchAdaptive pa;
+        pa.terms = a.terms;
+        pa.idle = topo->idle;
+        pa.n_idle = topo->n_idle;
+        pa.check_every = check_every;
+        pa.flags = a.flags;
+        pa.scalars = a.ascal;
+        pa.abort_word = a.patch_abort;
+        e = nimble::launch_patches(d, *p, 1, d_traffic, nullptr, nullptr, eps, max_iters,
+                                   topo->spin_limit, d_splits, d_lambda, s, &pa);
+        if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
+        return adaptive_results(topo, iters_done, lower_bound, s);
+    }
     const double gap = (1.0 + eps) * (1.0 + eps);
     // The device takes the stop decision and publishes it, with the number of checks made, in
     // pinned host memory.  The host enqueues ahead without ever synchronising the stream; it
@@ -1281,18 +1344,11 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
         (void)hipStreamSynchronize(s);
         return fail(NIMBLE_ERR_HIP, "adaptive solve: the device made no progress for 30 s");
     }
-    int32_t flags_host[2] = {0, 0};
     nimble::launch_ad_lambda(d, a, gap, 0, s);
     e = nimble::launch_ad_histogram(d, a, topo->choice_log, topo->log_stride, d_splits, d_lambda, s);
     if (e != hipSuccess) return fail_hip(e, "kernel launch (adaptive regime)");
-    double ascal_host[4] = {0, 0, 0, 0};
-    e = hipMemcpyAsync(flags_host, a.flags, sizeof(flags_host), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(ascal_host, a.ascal, sizeof(ascal_host), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (e != hipSuccess) return fail_hip(e, "adaptive solve (results)");
-    *iters_done = flags_host[1];
-    *lower_bound = ascal_host[2];
+    st = adaptive_results(topo, iters_done, lower_bound, s);
+    if (st != NIMBLE_OK) return st;
     topo->state_ready = true;
     topo->state_log = topo->choice_log;
     return NIMBLE_OK;

@@ -19,10 +19,26 @@ struct DevicePatches {
     const int32_t *desc, *loc_link, *comm, *group;
     const uint32_t *words, *first;
     double *parts;               // [max_teams][2][n_parts]
-    double *maxima;              // [max_teams][2][n_patches]
+    double *maxima;              // [max_teams][2][kPatchCopies][n_patches]
     uint32_t *abort_word;
     double iteration_us;         // estimate of one iteration of max_teams plans
+    bool adaptive;               // the kernel of variable step runs on it
 };
+
+// What a solve of variable step needs besides.
+struct PatchAdaptive {
+    double *terms;               // [patch_adaptive_words]
+    const int32_t *idle;         // links no candidate uses
+    int32_t n_idle, check_every;
+    int32_t *flags;              // out: [0] 2 if the solve was given up, [1] iterations made
+    double *scalars;             // out: [2] best bound
+    uint32_t *abort_word;
+};
+// two buffers of the terms and chunk sums of a check
+inline int64_t patch_adaptive_words(int64_t K, int64_t E)
+{
+    return 2 * (K + E + (K + 255) / 256 + (E + 255) / 256);
+}
 
 struct PatchArgs {
     const int32_t *desc, *loc_link, *comm, *group;
@@ -36,9 +52,14 @@ struct PatchArgs {
     double *parts, *maxima;
     uint32_t *abort_word;
     int64_t n_parts;
-    int32_t K, P, n_patches, plans, teams, iters;
+    int32_t K, P, E, n_patches, plans, teams, iters;
     uint32_t spin_limit;
     double eps;
+    double *terms;               // see PatchAdaptive
+    const int32_t *idle;
+    int32_t n_idle, check_every;
+    int32_t *ad_flags;
+    double *ad_scalars;
 };
 
 // Device-side view of one topology plus the workspace of one solve.
@@ -224,14 +245,14 @@ hipError_t launch_resident(const DeviceTopo &t, int32_t batch, const double *dem
                            int32_t iters, double *splits, double *lambda, hipStream_t s);
 
 // ---- patch kernels: one kernel per solve, a workgroup per patch of the fabric -----------------
-size_t patch_lds_bytes(const DevicePatches &p);      // of the largest patch
+size_t patch_lds_bytes(const DevicePatches &p, bool adaptive);      // of the largest patch
 // workgroups of the kernel a compute unit holds at once (0: it cannot run)
-int patch_blocks_per_cu(const DevicePatches &p, bool cost_max);
+int patch_blocks_per_cu(const DevicePatches &p, bool cost_max, bool adaptive);
 constexpr int32_t kPatchMaxIters = 65535;      // choices are counted in 16 bits
 hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t plans,
                           const double *demand, const double *len_in, double *len_out, double eps,
                           int32_t iters, uint32_t spin_limit, double *splits, double *lambda,
-                          hipStream_t s);
+                          hipStream_t s, const PatchAdaptive *adaptive = nullptr);
 
 // ---- persistent regime: one kernel per solve, grid barriers between the phases -------------
 // `sync_words` is device memory of persistent_sync_bytes() bytes owned by the topology.
@@ -266,6 +287,8 @@ struct AdaptiveState {
     int32_t *host_words;       // pinned host memory the device writes: [0] stopped, [1] checks
                                // made (the device's address of it)
     int32_t *host_words_host;  // the host's address of the same words
+    double *terms;             // patch kernels: terms and chunk sums (PatchAdaptive)
+    uint32_t *patch_abort;
 };
 void launch_ad_reset(const AdaptiveState &a, hipStream_t s);
 // the weak-duality bound under the prices the choices in `choice` were made with

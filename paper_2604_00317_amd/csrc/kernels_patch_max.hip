@@ -6,7 +6,7 @@ namespace nimble {
 
 namespace patch {
 
-PatchKernel multi_kernel_max(const PatchShape &s) { return kernel_for<true, true>(s); }
+PatchKernel multi_kernel_max(const PatchShape &s) { return kernel_for<true, true, false>(s); }
 
 }  // namespace patch
 

@@ -1,4 +1,6 @@
 // Patch kernels for fabrics of one patch (no exchange), and the launcher of all patch kernels.
+#include <algorithm>
+
 #include "patch_kernel.hpp"
 
 namespace nimble {
@@ -7,44 +9,52 @@ namespace patch {
 
 PatchKernel multi_kernel_sum(const PatchShape &s);
 PatchKernel multi_kernel_max(const PatchShape &s);
+PatchKernel adaptive_kernel(const PatchShape &s, bool multi);
 
 namespace {
 
 // every word of the exchange starts with the sign of an exchange that has not happened yet
 __global__ __launch_bounds__(256) void k_patch_clear(unsigned long long *parts, int64_t n_parts,
                                                      unsigned long long *maxima, int64_t n_maxima,
-                                                     uint32_t *abort_word, double *lambda,
-                                                     int plans)
+                                                     unsigned long long *terms, int64_t n_terms,
+                                                     uint32_t *abort_word, int32_t *ad_flags,
+                                                     double *lambda, int plans)
 {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     for (int64_t i = i0; i < n_parts; i += stride) parts[i] = kSign;
     for (int64_t i = i0; i < n_maxima; i += stride) maxima[i] = kSign;
+    for (int64_t i = i0; i < n_terms; i += stride) terms[i] = kSign;
     for (int64_t i = i0; i < plans; i += stride) lambda[i] = 0.0;
-    if (i0 == 0) *abort_word = 0u;
+    if (i0 == 0) {
+        *abort_word = 0u;
+        if (ad_flags != nullptr) ad_flags[0] = 0;
+    }
 }
 
-PatchKernel kernel_of(const DevicePatches &p, bool cost_max)
+PatchKernel kernel_of(const DevicePatches &p, bool cost_max, bool adaptive)
 {
+    if (adaptive) return cost_max ? nullptr : adaptive_kernel(p.shape, p.n_patches > 1);
     if (p.n_patches > 1) return cost_max ? multi_kernel_max(p.shape) : multi_kernel_sum(p.shape);
-    return cost_max ? kernel_for<true, false>(p.shape) : kernel_for<false, false>(p.shape);
+    return cost_max ? kernel_for<true, false, false>(p.shape)
+                    : kernel_for<false, false, false>(p.shape);
 }
 
 }  // namespace
 
 }  // namespace patch
 
-size_t patch_lds_bytes(const DevicePatches &p)
+size_t patch_lds_bytes(const DevicePatches &p, bool adaptive)
 {
     return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups, p.max_comm,
-                                                 p.shape.lanes * p.shape.quads)
+                                                 p.shape.lanes * p.shape.quads, adaptive ? 32 : 8)
                                    .bytes);
 }
 
-int patch_blocks_per_cu(const DevicePatches &p, bool cost_max)
+int patch_blocks_per_cu(const DevicePatches &p, bool cost_max, bool adaptive)
 {
-    const patch::PatchKernel k = patch::kernel_of(p, cost_max);
-    const size_t lds = patch_lds_bytes(p);
+    const patch::PatchKernel k = patch::kernel_of(p, cost_max, adaptive);
+    const size_t lds = patch_lds_bytes(p, adaptive);
     if (k == nullptr || lds > 160 * 1024) return 0;
     const void *f = reinterpret_cast<const void *>(k);
     int n = 0;
@@ -60,11 +70,11 @@ int patch_blocks_per_cu(const DevicePatches &p, bool cost_max)
 hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t plans,
                           const double *demand, const double *len_in, double *len_out, double eps,
                           int32_t iters, uint32_t spin_limit, double *splits, double *lambda,
-                          hipStream_t s)
+                          hipStream_t s, const PatchAdaptive *adaptive)
 {
-    const patch::PatchKernel k = patch::kernel_of(p, t.cost_max);
+    const patch::PatchKernel k = patch::kernel_of(p, t.cost_max, adaptive != nullptr);
     if (k == nullptr) return hipErrorInvalidValue;
-    PatchArgs a;
+    PatchArgs a = {};
     a.desc = p.desc;
     a.loc_link = p.loc_link;
     a.comm = p.comm;
@@ -84,13 +94,25 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     a.n_parts = p.n_parts;
     a.K = t.K;
     a.P = t.P;
+    a.E = t.E;
     a.n_patches = p.n_patches;
     a.plans = plans;
     a.teams = plans < p.max_teams ? plans : p.max_teams;
     a.iters = iters;
     a.spin_limit = spin_limit;
     a.eps = eps;
-    const size_t lds = patch_lds_bytes(p);
+    int64_t n_terms = 0;
+    if (adaptive != nullptr) {
+        a.terms = adaptive->terms;
+        a.idle = adaptive->idle;
+        a.n_idle = adaptive->n_idle;
+        a.check_every = adaptive->check_every;
+        a.ad_flags = adaptive->flags;
+        a.ad_scalars = adaptive->scalars;
+        a.abort_word = adaptive->abort_word;
+        n_terms = patch_adaptive_words(t.K, t.E);
+    }
+    const size_t lds = patch_lds_bytes(p, adaptive != nullptr);
     const void *f = reinterpret_cast<const void *>(k);
     if (lds > 64 * 1024) {
         const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -98,16 +120,20 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
         if (e != hipSuccess) return e;
     }
     void *args[] = {&a};
-    if (p.n_patches == 1)
+    if (p.n_patches == 1 && adaptive == nullptr)
         return hipLaunchKernel(f, dim3(plans), dim3(p.shape.threads), args, lds, s);
-    const int64_t words = a.teams * 2 * p.n_parts;
-    int64_t grid = (words + 255) / 256;
+    const int64_t words = p.n_patches > 1 ? a.teams * 2 * p.n_parts : 0;
+    const int64_t maxima =
+        p.n_patches > 1 ? static_cast<int64_t>(a.teams) * 2 * kPatchCopies * p.n_patches
+                         : 0;
+    int64_t grid = (std::max(words, n_terms) + 255) / 256;
     if (grid > 1024) grid = 1024;
     hipLaunchKernelGGL(patch::k_patch_clear, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s,
                        reinterpret_cast<unsigned long long *>(p.parts), words,
-                       reinterpret_cast<unsigned long long *>(p.maxima),
-                       static_cast<int64_t>(a.teams) * 2 * p.n_patches, p.abort_word, lambda,
-                       plans);
+                       reinterpret_cast<unsigned long long *>(p.maxima), maxima,
+                       reinterpret_cast<unsigned long long *>(a.terms), n_terms, a.abort_word,
+                       a.ad_flags, lambda, plans);
+    if (p.n_patches == 1) return hipLaunchKernel(f, dim3(1), dim3(p.shape.threads), args, lds, s);
     // patches wait for each other, so all of them have to be resident at once: a cooperative
     // launch is refused otherwise
     return hipLaunchCooperativeKernel(f, dim3(a.teams * p.n_patches), dim3(p.shape.threads), args,

@@ -6,7 +6,7 @@ namespace nimble {
 
 namespace patch {
 
-PatchKernel multi_kernel_sum(const PatchShape &s) { return kernel_for<false, true>(s); }
+PatchKernel multi_kernel_sum(const PatchShape &s) { return kernel_for<false, true, false>(s); }
 
 }  // namespace patch
 

@@ -43,7 +43,8 @@ constexpr int kSumBits = 61, kLowBits = 44;
 
 // LDS of a patch, byte offsets.  The prices come first: a slot's offsets are LDS addresses.  The
 // state of a link is one record; the choices of a candidate are counted in 16 bits, those of slot
-// s (of all the lanes' slots) of the patch's commodity c at count + (c * slots + s) * 8.
+// s (of all the lanes' slots) of the patch's commodity c at count + (c * slots + s) * 8.  A solve
+// of variable step sums its steps instead, a double per candidate (slot_bytes 32).
 struct LinkState {
     unsigned long long load, low;      // load so far, see Grid
     double len, S, invcap;
@@ -52,7 +53,8 @@ struct Lds {
     int link, red, group, count, bytes;
 };
 
-__host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int n_comm, int slots)
+__host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int n_comm, int slots,
+                                          int slot_bytes)
 {
     Lds l;
     int o = 8 * (n_local + 2);                  // [n_local] +0.0, [n_local + 1] +inf
@@ -60,7 +62,7 @@ __host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int n_comm,
     l.red = o;     o += 8 * 40;
     o = (o + 15) & ~15;
     l.group = o;   o += 16 * n_groups;
-    l.count = o;   o += 8 * n_comm * slots;
+    l.count = o;   o += slot_bytes * n_comm * slots;
     l.bytes = o;
     return l;
 }
@@ -303,7 +305,53 @@ __device__ __forceinline__ void take_words(uint32_t (&keep)[NW], const uint32_t 
     for (int x = 0; x < NW; ++x) keep[x] = select(better, w[x], keep[x]);
 }
 
-template <bool PRODUCT, int L, int QL, bool MAXC, bool MULTI>
+// x[0] + x[1] + ... + x[n-1] in that order, of words other patches (or this one) publish.  256
+// words are asked for together; the additions are one dependent chain whatever is done, so every
+// lane makes all of them, the terms broadcast lane by lane.
+__device__ __forceinline__ double sum_in_order(const double *x, int n, unsigned phase,
+                                               unsigned limit, unsigned *abort_word, int &dead,
+                                               int lane)
+{
+    double s = 0.0;
+    for (int b = 0; b < n; b += 4 * kWave) {                          // wave-uniform, as all below
+        unsigned long long v[4];
+        unsigned polls = 0;
+        for (;;) {
+            bool wrong = false;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = b + q * kWave + lane;
+                v[q] = static_cast<unsigned long long>(phase) << 63;
+                if (i < n) v[q] = get_word(x + i);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) wrong = wrong || static_cast<unsigned>(v[q] >> 63) != phase;
+            if (__builtin_amdgcn_ballot_w64(wrong) == 0ull || dead) break;
+            int late = keep_waiting(polls, limit, abort_word) ? 0 : 1;
+            dead = __builtin_amdgcn_readfirstlane(late);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const double w = word_value(v[q]);
+            const int lo = __double2loint(w), hi = __double2hiint(w);
+            const int m = n - b - q * kWave;
+            if (m >= kWave) {
+#pragma unroll 8
+                for (int i = 0; i < kWave; ++i)
+                    s = s + __hiloint2double(__builtin_amdgcn_readlane(hi, i),
+                                             __builtin_amdgcn_readlane(lo, i));
+            } else {
+                for (int i = 0; i < m; ++i)
+                    s = s + __hiloint2double(__builtin_amdgcn_readlane(hi, i),
+                                             __builtin_amdgcn_readlane(lo, i));
+            }
+        }
+    }
+    return s;
+}
+
+// ADAPT: the solve of variable step (one plan, path cost = the sum of the prices).
+template <bool PRODUCT, int L, int QL, bool MAXC, bool MULTI, bool ADAPT>
 __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
 {
     constexpr int NW = PRODUCT ? kPatchWordsProduct : kPatchWordsPlain;
@@ -317,7 +365,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
     const int n_comm = dsc[6];
     const int32_t *comm = a.comm + dsc[5];
     const int32_t *loc_link = a.loc_link + dsc[0];
-    const Lds l = lds_layout(n_local, n_groups, n_comm, L * QL);
+    constexpr int kSlotBytes = ADAPT ? 32 : 8;
+    const Lds l = lds_layout(n_local, n_groups, n_comm, L * QL, kSlotBytes);
     const uint32_t pad = 8u * static_cast<uint32_t>(n_local);
     double *price = lds_ptr(0), *red = lds_ptr(l.red);
     LinkState *links = reinterpret_cast<LinkState *>(lds_ptr(l.link));
@@ -343,7 +392,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
     double *parts_of_team = nullptr, *maxima_of_team = nullptr;
     if constexpr (MULTI) {
         parts_of_team = a.parts + static_cast<size_t>(team) * 2 * a.n_parts;
-        maxima_of_team = a.maxima + static_cast<size_t>(team) * 2 * a.n_patches;
+        maxima_of_team = a.maxima + static_cast<size_t>(team) * 2 * kPatchCopies * a.n_patches;
     }
 
     for (int plan = team; plan < a.plans; plan += MULTI ? a.teams : a.plans) {
@@ -362,7 +411,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             links[i].invcap = ic;
             price[i] = MAXC ? l0 : l0 * ic;
         }
-        for (int i = t; i < n_comm * L * QL; i += NT) lds_ptr(l.count)[i] = 0.0;
+        for (int i = t; i < n_comm * L * QL * (kSlotBytes / 8); i += NT) lds_ptr(l.count)[i] = 0.0;
         if (t == 0) {
             price[n_local] = 0.0;
             price[n_local + 1] = __builtin_inf();
@@ -401,22 +450,24 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         }
         const Demand units = on_grid(d, gr);
         // width rho: every commodity that can reach a link counts once
+        if constexpr (!ADAPT) {
 #pragma unroll
-        for (int q = 0; q < QL; ++q) {
-            const uint32_t once = a.first[(static_cast<size_t>(p) * QL + q) * NT + t];
-            constexpr int n_off = PRODUCT ? 9 : 20;
-            uint32_t off[n_off];
+            for (int q = 0; q < QL; ++q) {
+                const uint32_t once = a.first[(static_cast<size_t>(p) * QL + q) * NT + t];
+                constexpr int n_off = PRODUCT ? 9 : 20;
+                uint32_t off[n_off];
 #pragma unroll
-            for (int x = 0; x < n_off; ++x) {
-                // where offset x of a slot is kept (see host_patch.hpp)
-                const uint32_t word = PRODUCT ? w[q][x < 4 ? x / 2 : x == 4 ? 2 : (x + 1) / 2]
-                                              : w[q][x % 5 == 4 ? 8 + x / 10 : 2 * (x / 5) + (x % 5) / 2];
-                const bool high = PRODUCT ? (x < 4 ? x & 1 : x != 4 && !(x & 1))
-                                          : (x % 5 == 4 ? (x / 5) & 1 : (x % 5) & 1);
-                off[x] = high ? word >> 16 : word & 0xFFFFu;
-                if (!((once >> x) & 1u)) off[x] = pad;
+                for (int x = 0; x < n_off; ++x) {
+                    // where offset x of a slot is kept (see host_patch.hpp)
+                    const uint32_t word = PRODUCT ? w[q][x < 4 ? x / 2 : x == 4 ? 2 : (x + 1) / 2]
+                                                  : w[q][x % 5 == 4 ? 8 + x / 10 : 2 * (x / 5) + (x % 5) / 2];
+                    const bool high = PRODUCT ? (x < 4 ? x & 1 : x != 4 && !(x & 1))
+                                              : (x % 5 == 4 ? (x / 5) & 1 : (x % 5) & 1);
+                    off[x] = high ? word >> 16 : word & 0xFFFFu;
+                    if (!((once >> x) & 1u)) off[x] = pad;
+                }
+                add_loads<n_off>(links, pad, off, gr, units);
             }
-            add_loads<n_off>(links, pad, off, gr, units);
         }
         __syncthreads();
         double wmax = 0.0;
@@ -426,11 +477,12 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             for (int c = gd.z; c < gd.y; c += gd.w)
                 put_word(dst + c * kPatchGroup, c == gd.z ? v : 0.0, (exchange >> 1) & 1u);
         };
-        for (int i = t; i < n_local; i += NT) {
-            const double reach = take_load(links[i], gr);
-            if (MULTI && i < n_shared) publish(reach, i);
-            else wmax = fmax(wmax, reach * links[i].invcap);
-        }
+        if constexpr (!ADAPT)
+            for (int i = t; i < n_local; i += NT) {
+                const double reach = take_load(links[i], gr);
+                if (MULTI && i < n_shared) publish(reach, i);
+                else wmax = fmax(wmax, reach * links[i].invcap);
+            }
         // f(local link, load) for the shared links, a lane each; the groups of a patch are dealt
         // to its waves in bundles
         auto bundle_of = [&](int q0) {
@@ -453,38 +505,40 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                     f(q0 * kPatchGroup + lane, load);
             }
         };
-        if constexpr (MULTI) {
+        if constexpr (MULTI && !ADAPT) {
             for_shared([&](int i, double reach) { wmax = fmax(wmax, reach * links[i].invcap); });
             exchange += 1u;
         }
-        wmax = wave_max(wmax);
-        __syncthreads();
-        if (lane == 0) red[wave] = wmax;
-        __syncthreads();
-        for (int q = 0; q < n_waves; ++q) wmax = fmax(wmax, red[q]);
-        if constexpr (MULTI) {
-            // the maximum over all patches of the team
-            double *mx = maxima_of_team + (meeting & 1u) * a.n_patches;
-            const unsigned phase = (meeting >> 1) & 1u;
-            if (t == 0) put_word(mx + p, wmax, phase);
-            for (int b = t; b < a.n_patches; b += NT) {
-                unsigned polls = 0;
-                unsigned long long v;
-                for (;;) {
-                    v = get_word(mx + b);
-                    if (static_cast<unsigned>(v >> 63) == phase || dead) break;
-                    if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
-                }
-                wmax = fmax(wmax, word_value(v));
-            }
-            meeting += 1u;
-            dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
+        if constexpr (!ADAPT) {
             wmax = wave_max(wmax);
             __syncthreads();
             if (lane == 0) red[wave] = wmax;
-            if (dead) *s_flag = 1;
             __syncthreads();
             for (int q = 0; q < n_waves; ++q) wmax = fmax(wmax, red[q]);
+            if constexpr (MULTI) {
+                // the maximum over all patches of the team
+                double *mx = maxima_of_team + (meeting & 1u) * (kPatchCopies * a.n_patches);
+                const unsigned phase = (meeting >> 1) & 1u;
+                if (t == 0) put_word(mx + p, wmax, phase);
+                for (int b = t; b < a.n_patches; b += NT) {
+                    unsigned polls = 0;
+                    unsigned long long v;
+                    for (;;) {
+                        v = get_word(mx + b);
+                        if (static_cast<unsigned>(v >> 63) == phase || dead) break;
+                        if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
+                    }
+                    wmax = fmax(wmax, word_value(v));
+                }
+                meeting += 1u;
+                dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
+                wmax = wave_max(wmax);
+                __syncthreads();
+                if (lane == 0) red[wave] = wmax;
+                if (dead) *s_flag = 1;
+                __syncthreads();
+                for (int q = 0; q < n_waves; ++q) wmax = fmax(wmax, red[q]);
+            }
         }
         const double invrho = wmax > 0.0 ? 1.0 / wmax : 0.0;
 
@@ -500,8 +554,10 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             s.len = ln;
             price[i] = MAXC ? ln : ln * ic;
         };
-        // Scan and scatter of an iteration.
-        auto pass = [&]() {
+        // Scan and scatter of an iteration.  ADAPT: `mark` receives the LDS offset of the chosen
+        // candidate's weight (0: not this lane's to keep), and where `terms` is given the
+        // commodity's term of the bound, demand times cheapest cost, is published there.
+        auto pass = [&](double *terms, unsigned term_phase, uint32_t &mark) {
             double best = 0.0;
             uint32_t wb[NW];             // the slot that holds the best candidate so far
             int sb = 0, pos = 0;
@@ -594,15 +650,166 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             }
             if (mine) {
                 add_loads<5>(links, pad, off, gr, units);
-                uint32_t *n = reinterpret_cast<uint32_t *>(
-                    lds_ptr(l.count + 8 * (g * (L * QL) + sb * L + j) + 4 * (pos >> 1)));
-                (void)__hip_atomic_fetch_add(n, 1u << (16 * (pos & 1)), __ATOMIC_RELAXED,
-                                             __HIP_MEMORY_SCOPE_WORKGROUP);
+                const int slot = l.count + kSlotBytes * (g * (L * QL) + sb * L + j);
+                if constexpr (ADAPT) {
+                    mark = static_cast<uint32_t>(slot + 8 * pos);
+                    if (terms != nullptr) put_word(terms + comm[g], d * best, term_phase);
+                } else {
+                    (void)__hip_atomic_fetch_add(
+                        reinterpret_cast<uint32_t *>(lds_ptr(slot + 4 * (pos >> 1))),
+                        1u << (16 * (pos & 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
             }
         };
 
-        for (int it = 0; it < a.iters; ++it) {
-            if (busy) pass();                                                // wave-uniform
+        double W = 0.0;                  // ADAPT: sum of the steps
+        if constexpr (ADAPT) {
+            // Iteration t steps by sigma = 1 / (largest normalised load of any link), so all
+            // patches meet once more per iteration.  Every check_every iterations the bound
+            // (sum of demand * cheapest cost) / (sum of lengths) is taken with sums in index
+            // order: patches publish the terms, the chunks of 256 terms are dealt to the waves of
+            // all patches, and the first wave of every patch adds the chunk sums and decides --
+            // all alike, so nobody has to be told.
+            const int n_alpha = (a.K + 255) / 256, n_d = (a.E + 255) / 256;
+            const int64_t n_words = static_cast<int64_t>(a.K) + a.E + n_alpha + n_d;
+            const double gap = (1.0 + a.eps) * (1.0 + a.eps);
+            double lb_best = 0.0;
+            int done = 0, until_check = a.check_every;
+            unsigned checks = 0u;
+            // The largest v of all patches; `row` alternates between calls.  The first wave leaves
+            // its patch's maximum in every copy of the list and waits for the others' in its own
+            // copy: one list polled by every wave of every patch made the few cache lines it
+            // lies in the bottleneck.
+            auto meet = [&](double v, int row) {
+                double *r = red + 16 * row;
+                v = wave_max(v);
+                if (lane == 0) r[wave] = v;
+                __syncthreads();
+                if (MULTI ? wave == 0 : true)
+                    for (int q = 0; q < n_waves; ++q) v = fmax(v, r[q]);
+                if constexpr (MULTI) {
+                    if (wave == 0) {
+                        double *mx = maxima_of_team + (meeting & 1u) * (kPatchCopies * a.n_patches);
+                        const unsigned phase = (meeting >> 1) & 1u;
+                        if (lane < kPatchCopies) put_word(mx + lane * a.n_patches + p, v, phase);
+                        mx += (p & (kPatchCopies - 1)) * a.n_patches;
+                        for (int b = lane; b < a.n_patches; b += kWave) {
+                            unsigned polls = 0;
+                            unsigned long long x;
+                            for (;;) {
+                                x = get_word(mx + b);
+                                if (static_cast<unsigned>(x >> 63) == phase || dead) break;
+                                if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
+                            }
+                            v = fmax(v, word_value(x));
+                        }
+                        dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
+                        v = wave_max(v);
+                        if (lane == 0) r[0] = v;
+                    }
+                    meeting += 1u;
+                    __syncthreads();
+                    v = r[0];
+                }
+                return v;
+            };
+            for (;;) {
+                until_check -= 1;
+                const bool check = until_check == 0;                         // uniform
+                double *terms = a.terms + (checks & 1u) * n_words;
+                const unsigned phase = (checks >> 1) & 1u;
+                uint32_t mark = 0u;
+                if (busy) pass(check ? terms : nullptr, phase, mark);        // wave-uniform
+                __syncthreads();
+                double m = 0.0;
+                // the normalised load of a link waits for the step where its price was
+                auto put_u = [&](int i, double load) {
+                    const double u = load * links[i].invcap;
+                    price[i] = u;
+                    m = fmax(m, u);
+                };
+                if constexpr (MULTI)
+                    for (int i = t; i < n_shared; i += NT) publish(take_load(links[i], gr), i);
+                for (int i = n_shared + t; i < n_local; i += NT) put_u(i, take_load(links[i], gr));
+                if (check) {
+                    for (int i = t; i < n_local; i += NT) {
+                        const int e = loc_link[i];
+                        if (e >= 0 && (e & kPatchExport))
+                            put_word(terms + a.K + (e & ~kPatchExport), links[i].len, phase);
+                    }
+                    if (p == 0)                      // links no candidate uses keep length 1
+                        for (int i = t; i < a.n_idle; i += NT)
+                            put_word(terms + a.K + a.idle[i], 1.0, phase);
+                }
+                if constexpr (MULTI) {
+                    for_shared(put_u);
+                    exchange += 1u;
+                }
+                const double umax = meet(m, 0);
+                double smax = 0.0;
+                const bool traffic = umax > 0.0;
+                if (traffic) {
+                    const double sigma = 1.0 / umax;
+                    W = W + sigma;
+                    for (int i = t; i < n_local; i += NT) {
+                        LinkState &s = links[i];
+                        const double su = sigma * price[i];
+                        const double S = s.S + su;
+                        s.S = S;
+                        smax = fmax(smax, S);
+                        const double t1 = a.eps * su;
+                        const double t2 = 1.0 + t1;
+                        const double ln = s.len * t2;
+                        s.len = ln;
+                        price[i] = MAXC ? ln : ln * s.invcap;
+                    }
+                    if (mark != 0u) *lds_ptr(mark) = *lds_ptr(mark) + sigma;
+                    done += 1;
+                }
+                bool stop = !traffic || done == a.iters;
+                if (check) {
+                    double *sums = terms + a.K + a.E;
+                    for (int c = p * n_waves + wave; c < n_alpha + n_d; c += a.n_patches * n_waves) {
+                        const bool alpha = c < n_alpha;
+                        const int at = 256 * (alpha ? c : c - n_alpha);
+                        const int n = (alpha ? a.K : a.E) - at;
+                        const double v = sum_in_order(terms + (alpha ? 0 : a.K) + at,
+                                                      n < 256 ? n : 256, phase, a.spin_limit,
+                                                      a.abort_word, dead, lane);
+                        if (lane == 0) put_word(sums + c, v, phase);
+                    }
+                    smax = meet(smax, 1);
+                    if (wave == 0 && traffic) {
+                        const double alpha = sum_in_order(sums, n_alpha, phase, a.spin_limit,
+                                                          a.abort_word, dead, lane);
+                        const double D = sum_in_order(sums + n_alpha, n_d, phase, a.spin_limit,
+                                                      a.abort_word, dead, lane);
+                        const double lb = alpha / D;
+                        if (lb > lb_best) lb_best = lb;
+                        const double lam = smax / W;
+                        const double bound = gap * lb_best;
+                        if (lam <= bound) stop = true;
+                    }
+                    until_check = a.check_every;
+                    checks += 1u;
+                }
+                if (dead) atomicOr(s_flag, 1);
+                // (`stop` may be set in the first wave only: the flag is what counts)
+                else if (stop && wave == 0 && lane == 0) atomicOr(s_flag, 2);
+                __syncthreads();
+                if (__builtin_amdgcn_readfirstlane(*s_flag) != 0) break;     // workgroup-uniform
+            }
+            if (t == 0) {
+                if (*s_flag & 1) a.ad_flags[0] = 2;
+                if (p == 0) {
+                    a.ad_flags[1] = done;
+                    a.ad_scalars[2] = lb_best;
+                }
+            }
+        }
+        for (int it = 0; !ADAPT && it < a.iters; ++it) {
+            uint32_t mark;
+            if (busy) pass(nullptr, 0u, mark);                               // wave-uniform
             __syncthreads();
             if constexpr (MULTI) {
                 for (int i = t; i < n_shared; i += NT) publish(take_load(links[i], gr), i);
@@ -617,7 +824,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             if constexpr (MULTI)
                 if (__builtin_amdgcn_readfirstlane(*s_flag) != 0) break;     // workgroup-uniform
         }
-        const double T = static_cast<double>(a.iters);
+        const double T = ADAPT ? W : static_cast<double>(a.iters);
         if (g < n_comm) {
             double *out0 = splits + a.comm_ptr[comm[g]];
 #pragma unroll
@@ -627,8 +834,17 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 const int shift = static_cast<int>((meta >> 7) & 3u);
                 if (n == 0) continue;
                 double *out = out0 + (meta & 127u);
-                const uint2 c = *reinterpret_cast<const uint2 *>(
-                    lds_ptr(l.count + 8 * (g * (L * QL) + q * L + j)));
+                const int slot = l.count + kSlotBytes * (g * (L * QL) + q * L + j);
+                if constexpr (ADAPT) {
+                    const int first = static_cast<int>(meta & 127u);
+#pragma unroll
+                    for (int pos = 0; pos < 4; ++pos)
+                        if ((pos & ((1 << shift) - 1)) == 0 && (pos >> shift) < n)
+                            out[pos >> shift] = T > 0.0 ? lds_ptr(slot)[pos] / T
+                                                        : (first + (pos >> shift) == 0 ? 1.0 : 0.0);
+                    continue;
+                }
+                const uint2 c = *reinterpret_cast<const uint2 *>(lds_ptr(slot));
                 const uint32_t n4[4] = {c.x & 0xFFFFu, c.x >> 16, c.y & 0xFFFFu, c.y >> 16};
 #pragma unroll
                 for (int pos = 0; pos < 4; ++pos)
@@ -648,11 +864,11 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         __syncthreads();
         if (t == 0) {
             for (int q = 0; q < n_waves; ++q) smax = fmax(smax, red[q]);
-            double lam = smax / T;
+            double lam = ADAPT && !(T > 0.0) ? 0.0 : smax / T;
             if constexpr (MULTI) {
                 // (the largest of non-negative numbers is the largest of their bit patterns, and
                 // a quiet NaN is above them all)
-                if (*s_flag != 0) lam = __longlong_as_double(0x7FF8000000000000ll);
+                if (*s_flag & 1) lam = __longlong_as_double(0x7FF8000000000000ll);
                 (void)__hip_atomic_fetch_max(
                     reinterpret_cast<unsigned long long *>(a.lambda + plan),
                     static_cast<unsigned long long>(__double_as_longlong(lam)), __ATOMIC_RELAXED,
@@ -662,7 +878,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             }
         }
         if constexpr (MULTI) {
-            if (*s_flag != 0) {
+            if (!ADAPT && *s_flag != 0) {
                 // a team that gave up leaves its other plans undone
                 if (t == 0)
                     for (int rest = plan + a.teams; rest < a.plans; rest += a.teams)
@@ -677,12 +893,12 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
 
 using PatchKernel = void (*)(PatchArgs);
 
-template <bool MAXC, bool MULTI>
+template <bool MAXC, bool MULTI, bool ADAPT>
 PatchKernel kernel_for(const PatchShape &s)
 {
 #define NIMBLE_PATCH(PR, LL, QQ)                                                               \
     if (s.product == PR && s.lanes == LL && s.quads == QQ)                                     \
-        return k_patch<PR != 0, LL, QQ, MAXC, MULTI>;
+        return k_patch<PR != 0, LL, QQ, MAXC, MULTI, ADAPT>;
     NIMBLE_PATCH_SHAPES(NIMBLE_PATCH)
 #undef NIMBLE_PATCH
     return nullptr;

@@ -100,6 +100,45 @@ def test_fractional_demands_are_deterministic(monkeypatch, strips):
         assert np.mean(a[0] != ref["splits"]) < 0.05
 
 
+def _adaptive(h, t, d, eps, iters, every):
+    import torch
+    splits = torch.full((t.n_paths,), float("nan"), dtype=torch.float64, device="cuda:0")
+    lam = torch.full((1,), float("nan"), dtype=torch.float64, device="cuda:0")
+    done, lb = B.nimble_plan_solve_adaptive(h, torch.as_tensor(d).to("cuda:0"), eps, iters, every,
+                                            splits, lam)
+    return splits.cpu().numpy(), float(lam.item()), done, lb
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("strips,lanes", [(1, 1), (1, 4), (2, 2), (3, 0)])
+def test_variable_step_matches_the_oracle(monkeypatch, strips, lanes):
+    """The solve of variable step in one launch: the oracle's bits, its stop iteration and bound,
+    with checks every iteration, never, and on the last; sums of 1, 255..257 and more terms (1x4:
+    12, 3x4 xor: 132, 2x8: 240, 2x9: 306 pairs); no traffic; links no candidate uses; several
+    solves with one handle; the launched solve as well."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_LANES", str(lanes))
+    cases = [(f, fabric(*f)) for f in FABRICS + [(2, 9, "own")]] + \
+            [(r, _random(*r)) for r in RANDOM + [(8, 300, 256, 6, 3), (9, 257, 257, 3, 2)]]
+    for name, t in cases:
+        d = np.floor(np.random.default_rng(3).pareto(1.1, t.n_comm) * 1e6)
+        h = B.nimble_topo_create(*t.csr())
+        try:
+            for iters, every in ((1, 1), (40, 1), (41, 7), (30, 31), (300, 25)):
+                print(f"[patch adaptive] {name} strips={strips} lanes={lanes} {iters}/{every}",
+                      flush=True)
+                ref = oracle.solve_adaptive(*t.csr(), d, 0.1, iters, every)
+                splits, lam, done, lb = _adaptive(h, t, d, 0.1, iters, every)
+                assert (done, lb, lam) == (ref["iters"], ref["lb"], ref["lam"]), (name, iters)
+                assert np.array_equal(splits, ref["splits"]), (name, iters)
+            ref = oracle.solve_adaptive(*t.csr(), 0 * d, 0.1, 9, 1)
+            splits, lam, done, lb = _adaptive(h, t, 0 * d, 0.1, 9, 1)
+            assert (done, lb, lam) == (0, 0.0, 0.0) and np.array_equal(splits, ref["splits"])
+        finally:
+            h.close()
+
+
 @pytest.mark.gpu
 def test_a_team_that_cannot_meet_gives_up(monkeypatch):
     """A poll limit of zero: patches that have to wait for each other abandon the solve, lambda is
