@@ -96,6 +96,29 @@ def test_every_group_width_with_ties(oracle_mod, B, max_paths, iters):
         assert np.array_equal(got, ref)
 
 
+@pytest.mark.parametrize("max_paths", [5, 16, 32, 64])
+@pytest.mark.parametrize("iters", [1, 977, (1 << 24) - 1, 1 << 24])
+def test_quotas_at_the_ends_of_their_range(oracle_mod, B, max_paths, iters):
+    """Chunk numbers up to 2^31 - 1, quotients that are whole or one step from it, on both sides of
+    the iteration count from which 64-bit remainders are kept.  (Chunks of at most 2^31 bytes: a
+    demand of 2^31 chunks then stays below 2^63, the bytes that 64-bit whole numbers hold.)"""
+    rng = np.random.default_rng(iters + max_paths)
+    t = W.random_topology(rng, 40, 150, max_paths, 2)
+    cp = t.comm_path_ptr
+    splits = np.zeros(t.n_paths)
+    for k in range(t.n_comm):
+        n = cp[k + 1] - cp[k]
+        splits[cp[k]:cp[k + 1]] = rng.multinomial(iters, rng.dirichlet(np.ones(n) * 0.5)) / iters
+    whole = np.r_[(1 << 31) - 1, 0, 1, iters, max(1, iters - 1), (1 << 31) // iters * iters - 1,
+                  rng.integers(0, 1 << 31, t.n_comm - 6)].astype(np.float64)
+    whole = np.minimum(whole, (1 << 31) - 1)
+    for chi in (1, 3, 4096, 1 << 31):
+        d = whole * float(chi) + (chi // 2 if chi < 1 << 20 else 0)
+        ref = oracle_mod.quantize(cp, d, splits, iters, chi, 0.0)
+        got = gpu_quantize(B, t, d, splits, iters, chi, 0.0)
+        assert np.array_equal(got, ref), chi
+
+
 def test_too_many_chunks_is_flagged_and_bad_arguments_are_refused(B):
     import torch
     w = W.make_config(0)
