@@ -52,10 +52,12 @@ enum {
 
 /* kernel regimes, for nimble_topo_set_regime (testing and benchmarking) */
 enum {
-    NIMBLE_REGIME_AUTO = 0,     /* chosen from the problem size and the number of plans: resident
-                                   when the per-plan state fits in LDS, unless so few plans of a
-                                   fabric with long reverse rows are asked for that streaming
-                                   them one after the other is faster */
+    NIMBLE_REGIME_AUTO = 0,     /* chosen from the problem size and the number of plans: the patch
+                                   kernels where the fabric fits them (reported as resident if
+                                   one workgroup solves a plan, else as persistent); otherwise
+                                   resident when the per-plan state fits in LDS, unless so few
+                                   plans of a fabric with long reverse rows are asked for that
+                                   streaming them one after the other is faster */
     NIMBLE_REGIME_RESIDENT = 1, /* one workgroup per plan, whole iteration loop in one kernel,
                                    state in LDS */
     NIMBLE_REGIME_STREAM = 2,   /* one kernel per phase: two or three launches per iteration
@@ -109,7 +111,7 @@ void nimble_topo_destroy(nimble_topo_t *topo);
  *               could overflow: NIMBLE_ERR_RANGE)
  *   d_splits    device [n_paths] out: times chosen / iters; sums to 1 per commodity
  *   d_lambda    device [1] out: max_e (1/cap_e) * sum_p d_k(p) splits_p, in seconds
- *               (NaN if the persistent regime abandoned the solve, see
+ *               (NaN if patches that wait for each other, or the persistent regime, abandoned the solve, see
  *               nimble_debug_set_spin_limit)
  *   hip_stream  hipStream_t (NULL = default stream).  The call only enqueues work; outputs are
  *               valid after the stream is synchronised.  No host synchronisation inside.

@@ -516,7 +516,8 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
     done = false;
     if (topo->forced_regime != NIMBLE_REGIME_AUTO && topo->forced_regime != NIMBLE_REGIME_RESIDENT)
         return NIMBLE_OK;
-    // (lists of a single node: a thread per commodity and link with everything in registers)
+    // (lists of a single node: a thread per commodity and link with everything in registers; one
+    // node of 8 GPUs, 200 iterations: 82 us, with the patch kernel 116)
     if (d_len == nullptr && nimble::resident_in_registers(topo->d)) return NIMBLE_OK;
     const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s,
                                                   topo->forced_regime == NIMBLE_REGIME_RESIDENT);

@@ -26,6 +26,11 @@
 // 2^-61 of the patch's total and 2^-105 of it, and the sum is rounded once at the end.  (64-bit
 // integer additions also take the LDS 6.2 cycles a wave where binary64 ones take 8.2, and 2
 // instead of 3 for every lane that meets another on the same link.)
+//
+// What bounds it and what it measured, us per iteration against two launches per iteration (and,
+// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 2.64 -> 0.84 (one
+// patch: the chain scan, barrier, scatter, update), 16 nodes 7.2 -> 2.7 (the trip of a word from
+// patch to patch takes 1.6), 64 nodes 18.5 -> 7.7 (scan 3.6, then the parts of 31 users).
 #pragma once
 #include <hip/hip_runtime.h>
 
