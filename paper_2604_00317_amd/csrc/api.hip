@@ -112,6 +112,7 @@ struct nimble_topo {
     int32_t last_regime = NIMBLE_REGIME_AUTO;
     int64_t bytes_per_iter = 0, bytes_argmin = 0, bytes_reduce = 0, bytes_update = 0;
     int64_t bytes_lds_argmin = 0;   // LDS bytes the lane-major record kernels read per launch
+    bool patch_solved = false;  // a solve ran on the patch kernels (which leave the workspace alone)
     bool state_ready = false;   // a stream-regime solve has initialised the workspace
     uint8_t *state_log = nullptr;   // the log that solve wrote its choices to (null: counters)
     // per-iteration choice log of the streaming regime (rows of log_stride bytes); grows on
@@ -527,6 +528,7 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
                                topo->spin_limit, d_splits, d_lambda, s);
     if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
     topo->last_regime = p->n_patches > 1 ? NIMBLE_REGIME_PERSISTENT : NIMBLE_REGIME_RESIDENT;
+    topo->patch_solved = true;
     done = true;
     return NIMBLE_OK;
 }
@@ -1393,11 +1395,22 @@ nimble_status_t nimble_debug_run_phase(nimble_topo_t *topo, int32_t phase, int32
     if (phase < 0 || phase > 2 || reps < 1) return fail(NIMBLE_ERR_INVALID, "bad phase or reps");
     if (phase == 2 && (topo->d.n_blocks > 0 || topo->d.n_gblocks > 0))
         return fail(NIMBLE_ERR_INVALID, "the length update is part of phase 1 on this topology");
-    if (!topo->state_ready)
+    if (!topo->state_ready && !topo->patch_solved)
         return fail(NIMBLE_ERR_INVALID, "run a streaming-regime solve on this topology first");
     nimble_status_t st = check_device(topo);
     if (st != NIMBLE_OK) return st;
     hipStream_t s = static_cast<hipStream_t>(hip_stream);
+    if (!topo->state_ready) {
+        // the workspace as the prologue and the first scan of a streamed solve leave it
+        nimble::DeviceTopo d = topo->d;
+        d.batch = 1;
+        topo->state_log = own_log(topo, 1);
+        nimble::launch_init(d, d_traffic, nullptr, s);
+        nimble::launch_width(d, d_traffic, s);
+        nimble::launch_argmin(d, topo->state_log ? topo->state_log : d.choice,
+                              topo->state_log ? nullptr : d.count, s);
+        topo->state_ready = true;
+    }
     for (int32_t r = 0; r < reps; ++r) {
         uint8_t *row = topo->state_log ? topo->state_log : topo->d.choice;
         if (phase == 0) nimble::launch_argmin(topo->d, row, topo->state_log ? nullptr : topo->d.count, s);

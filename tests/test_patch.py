@@ -158,3 +158,25 @@ def test_a_team_that_cannot_meet_gives_up(monkeypatch):
         assert lam == ref["lam"] and np.array_equal(splits, ref["splits"])
     finally:
         h.close()
+
+
+@pytest.mark.gpu
+def test_phases_can_be_timed_after_a_solve_in_one_launch():
+    """The patch kernels leave the streaming workspace alone: the phases set it up themselves, a
+    topology that solved nothing is still refused, and plans are the same afterwards."""
+    import torch
+    t = fabric(7, 6, "pair")
+    d = np.floor(np.random.default_rng(9).pareto(1.1, t.n_comm) * 1e6)
+    dd = torch.as_tensor(d).to("cuda:0")
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        with pytest.raises(B.NimbleError):
+            B.nimble_debug_run_phase(h, 0, 1, dd)
+        splits, lam = B.plan(h, d, 0.05, 30)
+        for phase in (1, 0, 1):
+            B.nimble_debug_run_phase(h, phase, 2, dd)
+        torch.cuda.synchronize()
+        again, lam2 = B.plan(h, d, 0.05, 30)
+        assert lam == lam2 and np.array_equal(splits, again)
+    finally:
+        h.close()
