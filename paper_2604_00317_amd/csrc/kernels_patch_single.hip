@@ -126,13 +126,16 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     const int64_t maxima =
         p.n_patches > 1 ? static_cast<int64_t>(a.teams) * 2 * kPatchCopies * p.n_patches
                          : 0;
-    int64_t grid = (std::max(words, n_terms) + 255) / 256;
+    // (patches that share no link have no parts, but maxima, an abort word and a lambda all the same)
+    int64_t grid = (std::max({words, maxima, n_terms, static_cast<int64_t>(plans)}) + 255) / 256;
     if (grid > 1024) grid = 1024;
     hipLaunchKernelGGL(patch::k_patch_clear, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s,
                        reinterpret_cast<unsigned long long *>(p.parts), words,
                        reinterpret_cast<unsigned long long *>(p.maxima), maxima,
                        reinterpret_cast<unsigned long long *>(a.terms), n_terms, a.abort_word,
                        a.ad_flags, lambda, plans);
+    const hipError_t cleared = hipGetLastError();
+    if (cleared != hipSuccess) return cleared;
     if (p.n_patches == 1) return hipLaunchKernel(f, dim3(1), dim3(p.shape.threads), args, lds, s);
     // patches wait for each other, so all of them have to be resident at once: a cooperative
     // launch is refused otherwise

@@ -24,6 +24,34 @@ RANDOM = [(1, 7, 3, 4, 3), (2, 40, 130, 9, 5), (3, 64, 65, 30, 4), (4, 1, 5, 1, 
           (5, 500, 1500, 12, 2)]
 
 
+def _topology(links, caps, lists):
+    """A topology from per-commodity lists of candidate paths (lists of link ids)."""
+    cp = np.cumsum([0] + [len(c) for c in lists]).astype(np.int32)
+    paths = [p for c in lists for p in c]
+    lp = np.cumsum([0] + [len(p) for p in paths]).astype(np.int32)
+    pl = np.array([e for p in paths for e in p], dtype=np.int32)
+    k = len(lists)
+    return W.Topology(n_links=links, cap=np.asarray(caps, dtype=np.float64), n_comm=k,
+                      comm_path_ptr=cp, n_paths=len(paths), path_link_ptr=lp, path_links=pl,
+                      src=np.zeros(k, dtype=np.int32), dst=np.zeros(k, dtype=np.int32),
+                      meta=dict(kind="lists"))
+
+
+def direct_mesh(gpus):
+    """Every pair has one link of its own: patches that share nothing."""
+    k = gpus * (gpus - 1)
+    return _topology(k, 1e9 * (1 + np.arange(k) % 5), [[[e]] for e in range(k)])
+
+
+def islands(n, gpus):
+    """n nodes without links between them."""
+    t = W.build_fabric(1, gpus)
+    one = [[[int(e) for e in t.path_links[t.path_link_ptr[p]:t.path_link_ptr[p + 1]]]
+            for p in range(t.comm_path_ptr[k], t.comm_path_ptr[k + 1])] for k in range(t.n_comm)]
+    return _topology(n * t.n_links, np.tile(t.cap, n),
+                     [[[e + i * t.n_links for e in p] for p in c] for i in range(n) for c in one])
+
+
 def _random(seed, E, K, pm, lm):
     return W.random_topology(np.random.default_rng(seed), E, K, pm, lm)
 
@@ -180,3 +208,57 @@ def test_phases_can_be_timed_after_a_solve_in_one_launch():
         assert lam == lam2 and np.array_equal(splits, again)
     finally:
         h.close()
+
+
+def test_patches_without_a_shared_link():
+    """Fabrics the library cuts into several patches that have nothing to exchange but the width."""
+    for t, strips in ((direct_mesh(64), 4), (islands(40, 8), 3), (direct_mesh(64), 6),
+                      (islands(40, 8), 6)):
+        s = B.nimble_host_patch_check(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths,
+                                      t.path_link_ptr, t.path_links, strips)
+        assert s["failed"] == 0 and s["patches"] > 1 and s["parts"] == 0, s
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("strips", [0, 4, 6])
+def test_patches_without_a_shared_link_match_the_oracle(monkeypatch, strips, flags):
+    """What patches meet over is cleared before every solve although no part of a link's load is
+    exchanged: solves in a row with one handle (lambda starts as NaN), a batch, a warm start, a
+    variable step."""
+    import oracle
+    import torch
+    if strips:
+        monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    for name, t in (("mesh", direct_mesh(64)), ("islands", islands(40, 8))):
+        print(f"[patch] {name} strips={strips} flags={flags}", flush=True)
+        d = np.floor(np.random.default_rng(11).pareto(1.1, (4, t.n_comm)) * 1e6)
+        d[2] = 0.0
+        ref = [oracle.solve(*t.csr(), d[b], 0.05, 20, flags=flags) for b in range(4)]
+        h = B.nimble_topo_create(*t.csr(), flags=flags)
+        try:
+            dd = torch.as_tensor(d).to("cuda:0")
+            splits = torch.empty((4, t.n_paths), dtype=torch.float64, device="cuda:0")
+            lam = torch.full((4,), float("nan"), dtype=torch.float64, device="cuda:0")
+            for b in (0, 1, 2, 3, 0):
+                lam.fill_(float("nan"))
+                B.nimble_plan_solve(h, dd[b], 0.05, 20, splits[b], lam[b:b + 1])
+                assert float(lam[b].item()) == ref[b]["lam"], (name, b)
+                assert np.array_equal(splits[b].cpu().numpy(), ref[b]["splits"]), (name, b)
+            lam.fill_(float("nan"))
+            B.nimble_plan_solve_batch(h, 4, dd.reshape(-1), 0.05, 20, splits.reshape(-1), lam)
+            assert lam.cpu().numpy().tolist() == [r["lam"] for r in ref]
+            for b in range(4):
+                assert np.array_equal(splits[b].cpu().numpy(), ref[b]["splits"]), (name, b)
+            ln = torch.ones(t.n_links, dtype=torch.float64, device="cuda:0")
+            B.nimble_plan_solve_warm(h, dd[1], 0.05, 20, ln, splits[0], lam[:1])
+            warm = oracle.solve(*t.csr(), d[1], 0.05, 20, flags=flags, len0=np.ones(t.n_links))
+            assert float(lam[0].item()) == warm["lam"]
+            assert np.array_equal(ln.cpu().numpy(), warm["len"])
+            if not flags:
+                a = oracle.solve_adaptive(*t.csr(), d[3], 0.1, 40, 7)
+                got = _adaptive(h, t, d[3], 0.1, 40, 7)
+                assert got[1:] == (a["lam"], a["iters"], a["lb"])
+                assert np.array_equal(got[0], a["splits"])
+        finally:
+            h.close()
