@@ -111,8 +111,9 @@ void nimble_topo_destroy(nimble_topo_t *topo);
  *               could overflow: NIMBLE_ERR_RANGE)
  *   d_splits    device [n_paths] out: times chosen / iters; sums to 1 per commodity
  *   d_lambda    device [1] out: max_e (1/cap_e) * sum_p d_k(p) splits_p, in seconds
- *               (NaN if patches that wait for each other, or the persistent regime, abandoned the solve, see
- *               nimble_debug_set_spin_limit)
+ *               (NaN if the persistent regime abandoned the solve, see
+ *               nimble_debug_set_spin_limit; patches that give up waiting for each other are
+ *               followed by a kernel that waits for nobody and completes the plan)
  *   hip_stream  hipStream_t (NULL = default stream).  The call only enqueues work; outputs are
  *               valid after the stream is synchronised.  No host synchronisation inside.
  * Nothing is allocated or freed here, so a caller may capture the call into a HIP graph on its

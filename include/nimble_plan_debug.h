@@ -96,6 +96,14 @@ int64_t nimble_debug_live_allocations(void);
 nimble_status_t nimble_debug_set_spin_limit(nimble_topo_t *topo, uint32_t polls);
 
 /*
+ * Test helper for the patch kernels, whose waits between patches have the same limit (0: no patch
+ * waits for another, so a solve of several patches is always given up).  What they give up is
+ * solved without them, so results do not tell: out receives 1 if patches gave up in the last solve
+ * on this topology, else 0.  Synchronises the device.
+ */
+nimble_status_t nimble_debug_patches_gave_up(const nimble_topo_t *topo, int32_t *out);
+
+/*
  * Host-only helper (no device call): the reverse CSR exactly as nimble_topo_create builds it,
  * unpadded.  rev_ptr is host [n_links+1] out; rev_comm / rev_path are host [nnz] out (the
  * commodity and the candidate index inside that commodity of every incidence).  Returns the

@@ -37,7 +37,7 @@ EXPORTS = [
     "nimble_plan_solve_static", "nimble_static_scratch_bytes", "nimble_debug_barrier_probe",
     "nimble_topo_reserve_batch", "nimble_debug_fail_allocation",
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
-    "nimble_host_patch_check",
+    "nimble_host_patch_check", "nimble_debug_patches_gave_up",
 ]
 
 _lib = None
@@ -111,6 +111,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.nimble_debug_live_allocations.argtypes = []
     lib.nimble_debug_stream_read.restype = ctypes.c_int
     lib.nimble_debug_stream_read.argtypes = [vp, i64, i32, vp, vp]
+    lib.nimble_debug_patches_gave_up.restype = ctypes.c_int
+    lib.nimble_debug_patches_gave_up.argtypes = [vp, vp]
     lib.nimble_debug_set_spin_limit.restype = ctypes.c_int
     lib.nimble_debug_set_spin_limit.argtypes = [vp, u32]
     lib.nimble_host_records_roundtrip.restype = ctypes.c_int
@@ -353,6 +355,12 @@ def nimble_debug_barrier_probe(kind: int, blocks_per_cu: int, threads: int, roun
         int(kind), int(blocks_per_cu), int(threads), int(rounds), int(spin_limit),
         ctypes.c_void_p(d_work.data_ptr()), int(d_work.numel() * d_work.element_size()),
         _dev_ptr(d_out, "int32", 32, "d_out"), _stream_ptr(stream)))
+
+
+def nimble_debug_patches_gave_up(topo: Topo) -> bool:
+    out = ctypes.c_int32(-1)
+    _check(load_library().nimble_debug_patches_gave_up(topo.handle, ctypes.byref(out)))
+    return out.value != 0
 
 
 def nimble_debug_set_spin_limit(topo: Topo, polls: int) -> None:

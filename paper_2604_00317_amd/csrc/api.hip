@@ -129,6 +129,8 @@ struct nimble_topo {
     bool ad_ready = false;
     int64_t ad_sigma_rows = 0;
     void *sync_words = nullptr; // barrier counter and reductions of the persistent kernel
+    const uint32_t *gave_up = nullptr;            // set on the device if the patches of the last
+                                                  // solve gave up (null: it had no waits)
     std::vector<nimble::DevicePatches> patches;   // layouts of the patch kernels (may be none)
     const int32_t *idle = nullptr;                // links no candidate uses
     int32_t n_idle = 0;
@@ -311,6 +313,7 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     p.max_teams = 1 << 30;
     p.parts = nullptr;
     p.maxima = nullptr;
+    p.len_done = nullptr;
     p.abort_word = nullptr;
     p.iteration_us = nimble::patch_scan_us(l.shape) +
                      nimble::patch_exchange_us(l.n_patches, l.max_parts);
@@ -326,6 +329,7 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
         if (e == hipSuccess)
             e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * nimble::kPatchCopies * l.n_patches,
                          &p.maxima);
+        if (e == hipSuccess) e = allocate(t, static_cast<size_t>(t->d.E), &p.len_done);
         if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
     }
     p.n_patches = e == hipSuccess ? l.n_patches : 0;
@@ -515,6 +519,7 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
                               hipStream_t s, bool &done)
 {
     done = false;
+    topo->gave_up = nullptr;
     if (topo->forced_regime != NIMBLE_REGIME_AUTO && topo->forced_regime != NIMBLE_REGIME_RESIDENT)
         return NIMBLE_OK;
     // (lists of a single node: a thread per commodity and link with everything in registers; one
@@ -523,10 +528,15 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
     const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s,
                                                   topo->forced_regime == NIMBLE_REGIME_RESIDENT);
     if (p == nullptr) return NIMBLE_OK;
-    const hipError_t e =
-        nimble::launch_patches(topo->d, *p, plans, d_traffic, d_len, d_len, eps, iters,
-                               topo->spin_limit, d_splits, d_lambda, s);
+    hipError_t e = nimble::launch_patches(topo->d, *p, plans, d_traffic, d_len, eps, iters,
+                                          topo->spin_limit, d_splits, d_lambda, s);
     if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
+    if (p->n_patches > 1) {
+        e = nimble::launch_alone(topo->d, topo->sync_words, p->abort_word, plans, d_traffic, eps,
+                                 iters, p->len_done, d_len, d_splits, d_lambda, s);
+        if (e != hipSuccess) return fail_hip(e, "kernel launch (after the patch kernels)");
+        topo->gave_up = p->abort_word;
+    }
     topo->last_regime = p->n_patches > 1 ? NIMBLE_REGIME_PERSISTENT : NIMBLE_REGIME_RESIDENT;
     topo->patch_solved = true;
     done = true;
@@ -561,9 +571,10 @@ static const nimble::DevicePatches *adaptive_patches(const nimble_topo_t *t, int
     return best;
 }
 
-// Waits for an adaptive solve and hands its host outputs over.
+// Waits for an adaptive solve and hands its host outputs over; `gave_up`: patches gave up waiting
+// for each other and there are none.
 static nimble_status_t adaptive_results(nimble_topo_t *t, int32_t *iters_done, double *lower_bound,
-                                        hipStream_t s)
+                                        hipStream_t s, bool &gave_up)
 {
     int32_t flags[2] = {0, 0};
     double ascal[4] = {0, 0, 0, 0};
@@ -572,7 +583,8 @@ static nimble_status_t adaptive_results(nimble_topo_t *t, int32_t *iters_done, d
         e = hipMemcpyAsync(ascal, t->ad.ascal, sizeof(ascal), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) return fail_hip(e, "adaptive solve (results)");
-    if (flags[0] == 2) return fail(NIMBLE_ERR_HIP, "adaptive solve: a wait between patches expired");
+    gave_up = flags[0] == 2;
+    if (gave_up) return NIMBLE_OK;
     *iters_done = flags[1];
     *lower_bound = ascal[2];
     return NIMBLE_OK;
@@ -1237,8 +1249,9 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
     st = grow_choice_log(topo, max_iters);
     if (st != NIMBLE_OK) return st;
     topo->last_regime = NIMBLE_REGIME_STREAM;
+    bool gave_up = false;
     if (const nimble::DevicePatches *p = adaptive_patches(topo, max_iters)) {
-        // the whole solve in one launch
+        // the whole solve in one launch (and kernel by kernel after all if patches give up)
         nimble::PatchAdaptive pa;
         pa.terms = a.terms;
         pa.idle = topo->idle;
@@ -1247,10 +1260,12 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
         pa.flags = a.flags;
         pa.scalars = a.ascal;
         pa.abort_word = a.patch_abort;
-        e = nimble::launch_patches(d, *p, 1, d_traffic, nullptr, nullptr, eps, max_iters,
-                                   topo->spin_limit, d_splits, d_lambda, s, &pa);
+        e = nimble::launch_patches(d, *p, 1, d_traffic, nullptr, eps, max_iters, topo->spin_limit,
+                                   d_splits, d_lambda, s, &pa);
         if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
-        return adaptive_results(topo, iters_done, lower_bound, s);
+        topo->gave_up = a.patch_abort;
+        st = adaptive_results(topo, iters_done, lower_bound, s, gave_up);
+        if (st != NIMBLE_OK || !gave_up) return st;
     }
     const double gap = (1.0 + eps) * (1.0 + eps);
     // The device takes the stop decision and publishes it, with the number of checks made, in
@@ -1350,7 +1365,7 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
     nimble::launch_ad_lambda(d, a, gap, 0, s);
     e = nimble::launch_ad_histogram(d, a, topo->choice_log, topo->log_stride, d_splits, d_lambda, s);
     if (e != hipSuccess) return fail_hip(e, "kernel launch (adaptive regime)");
-    st = adaptive_results(topo, iters_done, lower_bound, s);
+    st = adaptive_results(topo, iters_done, lower_bound, s, gave_up);
     if (st != NIMBLE_OK) return st;
     topo->state_ready = true;
     topo->state_log = topo->choice_log;
@@ -1384,6 +1399,20 @@ nimble_status_t nimble_debug_set_spin_limit(nimble_topo_t *topo, uint32_t polls)
     g_last_error.clear();
     if (!topo) return fail(NIMBLE_ERR_INVALID, "topology handle is NULL");
     topo->spin_limit = polls;
+    return NIMBLE_OK;
+}
+
+nimble_status_t nimble_debug_patches_gave_up(const nimble_topo_t *topo, int32_t *out)
+{
+    g_last_error.clear();
+    if (!topo || !out) return fail(NIMBLE_ERR_INVALID, "NULL argument");
+    uint32_t word = 0;
+    if (topo->gave_up != nullptr) {
+        hipError_t e = hipDeviceSynchronize();
+        if (e == hipSuccess) e = hipMemcpy(&word, topo->gave_up, sizeof(word), hipMemcpyDeviceToHost);
+        if (e != hipSuccess) return fail_hip(e, "word of the patch kernels");
+    }
+    *out = word != 0 ? 1 : 0;
     return NIMBLE_OK;
 }
 

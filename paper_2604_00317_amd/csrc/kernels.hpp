@@ -20,6 +20,7 @@ struct DevicePatches {
     const uint32_t *words, *first;
     double *parts;               // [max_teams][2][n_parts]
     double *maxima;              // [max_teams][2][kPatchCopies][n_patches]
+    double *len_done;            // [E] lengths a warm solve ended with, until it is known to be whole
     uint32_t *abort_word;
     double iteration_us;         // estimate of one iteration of max_teams plans
     bool adaptive;               // the kernel of variable step runs on it
@@ -250,8 +251,8 @@ size_t patch_lds_bytes(const DevicePatches &p, bool adaptive);      // of the la
 int patch_blocks_per_cu(const DevicePatches &p, bool cost_max, bool adaptive);
 constexpr int32_t kPatchMaxIters = 65535;      // choices are counted in 16 bits
 hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t plans,
-                          const double *demand, const double *len_in, double *len_out, double eps,
-                          int32_t iters, uint32_t spin_limit, double *splits, double *lambda,
+                          const double *demand, double *len_io, double eps, int32_t iters,
+                          uint32_t spin_limit, double *splits, double *lambda,
                           hipStream_t s, const PatchAdaptive *adaptive = nullptr);
 
 // ---- persistent regime: one kernel per solve, grid barriers between the phases -------------
@@ -262,6 +263,13 @@ size_t persistent_sync_bytes();
 hipError_t launch_persistent(const DeviceTopo &t, void *sync_words, int n_cu,
                              unsigned int spin_limit, const double *demand, double eps,
                              int32_t iters, double *splits, double *lambda, hipStream_t s);
+// Follows a solve of several patches: completes it where patches gave up waiting for each other
+// (one workgroup, no waits), else copies the lengths of a warm start from `len_done` to `len_io`
+// (null: nobody wants them).
+hipError_t launch_alone(const DeviceTopo &t, void *sync_words, const uint32_t *gave_up,
+                        int32_t plans, const double *demand, double eps, int32_t iters,
+                        const double *len_done, double *len_io, double *splits, double *lambda,
+                        hipStream_t s);
 
 // ---- probe of grid-wide barriers (benchmark only) -------------------------------------------
 // `work` is device memory of barrier_probe_bytes(blocks) bytes; `out` is device int32 [32].

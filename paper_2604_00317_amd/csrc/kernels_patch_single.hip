@@ -13,12 +13,13 @@ PatchKernel adaptive_kernel(const PatchShape &s, bool multi);
 
 namespace {
 
-// every word of the exchange starts with the sign of an exchange that has not happened yet
+// Every word of the exchange starts with the sign of an exchange that has not happened yet.
 __global__ __launch_bounds__(256) void k_patch_clear(unsigned long long *parts, int64_t n_parts,
                                                      unsigned long long *maxima, int64_t n_maxima,
                                                      unsigned long long *terms, int64_t n_terms,
-                                                     uint32_t *abort_word, int32_t *ad_flags,
-                                                     double *lambda, int plans)
+                                                     uint32_t *abort_word, uint32_t given_up,
+                                                     int32_t *ad_flags, double *lambda, int plans,
+                                                     const double *len_in, double *len_done, int E)
 {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -26,8 +27,10 @@ __global__ __launch_bounds__(256) void k_patch_clear(unsigned long long *parts, 
     for (int64_t i = i0; i < n_maxima; i += stride) maxima[i] = kSign;
     for (int64_t i = i0; i < n_terms; i += stride) terms[i] = kSign;
     for (int64_t i = i0; i < plans; i += stride) lambda[i] = 0.0;
+    if (len_in != nullptr)           // (links no candidate uses keep their length)
+        for (int64_t i = i0; i < E; i += stride) len_done[i] = len_in[i];
     if (i0 == 0) {
-        *abort_word = 0u;
+        *abort_word = given_up;
         if (ad_flags != nullptr) ad_flags[0] = 0;
     }
 }
@@ -68,7 +71,7 @@ int patch_blocks_per_cu(const DevicePatches &p, bool cost_max, bool adaptive)
 }
 
 hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t plans,
-                          const double *demand, const double *len_in, double *len_out, double eps,
+                          const double *demand, double *len_io, double eps,
                           int32_t iters, uint32_t spin_limit, double *splits, double *lambda,
                           hipStream_t s, const PatchAdaptive *adaptive)
 {
@@ -84,8 +87,10 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     a.comm_ptr = t.comm_ptr;
     a.invcap = t.invcap;
     a.demand = demand;
-    a.len_in = len_in;
-    a.len_out = len_out;
+    // several patches leave their lengths where a solve that is given up half way does no harm
+    const bool warm = len_io != nullptr;
+    a.len_in = len_io;
+    a.len_out = warm && p.n_patches > 1 ? p.len_done : len_io;
     a.splits = splits;
     a.lambda = lambda;
     a.parts = p.parts;
@@ -127,13 +132,15 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
         p.n_patches > 1 ? static_cast<int64_t>(a.teams) * 2 * kPatchCopies * p.n_patches
                          : 0;
     // (patches that share no link have no parts, but maxima, an abort word and a lambda all the same)
-    int64_t grid = (std::max({words, maxima, n_terms, static_cast<int64_t>(plans)}) + 255) / 256;
+    int64_t grid = (std::max({words, maxima, n_terms, static_cast<int64_t>(plans),
+                             static_cast<int64_t>(warm ? t.E : 0)}) + 255) / 256;
     if (grid > 1024) grid = 1024;
     hipLaunchKernelGGL(patch::k_patch_clear, dim3(static_cast<unsigned>(grid)), dim3(256), 0, s,
                        reinterpret_cast<unsigned long long *>(p.parts), words,
                        reinterpret_cast<unsigned long long *>(p.maxima), maxima,
                        reinterpret_cast<unsigned long long *>(a.terms), n_terms, a.abort_word,
-                       a.ad_flags, lambda, plans);
+                       spin_limit == 0 ? 1u : 0u, a.ad_flags, lambda, plans, a.len_in, p.len_done,
+                       t.E);
     const hipError_t cleared = hipGetLastError();
     if (cleared != hipSuccess) return cleared;
     if (p.n_patches == 1) return hipLaunchKernel(f, dim3(1), dim3(p.shape.threads), args, lds, s);

@@ -8,6 +8,13 @@
 // blocks' writes visible.  The wait is bounded: after `spin_limit` polls a block raises the
 // abort word, every block sees it at its next poll and leaves the kernel, and the epilogue is
 // skipped (lambda is set to NaN by the block that gave up), so no wave can wait forever.
+//
+// The same kernel with one workgroup (ALONE) waits for nobody.  It follows every solve of several
+// patches (patch_kernel.hpp) in the stream: where that went through, it hands over the lengths of
+// a warm start or returns at once (2 us); where patches gave up waiting for each other, it solves
+// the plans they left undone, slowly but surely.
+#include <algorithm>
+
 #include "host_topo.hpp"
 #include "kernels.hpp"
 #include "phases.hpp"
@@ -41,6 +48,7 @@ __device__ __forceinline__ bool grid_barrier(SyncWords *w, unsigned int n_blocks
                                              unsigned int spin_limit, int *s_flag)
 {
     __syncthreads();
+    if (n_blocks == 1u) return true;             // (a workgroup sees its own writes)
     if (threadIdx.x == 0) {
         __threadfence();
         const unsigned int old = __hip_atomic_fetch_add(&w->arrivals, 1u, __ATOMIC_RELAXED,
@@ -100,6 +108,12 @@ struct PersistentArgs {
     int iters;
     double *splits, *lambda;
     unsigned int spin_limit;
+    // ALONE: the word that says whether the patches gave up, their lengths (null: nobody wants
+    // them) and the caller's, and how many plans there are
+    const uint32_t *gave_up;
+    const double *len_done;
+    double *len_io;
+    int plans;
 };
 
 template <int MODE>
@@ -126,23 +140,24 @@ __device__ __forceinline__ void atomic_max_bits(unsigned long long *addr, double
                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// One plan, by `nb` workgroups.
 template <int L, int LMAX, bool MAXC>
-__global__ __launch_bounds__(kPBlock) void k_persistent(PersistentArgs a)
+__device__ __forceinline__ void solve_plan(const PersistentArgs &a, unsigned int nb, double *red,
+                                           int &s_flag)
 {
-    __shared__ double red[16];
-    __shared__ int s_flag;
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int n_waves = (gridDim.x * blockDim.x) >> 6;
+    const int n_waves = (nb * blockDim.x) >> 6;
     const int tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const int n_threads = gridDim.x * blockDim.x;
-    const unsigned int nb = gridDim.x;
+    const int n_threads = nb * blockDim.x;
 
     // prologue: state and the width rho
-    for (int e = tid; e < a.E; e += n_threads) {
-        a.len[e] = 1.0;
-        a.price[e] = MAXC ? 1.0 : a.invcap[e];
-        a.S[e] = 0.0;
+    for (int i = tid; i < a.E; i += n_threads) {
+        const int e = a.pos_link[i];             // lengths and sums by position, prices by link id
+        const double l0 = a.len_io != nullptr ? a.len_io[e] : 1.0;
+        a.len[i] = l0;
+        a.price[e] = MAXC ? l0 : l0 * a.invcap[e];
+        a.S[i] = 0.0;
     }
     for (int p = tid; p < a.P; p += n_threads) a.count[p] = 0u;
     for (int k = tid; k < a.K; k += n_threads) {
@@ -197,14 +212,58 @@ __global__ __launch_bounds__(kPBlock) void k_persistent(PersistentArgs a)
             a.lambda[0] = smax / T;
         }
     }
+    if (a.len_io != nullptr)
+        for (int i = tid; i < a.E; i += n_threads) a.len_io[a.pos_link[i]] = a.len[i];
     return;
 abandoned:
     if (tid == 0) a.lambda[0] = __builtin_nan("");
 }
 
 template <int L, int LMAX, bool MAXC>
+__global__ __launch_bounds__(kPBlock) void k_persistent(PersistentArgs a)
+{
+    __shared__ double red[16];
+    __shared__ int s_flag;
+    solve_plan<L, LMAX, MAXC>(a, gridDim.x, red, s_flag);
+}
+
+template <int L, int LMAX, bool MAXC>
+__global__ __launch_bounds__(kPBlock) void k_alone(PersistentArgs a)
+{
+    __shared__ double red[16];
+    __shared__ int s_flag;
+    if (*a.gave_up == 0u) {
+        if (a.len_io != nullptr)
+            for (int e = blockIdx.x * kPBlock + threadIdx.x; e < a.E; e += gridDim.x * kPBlock)
+                a.len_io[e] = a.len_done[e];
+        return;
+    }
+    if (blockIdx.x != 0) return;
+    const int plans = a.plans;
+    for (int plan = 0; plan < plans; ++plan) {
+        // (a plan some patch gave up has lambda NaN; the same for all threads)
+        if (a.lambda[0] != a.lambda[0]) {
+            if (threadIdx.x == 0) {
+                a.sync->rho_bits = 0ull;
+                a.sync->smax_bits = 0ull;
+            }
+            solve_plan<L, LMAX, MAXC>(a, 1u, red, s_flag);
+            __syncthreads();
+        }
+        a.demand += a.K;
+        a.splits += a.P;
+        a.lambda += 1;
+    }
+}
+
+template <int L, int LMAX, bool MAXC>
 hipError_t launch_one(const PersistentArgs &a, int n_cu, hipStream_t s, int *grid_out)
 {
+    if (a.gave_up != nullptr) {
+        const int grid = a.len_io == nullptr ? 1 : std::min(64, (a.E + kPBlock - 1) / kPBlock);
+        hipLaunchKernelGGL((k_alone<L, LMAX, MAXC>), dim3(grid), dim3(kPBlock), 0, s, a);
+        return hipGetLastError();
+    }
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
         &per_cu, reinterpret_cast<const void *>(&k_persistent<L, LMAX, MAXC>), kPBlock, 0);
@@ -250,11 +309,10 @@ hipError_t launch_l(const PersistentArgs &a, int L, int lmax, int n_cu, hipStrea
 
 size_t persistent_sync_bytes() { return sizeof(SyncWords); }
 
-hipError_t launch_persistent(const DeviceTopo &t, void *sync_words, int n_cu,
-                             unsigned int spin_limit, const double *demand, double eps,
-                             int32_t iters, double *splits, double *lambda, hipStream_t s)
+static PersistentArgs persistent_args(const DeviceTopo &t, void *sync_words, const double *demand,
+                                      double eps, int32_t iters, double *splits, double *lambda)
 {
-    PersistentArgs a;
+    PersistentArgs a = {};
     a.E = t.E;
     a.K = t.K;
     a.P = t.P;
@@ -303,11 +361,34 @@ hipError_t launch_persistent(const DeviceTopo &t, void *sync_words, int n_cu,
     a.iters = iters;
     a.splits = splits;
     a.lambda = lambda;
+    return a;
+}
+
+hipError_t launch_persistent(const DeviceTopo &t, void *sync_words, int n_cu,
+                             unsigned int spin_limit, const double *demand, double eps,
+                             int32_t iters, double *splits, double *lambda, hipStream_t s)
+{
+    PersistentArgs a = persistent_args(t, sync_words, demand, eps, iters, splits, lambda);
     a.spin_limit = spin_limit;
     hipLaunchKernelGGL(k_sync_reset, dim3(1), dim3(64), 0, s, a.sync);
     const int L = lanes_per_commodity(t.pmax);
     if (t.cost_max) return launch_l<true>(a, L, t.lmax, n_cu, s, nullptr);
     return launch_l<false>(a, L, t.lmax, n_cu, s, nullptr);
+}
+
+hipError_t launch_alone(const DeviceTopo &t, void *sync_words, const uint32_t *gave_up,
+                        int32_t plans, const double *demand, double eps, int32_t iters,
+                        const double *len_done, double *len_io, double *splits, double *lambda,
+                        hipStream_t s)
+{
+    PersistentArgs a = persistent_args(t, sync_words, demand, eps, iters, splits, lambda);
+    a.gave_up = gave_up;
+    a.len_done = len_done;
+    a.len_io = len_io;
+    a.plans = plans;
+    const int L = lanes_per_commodity(t.pmax);
+    if (t.cost_max) return launch_l<true>(a, L, t.lmax, 1, s, nullptr);
+    return launch_l<false>(a, L, t.lmax, 1, s, nullptr);
 }
 
 }  // namespace nimble

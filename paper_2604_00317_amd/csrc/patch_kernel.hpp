@@ -18,7 +18,9 @@
 // (n >> 1) & 1; all words start with the sign set.  A patch overwrites its part of exchange n
 // with that of n + 2 only after it has read all parts of n + 1 of the groups it shares, which
 // their writers published after reading n: nobody misses a word.  Every wait is bounded; when one
-// expires the team gives up and lambda becomes NaN.
+// expires the team gives up, lambda becomes NaN, and whatever follows in the stream (launch_alone;
+// the host, after a solve of variable step) solves the plan without patches.  A limit of zero
+// means that nobody waits at all.
 //
 // Sums of loads do not depend on the order of the atomics: they are sums of integers.  Where the
 // demands of a patch lie on a power-of-two grid with a total below 2^53 units (byte counts) those
@@ -393,7 +395,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
 
     unsigned exchange = 0u;          // exchanges made so far, the same in all patches of a team
     unsigned meeting = 0u;           // maxima folded over all patches so far
-    int dead = 0;                    // this wave has given up waiting
+    int dead = a.spin_limit == 0u ? 1 : 0;       // this wave has given up waiting
     double *parts_of_team = nullptr, *maxima_of_team = nullptr;
     if constexpr (MULTI) {
         parts_of_team = a.parts + static_cast<size_t>(team) * 2 * a.n_parts;

@@ -262,3 +262,64 @@ def test_patches_without_a_shared_link_match_the_oracle(monkeypatch, strips, fla
                 assert np.array_equal(got[0], a["splits"])
         finally:
             h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, 1])
+def test_what_patches_give_up_is_solved_without_them(monkeypatch, flags):
+    """Nobody waits (limit zero): a plan, a batch of more plans than teams, a warm start (whose
+    lengths come back whole) and a variable step still give the oracle's bits, as they do with the
+    ordinary limit before and after; a fabric of one patch has no waits to give up."""
+    import oracle
+    import torch
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "3")
+    for t in (fabric(7, 6, "pair"), fabric(3, 8, "xor"), _random(5, 500, 1500, 12, 2)):
+        n = 70
+        rng = np.random.default_rng(9)
+        d = np.floor(rng.pareto(1.1, (n, t.n_comm)) * 1e6)
+        d[3] = 0.0
+        ref = [oracle.solve(*t.csr(), d[b], 0.05, 5, flags=flags) for b in range(n)]
+        len0 = 1.0 + rng.random(t.n_links)
+        warm = oracle.solve(*t.csr(), d[1], 0.05, 9, flags=flags, len0=len0)
+        h = B.nimble_topo_create(*t.csr(), flags=flags)
+        try:
+            dd = torch.as_tensor(d).to("cuda:0")
+            splits = torch.empty((n, t.n_paths), dtype=torch.float64, device="cuda:0")
+            lam = torch.empty(n, dtype=torch.float64, device="cuda:0")
+            for limit in (1 << 22, 0, 1 << 22):
+                print(f"[patch] gives up K={t.n_comm} flags={flags} limit={limit}", flush=True)
+                B.nimble_debug_set_spin_limit(h, limit)
+                s, l = B.plan(h, d[0], 0.05, 5)
+                assert B.nimble_debug_patches_gave_up(h) == (limit == 0)
+                assert l == ref[0]["lam"] and np.array_equal(s, ref[0]["splits"])
+                B.nimble_plan_solve_batch(h, n, dd.reshape(-1), 0.05, 5, splits.reshape(-1), lam)
+                assert B.nimble_debug_patches_gave_up(h) == (limit == 0)
+                assert lam.cpu().numpy().tolist() == [r["lam"] for r in ref]
+                for b in range(n):
+                    assert np.array_equal(splits[b].cpu().numpy(), ref[b]["splits"]), b
+                ln = torch.as_tensor(len0).to("cuda:0")
+                B.nimble_plan_solve_warm(h, dd[1], 0.05, 9, ln, splits[0], lam[:1])
+                assert B.nimble_debug_patches_gave_up(h) == (limit == 0)
+                assert float(lam[0].item()) == warm["lam"]
+                assert np.array_equal(ln.cpu().numpy(), warm["len"])
+                assert np.array_equal(splits[0].cpu().numpy(), warm["splits"])
+                if not flags:
+                    a = oracle.solve_adaptive(*t.csr(), d[2], 0.1, 30, 4)
+                    got = _adaptive(h, t, d[2], 0.1, 30, 4)
+                    assert B.nimble_debug_patches_gave_up(h) == (limit == 0)
+                    assert got[1:] == (a["lam"], a["iters"], a["lb"])
+                    assert np.array_equal(got[0], a["splits"])
+        finally:
+            h.close()
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "1")
+    t = fabric(2, 8, "pair")
+    h = B.nimble_topo_create(*t.csr(), flags=flags)
+    try:
+        B.nimble_debug_set_spin_limit(h, 0)
+        d = np.floor(np.random.default_rng(9).pareto(1.1, t.n_comm) * 1e6)
+        s, l = B.plan(h, d, 0.05, 5)
+        assert not B.nimble_debug_patches_gave_up(h)
+        ref = oracle.solve(*t.csr(), d, 0.05, 5, flags=flags)
+        assert l == ref["lam"] and np.array_equal(s, ref["splits"])
+    finally:
+        h.close()
