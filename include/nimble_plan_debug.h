@@ -103,6 +103,10 @@ nimble_status_t nimble_debug_set_spin_limit(nimble_topo_t *topo, uint32_t polls)
  */
 nimble_status_t nimble_debug_patches_gave_up(const nimble_topo_t *topo, int32_t *out);
 
+/* Test helper: the next cooperative launch of the patch kernels is taken as refused by the device;
+ * the solve then runs on kernels that need none. */
+void nimble_debug_refuse_cooperative(void);
+
 /*
  * Host-only helper (no device call): the reverse CSR exactly as nimble_topo_create builds it,
  * unpadded.  rev_ptr is host [n_links+1] out; rev_comm / rev_path are host [nnz] out (the

@@ -55,6 +55,7 @@ nimble_status_t fail_hip(hipError_t e, const char *what)
 std::atomic<int32_t> g_fail_alloc_in{-1};     // allocations until one fails; -1: none does
 std::atomic<int64_t> g_live_allocs{0};
 std::atomic<int32_t> g_fail_host_alloc{0};    // the next topology build throws std::bad_alloc
+std::atomic<int32_t> g_refuse_cooperative{0}; // the next cooperative launch of patches is refused
 
 hipError_t dev_malloc(void **p, size_t bytes)
 {
@@ -514,6 +515,28 @@ uint8_t *own_log(const nimble_topo *topo, int32_t iters, int32_t plans = 1)
             topo->log_rows >= static_cast<int64_t>(iters) * plans) ? topo->choice_log : nullptr;
 }
 
+// Launches the patch kernels.  `refused`: the device does not take the cooperative launch of
+// several patches just now (fewer compute units than the topology was made for, say) and nothing
+// of the solve has run; the kernels that need no cooperative launch are to be used.
+hipError_t launch_patches(nimble_topo *topo, const nimble::DevicePatches &p, int32_t plans,
+                          const double *d_traffic, double *d_len, double eps, int32_t iters,
+                          double *d_splits, double *d_lambda, hipStream_t s, bool &refused,
+                          const nimble::PatchAdaptive *adaptive = nullptr)
+{
+    refused = false;
+    hipError_t e = hipErrorCooperativeLaunchTooLarge;
+    if (p.n_patches == 1 || g_refuse_cooperative.exchange(0) == 0)
+        e = nimble::launch_patches(topo->d, p, plans, d_traffic, d_len, eps, iters,
+                                   topo->spin_limit, d_splits, d_lambda, s, adaptive);
+    if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorLaunchOutOfResources ||
+        e == hipErrorNotSupported) {
+        (void)hipGetLastError();
+        refused = true;
+        return hipSuccess;
+    }
+    return e;
+}
+
 nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_traffic, double eps,
                               int32_t iters, double *d_len, double *d_splits, double *d_lambda,
                               hipStream_t s, bool &done)
@@ -528,9 +551,11 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
     const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s,
                                                   topo->forced_regime == NIMBLE_REGIME_RESIDENT);
     if (p == nullptr) return NIMBLE_OK;
-    hipError_t e = nimble::launch_patches(topo->d, *p, plans, d_traffic, d_len, eps, iters,
-                                          topo->spin_limit, d_splits, d_lambda, s);
+    bool refused = false;
+    hipError_t e = launch_patches(topo, *p, plans, d_traffic, d_len, eps, iters, d_splits, d_lambda,
+                                  s, refused);
     if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
+    if (refused) return NIMBLE_OK;
     if (p->n_patches > 1) {
         e = nimble::launch_alone(topo->d, topo->sync_words, p->abort_word, plans, d_traffic, eps,
                                  iters, p->len_done, d_len, d_splits, d_lambda, s);
@@ -1251,7 +1276,8 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
     topo->last_regime = NIMBLE_REGIME_STREAM;
     bool gave_up = false;
     if (const nimble::DevicePatches *p = adaptive_patches(topo, max_iters)) {
-        // the whole solve in one launch (and kernel by kernel after all if patches give up)
+        // the whole solve in one launch (and kernel by kernel after all if it is refused, or if
+        // patches give up)
         nimble::PatchAdaptive pa;
         pa.terms = a.terms;
         pa.idle = topo->idle;
@@ -1260,12 +1286,15 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
         pa.flags = a.flags;
         pa.scalars = a.ascal;
         pa.abort_word = a.patch_abort;
-        e = nimble::launch_patches(d, *p, 1, d_traffic, nullptr, eps, max_iters, topo->spin_limit,
-                                   d_splits, d_lambda, s, &pa);
+        bool refused = false;
+        e = launch_patches(topo, *p, 1, d_traffic, nullptr, eps, max_iters, d_splits, d_lambda, s,
+                           refused, &pa);
         if (e != hipSuccess) return fail_hip(e, "kernel launch (patch kernels)");
-        topo->gave_up = a.patch_abort;
-        st = adaptive_results(topo, iters_done, lower_bound, s, gave_up);
-        if (st != NIMBLE_OK || !gave_up) return st;
+        if (!refused) {
+            topo->gave_up = a.patch_abort;
+            st = adaptive_results(topo, iters_done, lower_bound, s, gave_up);
+            if (st != NIMBLE_OK || !gave_up) return st;
+        }
     }
     const double gap = (1.0 + eps) * (1.0 + eps);
     // The device takes the stop decision and publishes it, with the number of checks made, in
@@ -1401,6 +1430,8 @@ nimble_status_t nimble_debug_set_spin_limit(nimble_topo_t *topo, uint32_t polls)
     topo->spin_limit = polls;
     return NIMBLE_OK;
 }
+
+void nimble_debug_refuse_cooperative(void) { g_refuse_cooperative.store(1); }
 
 nimble_status_t nimble_debug_patches_gave_up(const nimble_topo_t *topo, int32_t *out)
 {

@@ -323,3 +323,43 @@ def test_what_patches_give_up_is_solved_without_them(monkeypatch, flags):
         assert l == ref["lam"] and np.array_equal(s, ref["splits"])
     finally:
         h.close()
+
+
+@pytest.mark.gpu
+def test_a_refused_launch_falls_back(monkeypatch):
+    """Where the device does not take the launch of several patches, every kind of solve runs on the
+    streaming kernels, once: the next call is on patches again."""
+    import oracle
+    import torch
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "3")
+    lib = B.load_library()
+    t = fabric(7, 6, "pair")
+    d = np.floor(np.random.default_rng(9).pareto(1.1, (3, t.n_comm)) * 1e6)
+    ref = [oracle.solve(*t.csr(), d[b], 0.05, 30) for b in range(3)]
+    warm = oracle.solve(*t.csr(), d[1], 0.05, 9, len0=np.ones(t.n_links))
+    a = oracle.solve_adaptive(*t.csr(), d[2], 0.1, 30, 4)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        for refuse in (True, False):
+            for plans in (0, slice(0, 3)):
+                if refuse:
+                    lib.nimble_debug_refuse_cooperative()
+                splits, lam = B.plan(h, d[plans], 0.05, 30)
+                assert h.regime == (B.NIMBLE_REGIME_STREAM if refuse else B.NIMBLE_REGIME_PERSISTENT)
+                for b in range(3 if plans else 1):
+                    got = (splits[b], lam[b]) if plans else (splits, lam)
+                    assert got[1] == ref[b]["lam"] and np.array_equal(got[0], ref[b]["splits"]), b
+            if refuse:
+                lib.nimble_debug_refuse_cooperative()
+            ln = torch.ones(t.n_links, dtype=torch.float64, device="cuda:0")
+            splits = torch.empty(t.n_paths, dtype=torch.float64, device="cuda:0")
+            lam = torch.empty(1, dtype=torch.float64, device="cuda:0")
+            B.nimble_plan_solve_warm(h, torch.as_tensor(d[1]).to("cuda:0"), 0.05, 9, ln, splits, lam)
+            assert float(lam.item()) == warm["lam"]
+            assert np.array_equal(ln.cpu().numpy(), warm["len"])
+            if refuse:
+                lib.nimble_debug_refuse_cooperative()
+            got = _adaptive(h, t, d[2], 0.1, 30, 4)
+            assert got[1:] == (a["lam"], a["iters"], a["lb"]) and np.array_equal(got[0], a["splits"])
+    finally:
+        h.close()
