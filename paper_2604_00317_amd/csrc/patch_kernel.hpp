@@ -25,9 +25,13 @@
 // Sums of loads do not depend on the order of the atomics: they are sums of integers.  Where the
 // demands of a patch lie on a power-of-two grid with a total below 2^53 units (byte counts) those
 // are the units, and the sum is what exact additions give; elsewhere a demand is split into
-// 2^-61 of the patch's total and 2^-105 of it, and the sum is rounded once at the end.  (64-bit
-// integer additions also take the LDS 6.2 cycles a wave where binary64 ones take 8.2, and 2
-// instead of 3 for every lane that meets another on the same link.)
+// 2^-61 of the patch's total and 2^-105 of it, which holds every demand that is not below 2^-52 of
+// the total to the last bit; both sums are exact, each is rounded to binary64, and so is what they
+// add up to.  (64-bit integer additions also take the LDS 6.2 cycles a wave where binary64 ones
+// take 8.2, and 2 instead of 3 for every lane that meets another on the same link.)
+// Demands that lie further apart, or whose total overflows, are on no such grid: one patch adds
+// them as binary64 numbers one after the other, in code of its own (solve_wide: a branch in the
+// ordinary loop cost plans of one patch 4 to 15 %); several patches mark the plan as given up.
 //
 // What bounds it and what it measured, us per iteration against two launches per iteration (and,
 // on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 2.64 -> 0.84 (one
@@ -113,7 +117,8 @@ __device__ __forceinline__ void keep_in_loop(uint32_t &v) { asm volatile("" : "+
 __device__ __forceinline__ void keep_in_loop(double &v) { asm volatile("" : "+v"(v)); }
 
 // How the loads of a patch are summed: as whole numbers of units of 2^unit, and where the demands
-// are no such whole numbers also of 2^(unit - kLowBits).
+// are no such whole numbers also of 2^(unit - kLowBits).  (That not even those hold them is noted
+// in LDS: looked at hardly ever, it is not worth a register.)
 struct Grid {
     bool exact;
     int unit;
@@ -357,6 +362,146 @@ __device__ __forceinline__ double sum_in_order(const double *x, int n, unsigned 
     return s;
 }
 
+// One plan of a fabric of one patch whose demands no grid holds: the thread of a commodity scans
+// its slots where they lie in memory, and loads are added as binary64 numbers thread after thread,
+// so always in the same order.  Prices, lengths and counts stand at their start.
+template <bool PRODUCT, int L, int QL, bool MAXC>
+__device__ __forceinline__ void solve_wide(const PatchArgs &a, int plan, int n_comm, int n_local,
+                                           const int32_t *loc_link, int count, LinkState *links,
+                                           double *red)
+{
+    constexpr int NW = PRODUCT ? kPatchWordsProduct : kPatchWordsPlain;
+    const int t = threadIdx.x, NT = blockDim.x, lane = t & (kWave - 1), wave = t >> 6;
+    const int n_waves = NT >> 6;
+    const uint32_t pad = 8u * static_cast<uint32_t>(n_local);
+    double *price = lds_ptr(0);
+    const int k = t < n_comm ? a.comm[t] : -1;
+    const double d = k >= 0 ? a.demand[static_cast<size_t>(plan) * a.K + k] : 0.0;
+    auto half = [&](int si, int x, int h) {
+        const uint32_t w = a.words[(static_cast<size_t>(si / L) * NW + x) * NT + t * L + si % L];
+        return (w >> (16 * h)) & 0xFFFFu;
+    };
+    // offset x of slot si, in the order of the first-use bits (see host_patch.hpp)
+    auto offset = [&](int si, int x) {
+        if constexpr (PRODUCT)
+            return x < 4 ? half(si, x / 2, x & 1) : x == 4 ? half(si, 2, 0) : half(si, (x + 1) / 2, 1 - (x & 1));
+        else
+            return x % 5 == 4 ? half(si, 8 + x / 10, x / 5 & 1) : half(si, 2 * (x / 5) + x % 5 / 2, x % 5 & 1);
+    };
+    // link i of the path in place `pos` of slot si
+    auto step = [&](int si, int pos, int i) {
+        if constexpr (PRODUCT) return offset(si, i < 2 ? 2 * i + (pos >> 1) : i == 2 ? 4 : 2 * i - 1 + (pos & 1));
+        else return offset(si, 5 * pos + i);
+    };
+    auto add = [&](uint32_t off) {
+        if (off >= pad) return;
+        LinkState &s = links[off / 8u];
+        s.load = static_cast<unsigned long long>(
+            __double_as_longlong(__longlong_as_double(static_cast<long long>(s.load)) + d));
+    };
+    auto in_turn = [&](auto f) {
+#pragma unroll 1
+        for (int turn = 0; turn < n_waves; ++turn) {
+            if (turn == wave)
+#pragma unroll 1
+                for (int i = 0; i < kWave; ++i) {
+                    if (i == lane && k >= 0) f();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+                    __builtin_amdgcn_wave_barrier();
+                }
+            __syncthreads();
+        }
+    };
+    auto take = [&](int i) {
+        const double v = __longlong_as_double(static_cast<long long>(links[i].load));
+        links[i].load = 0ull;
+        return v;
+    };
+    auto largest = [&](double v) {
+        v = wave_max(v);
+        __syncthreads();
+        if (lane == 0) red[wave] = v;
+        __syncthreads();
+        for (int q = 0; q < n_waves; ++q) v = fmax(v, red[q]);
+        return v;
+    };
+    for (int i = t; i < n_local; i += NT) links[i].load = 0ull;
+    __syncthreads();
+    in_turn([&] {
+#pragma unroll 1
+        for (int si = 0; si < L * QL; ++si) {
+            const uint32_t once = a.first[static_cast<size_t>(si / L) * NT + t * L + si % L];
+#pragma unroll 1
+            for (int x = 0; x < (PRODUCT ? 9 : 20); ++x)
+                if ((once >> x) & 1u) add(offset(si, x));
+        }
+    });
+    double wmax = 0.0;
+    for (int i = t; i < n_local; i += NT) wmax = fmax(wmax, take(i) * links[i].invcap);
+    wmax = largest(wmax);
+    const double invrho = wmax > 0.0 ? 1.0 / wmax : 0.0;
+#pragma unroll 1
+    for (int it = 0; it < a.iters; ++it) {
+        double best = 0.0;
+        int at = -1;                             // 4 * slot + place of the cheapest, first in order
+#pragma unroll 1
+        for (int si = 0; k >= 0 && si < L * QL; ++si) {
+            const uint32_t meta = half(si, PRODUCT ? 2 : NW - 1, 1);
+#pragma unroll 1
+            for (int c = 0; c < static_cast<int>(meta >> 9); ++c) {
+                const int pos = c << ((meta >> 7) & 3u);
+                double cost = lds_f64(step(si, pos, 0));
+#pragma unroll 1
+                for (int i = 1; i < 5; ++i) cost = join<MAXC>(cost, lds_f64(step(si, pos, i)));
+                if (at < 0 || cost < best) {
+                    best = cost;
+                    at = 4 * si + pos;
+                }
+            }
+        }
+        if (at >= 0)                             // (no other thread counts in this word)
+            *reinterpret_cast<uint32_t *>(lds_ptr(count + 8 * (t * (L * QL) + at / 4) + 4 * ((at >> 1) & 1))) +=
+                1u << (16 * (at & 1));
+        in_turn([&] {
+#pragma unroll 1
+            for (int i = 0; i < 5; ++i) add(step(at / 4, at & 3, i));
+        });
+        for (int i = t; i < n_local; i += NT) {
+            LinkState &s = links[i];
+            const double u = take(i) * s.invcap;
+            s.S = s.S + u;
+            const double gn = u * invrho;
+            const double t1 = a.eps * gn;
+            const double t2 = 1.0 + t1;
+            const double ln = s.len * t2;
+            s.len = ln;
+            price[i] = MAXC ? ln : ln * s.invcap;
+        }
+        __syncthreads();
+    }
+    const double T = static_cast<double>(a.iters);
+    double *out = k >= 0 ? a.splits + static_cast<size_t>(plan) * a.P + a.comm_ptr[k] : nullptr;
+#pragma unroll 1
+    for (int si = 0; k >= 0 && si < L * QL; ++si) {
+        const uint32_t meta = half(si, PRODUCT ? 2 : NW - 1, 1);
+#pragma unroll 1
+        for (int c = 0; c < static_cast<int>(meta >> 9); ++c) {
+            const int pos = c << ((meta >> 7) & 3u);
+            const uint32_t two = *reinterpret_cast<const uint32_t *>(
+                lds_ptr(count + 8 * (t * (L * QL) + si) + 4 * (pos >> 1)));
+            out[(meta & 127u) + c] = static_cast<double>((two >> (16 * (pos & 1))) & 0xFFFFu) / T;
+        }
+    }
+    double smax = 0.0;
+    for (int i = t; i < n_local; i += NT) {
+        smax = fmax(smax, links[i].S);
+        if (a.len_out != nullptr && (loc_link[i] & kPatchExport) && loc_link[i] >= 0)
+            a.len_out[loc_link[i] & ~kPatchExport] = links[i].len;
+    }
+    smax = largest(smax);
+    if (t == 0) a.lambda[plan] = smax / T;
+}
+
 // ADAPT: the solve of variable step (one plan, path cost = the sum of the prices).
 template <bool PRODUCT, int L, int QL, bool MAXC, bool MULTI, bool ADAPT>
 __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
@@ -377,7 +522,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
     const uint32_t pad = 8u * static_cast<uint32_t>(n_local);
     double *price = lds_ptr(0), *red = lds_ptr(l.red);
     LinkState *links = reinterpret_cast<LinkState *>(lds_ptr(l.link));
-    int *s_flag = reinterpret_cast<int *>(red + 39);
+    int *s_flag = reinterpret_cast<int *>(red + 39), *s_wide = s_flag + 1;
     int4 *groups = reinterpret_cast<int4 *>(s_lds + l.group);
 
     // this lane's share of the lists, for the whole solve
@@ -454,6 +599,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             gr.exact = __builtin_amdgcn_readfirstlane(!some || top - fine <= 53 ? 1 : 0) != 0;
             gr.unit = __builtin_amdgcn_readfirstlane(
                 !some ? 0 : gr.exact ? fine : top - kSumBits);
+            if (t == 0)
+                *s_wide = total == __builtin_inf() || (some && top - fine > kSumBits + kLowBits);
         }
         const Demand units = on_grid(d, gr);
         // width rho: every commodity that can reach a link counts once
@@ -477,6 +624,12 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             }
         }
         __syncthreads();
+        if constexpr (!MULTI && !ADAPT)
+            if (__builtin_amdgcn_readfirstlane(*s_wide) != 0) {              // workgroup-uniform
+                solve_wide<PRODUCT, L, QL, MAXC>(a, plan, n_comm, n_local, loc_link, l.count, links,
+                                                 red);
+                return;
+            }
         double wmax = 0.0;
         auto publish = [&](double v, int i) {
             const int4 gd = groups[i / kPatchGroup];       // first part, parts, own part, users
@@ -807,7 +960,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 if (__builtin_amdgcn_readfirstlane(*s_flag) != 0) break;     // workgroup-uniform
             }
             if (t == 0) {
-                if (*s_flag & 1) a.ad_flags[0] = 2;
+                if ((*s_flag & 1) || *s_wide != 0) a.ad_flags[0] = 2;
                 if (p == 0) {
                     a.ad_flags[1] = done;
                     a.ad_scalars[2] = lb_best;
@@ -875,7 +1028,9 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             if constexpr (MULTI) {
                 // (the largest of non-negative numbers is the largest of their bit patterns, and
                 // a quiet NaN is above them all)
-                if (*s_flag & 1) lam = __longlong_as_double(0x7FF8000000000000ll);
+                if ((*s_flag & 1) || *s_wide != 0) lam = __longlong_as_double(0x7FF8000000000000ll);
+                if (!ADAPT && *s_wide != 0)
+                    __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 (void)__hip_atomic_fetch_max(
                     reinterpret_cast<unsigned long long *>(a.lambda + plan),
                     static_cast<unsigned long long>(__double_as_longlong(lam)), __ATOMIC_RELAXED,

@@ -43,9 +43,8 @@ def direct_mesh(gpus):
     return _topology(k, 1e9 * (1 + np.arange(k) % 5), [[[e]] for e in range(k)])
 
 
-def islands(n, gpus):
-    """n nodes without links between them."""
-    t = W.build_fabric(1, gpus)
+def islands(n, t):
+    """n copies of a fabric without links between them."""
     one = [[[int(e) for e in t.path_links[t.path_link_ptr[p]:t.path_link_ptr[p + 1]]]
             for p in range(t.comm_path_ptr[k], t.comm_path_ptr[k + 1])] for k in range(t.n_comm)]
     return _topology(n * t.n_links, np.tile(t.cap, n),
@@ -212,8 +211,8 @@ def test_phases_can_be_timed_after_a_solve_in_one_launch():
 
 def test_patches_without_a_shared_link():
     """Fabrics the library cuts into several patches that have nothing to exchange but the width."""
-    for t, strips in ((direct_mesh(64), 4), (islands(40, 8), 3), (direct_mesh(64), 6),
-                      (islands(40, 8), 6)):
+    for t, strips in ((direct_mesh(64), 4), (islands(40, W.build_fabric(1, 8)), 3), (direct_mesh(64), 6),
+                      (islands(40, W.build_fabric(1, 8)), 6)):
         s = B.nimble_host_patch_check(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths,
                                       t.path_link_ptr, t.path_links, strips)
         assert s["failed"] == 0 and s["patches"] > 1 and s["parts"] == 0, s
@@ -230,7 +229,7 @@ def test_patches_without_a_shared_link_match_the_oracle(monkeypatch, strips, fla
     import torch
     if strips:
         monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
-    for name, t in (("mesh", direct_mesh(64)), ("islands", islands(40, 8))):
+    for name, t in (("mesh", direct_mesh(64)), ("islands", islands(40, W.build_fabric(1, 8)))):
         print(f"[patch] {name} strips={strips} flags={flags}", flush=True)
         d = np.floor(np.random.default_rng(11).pareto(1.1, (4, t.n_comm)) * 1e6)
         d[2] = 0.0
@@ -363,3 +362,44 @@ def test_a_refused_launch_falls_back(monkeypatch):
             assert got[1:] == (a["lam"], a["iters"], a["lb"]) and np.array_equal(got[0], a["splits"])
     finally:
         h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("strips", [1, 2, 3])
+def test_demands_of_any_range_keep_every_load(monkeypatch, strips, flags):
+    """Two separate fabrics, the second with demands and capacities 2^120 times the first one's (no
+    single grid holds both), and demands whose total over a patch overflows although no link's
+    load does.  Scaling by a power of two changes no bit of any quantity, and sums of whole numbers
+    below 2^53 units are exact in any order, so the oracle's bits are demanded."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    one = fabric(2, 8, "pair")
+    t = islands(2, one)
+    rng = np.random.default_rng(21)
+    d1 = np.floor(rng.pareto(1.1, one.n_comm) * 1e6)
+    t.cap = np.r_[one.cap, one.cap * 2.0 ** 120]
+    for name, d in (("apart", np.r_[d1, d1[::-1] * 2.0 ** 120]),
+                    ("further", np.r_[d1 * 2.0 ** -900, d1[::-1] * 2.0 ** 120])):
+        if name == "further":
+            t.cap = np.r_[one.cap * 2.0 ** -900, one.cap * 2.0 ** 120]
+        print(f"[patch] {name} strips={strips} flags={flags}", flush=True)
+        ref = oracle.solve(*t.csr(), d, 0.05, 60, flags=flags)
+        splits, lam, _ = _solve(t, d[None], 0.05, 60, flags)
+        assert lam[0] == ref["lam"] and np.array_equal(splits[0], ref["splits"]), name
+        if not flags:
+            ref = oracle.solve_adaptive(*t.csr(), d, 0.1, 60, 7)
+            h = B.nimble_topo_create(*t.csr())
+            try:
+                got = _adaptive(h, t, d, 0.1, 60, 7)
+            finally:
+                h.close()
+            assert got[1:] == (ref["lam"], ref["iters"], ref["lb"]), name
+            assert np.array_equal(got[0], ref["splits"]), name
+    # rail links carry 64 pairs: 2^1022 there, 480 pairs together overflow
+    t.cap = np.r_[one.cap, one.cap] * 2.0 ** 900
+    d = np.full(t.n_comm, 2.0 ** 1016)
+    ref = oracle.solve(*t.csr(), d, 0.05, 60, flags=flags)
+    assert np.isfinite(ref["lam"])
+    splits, lam, _ = _solve(t, d[None], 0.05, 60, flags)
+    assert lam[0] == ref["lam"] and np.array_equal(splits[0], ref["splits"])
