@@ -85,6 +85,11 @@ nimble_status_t nimble_debug_fail_allocation(int32_t nth);
 void nimble_debug_fail_host_allocation(void);
 int64_t nimble_debug_live_allocations(void);
 
+/* The same for the host-side build of the patch layout: 1 makes it run out of memory in the calling
+ * thread, 2 in a worker thread (either once), 3 lets no worker be started until 0 switches the hook
+ * off.  1 and 2 give NIMBLE_ERR_ALLOC; 3 only costs time. */
+void nimble_debug_fail_patch_build(int32_t where);
+
 /*
  * Test helper for the persistent regime: every grid-wide barrier of that kernel waits at most
  * `polls` polls of its arrival counter (default 2^22, about a second).  When a wait expires the

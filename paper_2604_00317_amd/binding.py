@@ -38,7 +38,7 @@ EXPORTS = [
     "nimble_topo_reserve_batch", "nimble_debug_fail_allocation",
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
     "nimble_host_patch_check", "nimble_debug_patches_gave_up",
-    "nimble_debug_refuse_cooperative",
+    "nimble_debug_refuse_cooperative", "nimble_debug_fail_patch_build",
 ]
 
 _lib = None
@@ -112,6 +112,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.nimble_debug_live_allocations.argtypes = []
     lib.nimble_debug_stream_read.restype = ctypes.c_int
     lib.nimble_debug_stream_read.argtypes = [vp, i64, i32, vp, vp]
+    lib.nimble_debug_fail_patch_build.restype = None
+    lib.nimble_debug_fail_patch_build.argtypes = [i32]
     lib.nimble_debug_refuse_cooperative.restype = None
     lib.nimble_debug_refuse_cooperative.argtypes = []
     lib.nimble_debug_patches_gave_up.restype = ctypes.c_int

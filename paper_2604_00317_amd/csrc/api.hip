@@ -11,6 +11,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <new>
 #include <string>
@@ -870,7 +871,13 @@ nimble_status_t nimble_topo_create(int32_t n_links, const double *cap, int32_t n
                    "record bodies");
     }
 
-    NIMBLE_TRY(make_patches(t, comm_path_ptr, path_link_ptr, path_links), "patch layouts");
+    try {
+        NIMBLE_TRY(make_patches(t, comm_path_ptr, path_link_ptr, path_links), "patch layouts");
+    } catch (const std::exception &) {           // out of memory, in whatever thread
+        release(t);
+        delete t;
+        return fail(NIMBLE_ERR_ALLOC, "host allocation failed (patch layouts)");
+    }
     {
         // the address of the static scratch on this device (nimble_plan_solve_static)
         unsigned char *sp = nullptr;

@@ -4,7 +4,9 @@
 #include <algorithm>
 #include <atomic>
 #include <climits>
+#include <exception>
 #include <map>
+#include <new>
 #include <thread>
 
 #include "../../include/nimble_plan.h"
@@ -165,20 +167,55 @@ int32_t slots_of(int32_t n_cand, int32_t p0, const int32_t *path_link_ptr,
 // the parts of a group are read eight users at a time
 int32_t padded_parts(int32_t users) { return (users + 7) / 8 * 8; }
 
+// Test hook: 1 the next range of a calling thread, 2 of a worker runs out of memory, 3 no worker
+// can be started.
+std::atomic<int32_t> g_fault{0};
+
+void fault_point(int32_t where)
+{
+    int32_t want = where;
+    if (g_fault.load() == where && g_fault.compare_exchange_strong(want, 0)) throw std::bad_alloc();
+}
+
+// f(begin, end) over ranges that cover 0..n-1, on up to eight threads.  Ranges whose thread cannot
+// be started run in the calling one; an exception of any range is thrown again here, once all
+// threads have ended.
 template <typename F>
 void parallel_ranges(int64_t n, F f, int64_t grain = 1)
 {
     int64_t want = std::max<int64_t>(1, std::min<int64_t>(8, std::thread::hardware_concurrency()));
     want = std::min(want, std::max<int64_t>(1, n / grain));
     if (want <= 1) {
+        fault_point(1);
         f(int64_t(0), n);
         return;
     }
+    std::vector<std::exception_ptr> thrown(static_cast<size_t>(want));
     std::vector<std::thread> pool;
-    for (int64_t w = 1; w < want; ++w)
-        pool.emplace_back([=] { f(n * w / want, n * (w + 1) / want); });
-    f(int64_t(0), n / want);
+    pool.reserve(static_cast<size_t>(want));
+    auto run = [&](int64_t w) {
+        try {
+            fault_point(w > 0 ? 2 : 1);
+            f(n * w / want, n * (w + 1) / want);
+        } catch (...) {
+            thrown[static_cast<size_t>(w)] = std::current_exception();
+        }
+    };
+    int64_t started = 1;
+    for (; started < want; ++started) {
+        try {
+            const int64_t w = started;
+            if (g_fault.load() == 3) throw std::bad_alloc();
+            pool.emplace_back([&run, w] { run(w); });
+        } catch (...) {
+            break;
+        }
+    }
+    run(0);
+    for (int64_t w = started; w < want; ++w) run(w);
     for (auto &t : pool) t.join();
+    for (const std::exception_ptr &e : thrown)
+        if (e) std::rethrow_exception(e);
 }
 
 }  // namespace
@@ -703,38 +740,44 @@ int check_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int3
 
 }  // namespace nimble
 
+extern "C" void nimble_debug_fail_patch_build(int32_t where) { nimble::g_fault.store(where); }
+
 extern "C" nimble_status_t nimble_host_patch_check(int32_t n_links, int32_t n_comm,
                                                    const int32_t *comm_path_ptr, int32_t n_paths,
                                                    const int32_t *path_link_ptr,
                                                    const int32_t *path_links, int32_t strips,
                                                    int32_t lanes, int64_t *out)
 {
-    std::string why;
-    nimble_status_t st = nimble::validate_csr(n_links, nullptr, n_comm, comm_path_ptr, n_paths,
-                                              path_link_ptr, path_links, why);
-    if (st != NIMBLE_OK) return st;
-    if (!out || strips < 1 || strips > 64 || lanes < 0) return NIMBLE_ERR_INVALID;
-    nimble::PatchScan scan;
-    nimble::PatchLayout t;
-    nimble::scan_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links, scan);
-    nimble::PatchCut cut;
-    nimble::PatchShape shape;
-    if (scan.fits) nimble::cut_patches(n_comm, scan, strips, cut);
-    if (scan.fits && nimble::patch_shape(scan, cut.most, lanes, shape))
-        nimble::build_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links, scan, cut,
-                              shape, t);
-    out[0] = t.n_patches;
-    out[1] = t.n_patches > 0 ? nimble::check_patches(n_links, n_comm, comm_path_ptr, path_link_ptr,
-                                                     path_links, t)
-                             : 0;
-    out[2] = t.shape.product;
-    out[3] = t.shape.lanes;
-    out[4] = t.shape.quads;
-    out[5] = t.shape.threads;
-    out[6] = t.max_local;
-    out[7] = t.max_groups;
-    out[8] = t.max_users;
-    out[9] = t.max_parts;
-    out[10] = t.n_parts;
-    return NIMBLE_OK;
+    try {
+        std::string why;
+        nimble_status_t st = nimble::validate_csr(n_links, nullptr, n_comm, comm_path_ptr, n_paths,
+                                                  path_link_ptr, path_links, why);
+        if (st != NIMBLE_OK) return st;
+        if (!out || strips < 1 || strips > 64 || lanes < 0) return NIMBLE_ERR_INVALID;
+        nimble::PatchScan scan;
+        nimble::PatchLayout t;
+        nimble::scan_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links, scan);
+        nimble::PatchCut cut;
+        nimble::PatchShape shape;
+        if (scan.fits) nimble::cut_patches(n_comm, scan, strips, cut);
+        if (scan.fits && nimble::patch_shape(scan, cut.most, lanes, shape))
+            nimble::build_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links, scan, cut,
+                                  shape, t);
+        out[0] = t.n_patches;
+        out[1] = t.n_patches > 0 ? nimble::check_patches(n_links, n_comm, comm_path_ptr, path_link_ptr,
+                                                         path_links, t)
+                                 : 0;
+        out[2] = t.shape.product;
+        out[3] = t.shape.lanes;
+        out[4] = t.shape.quads;
+        out[5] = t.shape.threads;
+        out[6] = t.max_local;
+        out[7] = t.max_groups;
+        out[8] = t.max_users;
+        out[9] = t.max_parts;
+        out[10] = t.n_parts;
+        return NIMBLE_OK;
+    } catch (const std::exception &) {           // out of memory, in whatever thread
+        return NIMBLE_ERR_ALLOC;
+    }
 }

@@ -403,3 +403,42 @@ def test_demands_of_any_range_keep_every_load(monkeypatch, strips, flags):
     assert np.isfinite(ref["lam"])
     splits, lam, _ = _solve(t, d[None], 0.05, 60, flags)
     assert lam[0] == ref["lam"] and np.array_equal(splits[0], ref["splits"])
+
+
+
+@pytest.mark.parametrize("where,status", [(1, 2), (2, 2), (3, 0)])
+def test_host_memory_running_out_is_a_status(where, status):
+    """The builder of the patch layout out of memory in the calling thread (1) or in a worker (2) is
+    a status; a worker that cannot be started (3) is done without.  (2: NIMBLE_ERR_ALLOC)"""
+    t = fabric(12, 8, "pair")                    # enough commodities for several workers
+    out = np.zeros(12, dtype=np.int64)
+    lib = B.load_library()
+    for fault in (where, 0):
+        lib.nimble_debug_fail_patch_build(fault)
+        st = lib.nimble_host_patch_check(t.n_links, t.n_comm, B._hp(t.comm_path_ptr), t.n_paths,
+                                         B._hp(t.path_link_ptr), B._hp(t.path_links), 4, 0,
+                                         B._hp(out))
+        assert st == (status if fault else B.NIMBLE_OK)
+        if st == B.NIMBLE_OK:
+            assert out[0] == 16 and out[1] == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", [1, 2, 3])
+def test_a_topology_survives_a_failed_patch_build(where):
+    """The same in nimble_topo_create, which gives back what it had allocated on the device."""
+    lib = B.load_library()
+    t = fabric(12, 8, "pair")
+    held = lib.nimble_debug_live_allocations()
+    lib.nimble_debug_fail_patch_build(where)
+    try:
+        if where == 3:
+            B.nimble_topo_create(*t.csr()).close()
+        else:
+            with pytest.raises(B.NimbleError) as ei:
+                B.nimble_topo_create(*t.csr())
+            assert ei.value.status == B.NIMBLE_ERR_ALLOC
+    finally:
+        lib.nimble_debug_fail_patch_build(0)
+    assert lib.nimble_debug_live_allocations() == held
+    B.nimble_topo_create(*t.csr()).close()
