@@ -47,6 +47,8 @@ PatchKernel kernel_of(const DevicePatches &p, bool cost_max, bool adaptive)
 
 }  // namespace patch
 
+constexpr size_t kLdsBytes = 160 * 1024;         // of a compute unit
+
 size_t patch_lds_bytes(const DevicePatches &p, bool adaptive)
 {
     return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups, p.max_comm,
@@ -58,11 +60,13 @@ int patch_blocks_per_cu(const DevicePatches &p, bool cost_max, bool adaptive)
 {
     const patch::PatchKernel k = patch::kernel_of(p, cost_max, adaptive);
     const size_t lds = patch_lds_bytes(p, adaptive);
-    if (k == nullptr || lds > 160 * 1024) return 0;
+    if (k == nullptr || lds > kLdsBytes) return 0;
     const void *f = reinterpret_cast<const void *>(k);
     int n = 0;
-    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds)) !=
-            hipSuccess ||
+    // (the limit belongs to the kernel, which topologies with patches of other sizes share: it is
+    // always set to all there is)
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            static_cast<int>(kLdsBytes)) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, p.shape.threads, lds) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
@@ -119,11 +123,6 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     }
     const size_t lds = patch_lds_bytes(p, adaptive != nullptr);
     const void *f = reinterpret_cast<const void *>(k);
-    if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 static_cast<int>(lds));
-        if (e != hipSuccess) return e;
-    }
     void *args[] = {&a};
     if (p.n_patches == 1 && adaptive == nullptr)
         return hipLaunchKernel(f, dim3(plans), dim3(p.shape.threads), args, lds, s);

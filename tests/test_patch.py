@@ -442,3 +442,28 @@ def test_a_topology_survives_a_failed_patch_build(where):
         lib.nimble_debug_fail_patch_build(0)
     assert lib.nimble_debug_live_allocations() == held
     B.nimble_topo_create(*t.csr()).close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("large,small,strips", [((3, 8, "pair"), (2, 8, "pair"), 1),
+                                                ((8, 8, "xor"), (4, 8, "xor"), 2)])
+def test_topologies_share_a_kernel_whatever_their_patches_need(monkeypatch, large, small, strips):
+    """A topology made after another one, with smaller patches of the same shape (and so the same
+    kernel), leaves the first one's solves as they were; with less and with more than 64 KB of
+    LDS."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_LANES", "1")
+    handles = []
+    try:
+        for f in (large, small):
+            t = fabric(*f)
+            d = np.floor(np.random.default_rng(5).pareto(1.1, t.n_comm) * 1e6)
+            handles.append((t, d, B.nimble_topo_create(*t.csr())))
+        for t, d, h in handles + handles:
+            splits, lam = B.plan(h, d, 0.05, 20)
+            ref = oracle.solve(*t.csr(), d, 0.05, 20)
+            assert lam == ref["lam"] and np.array_equal(splits, ref["splits"])
+    finally:
+        for _, _, h in handles:
+            h.close()
