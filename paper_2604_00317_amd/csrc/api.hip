@@ -1300,7 +1300,10 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
         if (!refused) {
             topo->gave_up = a.patch_abort;
             st = adaptive_results(topo, iters_done, lower_bound, s, gave_up);
-            if (st != NIMBLE_OK || !gave_up) return st;
+            if (st != NIMBLE_OK || !gave_up) {
+                topo->patch_solved = topo->patch_solved || st == NIMBLE_OK;
+                return st;
+            }
         }
     }
     const double gap = (1.0 + eps) * (1.0 + eps);

@@ -467,3 +467,23 @@ def test_topologies_share_a_kernel_whatever_their_patches_need(monkeypatch, larg
     finally:
         for _, _, h in handles:
             h.close()
+
+
+@pytest.mark.gpu
+def test_phases_can_be_timed_after_a_variable_step_in_one_launch():
+    """As after a solve of fixed step: a variable-step solve is a solve, whatever kernels it took."""
+    import torch
+    for t in (fabric(2, 8, "pair"), fabric(7, 6, "pair")):
+        d = np.floor(np.random.default_rng(9).pareto(1.1, t.n_comm) * 1e6)
+        h = B.nimble_topo_create(*t.csr())
+        try:
+            with pytest.raises(B.NimbleError):
+                B.nimble_debug_run_phase(h, 0, 1, torch.as_tensor(d).to("cuda:0"))
+            before = _adaptive(h, t, d, 0.1, 30, 4)
+            for phase in (1, 0, 1):
+                B.nimble_debug_run_phase(h, phase, 2, torch.as_tensor(d).to("cuda:0"))
+            torch.cuda.synchronize()
+            after = _adaptive(h, t, d, 0.1, 30, 4)
+            assert before[1:] == after[1:] and np.array_equal(before[0], after[0])
+        finally:
+            h.close()
