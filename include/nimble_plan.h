@@ -57,7 +57,8 @@ enum {
                                    one workgroup solves a plan, else as persistent); otherwise
                                    resident when the per-plan state fits in LDS, unless so few
                                    plans of a fabric with long reverse rows are asked for that
-                                   streaming them one after the other is faster */
+                                   streaming them one after the other is faster.  (The regimes
+                                   below, asked for by name, never run the patch kernels.) */
     NIMBLE_REGIME_RESIDENT = 1, /* one workgroup per plan, whole iteration loop in one kernel,
                                    state in LDS */
     NIMBLE_REGIME_STREAM = 2,   /* one kernel per phase: two or three launches per iteration

@@ -14,6 +14,11 @@
 extern "C" {
 #endif
 
+/* The patches (one workgroup each) the last solve on this topology was cut into: 1 or more if it
+ * was made in one launch by the patch kernels, 0 if it ran on the kernels of the regime that
+ * nimble_topo_regime reports, -1 for a NULL handle. */
+int32_t nimble_topo_last_patches(const nimble_topo_t *topo);
+
 /* 1 if nimble_plan_solve_adaptive, where it is not solved in one launch, applies the step of an
  * iteration inside the record kernel of the next one on this topology (two launches per iteration; the prices of the scan are formed
  * from the lengths before the step, the loads and the step, with the operations of the step

@@ -112,6 +112,7 @@ struct nimble_topo {
     int device = -1;
     int32_t forced_regime = NIMBLE_REGIME_AUTO;
     int32_t last_regime = NIMBLE_REGIME_AUTO;
+    int32_t last_patches = 0;       // patches of the last solve (0: it ran on other kernels)
     int64_t bytes_per_iter = 0, bytes_argmin = 0, bytes_reduce = 0, bytes_update = 0;
     int64_t bytes_lds_argmin = 0;   // LDS bytes the lane-major record kernels read per launch
     bool patch_solved = false;  // a solve ran on the patch kernels (which leave the workspace alone)
@@ -404,13 +405,12 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
 // iterations than the kernels count, or a stream under capture (a cooperative launch cannot be
 // recorded everywhere; the streaming regime can).
 const nimble::DevicePatches *pick_patches(const nimble_topo *t, int32_t plans, int32_t iters,
-                                          hipStream_t s, bool single_only = false)
+                                          hipStream_t s)
 {
     if (iters > nimble::kPatchMaxIters) return nullptr;
     const nimble::DevicePatches *best = nullptr;
     double best_us = 0.0;
     for (const nimble::DevicePatches &p : t->patches) {
-        if (single_only && p.n_patches > 1) continue;
         const int32_t at_once = p.n_patches > 1 ? p.max_teams : t->n_cu;
         const double us = p.iteration_us * ((plans + at_once - 1) / at_once);
         if (best == nullptr || us < best_us) {
@@ -544,13 +544,13 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
 {
     done = false;
     topo->gave_up = nullptr;
-    if (topo->forced_regime != NIMBLE_REGIME_AUTO && topo->forced_regime != NIMBLE_REGIME_RESIDENT)
-        return NIMBLE_OK;
+    topo->last_patches = 0;
+    // (a regime asked for by name is that regime's kernels, in their order of additions)
+    if (topo->forced_regime != NIMBLE_REGIME_AUTO) return NIMBLE_OK;
     // (lists of a single node: a thread per commodity and link with everything in registers; one
     // node of 8 GPUs, 200 iterations: 82 us, with the patch kernel 116)
     if (d_len == nullptr && nimble::resident_in_registers(topo->d)) return NIMBLE_OK;
-    const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s,
-                                                  topo->forced_regime == NIMBLE_REGIME_RESIDENT);
+    const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s);
     if (p == nullptr) return NIMBLE_OK;
     bool refused = false;
     hipError_t e = launch_patches(topo, *p, plans, d_traffic, d_len, eps, iters, d_splits, d_lambda,
@@ -565,6 +565,7 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
     }
     topo->last_regime = p->n_patches > 1 ? NIMBLE_REGIME_PERSISTENT : NIMBLE_REGIME_RESIDENT;
     topo->patch_solved = true;
+    topo->last_patches = p->n_patches;
     done = true;
     return NIMBLE_OK;
 }
@@ -951,6 +952,8 @@ int32_t nimble_topo_num_paths(const nimble_topo_t *t) { return t ? t->d.P : -1; 
 int64_t nimble_topo_nnz(const nimble_topo_t *t) { return t ? t->d.nnz : -1; }
 int64_t nimble_topo_bytes_per_iter(const nimble_topo_t *t) { return t ? t->bytes_per_iter : -1; }
 int32_t nimble_topo_regime(const nimble_topo_t *t) { return t ? t->last_regime : -1; }
+int32_t nimble_topo_last_patches(const nimble_topo_t *t) { return t ? t->last_patches : -1; }
+
 int32_t nimble_topo_adaptive_folds(const nimble_topo_t *t)
 {
     return t ? (adaptive_folds(t) ? 1 : 0) : -1;
@@ -1117,6 +1120,7 @@ nimble_status_t nimble_plan_solve_static(nimble_topo_t *topo, const double *d_tr
     hipError_t e = static_scratch_of(topo->device, &log);
     if (e != hipSuccess) return fail_hip(e, "hipGetSymbolAddress (static scratch)");
     topo->last_regime = NIMBLE_REGIME_STREAM;
+    topo->last_patches = 0;
     // every row of the log is written (entries 0..K-1) before it is read and nothing has to
     // start at zero, so what the previous call left behind does no harm
     return solve_stream(topo, d_traffic, eps, iters, d_splits, d_lambda,
@@ -1282,6 +1286,7 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
     if (st != NIMBLE_OK) return st;
     topo->last_regime = NIMBLE_REGIME_STREAM;
     bool gave_up = false;
+    topo->last_patches = 0;
     if (const nimble::DevicePatches *p = adaptive_patches(topo, max_iters)) {
         // the whole solve in one launch (and kernel by kernel after all if it is refused, or if
         // patches give up)
@@ -1302,6 +1307,7 @@ nimble_status_t nimble_plan_solve_adaptive(nimble_topo_t *topo, const double *d_
             st = adaptive_results(topo, iters_done, lower_bound, s, gave_up);
             if (st != NIMBLE_OK || !gave_up) {
                 topo->patch_solved = topo->patch_solved || st == NIMBLE_OK;
+                topo->last_patches = p->n_patches;
                 return st;
             }
         }

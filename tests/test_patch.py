@@ -487,3 +487,27 @@ def test_phases_can_be_timed_after_a_variable_step_in_one_launch():
             assert before[1:] == after[1:] and np.array_equal(before[0], after[0])
         finally:
             h.close()
+
+
+@pytest.mark.gpu
+def test_a_regime_asked_for_runs_its_own_kernels():
+    """Patch kernels are what the library picks by itself.  Asked for by name, the resident regime
+    runs its kernels, whose thread per link adds in the oracle's order: demands on no grid give the
+    oracle's bits in a batch of more plans than compute units."""
+    import oracle
+    w = W.make_config(1)
+    t, n = w.topo, 257
+    d = w.traffic * (1.0 + np.random.default_rng(0).random((n, t.n_comm)))
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        B.plan(h, d[0], w.eps, 30)
+        assert h.last_patches == 1 and h.regime == B.NIMBLE_REGIME_RESIDENT
+        for regime in (B.NIMBLE_REGIME_STREAM, B.NIMBLE_REGIME_PERSISTENT, B.NIMBLE_REGIME_RESIDENT):
+            B.nimble_topo_set_regime(h, regime)
+            splits, lam = B.plan(h, d[:3] if regime != B.NIMBLE_REGIME_RESIDENT else d, w.eps, 30)
+            assert h.last_patches == 0 and h.regime == regime
+        for b in (0, 1, 100, n - 1):
+            ref = oracle.solve(*t.csr(), d[b], w.eps, 30)
+            assert np.array_equal(splits[b], ref["splits"]) and lam[b] == ref["lam"], b
+    finally:
+        h.close()
