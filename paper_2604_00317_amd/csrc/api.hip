@@ -137,6 +137,7 @@ struct nimble_topo {
     std::vector<nimble::DevicePatches> patches;   // layouts of the patch kernels (may be none)
     const int32_t *idle = nullptr;                // links no candidate uses
     int32_t n_idle = 0;
+    bool patches_forced = false;                  // a switch asks for a layout: it is always used
     bool ad_fold_forced = false;                  // a switch asks for the launched adaptive solve
     // per-plan state: state_plans blocks of d.state_stride bytes in one allocation; the state
     // pointers of `d` are those of block 0
@@ -318,8 +319,8 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     p.maxima = nullptr;
     p.len_done = nullptr;
     p.abort_word = nullptr;
-    p.iteration_us = nimble::patch_scan_us(l.shape) +
-                     nimble::patch_exchange_us(l.n_patches, l.max_parts);
+    p.iteration_us = nimble::patch_iteration_us(l.shape, l.n_patches, l.max_groups, l.max_parts);
+    p.list_bytes = 4 * static_cast<int64_t>(l.words.size() + l.first.size());
     hipError_t e = upload(t, l.desc.data(), l.desc.size(), &p.desc);
     if (e == hipSuccess) e = upload(t, l.loc_link.data(), l.loc_link.size(), &p.loc_link);
     if (e == hipSuccess) e = upload(t, l.comm.data(), l.comm.size(), &p.comm);
@@ -339,55 +340,73 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     return e;
 }
 
+// Estimate of an iteration of `plans` plans without patches, in microseconds.  Streamed: two launches
+// of 3.2 us that read the layouts, and what every further plan of a launch adds (measured on 18
+// fabrics and 11 irregular topologies: 0.16 to 0.33 us per MB for one plan, 0.1 to 0.4 for further
+// ones).  `streamed`: the resident kernels are no choice (warm start, variable step).
+double general_iteration_us(const nimble_topo *t, int32_t plans, bool streamed)
+{
+    const double mb = 1e-6 * static_cast<double>(t->bytes_per_iter);
+    const int32_t side = std::min(plans, std::max(1, t->state_plans));
+    const double stream_us = ((plans + side - 1) / side) * (6.5 + mb * (0.23 + 0.35 * (side - 1)));
+    if (streamed || !nimble::resident_fits(t->d)) return stream_us;
+    if (nimble::resident_in_registers(t->d)) return 0.0;
+    return std::min(stream_us, nimble::resident_iteration_us(t->d, plans));
+}
+
+// How many microseconds `plans` plans of `iters` iterations take less on the layout than without
+// patches, by the estimates.  A solve of several patches has some 14 us more before its first
+// iteration (words of the exchange to clear, a cooperative launch) and loads the lists at about
+// 1 TB/s: one iteration of the 16-node fabric takes 41 us against 31 streamed, of the 64-node
+// fabric 130 against 83, and 16 iterations 83 against 140 and 256 against 358.
+double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int32_t plans,
+                       int32_t iters, bool streamed)
+{
+    const int32_t at_once = p.n_patches > 1 ? p.max_teams : t->n_cu;
+    const double us = p.iteration_us * ((plans + at_once - 1) / at_once);
+    const double before = p.n_patches > 1 ? 14.0 + 0.9e-6 * static_cast<double>(p.list_bytes) : 0.0;
+    return iters * (general_iteration_us(t, plans, streamed) - us) - before;
+}
+
 // Builds the patch layouts of a fabric: the one with the fewest patches, which solves the most
 // plans side by side, and the one whose estimate is lowest for a single plan, if that is another.
+// (Layouts that would never be faster than what runs without them are not made.)
 hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, const int32_t *pl)
 {
     const nimble::DeviceTopo &d = t->d;
     const char *env = std::getenv("NIMBLE_TUNE_PATCH_STRIPS");
     const char *env_lanes = std::getenv("NIMBLE_TUNE_PATCH_LANES");
     const int32_t forced = env ? std::atoi(env) : -1, lanes = env_lanes ? std::atoi(env_lanes) : 0;
-    if (forced == 0 || d.resident_generic) return hipSuccess;
+    t->patches_forced = forced > 0;
+    if (forced == 0 || d.resident_generic ||
+        d.K > static_cast<int64_t>(t->n_cu) * nimble::kPatchThreads)
+        return hipSuccess;
     nimble::PatchScan scan;
     nimble::scan_patches(d.E, d.K, cp, lp, pl, scan);
     if (!scan.fits) return hipSuccess;
-    nimble::PatchLayout built[2];
-    int32_t n_built = 0, best_strips = 0;
-    double best_us = 0.0;
-    int32_t parts = 0;            // of the layout with the fewest patches: about the same for all
-    for (int32_t strips = 1; strips * strips <= t->n_cu; ++strips) {
-        if (forced > 0 && strips != forced) continue;
-        // (most grids are ruled out by their size alone)
-        if (d.K > static_cast<int64_t>(strips) * strips * nimble::kPatchThreads) continue;
+    const nimble::PatchChoice c = nimble::choose_cuts(d.E, d.K, scan, t->n_cu, forced, lanes);
+    if (c.best == 0) return hipSuccess;
+    for (int32_t i = 0; i < 2; ++i) {
+        const int32_t strips = i == 0 ? c.best : c.fewest;
+        if (i == 1 && strips == c.best) break;
         nimble::PatchCut cut;
         nimble::PatchShape shape;
+        nimble::PatchLayout built;
         nimble::cut_patches(d.K, scan, strips, cut);
-        if (!nimble::patch_shape(scan, cut.most, lanes, shape)) continue;
-        if (n_built == 0) {
-            if (!nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, shape, built[0])) continue;
-            n_built = 1;
-            parts = built[0].max_parts;
-        }
-        const int64_t n = strips == 1 ? 1 : static_cast<int64_t>(strips) * strips;
-        const double us = nimble::patch_scan_us(shape) + nimble::patch_exchange_us(n, parts);
-        if (best_strips == 0 || us < best_us) {
-            best_us = us;
-            best_strips = strips;
-        }
-    }
-    if (n_built == 0) return hipSuccess;
-    {
-        nimble::PatchCut cut;
-        nimble::PatchShape shape;
-        nimble::cut_patches(d.K, scan, best_strips, cut);
-        if (static_cast<int32_t>(cut.members.size()) != built[0].n_patches &&
-            nimble::patch_shape(scan, cut.most, lanes, shape) &&
-            nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, shape, built[1]))
-            n_built = 2;
-    }
-    for (int32_t i = n_built - 1; i >= 0; --i) {
+        if (!nimble::patch_shape(scan, cut.most, lanes, shape) ||
+            !nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, shape, built))
+            continue;
         nimble::DevicePatches p;
-        const hipError_t e = upload_patches(t, built[i], p);
+        p.n_patches = built.n_patches;
+        p.max_teams = t->n_cu / built.n_patches;
+        p.iteration_us = nimble::patch_iteration_us(shape, built.n_patches, built.max_groups,
+                                                    built.max_parts);
+        p.list_bytes = 0;
+        if (!t->patches_forced && patches_gain_us(t, p, 1, 1000, true) <= 0.0 &&
+            patches_gain_us(t, p, 1, 1000, false) <= 0.0 &&
+            patches_gain_us(t, p, p.max_teams, 1000, false) <= 0.0)
+            continue;
+        const hipError_t e = upload_patches(t, built, p);
         if (e != hipSuccess) return e;
         p.adaptive = !d.cost_max && nimble::patch_blocks_per_cu(p, false, true) >= 1;
         if (nimble::patch_blocks_per_cu(p, d.cost_max, false) >= 1) t->patches.push_back(p);
@@ -401,21 +420,21 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
     return hipSuccess;
 }
 
-// The layout for `plans` plans on stream `s`, or null: no layout fits the fabric, more
-// iterations than the kernels count, or a stream under capture (a cooperative launch cannot be
-// recorded everywhere; the streaming regime can).
+// The layout for `plans` plans on stream `s`, or null: no layout fits the fabric or is faster than
+// what runs without one (`streamed`: the streaming kernels), more iterations than the kernels
+// count, or a stream under capture (a cooperative launch cannot be recorded everywhere; the
+// streaming regime can).
 const nimble::DevicePatches *pick_patches(const nimble_topo *t, int32_t plans, int32_t iters,
-                                          hipStream_t s)
+                                          hipStream_t s, bool streamed)
 {
     if (iters > nimble::kPatchMaxIters) return nullptr;
     const nimble::DevicePatches *best = nullptr;
-    double best_us = 0.0;
+    double most = 0.0;
     for (const nimble::DevicePatches &p : t->patches) {
-        const int32_t at_once = p.n_patches > 1 ? p.max_teams : t->n_cu;
-        const double us = p.iteration_us * ((plans + at_once - 1) / at_once);
-        if (best == nullptr || us < best_us) {
+        const double gain = patches_gain_us(t, p, plans, iters, streamed);
+        if ((gain > 0.0 || t->patches_forced) && (best == nullptr || gain > most)) {
             best = &p;
-            best_us = us;
+            most = gain;
         }
     }
     if (best != nullptr && best->n_patches > 1) {
@@ -550,7 +569,7 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
     // (lists of a single node: a thread per commodity and link with everything in registers; one
     // node of 8 GPUs, 200 iterations: 82 us, with the patch kernel 116)
     if (d_len == nullptr && nimble::resident_in_registers(topo->d)) return NIMBLE_OK;
-    const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s);
+    const nimble::DevicePatches *p = pick_patches(topo, plans, iters, s, d_len != nullptr);
     if (p == nullptr) return NIMBLE_OK;
     bool refused = false;
     hipError_t e = launch_patches(topo, *p, plans, d_traffic, d_len, eps, iters, d_splits, d_lambda,
@@ -595,6 +614,10 @@ static const nimble::DevicePatches *adaptive_patches(const nimble_topo_t *t, int
     const nimble::DevicePatches *best = nullptr;
     for (const nimble::DevicePatches &p : t->patches)
         if (p.adaptive && (best == nullptr || p.iteration_us < best->iteration_us)) best = &p;
+    // (a step of variable size costs either way about 3 us more than one of fixed size)
+    if (best != nullptr && !t->patches_forced &&
+        best->iteration_us >= general_iteration_us(t, 1, true))
+        return nullptr;
     return best;
 }
 
@@ -872,19 +895,11 @@ nimble_status_t nimble_topo_create(int32_t n_links, const double *cap, int32_t n
                    "record bodies");
     }
 
-    try {
-        NIMBLE_TRY(make_patches(t, comm_path_ptr, path_link_ptr, path_links), "patch layouts");
-    } catch (const std::exception &) {           // out of memory, in whatever thread
-        release(t);
-        delete t;
-        return fail(NIMBLE_ERR_ALLOC, "host allocation failed (patch layouts)");
-    }
     {
         // the address of the static scratch on this device (nimble_plan_solve_static)
         unsigned char *sp = nullptr;
         NIMBLE_TRY(static_scratch_of(t->device, &sp), "hipGetSymbolAddress (static scratch)");
     }
-#undef NIMBLE_TRY
     // a choice log for solves of up to kDefaultLogRows iterations, when that is small; larger
     // ones are the caller's decision (nimble_topo_reserve)
     if (!t->no_choice_log &&
@@ -935,6 +950,16 @@ nimble_status_t nimble_topo_create(int32_t n_links, const double *cap, int32_t n
     // every step of the 8 candidates of its two quads (padding steps included), or 9 for a
     // quad in the product shape
     if (d.n_records > 0 && d.rec_lane_major) t->bytes_lds_argmin = 64 * 8 * h.rec_price_reads;
+
+    // (last: what runs without patches is known now)
+    try {
+        NIMBLE_TRY(make_patches(t, comm_path_ptr, path_link_ptr, path_links), "patch layouts");
+    } catch (const std::exception &) {           // out of memory, in whatever thread
+        release(t);
+        delete t;
+        return fail(NIMBLE_ERR_ALLOC, "host allocation failed (patch layouts)");
+    }
+#undef NIMBLE_TRY
     *out = t;
     return NIMBLE_OK;
 }

@@ -81,6 +81,11 @@ struct PatchScan {
     bool fits = false;              // paths and candidate lists suit the slots
     int32_t product = 0;            // 1: product slots, 0: plain slots
     int32_t slots = 0;              // most slots of a commodity
+    // links of commodity k, each once: links[k / kBlock] from link_ptr[k] to link_ptr[k + 1] or
+    // the end of that block
+    static constexpr int32_t kBlock = 1024;
+    std::vector<std::vector<int32_t>> links;
+    std::vector<int32_t> link_ptr;
     std::vector<int32_t> x, y;      // [n_comm] rank of the commodity's coordinates
     std::vector<int32_t> x_cross, y_cross;   // links a cut after rank r would divide
     std::vector<int64_t> x_count, y_count;   // commodities up to and including rank r
@@ -101,11 +106,29 @@ void cut_patches(int32_t n_comm, const PatchScan &scan, int32_t strips, PatchCut
 // at most `most` commodities; false when there is none.
 bool patch_shape(const PatchScan &scan, int64_t most, int32_t lanes, PatchShape &out);
 
-// Estimated times in microseconds: of the scan, scatter and update of one iteration, and of the
-// exchange between the patches (64-byte parts a patch reads).  Fitted to measurements on fabrics
-// of 2 to 64 nodes; only the choice of a layout depends on them.
+// What a cut needs, found without building its layout.
+struct PatchSizes {
+    bool fits = false;              // its patches keep to their limits, LDS among them
+    int32_t patches = 0;
+    int32_t max_comm = 0, max_local = 0, max_groups = 0, max_parts = 0;      // as in PatchLayout
+};
+PatchSizes measure_cut(int32_t n_links, const PatchScan &scan, const PatchCut &cut,
+                       const PatchShape &shape);
+
+// Estimated times in microseconds of an iteration: the scan, scatter and update of one patch, and
+// the same with the exchange between several (its largest numbers of groups and of 64-byte parts).
 double patch_scan_us(const PatchShape &s);
-double patch_exchange_us(int64_t patches, int32_t parts);
+double patch_iteration_us(const PatchShape &s, int32_t patches, int32_t groups, int32_t parts);
+constexpr double kPatchTripUs = 1.76;     // a trip of a word from patch to patch and the fixed steps
+
+// The grids (strips) with the fewest patches and with the lowest estimate for one plan, of those
+// whose patches keep to their limits and are at most `most_patches`; 0: there is none.  The same if
+// they have equally many patches.
+struct PatchChoice {
+    int32_t fewest = 0, best = 0;
+};
+PatchChoice choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan, int32_t most_patches,
+                        int32_t forced, int32_t lanes);
 
 // The layout of a cut.  Returns false, with out.n_patches = 0, when a patch exceeds its limits.
 bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *comm_path_ptr,

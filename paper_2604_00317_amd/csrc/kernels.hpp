@@ -23,6 +23,7 @@ struct DevicePatches {
     double *len_done;            // [E] lengths a warm solve ended with, until it is known to be whole
     uint32_t *abort_word;
     double iteration_us;         // estimate of one iteration of max_teams plans
+    int64_t list_bytes;          // candidate lists a solve loads
     bool adaptive;               // the kernel of variable step runs on it
 };
 
