@@ -535,9 +535,10 @@ uint8_t *own_log(const nimble_topo *topo, int32_t iters, int32_t plans = 1)
             topo->log_rows >= static_cast<int64_t>(iters) * plans) ? topo->choice_log : nullptr;
 }
 
-// Launches the patch kernels.  `refused`: the device does not take the cooperative launch of
-// several patches just now (fewer compute units than the topology was made for, say) and nothing
-// of the solve has run; the kernels that need no cooperative launch are to be used.
+// Launches the patch kernels.  `refused`: the cooperative launch of several patches is not to be had
+// (to one process at a time: while another one on this device has made such a launch, it ends with
+// "the operation cannot be performed in the present state") and nothing of the solve has run; the
+// kernels that need no cooperative launch are to be used, and report whatever else is wrong.
 hipError_t launch_patches(nimble_topo *topo, const nimble::DevicePatches &p, int32_t plans,
                           const double *d_traffic, double *d_len, double eps, int32_t iters,
                           double *d_splits, double *d_lambda, hipStream_t s, bool &refused,
@@ -548,8 +549,7 @@ hipError_t launch_patches(nimble_topo *topo, const nimble::DevicePatches &p, int
     if (p.n_patches == 1 || g_refuse_cooperative.exchange(0) == 0)
         e = nimble::launch_patches(topo->d, p, plans, d_traffic, d_len, eps, iters,
                                    topo->spin_limit, d_splits, d_lambda, s, adaptive);
-    if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorLaunchOutOfResources ||
-        e == hipErrorNotSupported) {
+    if (e != hipSuccess && p.n_patches > 1) {
         (void)hipGetLastError();
         refused = true;
         return hipSuccess;

@@ -551,3 +551,50 @@ def test_patches_are_taken_where_they_are_the_faster_way():
         ref = oracle.solve(*t.csr(), d[0], 0.05, iters)
         got = (splits[0], lam[0]) if batch > 1 else (splits, lam)
         assert got[1] == ref["lam"] and np.array_equal(got[0], ref["splits"])
+
+
+OTHER_PROCESS = """
+import sys
+sys.path[:0] = [sys.argv[1], sys.argv[1] + "/tests"]
+import numpy as np
+import test_patch as T
+B, t = T.B, T.fabric(7, 6, "pair")
+d = np.floor(np.random.default_rng(9).pareto(1.1, t.n_comm) * 1e6)
+h = B.nimble_topo_create(*t.csr())
+splits, lam = B.plan(h, d, 0.05, 30)
+a = T._adaptive(h, t, d, 0.1, 30, 4)
+np.savez(sys.argv[2], splits=splits, lam=lam, patches=h.last_patches, adaptive=a[0], rest=a[1:])
+h.close()
+"""
+
+
+@pytest.mark.gpu
+def test_two_processes_share_a_gpu(tmp_path):
+    """Cooperative launches are to be had by one process at a time: while this one has its patches, a
+    second one gets the same plans from whatever kernels it can launch."""
+    import oracle
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    t = fabric(7, 6, "pair")
+    d = np.floor(np.random.default_rng(9).pareto(1.1, t.n_comm) * 1e6)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        B.plan(h, d, 0.05, 30)
+        assert h.last_patches > 1
+        out = str(tmp_path / "other.npz")
+        r = subprocess.run([sys.executable, "-c", OTHER_PROCESS, root, out], capture_output=True,
+                           text=True, timeout=100)
+        assert r.returncode == 0, r.stderr[-800:]
+        other = np.load(out)
+        ref = oracle.solve(*t.csr(), d, 0.05, 30)
+        assert float(other["lam"]) == ref["lam"] and np.array_equal(other["splits"], ref["splits"])
+        a = oracle.solve_adaptive(*t.csr(), d, 0.1, 30, 4)
+        assert other["rest"].tolist() == [a["lam"], a["iters"], a["lb"]]
+        assert np.array_equal(other["adaptive"], a["splits"])
+        print(f"[patch] the other process had {int(other['patches'])} patches", flush=True)
+        splits, lam = B.plan(h, d, 0.05, 30)
+        assert h.last_patches > 1 and lam == ref["lam"] and np.array_equal(splits, ref["splits"])
+    finally:
+        h.close()
