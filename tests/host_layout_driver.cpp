@@ -1,9 +1,11 @@
 // Driver for the sanitizer run of the host-side layout code (tests/test_host_sanitizers.py builds
-// it with -fsanitize=address,undefined together with csrc/host_topo.cpp; no HIP involved).
+// it with -fsanitize=address,undefined together with csrc/host_topo.cpp and csrc/host_patch.cpp; no
+// HIP involved).
 // Reads a topology from four binary files in a directory (cap.bin float64, cp.bin / lp.bin /
 // pl.bin int32), runs every host-only helper of the library on it and checks the round trips:
-// the streaming layout decodes to the plain reverse CSR, and every incidence reads back through
-// the forward records.  Exit status 0 and a line "OK ..." on success.
+// the streaming layout decodes to the plain reverse CSR, every incidence reads back through
+// the forward records, and patch layouts of several grids read back to the CSR, also after a build
+// that ran out of memory.  Exit status 0 and a line "OK ..." on success.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -71,6 +73,27 @@ int main(int argc, char **argv)
     int64_t stats[22] = {0};
     if (nimble_host_layout_stats(E, K, cp.data(), P, lp.data(), pl.data(), stats) != NIMBLE_OK)
         return 8;
+    int64_t patch[12] = {0};
+    const bool with_patches = argc > 2 && std::string(argv[2]) == "patches";
+    for (int32_t strips : {1, 2, 3, 5, 8, 16})
+        for (int32_t lanes : {0, 1, 4}) {
+            if (!with_patches || (lanes != 0 && strips != 3)) continue;
+            if (nimble_host_patch_check(E, K, cp.data(), P, lp.data(), pl.data(), strips, lanes,
+                                        patch) != NIMBLE_OK ||
+                patch[1] != 0) {
+                std::fprintf(stderr, "patch layout %d/%d: check %lld\n", strips, lanes,
+                             static_cast<long long>(patch[1]));
+                return 9;
+            }
+        }
+    for (int32_t fault : {1, 2, 3, 0}) {
+        if (!with_patches) break;
+        nimble_debug_fail_patch_build(fault);
+        const nimble_status_t st = nimble_host_patch_check(E, K, cp.data(), P, lp.data(), pl.data(), 3,
+                                                           0, patch);
+        // (few commodities need no worker that could fail)
+        if (st != NIMBLE_OK && !(st == NIMBLE_ERR_ALLOC && (fault == 1 || fault == 2))) return 10;
+    }
     std::printf("OK records %d pairs %lld octets %lld pieces %lld blocks %lld bodies %lld groups %lld\n", n_rec,
                 static_cast<long long>(stats[0]), static_cast<long long>(stats[1]),
                 static_cast<long long>(stats[10]), static_cast<long long>(stats[8]),

@@ -43,8 +43,12 @@ def check(oracle_mod, B, topo, demand, eps, max_iters, check_every, flags=0, fol
     return ref
 
 
+@pytest.mark.parametrize("patches", [True, False])
 @pytest.mark.parametrize("cfg,check_every", [(0, 10), (0, 1), (1, 7), (3, 25)])
-def test_stops_where_the_oracle_stops(oracle_mod, B, cfg, check_every):
+def test_stops_where_the_oracle_stops(oracle_mod, B, monkeypatch, cfg, check_every, patches):
+    """In one launch on the patch kernels and, without them, kernel by kernel."""
+    if not patches:
+        monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "0")
     w = W.make_config(cfg)
     print(f"[adaptive] config {cfg} check_every={check_every}", flush=True)
     ref = check(oracle_mod, B, w.topo, w.traffic, w.eps, 5000, check_every)

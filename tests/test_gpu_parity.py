@@ -303,6 +303,7 @@ def test_cooperative_resident_kernels(oracle_mod, B, seed, E, K, pm, lm, kind, f
     try:
         B.nimble_topo_set_regime(h, 1)
         splits, lam = B.plan(h, d, 0.07, 30)
+        assert h.last_patches == 0
     finally:
         h.close()
     for b in range(3):
@@ -310,8 +311,10 @@ def test_cooperative_resident_kernels(oracle_mod, B, seed, E, K, pm, lm, kind, f
         assert np.array_equal(splits[b], ref["splits"]) and lam[b] == ref["lam"], b
 
 
-def test_resident_kernels_on_either_side_of_the_cooperative_limit(oracle_mod, B):
-    """Up to 256 plans of the two-node fabric get a workgroup each (lanes share commodities and
+@pytest.mark.parametrize("regime", [0, 1])
+def test_resident_kernels_on_either_side_of_the_cooperative_limit(oracle_mod, B, regime):
+    """The resident regime, asked for (1; what the library picks by itself, 0, are the patch
+    kernels): up to 256 plans of the two-node fabric get a workgroup each (lanes share commodities and
     links); one plan more and all of them run on the thread-per-commodity kernel, several to a
     workgroup.  Both must give the oracle's plans."""
     w = W.make_config(1)
@@ -321,8 +324,10 @@ def test_resident_kernels_on_either_side_of_the_cooperative_limit(oracle_mod, B)
         tr = np.stack([np.floor(w.traffic / (1 + b % 7)) for b in range(n)])
         h = B.nimble_topo_create(*t.csr())
         try:
+            B.nimble_topo_set_regime(h, regime)
             splits, lam = B.plan(h, tr, w.eps, iters)
             assert h.regime == B.NIMBLE_REGIME_RESIDENT
+            assert h.last_patches == (1 if regime == 0 else 0)
         finally:
             h.close()
         for b in (0, 1, 6, n - 1):

@@ -27,12 +27,17 @@ def gpu_warm(B, h, topo, demand, eps, iters, len0):
     return splits.cpu().numpy(), float(lam.item()), ln.cpu().numpy()
 
 
+@pytest.mark.parametrize("patches", [True, False])
 @pytest.mark.parametrize("cfg,t1,t2,flags", [(0, 40, 60, 0), (1, 50, 70, 0), (1, 50, 70, 1),
                                              (3, 30, 40, 0), (4, 12, 13, 0)])
-def test_two_solves_in_a_row_match_the_oracle(oracle_mod, B, cfg, t1, t2, flags):
+def test_two_solves_in_a_row_match_the_oracle(oracle_mod, B, monkeypatch, cfg, t1, t2, flags,
+                                              patches):
     """A first plan from unit lengths, then a plan for different traffic from the lengths the
     first one returned: splits, lambda and the returned lengths are bit-identical to the
-    oracle, on the fused (config 3) and the tiled (config 4) reduce alike."""
+    oracle, on the patch kernels and, without them, streamed on the fused (config 3) and the tiled
+    (config 4) reduce alike."""
+    if not patches:
+        monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "0")
     w = W.make_config(cfg)
     t = w.topo
     print(f"[warm] config {cfg}", flush=True)
@@ -43,6 +48,7 @@ def test_two_solves_in_a_row_match_the_oracle(oracle_mod, B, cfg, t1, t2, flags)
         s1, l1, len1 = gpu_warm(B, h, t, w.traffic, w.eps, t1, np.ones(t.n_links))
         s2, l2, len2 = gpu_warm(B, h, t, d2, w.eps, t2, len1)
         assert h.regime == B.NIMBLE_REGIME_STREAM
+        assert (h.last_patches > 0) == patches
     finally:
         h.close()
     r1 = oracle_mod.solve(*t.csr(), w.traffic, w.eps, t1, flags=flags, len0=np.ones(t.n_links))

@@ -1,7 +1,8 @@
 """The host-side layout code under AddressSanitizer and UndefinedBehaviorSanitizer (no GPU).
 
 csrc/host_topo.cpp -- validation, reverse CSR, octets / tiles / strips / link blocks, forward
-records in all their formats -- is index arithmetic over vectors.  It is compiled here with g++
+records in all their formats -- and csrc/host_patch.cpp -- the patch layout, its cuts and its
+threads -- are index arithmetic over vectors.  They are compiled here with g++
 -fsanitize=address,undefined (no HIP involved) together with a small driver that runs every
 host-only helper on a topology and checks the round trips, over the benchmark fabrics, ragged
 random topologies and the layout options that reach the other code paths.  Any out-of-bounds
@@ -25,7 +26,8 @@ def driver(tmp_path_factory):
            "-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-static-libasan",
            "-static-libubsan",
            "-o", str(out), os.path.join(ROOT, "tests", "host_layout_driver.cpp"),
-           os.path.join(ROOT, "paper_2604_00317_amd", "csrc", "host_topo.cpp")]
+           os.path.join(ROOT, "paper_2604_00317_amd", "csrc", "host_topo.cpp"),
+           os.path.join(ROOT, "paper_2604_00317_amd", "csrc", "host_patch.cpp"), "-pthread"]
     subprocess.run(cmd, check=True)
     return str(out)
 
@@ -73,6 +75,8 @@ def test_host_layouts_under_sanitizers(driver, tmp_path, env_name):
             continue                      # (the large one only where its size matters)
         d = str(tmp_path / name)
         _dump(t, d)
-        r = subprocess.run([driver, d], env=env, capture_output=True, text=True)
+        # (the patch layout takes none of these options)
+        args = ["patches"] if env_name == "default" else []
+        r = subprocess.run([driver, d, *args], env=env, capture_output=True, text=True)
         assert r.returncode == 0, (name, env_name, r.stdout[-300:], r.stderr[-2000:])
         assert r.stdout.startswith("OK"), (name, r.stdout)

@@ -108,10 +108,10 @@ def test_patch_kernels_match_the_oracle(monkeypatch, strips, lanes, flags):
 @pytest.mark.gpu
 @pytest.mark.parametrize("strips", [1, 3])
 def test_fractional_demands_are_deterministic(monkeypatch, strips):
-    """Demands on no common grid: the loads are summed as integers (one rounding at the end), so
-    two runs agree bit for bit; the oracle's sequential sums differ from them by at most one
-    rounding per addition, K * 2^-53 relative, which may turn a tie but moves lambda by less than
-    a commodity's choice in one of the iterations does."""
+    """Demands on no common grid: a patch sums its loads as integers and rounds when it puts their
+    two halves together, so two runs agree bit for bit; the oracle's sequential sums differ from
+    them by at most one rounding per addition, K * 2^-53 relative, which may turn a tie but moves
+    lambda by less than a commodity's choice in one of the iterations does."""
     import oracle
     monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
     for f in FABRICS[1:5]:
@@ -142,7 +142,7 @@ def test_variable_step_matches_the_oracle(monkeypatch, strips, lanes):
     """The solve of variable step in one launch: the oracle's bits, its stop iteration and bound,
     with checks every iteration, never, and on the last; sums of 1, 255..257 and more terms (1x4:
     12, 3x4 xor: 132, 2x8: 240, 2x9: 306 pairs); no traffic; links no candidate uses; several
-    solves with one handle; the launched solve as well."""
+    solves with one handle; solved kernel by kernel as well."""
     import oracle
     monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
     monkeypatch.setenv("NIMBLE_TUNE_PATCH_LANES", str(lanes))
@@ -156,9 +156,13 @@ def test_variable_step_matches_the_oracle(monkeypatch, strips, lanes):
                 print(f"[patch adaptive] {name} strips={strips} lanes={lanes} {iters}/{every}",
                       flush=True)
                 ref = oracle.solve_adaptive(*t.csr(), d, 0.1, iters, every)
-                splits, lam, done, lb = _adaptive(h, t, d, 0.1, iters, every)
-                assert (done, lb, lam) == (ref["iters"], ref["lb"], ref["lam"]), (name, iters)
-                assert np.array_equal(splits, ref["splits"]), (name, iters)
+                for one_launch in (True, False):
+                    B.nimble_topo_set_regime(h, 0 if one_launch else B.NIMBLE_REGIME_STREAM)
+                    splits, lam, done, lb = _adaptive(h, t, d, 0.1, iters, every)
+                    assert (h.last_patches > 0) <= one_launch
+                    assert (done, lb, lam) == (ref["iters"], ref["lb"], ref["lam"]), (name, iters)
+                    assert np.array_equal(splits, ref["splits"]), (name, iters)
+                B.nimble_topo_set_regime(h, 0)
             ref = oracle.solve_adaptive(*t.csr(), 0 * d, 0.1, 9, 1)
             splits, lam, done, lb = _adaptive(h, t, 0 * d, 0.1, 9, 1)
             assert (done, lb, lam) == (0, 0.0, 0.0) and np.array_equal(splits, ref["splits"])
@@ -168,8 +172,9 @@ def test_variable_step_matches_the_oracle(monkeypatch, strips, lanes):
 
 @pytest.mark.gpu
 def test_a_team_that_cannot_meet_gives_up(monkeypatch):
-    """A poll limit of zero: patches that have to wait for each other abandon the solve, lambda is
-    NaN (or right, where nobody had to wait), and the topology works again afterwards."""
+    """A poll limit of zero: patches that have to wait for each other abandon the solve; lambda is
+    right all the same (see test_what_patches_give_up_is_solved_without_them), and the topology
+    works again afterwards."""
     import oracle
     monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "3")
     t = fabric(7, 6, "pair")
@@ -598,3 +603,101 @@ def test_two_processes_share_a_gpu(tmp_path):
         assert h.last_patches > 1 and lam == ref["lam"] and np.array_equal(splits, ref["splits"])
     finally:
         h.close()
+
+
+# (product slots, lanes, slots per lane) there are kernels for
+SHAPES = {(1, 1, q) for q in (1, 2, 3, 4, 6, 8)} | {(1, 2, q) for q in (1, 2, 3, 4)} | \
+         {(1, 4, 1), (1, 4, 2)} | {(0, 1, q) for q in (1, 2, 4)} | \
+         {(0, 2, q) for q in (1, 2, 4)} | {(0, 4, 1), (0, 4, 2)}
+
+
+def slotted(product, slots, seed=0):
+    """Commodities of up to `slots` slots: four paths over one middle link, reached two ways and
+    left two ways (product slots), or paths of four links that have nothing in common (plain)."""
+    rng = np.random.default_rng(1000 * product + 10 * slots + seed)
+    links, lists = 90, []
+    for k in range(70):
+        mine = []
+        for _ in range(slots if k % 3 else 1 + k % slots):
+            e = [int(x) for x in rng.permutation(links)]
+            if product:
+                mine += [[a, e[4], d] for a in e[:2] for d in e[2:4]]
+            else:
+                mine += [e[4 * i:4 * i + 4] for i in range(4)]
+        lists.append(mine if k % 5 or product else mine[:-1])
+    return _topology(links, 1e9 * (1 + np.arange(links) % 7), lists)
+
+
+def _shapes(strips):
+    """The shapes that the topologies of `slotted` have on a grid: shape -> (topology, lanes)."""
+    found = {}
+    for product in (1, 0):
+        for slots in range(1, 9):
+            t = slotted(product, slots)
+            for lanes in (1, 2, 4):
+                s = B.nimble_host_patch_check(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths,
+                                              t.path_link_ptr, t.path_links, strips, lanes)
+                assert s["failed"] == 0
+                if s["patches"] > 0 and (s["patches"] > 1) == (strips > 1):
+                    found.setdefault((s["product"], s["lanes"], s["slots_per_lane"]), (t, lanes))
+    return found
+
+
+@pytest.mark.parametrize("strips", [1, 3])
+def test_every_shape_has_a_topology(strips):
+    assert set(_shapes(strips)) == SHAPES
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("strips", [1, 3])
+def test_every_shape_matches_the_oracle(monkeypatch, strips):
+    """All kernels: every shape, for one patch and for several, both path costs, fixed and variable
+    step."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    for shape, (t, lanes) in sorted(_shapes(strips).items()):
+        monkeypatch.setenv("NIMBLE_TUNE_PATCH_LANES", str(lanes))
+        d = np.floor(np.random.default_rng(3).pareto(1.1, t.n_comm) * 1e6)
+        for flags in (0, 1):
+            print(f"[patch] shape {shape} strips={strips} flags={flags}", flush=True)
+            h = B.nimble_topo_create(*t.csr(), flags=flags)
+            try:
+                splits, lam = B.plan(h, d, 0.05, 60)
+                assert (h.last_patches > 1) == (strips > 1) and h.last_patches > 0
+                ref = oracle.solve(*t.csr(), d, 0.05, 60, flags=flags)
+                assert lam == ref["lam"] and np.array_equal(splits, ref["splits"]), shape
+                if not flags:
+                    got = _adaptive(h, t, d, 0.1, 60, 7)
+                    assert h.last_patches > 0
+                    ref = oracle.solve_adaptive(*t.csr(), d, 0.1, 60, 7)
+                    assert got[1:] == (ref["lam"], ref["iters"], ref["lb"]), shape
+                    assert np.array_equal(got[0], ref["splits"]), shape
+            finally:
+                h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("iters", [1, 4, 7])
+def test_teams_that_solve_several_plans(monkeypatch, iters, flags):
+    """More than twice as many plans as teams, and no multiple of it: what a team counts over its
+    exchanges and meetings goes on from plan to plan, for odd and even numbers of exchanges; plans
+    without traffic in the middle."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "4")
+    for t in (fabric(5, 8, "xor"), fabric(7, 6, "pair")):
+        h = B.nimble_topo_create(*t.csr(), flags=flags)
+        try:
+            B.plan(h, np.ones(t.n_comm), 0.05, 1)
+            n = 2 * (256 // h.last_patches) + 3
+            d = np.floor(np.random.default_rng(4).pareto(1.1, (n, t.n_comm)) * 1e6)
+            d[n // 2] = 0.0
+            d[5] = 0.0
+            print(f"[patch] {n} plans, {h.last_patches} patches, {iters} iterations", flush=True)
+            splits, lam = B.plan(h, d, 0.05, iters)
+            assert h.last_patches > 1
+            for b in range(n):
+                ref = oracle.solve(*t.csr(), d[b], 0.05, iters, flags=flags)
+                assert lam[b] == ref["lam"] and np.array_equal(splits[b], ref["splits"]), b
+        finally:
+            h.close()
