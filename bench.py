@@ -32,12 +32,20 @@ REGIME_NAMES = {1: "resident", 2: "stream", 3: "persistent"}
 PHASES = ["argmin", "load_reduce", "update"]
 
 
-def plan_bytes(topo, regime, bytes_, iters):
-    """Bytes a plan moves: the streamed layouts every iteration, or, where several workgroups keep
-    the lists on the chip, lists, demands and splits once."""
-    if regime == 3:
+def plan_bytes(topo, patches, bytes_, iters):
+    """Bytes a plan moves: the streamed layouts every iteration, or, where the workgroups of the patch
+    kernels keep the lists on the chip, lists, demands and splits once."""
+    if patches > 0:
         return 4 * topo.nnz + 4 * topo.n_paths + 8 * topo.n_comm + 8 * topo.n_paths
     return bytes_["total"] * iters
+
+
+def adaptive_launches(h):
+    """Launches of the variable-step solve just made: clearing and solving where it ran on patches,
+    else two per iteration (the step applied inside the next record kernel) or three."""
+    if h.last_patches > 0:
+        return dict(launches_per_plan=2)
+    return dict(launches_per_iteration=2 if h.adaptive_folds else 3)
 
 
 def phase_bytes(lib_topo):
@@ -165,7 +173,7 @@ def run_config(B, W, torch, cfg, regime, steps, warmup, iters_override=0, batch_
     elapsed = time.perf_counter() - t0
     return dict(w=w, topo=topo, h=h, batch=batch, d_traffic=d_traffic, d_splits=d_splits,
                 d_lambda=d_lambda, elapsed=elapsed, event_s=ev0.elapsed_time(ev1) * 1e-3,
-                regime=h.regime, t_gen=t_gen, t_create=t_create)
+                regime=h.regime, patches=h.last_patches, t_gen=t_gen, t_create=t_create)
 
 
 def main() -> int:
@@ -207,7 +215,7 @@ def main() -> int:
     r = run_config(B, W, torch, args.config, args.regime, args.steps, args.warmup, args.iters,
                    args.batch, args.copy_calib, plans=args.plans)
     w, topo, h, batch = r["w"], r["topo"], r["h"], r["batch"]
-    elapsed, regime = r["elapsed"], r["regime"]
+    elapsed, regime, r_patches = r["elapsed"], r["regime"], r["patches"]
     ms_per_step = elapsed * 1e3 / args.steps
     iters_per_s = w.iters * batch * args.steps / elapsed
     plans_per_s = batch * args.steps / elapsed
@@ -280,11 +288,18 @@ def main() -> int:
     else:
         # one kernel per step: its duration is the step time measured with HIP events
         sec = r["event_s"] / args.steps
-        total = plan_bytes(topo, regime, bytes_, w.iters) * batch
+        total = plan_bytes(topo, r["patches"], bytes_, w.iters) * batch
         name = REGIME_NAMES.get(regime, "auto")
+        if r["patches"] > 0:
+            name = f"k_patch, {r['patches']} workgroups per plan"
         roofline = dict(bound="hbm", kernel=name, achieved=total / sec / 1e9, peak=HBM_PEAK_GBS,
                         unit="GB/s", frac=total / sec / 1e9 / HBM_PEAK_GBS,
-                        traffic=None)
+                        us_per_iteration=sec * 1e6 / w.iters, traffic=None)
+        if r["patches"] > 0:
+            roofline["bound"] = "latency"
+            roofline["note"] = ("lists, prices and loads stay on the chip for the whole plan: bound "
+                                "by the dependent steps of an iteration (scan, scatter, trip from "
+                                "patch to patch), not by the bytes, which are priced all the same")
 
     # ---- CPU baseline: the oracle on a bounded sample -------------------------------------
     cpu = None
@@ -376,7 +391,7 @@ def main() -> int:
                         gap=lam_ad / lb if lb > 0 else None, target_gap=(1 + w.eps) ** 2,
                         lambda_fixed_step=lam_fixed, fixed_step_iters=w.iters,
                         fixed_step_ms=ms_per_step,
-                        launches_per_iteration=2 if h.adaptive_folds else 3)
+                        patches=h.last_patches, **adaptive_launches(h))
     h.close()
     del r
 
@@ -392,17 +407,16 @@ def main() -> int:
                 plans_per_s=q["batch"] * steps / q["elapsed"],
                 ms_per_step=q["elapsed"] * 1e3 / steps,
                 us_per_iteration=q["elapsed"] * 1e6 / steps / q["w"].iters,
-                regime=REGIME_NAMES.get(q["regime"], "auto"), batch=q["batch"],
-                iters=q["w"].iters)
+                regime=REGIME_NAMES.get(q["regime"], "auto"), patches=q["patches"],
+                batch=q["batch"], iters=q["w"].iters)
             also[key] = entry
             if cfg == 3 and not plans:
-                # the 16-node fabric, named by the bandwidth target as well: its 5 MB per
-                # iteration stay in the caches, two dependent launches per iteration
+                # the 16-node fabric, named by the bandwidth target as well
                 single_c3 = entry["plans_per_s"]
                 b3 = phase_bytes(q["h"])
-                gbs = (plan_bytes(q["topo"], q["regime"], b3, q["w"].iters) * steps /
+                gbs = (plan_bytes(q["topo"], q["patches"], b3, q["w"].iters) * steps /
                        q["elapsed"] / 1e9)
-                entry["roofline"] = dict(bound="hbm", bytes_per_iter=b3["total"],
+                entry["roofline"] = dict(bound="latency" if q["patches"] else "hbm", bytes_per_iter=b3["total"],
                                          us_per_iter=entry["us_per_iteration"], achieved=gbs,
                                          peak=HBM_PEAK_GBS, unit="GB/s", frac=gbs / HBM_PEAK_GBS,
                                          note="bound by the dependent steps of an iteration, "
@@ -414,8 +428,7 @@ def main() -> int:
                         ks["reduce_update" if ph == 1 and not b3["update"] else name] = dict(
                             back_to_back_us=sec * 1e6, bytes=b3[name])
                 entry["kernels"] = ks
-                # the adaptive step on the same fabric (two launches per iteration where the
-                # step is applied inside the next record kernel, else three)
+                # the adaptive step on the same fabric
                 ws = q["w"]
                 for _ in range(2):
                     torch.cuda.synchronize()
@@ -428,8 +441,8 @@ def main() -> int:
                                               us_per_iteration=dt_ad * 1e6 / n_ad, check_every=25,
                                               lower_bound=lb_ad,
                                               lambda_=float(q["d_lambda"].item()),
-                                              launches_per_iteration=2 if q["h"].adaptive_folds
-                                              else 3)
+                                              patches=q["h"].last_patches,
+                                              **adaptive_launches(q["h"]))
             if cfg == 3 and plans and single_c3:
                 entry["speedup_over_one_plan_at_a_time"] = entry["plans_per_s"] / single_c3
             if cfg == 2:
@@ -504,6 +517,7 @@ def main() -> int:
                    "incidences": topo.nnz, "links": topo.n_links, "eps": w.eps, "iters": w.iters,
                    "batch": batch, "regime": REGIME_NAMES.get(regime, "auto")},
         "plans_per_s": plans_per_s,
+        "patches": r_patches,
         "lambda": float(lam[0]),
         "bytes_per_iter": bytes_["total"],
         "roofline": roofline,

@@ -106,7 +106,9 @@ void nimble_topo_destroy(nimble_topo_t *topo);
  *   d_traffic   device [n_comm], bytes, finite and >= 0 (not checked: checking would need a
  *               host synchronisation).  Results are bit-identical to the sequential
  *               definition when demands are integer-valued with total < 2^53; otherwise they
- *               are still identical from run to run, with loads summed in a fixed tree order.
+ *               are still identical from run to run: loads are summed exactly and rounded once or
+ *               twice by each of the workgroups a plan is cut into, or in a fixed order, depending
+ *               on the kernels, and so on the number of plans and iterations.
  *   eps         step size, 0 < eps <= 0.5
  *   iters       number of Jacobi iterations, >= 1, iters * log1p(eps) <= 700 (else lengths
  *               could overflow: NIMBLE_ERR_RANGE)
@@ -223,7 +225,7 @@ nimble_status_t nimble_alg1_solve_batch(nimble_topo_t *topo, int32_t batch,
  *   d_len   device [n_links], by link id, in and out; every entry finite and > 0 (1.0
  *           everywhere is the cold start).  Lengths grow by at most (1 + eps) per iteration:
  *           the caller rescales them (e.g. by a power of two, which changes nothing else)
- *           before they can overflow.
+ *           before they can overflow.  Written when the whole plan is made, not before.
  * The other arguments as for nimble_plan_solve.  Reported as the streaming regime; like
  * nimble_plan_solve it only enqueues work.
  */
@@ -251,14 +253,14 @@ nimble_status_t nimble_plan_solve_warm(nimble_topo_t *topo, const double *d_traf
  *   iters_done   host out: iterations made (0 for all-zero traffic: every pair then stays on
  *                its first candidate)
  *   lower_bound  host out: best LB seen (0 if no check was made)
- * The stop decision is taken on the device.  Fabrics that fit the patch kernels are solved in one
+ * The stop decision is taken on the device.  Fabrics that the patch kernels suit are solved in one
  * launch; on others the host enqueues ahead and follows the device's progress through two words
  * of pinned memory, so the stream is never synchronised during the solve (kernels enqueued after
  * the stop return at once).  Unlike nimble_plan_solve the call
  * waits for the stream before it returns, because iters_done and lower_bound are host outputs,
  * and it cannot be captured into a graph.  Reported as the streaming regime; needs the
- * per-iteration choice log of max_iters rows and grows it when it is shorter (NIMBLE_ERR_ALLOC if
- * it cannot be allocated,
+ * per-iteration choice log of max_iters rows (patch kernels that give up are followed by kernels
+ * that write it) and grows it when it is shorter (NIMBLE_ERR_ALLOC if it cannot be allocated,
  * NIMBLE_ERR_RANGE beyond 1 GiB), as well as a workspace of its own on the first call.
  * Bit-identical to the plain CPU definition for integer-valued demands.
  */

@@ -20,10 +20,10 @@ extern "C" {
 int32_t nimble_topo_last_patches(const nimble_topo_t *topo);
 
 /* 1 if nimble_plan_solve_adaptive, where it is not solved in one launch, applies the step of an
- * iteration inside the record kernel of the next one on this topology (two launches per iteration; the prices of the scan are formed
- * from the lengths before the step, the loads and the step, with the operations of the step
- * itself), 0 if in a launch of its own (three), -1 for a NULL handle.  Both give the same
- * bits. */
+ * iteration inside the record kernel of the next one on this topology (two launches per iteration;
+ * the prices of the scan are formed from the lengths before the step, the loads and the step, with
+ * the operations of the step itself), 0 if in a launch of its own (three), -1 for a NULL handle.
+ * Both give the same bits. */
 int32_t nimble_topo_adaptive_folds(const nimble_topo_t *topo);
 
 /* 1 if the resident regime would run this topology with one commodity and one link per thread,
@@ -38,7 +38,8 @@ int32_t nimble_topo_resident_in_registers(const nimble_topo_t *topo);
  * (phase 0: path-cost gather + argmin, 1: link-load reduce, 2: length update with step 0; on
  * topologies whose reduce and update run as one kernel phase 1 is that kernel and phase 2 is
  * refused with NIMBLE_ERR_INVALID).  The state must have been initialised by a previous
- * streaming-regime nimble_plan_solve on this topology with the same d_traffic.  Used to time a
+ * streaming-regime nimble_plan_solve on this topology with the same d_traffic; after solves on the
+ * patch kernels, which leave the state alone, the call initialises it itself.  Used to time a
  * kernel's average launch with HIP events.
  */
 nimble_status_t nimble_debug_run_phase(nimble_topo_t *topo, int32_t phase, int32_t reps,
@@ -96,7 +97,7 @@ int64_t nimble_debug_live_allocations(void);
 void nimble_debug_fail_patch_build(int32_t where);
 
 /*
- * Test helper for the persistent regime: every grid-wide barrier of that kernel waits at most
+ * Test helper for the persistent regime (and the patch kernels, see below): every grid-wide barrier of that kernel waits at most
  * `polls` polls of its arrival counter (default 2^22, about a second).  When a wait expires the
  * solve is abandoned -- every workgroup leaves the kernel at its next poll, d_splits is left
  * undefined and d_lambda[0] is written as NaN.  With polls = 0 the first barrier that is not
@@ -203,8 +204,9 @@ nimble_status_t nimble_host_resident_kernel(int32_t n_links, int32_t n_comm,
 
 /*
  * Host-only helper (no device call): builds the patch layout of a grid of strips x strips patches
- * (1..64), with `lanes` lanes per commodity (0: the library's choice), and checks it: every candidate reads back from the slots link by link,
- * every part of the exchange has one writer, every link in use one patch that reports it.
+ * (1..64), with `lanes` lanes per commodity (0: the library's choice), and checks it: every
+ * candidate reads back from the slots link by link, every part of the exchange has one writer, every
+ * link in use one patch that reports it, and its sizes are those found without building it.
  * out[11]: patches (0: the fabric or the grid does not suit the patch kernels), the number of
  * the check that failed (0: none), 1 for product slots, lanes per commodity, slots per lane,
  * threads, most local links of a patch, most groups, most users of a group, most parts (eight

@@ -602,7 +602,6 @@ nimble_status_t solve_persistent(nimble_topo *topo, const double *d_traffic, dou
 
 }  // namespace
 
-// whether nimble_plan_solve_adaptive applies a step inside the next iteration's record kernel
 // The layout the adaptive solve runs on in one launch, or null: it is then launched kernel by
 // kernel.  (Every iteration is a trip from patch to patch longer than the fixed step's; the
 // limit on the iterations keeps one launch to a few seconds.)
@@ -640,6 +639,7 @@ static nimble_status_t adaptive_results(nimble_topo_t *t, int32_t *iters_done, d
     return NIMBLE_OK;
 }
 
+// whether nimble_plan_solve_adaptive applies a step inside the next iteration's record kernel
 static bool adaptive_folds(const nimble_topo_t *t)
 {
     if (t->ad_fold == 0 || (t->d.n_blocks <= 0 && t->d.n_gblocks <= 0)) return false;

@@ -1,11 +1,11 @@
 // Patch kernels of the solve with variable step and certificate (path cost = the sum of the
 // prices), for fabrics of one patch and of several.
 //
-// The launched form takes two kernels per iteration (9.3 us on the 16-node fabric) and reads the
-// topology in each.  Here an iteration is the fixed step's (scan, scatter, exchange of the loads of
-// shared links: 2.9 us there) plus one more trip from patch to patch for the largest normalised
-// load (2.2 to 3 us), and a check of the bound, every 25 iterations, takes 11 us: 6.3 us per
-// iteration in all.  The two trips, about 1.6 us each, bound it.
+// The launched form takes two or three kernels per iteration and reads the topology in each.  Here
+// an iteration is the fixed step's (scan, scatter, exchange of the loads of shared links: 2.8 us on
+// the 16-node fabric) plus one more trip from patch to patch for the largest normalised load, 6.0 us
+// together, and a check of the bound takes another 11 us.  With a check every 25 iterations: 9.3 ->
+// 6.5 us per iteration on 16 nodes, 14.5 -> 8.2 on 24, 7.8 -> 2.1 on 2 (one patch, no trips).
 #include "patch_kernel.hpp"
 
 namespace nimble {

@@ -1,5 +1,5 @@
-// Patch kernels for fabrics of several patches, path cost = the largest price (a file of their own: they take long to
-// compile).
+// Patch kernels for fabrics of several patches, path cost = the largest price (a file of their own:
+// they take long to compile).
 #include "patch_kernel.hpp"
 
 namespace nimble {

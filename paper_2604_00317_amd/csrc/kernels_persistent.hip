@@ -9,9 +9,9 @@
 // abort word, every block sees it at its next poll and leaves the kernel, and the epilogue is
 // skipped (lambda is set to NaN by the block that gave up), so no wave can wait forever.
 //
-// The same kernel with one workgroup (ALONE) waits for nobody.  It follows every solve of several
+// The same with one workgroup (k_alone) waits for nobody.  It follows every solve of several
 // patches (patch_kernel.hpp) in the stream: where that went through, it hands over the lengths of
-// a warm start or returns at once (2 us); where patches gave up waiting for each other, it solves
+// a warm start or returns at once (1.3 to 5 us); where patches gave up waiting for each other, it solves
 // the plans they left undone, slowly but surely.
 #include <algorithm>
 
@@ -108,7 +108,7 @@ struct PersistentArgs {
     int iters;
     double *splits, *lambda;
     unsigned int spin_limit;
-    // ALONE: the word that says whether the patches gave up, their lengths (null: nobody wants
+    // k_alone: the word that says whether the patches gave up, their lengths (null: nobody wants
     // them) and the caller's, and how many plans there are
     const uint32_t *gave_up;
     const double *len_done;

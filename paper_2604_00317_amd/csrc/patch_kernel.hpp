@@ -27,16 +27,17 @@
 // are the units, and the sum is what exact additions give; elsewhere a demand is split into
 // 2^-61 of the patch's total and 2^-105 of it, which holds every demand that is not below 2^-52 of
 // the total to the last bit; both sums are exact, each is rounded to binary64, and so is what they
-// add up to.  (64-bit integer additions also take the LDS 6.2 cycles a wave where binary64 ones
-// take 8.2, and 2 instead of 3 for every lane that meets another on the same link.)
+// add up to (and, with several patches, what the parts of a link add up to).
 // Demands that lie further apart, or whose total overflows, are on no such grid: one patch adds
 // them as binary64 numbers one after the other, in code of its own (solve_wide: a branch in the
 // ordinary loop cost plans of one patch 4 to 15 %); several patches mark the plan as given up.
 //
 // What bounds it and what it measured, us per iteration against two launches per iteration (and,
-// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 2.64 -> 0.84 (one
-// patch: the chain scan, barrier, scatter, update), 16 nodes 7.2 -> 2.7 (the trip of a word from
-// patch to patch takes 1.6), 64 nodes 18.5 -> 7.7 (scan 3.6, then the parts of 31 users).
+// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 2.64 -> 0.91 (one
+// patch: the chain scan, barrier, scatter, update; the LDS is busy for half of it), 7 nodes of 6
+// 7.1 -> 2.4 and 16 nodes 7.3 -> 2.8 (the trip of a word from patch to patch and the fixed steps take
+// 1.8), 64 nodes 18.5 -> 7.9 (the LDS is busy for 7200 of 19000 cycles, half of them bank conflicts;
+// then the parts of 31 users).
 #pragma once
 #include <hip/hip_runtime.h>
 
