@@ -421,26 +421,31 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
 }
 
 // The layout for `plans` plans on stream `s`, or null: no layout fits the fabric or is faster than
-// what runs without one (`streamed`: the streaming kernels), more iterations than the kernels
-// count, or a stream under capture (a cooperative launch cannot be recorded everywhere; the
-// streaming regime can).
+// what runs without one (`streamed`: the streaming kernels), or more iterations than the kernels
+// count.  A stream under capture takes a layout of one patch or none (a cooperative launch cannot
+// be recorded everywhere; the streaming regime can).
 const nimble::DevicePatches *pick_patches(const nimble_topo *t, int32_t plans, int32_t iters,
                                           hipStream_t s, bool streamed)
 {
     if (iters > nimble::kPatchMaxIters) return nullptr;
-    const nimble::DevicePatches *best = nullptr;
-    double most = 0.0;
-    for (const nimble::DevicePatches &p : t->patches) {
-        const double gain = patches_gain_us(t, p, plans, iters, streamed);
-        if ((gain > 0.0 || t->patches_forced) && (best == nullptr || gain > most)) {
-            best = &p;
-            most = gain;
+    auto pick = [&](bool several) {
+        const nimble::DevicePatches *best = nullptr;
+        double most = 0.0;
+        for (const nimble::DevicePatches &p : t->patches) {
+            if (p.n_patches > 1 && !several) continue;
+            const double gain = patches_gain_us(t, p, plans, iters, streamed);
+            if ((gain > 0.0 || t->patches_forced) && (best == nullptr || gain > most)) {
+                best = &p;
+                most = gain;
+            }
         }
-    }
+        return best;
+    };
+    const nimble::DevicePatches *best = pick(true);
     if (best != nullptr && best->n_patches > 1) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
-        if (cap != hipStreamCaptureStatusNone) return nullptr;
+        if (cap != hipStreamCaptureStatusNone) return pick(false);
     }
     return best;
 }
@@ -610,13 +615,19 @@ static const nimble::DevicePatches *adaptive_patches(const nimble_topo_t *t, int
     if (t->d.cost_max || t->ad_fold_forced || max_iters > 1 << 20 ||
         t->forced_regime != NIMBLE_REGIME_AUTO)
         return nullptr;
+    // A step of variable size takes longer than one of fixed size: 0.9 us with one patch (2 nodes: 1.8
+    // against 0.9), 3.2 with several (16 nodes: 6.0 against 2.8; 24: 7.6 against 4.6), and about as
+    // much kernel by kernel (24 nodes: 13.9 against 10.7).
+    constexpr double kOnePatch = 0.9, kMore = 3.2;
     const nimble::DevicePatches *best = nullptr;
-    for (const nimble::DevicePatches &p : t->patches)
-        if (p.adaptive && (best == nullptr || p.iteration_us < best->iteration_us)) best = &p;
-    // (a step of variable size costs either way about 3 us more than one of fixed size)
-    if (best != nullptr && !t->patches_forced &&
-        best->iteration_us >= general_iteration_us(t, 1, true))
-        return nullptr;
+    double best_us = t->patches_forced ? 1e30 : general_iteration_us(t, 1, true) + kMore;
+    for (const nimble::DevicePatches &p : t->patches) {
+        const double us = p.iteration_us + (p.n_patches > 1 ? kMore : kOnePatch);
+        if (p.adaptive && us < best_us) {
+            best = &p;
+            best_us = us;
+        }
+    }
     return best;
 }
 

@@ -378,7 +378,9 @@ double patch_scan_us(const PatchShape &s)
     const double waves = s.threads / 64.0;
     const double lds = waves * (s.quads * (s.product ? 36.0 : 80.0) + 50.0 + 80.0 / s.lanes);
     const double valu = waves * (s.quads * (s.product ? 28.0 : 50.0) + (s.lanes > 1 ? 85.0 : 70.0));
-    return 0.3 + 0.06 * s.quads + std::max(lds, valu) / 2400.0;
+    // (fabrics of one patch, 240 to 992 pairs: 0.85, 1.28, 1.56, 1.99 and 2.16 us measured where this
+    // says 0.85, 1.43, 1.15, 2.09 and 2.07)
+    return 0.88 * (0.3 + 0.06 * s.quads + std::max(lds, valu) / 2400.0);
 }
 
 double patch_iteration_us(const PatchShape &s, int32_t patches, int32_t groups, int32_t parts)
@@ -496,8 +498,8 @@ PatchSizes measure_cut(int32_t n_links, const PatchScan &scan, const PatchCut &c
     return m;
 }
 
-PatchChoice choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan, int32_t most_patches,
-                        int32_t forced, int32_t lanes)
+PatchChoice choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan,
+                        int32_t most_patches, int32_t forced, int32_t lanes)
 {
     int32_t most_strips = 1;
     while ((most_strips + 1) * (most_strips + 1) <= most_patches) ++most_strips;
@@ -533,9 +535,8 @@ PatchChoice choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan, 
         for (int64_t s = s0; s < s1; ++s) try_strips(static_cast<int32_t>(s) + 2);
     }, n_comm < 2048 ? 16 : 1);
     for (int32_t s = 2; s <= most_strips; ++s) offer(s);
-    if (c.best != 0 &&
-        tried[static_cast<size_t>(c.best)].sizes.patches == tried[static_cast<size_t>(c.fewest)].sizes.patches)
-        c.fewest = c.best;
+    auto patches = [&](int32_t strips) { return tried[static_cast<size_t>(strips)].sizes.patches; };
+    if (c.best != 0 && patches(c.best) == patches(c.fewest)) c.fewest = c.best;
     return c;
 }
 

@@ -385,14 +385,18 @@ __device__ __forceinline__ void solve_wide(const PatchArgs &a, int plan, int n_c
     // offset x of slot si, in the order of the first-use bits (see host_patch.hpp)
     auto offset = [&](int si, int x) {
         if constexpr (PRODUCT)
-            return x < 4 ? half(si, x / 2, x & 1) : x == 4 ? half(si, 2, 0) : half(si, (x + 1) / 2, 1 - (x & 1));
+            return x < 4 ? half(si, x / 2, x & 1)
+                         : x == 4 ? half(si, 2, 0) : half(si, (x + 1) / 2, 1 - (x & 1));
         else
-            return x % 5 == 4 ? half(si, 8 + x / 10, x / 5 & 1) : half(si, 2 * (x / 5) + x % 5 / 2, x % 5 & 1);
+            return x % 5 == 4 ? half(si, 8 + x / 10, x / 5 & 1)
+                              : half(si, 2 * (x / 5) + x % 5 / 2, x % 5 & 1);
     };
     // link i of the path in place `pos` of slot si
     auto step = [&](int si, int pos, int i) {
-        if constexpr (PRODUCT) return offset(si, i < 2 ? 2 * i + (pos >> 1) : i == 2 ? 4 : 2 * i - 1 + (pos & 1));
-        else return offset(si, 5 * pos + i);
+        if constexpr (PRODUCT)
+            return offset(si, i < 2 ? 2 * i + (pos >> 1) : i == 2 ? 4 : 2 * i - 1 + (pos & 1));
+        else
+            return offset(si, 5 * pos + i);
     };
     auto add = [&](uint32_t off) {
         if (off >= pad) return;
@@ -461,8 +465,8 @@ __device__ __forceinline__ void solve_wide(const PatchArgs &a, int plan, int n_c
             }
         }
         if (at >= 0)                             // (no other thread counts in this word)
-            *reinterpret_cast<uint32_t *>(lds_ptr(count + 8 * (t * (L * QL) + at / 4) + 4 * ((at >> 1) & 1))) +=
-                1u << (16 * (at & 1));
+            *reinterpret_cast<uint32_t *>(lds_ptr(count + 8 * (t * (L * QL) + at / 4) +
+                                                  4 * ((at >> 1) & 1))) += 1u << (16 * (at & 1));
         in_turn([&] {
 #pragma unroll 1
             for (int i = 0; i < 5; ++i) add(step(at / 4, at & 3, i));

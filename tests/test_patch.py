@@ -701,3 +701,40 @@ def test_teams_that_solve_several_plans(monkeypatch, iters, flags):
                 assert lam[b] == ref["lam"] and np.array_equal(splits[b], ref["splits"]), b
         finally:
             h.close()
+
+
+@pytest.mark.gpu
+def test_a_stream_under_capture_takes_one_patch():
+    """Of a fabric with a layout of one patch and a faster one of several (4 nodes, a NIC per GPU
+    reachable from two), an eager plan takes the several, a captured one the single patch."""
+    import oracle
+    import torch
+    t = fabric(4, 8, "xor")
+    d = [np.floor(np.random.default_rng(s).pareto(1.1, t.n_comm) * 1e6) for s in (1, 2)]
+    ref = [oracle.solve(*t.csr(), x, 0.05, 60) for x in d]
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        dd = [torch.as_tensor(x).to("cuda:0") for x in d]
+        out = [(torch.empty(t.n_paths, dtype=torch.float64, device="cuda:0"),
+                torch.empty(1, dtype=torch.float64, device="cuda:0")) for _ in d]
+        side = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            B.nimble_plan_solve(h, dd[0], 0.05, 60, *out[0])
+            torch.cuda.synchronize()
+            assert h.last_patches > 1
+            with torch.cuda.graph(graph, stream=side):
+                B.nimble_plan_solve(h, dd[0], 0.05, 60, *out[0])
+            assert h.last_patches == 1
+        for _ in range(3):
+            out[0][0].zero_()
+            B.nimble_plan_solve(h, dd[1], 0.05, 60, *out[1])
+            assert h.last_patches > 1
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            for (splits, lam), r in zip(out, ref):
+                assert float(lam.item()) == r["lam"]
+                assert np.array_equal(splits.cpu().numpy(), r["splits"])
+    finally:
+        h.close()
