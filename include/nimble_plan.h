@@ -225,7 +225,7 @@ nimble_status_t nimble_alg1_solve_batch(nimble_topo_t *topo, int32_t batch,
  *   d_len   device [n_links], by link id, in and out; every entry finite and > 0 (1.0
  *           everywhere is the cold start).  Lengths grow by at most (1 + eps) per iteration:
  *           the caller rescales them (e.g. by a power of two, which changes nothing else)
- *           before they can overflow.  Written when the whole plan is made, not before.
+ *           before they can overflow.
  * The other arguments as for nimble_plan_solve.  Reported as the streaming regime; like
  * nimble_plan_solve it only enqueues work.
  */

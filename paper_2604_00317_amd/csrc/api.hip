@@ -317,7 +317,7 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     p.max_teams = 1 << 30;
     p.parts = nullptr;
     p.maxima = nullptr;
-    p.len_done = nullptr;
+    p.len_start = nullptr;
     p.abort_word = nullptr;
     p.iteration_us = nimble::patch_iteration_us(l.shape, l.n_patches, l.max_groups, l.max_parts);
     p.list_bytes = 4 * static_cast<int64_t>(l.words.size() + l.first.size());
@@ -333,7 +333,7 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
         if (e == hipSuccess)
             e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * nimble::kPatchCopies * l.n_patches,
                          &p.maxima);
-        if (e == hipSuccess) e = allocate(t, static_cast<size_t>(t->d.E), &p.len_done);
+        if (e == hipSuccess) e = allocate(t, static_cast<size_t>(t->d.E), &p.len_start);
         if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
     }
     p.n_patches = e == hipSuccess ? l.n_patches : 0;
@@ -583,7 +583,7 @@ nimble_status_t solve_patches(nimble_topo *topo, int32_t plans, const double *d_
     if (refused) return NIMBLE_OK;
     if (p->n_patches > 1) {
         e = nimble::launch_alone(topo->d, topo->sync_words, p->abort_word, plans, d_traffic, eps,
-                                 iters, p->len_done, d_len, d_splits, d_lambda, s);
+                                 iters, d_len ? p->len_start : nullptr, d_len, d_splits, d_lambda, s);
         if (e != hipSuccess) return fail_hip(e, "kernel launch (after the patch kernels)");
         topo->gave_up = p->abort_word;
     }

@@ -20,7 +20,7 @@ struct DevicePatches {
     const uint32_t *words, *first;
     double *parts;               // [max_teams][2][n_parts]
     double *maxima;              // [max_teams][2][kPatchCopies][n_patches]
-    double *len_done;            // [E] lengths a warm solve ended with, until it is known to be whole
+    double *len_start;           // [E] lengths a warm solve starts from, whatever becomes of it
     uint32_t *abort_word;
     double iteration_us;         // estimate of one iteration of max_teams plans
     int64_t list_bytes;          // candidate lists a solve loads
@@ -265,11 +265,10 @@ hipError_t launch_persistent(const DeviceTopo &t, void *sync_words, int n_cu,
                              unsigned int spin_limit, const double *demand, double eps,
                              int32_t iters, double *splits, double *lambda, hipStream_t s);
 // Follows a solve of several patches: completes it where patches gave up waiting for each other
-// (one workgroup, no waits), else copies the lengths of a warm start from `len_done` to `len_io`
-// (null: nobody wants them).
+// (one workgroup, no waits).  `len_in`, `len_out`: lengths of a warm start (null: there are none).
 hipError_t launch_alone(const DeviceTopo &t, void *sync_words, const uint32_t *gave_up,
                         int32_t plans, const double *demand, double eps, int32_t iters,
-                        const double *len_done, double *len_io, double *splits, double *lambda,
+                        const double *len_in, double *len_out, double *splits, double *lambda,
                         hipStream_t s);
 
 // ---- probe of grid-wide barriers (benchmark only) -------------------------------------------

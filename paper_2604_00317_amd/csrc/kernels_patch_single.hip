@@ -19,7 +19,7 @@ __global__ __launch_bounds__(256) void k_patch_clear(unsigned long long *parts, 
                                                      unsigned long long *terms, int64_t n_terms,
                                                      uint32_t *abort_word, uint32_t given_up,
                                                      int32_t *ad_flags, double *lambda, int plans,
-                                                     const double *len_in, double *len_done, int E)
+                                                     const double *len, double *len_start, int E)
 {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -27,8 +27,8 @@ __global__ __launch_bounds__(256) void k_patch_clear(unsigned long long *parts, 
     for (int64_t i = i0; i < n_maxima; i += stride) maxima[i] = kSign;
     for (int64_t i = i0; i < n_terms; i += stride) terms[i] = kSign;
     for (int64_t i = i0; i < plans; i += stride) lambda[i] = 0.0;
-    if (len_in != nullptr)           // (links no candidate uses keep their length)
-        for (int64_t i = i0; i < E; i += stride) len_done[i] = len_in[i];
+    if (len != nullptr)
+        for (int64_t i = i0; i < E; i += stride) len_start[i] = len[i];
     if (i0 == 0) {
         *abort_word = given_up;
         if (ad_flags != nullptr) ad_flags[0] = 0;
@@ -91,10 +91,11 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     a.comm_ptr = t.comm_ptr;
     a.invcap = t.invcap;
     a.demand = demand;
-    // several patches leave their lengths where a solve that is given up half way does no harm
+    // several patches start from a copy of the lengths: a solve that is given up half way has
+    // overwritten some of the caller's, and some patches may not have started by then
     const bool warm = len_io != nullptr;
-    a.len_in = len_io;
-    a.len_out = warm && p.n_patches > 1 ? p.len_done : len_io;
+    a.len_in = warm && p.n_patches > 1 ? p.len_start : len_io;
+    a.len_out = len_io;
     a.splits = splits;
     a.lambda = lambda;
     a.parts = p.parts;
@@ -138,8 +139,7 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
                        reinterpret_cast<unsigned long long *>(p.parts), words,
                        reinterpret_cast<unsigned long long *>(p.maxima), maxima,
                        reinterpret_cast<unsigned long long *>(a.terms), n_terms, a.abort_word,
-                       spin_limit == 0 ? 1u : 0u, a.ad_flags, lambda, plans, a.len_in, p.len_done,
-                       t.E);
+                       spin_limit == 0 ? 1u : 0u, a.ad_flags, lambda, plans, len_io, p.len_start, t.E);
     const hipError_t cleared = hipGetLastError();
     if (cleared != hipSuccess) return cleared;
     if (p.n_patches == 1) return hipLaunchKernel(f, dim3(1), dim3(p.shape.threads), args, lds, s);

@@ -10,11 +10,9 @@
 // skipped (lambda is set to NaN by the block that gave up), so no wave can wait forever.
 //
 // The same with one workgroup (k_alone) waits for nobody.  It follows every solve of several
-// patches (patch_kernel.hpp) in the stream: where that went through, it hands over the lengths of
-// a warm start or returns at once (1.3 to 5 us); where patches gave up waiting for each other, it solves
+// patches (patch_kernel.hpp) in the stream: where that went through, it returns at once (1.3 to
+// 2.8 us); where patches gave up waiting for each other, it solves
 // the plans they left undone, slowly but surely.
-#include <algorithm>
-
 #include "host_topo.hpp"
 #include "kernels.hpp"
 #include "phases.hpp"
@@ -108,11 +106,11 @@ struct PersistentArgs {
     int iters;
     double *splits, *lambda;
     unsigned int spin_limit;
-    // k_alone: the word that says whether the patches gave up, their lengths (null: nobody wants
-    // them) and the caller's, and how many plans there are
+    // k_alone: the word that says whether the patches gave up, the lengths a warm start begins with
+    // (null: all 1) and where those it ends with go, and how many plans there are
     const uint32_t *gave_up;
-    const double *len_done;
-    double *len_io;
+    const double *len_in;
+    double *len_out;
     int plans;
 };
 
@@ -154,7 +152,7 @@ __device__ __forceinline__ void solve_plan(const PersistentArgs &a, unsigned int
     // prologue: state and the width rho
     for (int i = tid; i < a.E; i += n_threads) {
         const int e = a.pos_link[i];             // lengths and sums by position, prices by link id
-        const double l0 = a.len_io != nullptr ? a.len_io[e] : 1.0;
+        const double l0 = a.len_in != nullptr ? a.len_in[e] : 1.0;
         a.len[i] = l0;
         a.price[e] = MAXC ? l0 : l0 * a.invcap[e];
         a.S[i] = 0.0;
@@ -212,8 +210,8 @@ __device__ __forceinline__ void solve_plan(const PersistentArgs &a, unsigned int
             a.lambda[0] = smax / T;
         }
     }
-    if (a.len_io != nullptr)
-        for (int i = tid; i < a.E; i += n_threads) a.len_io[a.pos_link[i]] = a.len[i];
+    if (a.len_out != nullptr)
+        for (int i = tid; i < a.E; i += n_threads) a.len_out[a.pos_link[i]] = a.len[i];
     return;
 abandoned:
     if (tid == 0) a.lambda[0] = __builtin_nan("");
@@ -232,13 +230,7 @@ __global__ __launch_bounds__(kPBlock) void k_alone(PersistentArgs a)
 {
     __shared__ double red[16];
     __shared__ int s_flag;
-    if (*a.gave_up == 0u) {
-        if (a.len_io != nullptr)
-            for (int e = blockIdx.x * kPBlock + threadIdx.x; e < a.E; e += gridDim.x * kPBlock)
-                a.len_io[e] = a.len_done[e];
-        return;
-    }
-    if (blockIdx.x != 0) return;
+    if (*a.gave_up == 0u) return;
     const int plans = a.plans;
     for (int plan = 0; plan < plans; ++plan) {
         // (a plan some patch gave up has lambda NaN; the same for all threads)
@@ -260,8 +252,7 @@ template <int L, int LMAX, bool MAXC>
 hipError_t launch_one(const PersistentArgs &a, int n_cu, hipStream_t s, int *grid_out)
 {
     if (a.gave_up != nullptr) {
-        const int grid = a.len_io == nullptr ? 1 : std::min(64, (a.E + kPBlock - 1) / kPBlock);
-        hipLaunchKernelGGL((k_alone<L, LMAX, MAXC>), dim3(grid), dim3(kPBlock), 0, s, a);
+        hipLaunchKernelGGL((k_alone<L, LMAX, MAXC>), dim3(1), dim3(kPBlock), 0, s, a);
         return hipGetLastError();
     }
     int per_cu = 0;
@@ -378,13 +369,13 @@ hipError_t launch_persistent(const DeviceTopo &t, void *sync_words, int n_cu,
 
 hipError_t launch_alone(const DeviceTopo &t, void *sync_words, const uint32_t *gave_up,
                         int32_t plans, const double *demand, double eps, int32_t iters,
-                        const double *len_done, double *len_io, double *splits, double *lambda,
+                        const double *len_in, double *len_out, double *splits, double *lambda,
                         hipStream_t s)
 {
     PersistentArgs a = persistent_args(t, sync_words, demand, eps, iters, splits, lambda);
     a.gave_up = gave_up;
-    a.len_done = len_done;
-    a.len_io = len_io;
+    a.len_in = len_in;
+    a.len_out = len_out;
     a.plans = plans;
     const int L = lanes_per_commodity(t.pmax);
     if (t.cost_max) return launch_l<true>(a, L, t.lmax, 1, s, nullptr);
