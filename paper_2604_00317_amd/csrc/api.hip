@@ -369,7 +369,8 @@ double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int
 }
 
 // Builds the patch layouts of a fabric: the one with the fewest patches, which solves the most
-// plans side by side, and the one whose estimate is lowest for a single plan, if that is another.
+// plans side by side, the one whose estimate is lowest for a single plan, if that is another, and
+// one for solves of variable step if they fit neither.
 // (Layouts that would never be faster than what runs without them are not made.)
 hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, const int32_t *pl)
 {
@@ -386,9 +387,9 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
     if (!scan.fits) return hipSuccess;
     const nimble::PatchChoice c = nimble::choose_cuts(d.E, d.K, scan, t->n_cu, forced, lanes);
     if (c.best == 0) return hipSuccess;
-    for (int32_t i = 0; i < 2; ++i) {
-        const int32_t strips = i == 0 ? c.best : c.fewest;
-        if (i == 1 && strips == c.best) break;
+    for (int32_t i = 0; i < 3; ++i) {
+        const int32_t strips = i == 0 ? c.best : i == 1 ? c.fewest : c.adaptive;
+        if ((i == 1 && strips == c.best) || strips == 0 || (i == 2 && d.cost_max)) continue;
         nimble::PatchCut cut;
         nimble::PatchShape shape;
         nimble::PatchLayout built;

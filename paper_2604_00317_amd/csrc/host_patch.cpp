@@ -492,9 +492,10 @@ PatchSizes measure_cut(int32_t n_links, const PatchScan &scan, const PatchCut &c
     m.patches = B;
     m.max_comm = static_cast<int32_t>(cut.most);
     // (prices, link states, groups and counts: lds_layout in patch_kernel.hpp)
-    const int64_t lds = 48ll * m.max_local + 16ll * m.max_groups + 512 +
-                        8ll * m.max_comm * shape.lanes * shape.quads;
-    m.fits = m.max_local <= kPatchMaxLocal && lds <= 160 * 1024;
+    const int64_t links_lds = 48ll * m.max_local + 16ll * m.max_groups + 512;
+    const int64_t slots = static_cast<int64_t>(m.max_comm) * shape.lanes * shape.quads;
+    m.fits = m.max_local <= kPatchMaxLocal && links_lds + 8 * slots <= 160 * 1024;
+    m.fits_adaptive = m.fits && links_lds + 32 * slots <= 160 * 1024;
     return m;
 }
 
@@ -530,13 +531,22 @@ PatchChoice choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan,
     // one patch that is done before words could go from patch to patch needs no comparison
     try_strips(1);
     offer(1);
-    if (c.best == 1 && tried[1].us < kPatchTripUs) return c;
+    if (c.best == 1 && tried[1].us < kPatchTripUs && tried[1].sizes.fits_adaptive) return c;
     parallel_ranges(most_strips - 1, [&](int64_t s0, int64_t s1) {
         for (int64_t s = s0; s < s1; ++s) try_strips(static_cast<int32_t>(s) + 2);
     }, n_comm < 2048 ? 16 : 1);
     for (int32_t s = 2; s <= most_strips; ++s) offer(s);
     auto patches = [&](int32_t strips) { return tried[static_cast<size_t>(strips)].sizes.patches; };
-    if (c.best != 0 && patches(c.best) == patches(c.fewest)) c.fewest = c.best;
+    if (c.best == 0) return c;
+    if (patches(c.best) == patches(c.fewest)) c.fewest = c.best;
+    if (!tried[static_cast<size_t>(c.best)].sizes.fits_adaptive &&
+        !tried[static_cast<size_t>(c.fewest)].sizes.fits_adaptive)
+        for (int32_t s = 1; s <= most_strips; ++s) {
+            const Tried &t = tried[static_cast<size_t>(s)];
+            if (t.sizes.fits_adaptive && t.sizes.patches <= most_patches &&
+                (c.adaptive == 0 || t.us < tried[static_cast<size_t>(c.adaptive)].us))
+                c.adaptive = s;
+        }
     return c;
 }
 

@@ -109,6 +109,7 @@ bool patch_shape(const PatchScan &scan, int64_t most, int32_t lanes, PatchShape 
 // What a cut needs, found without building its layout.
 struct PatchSizes {
     bool fits = false;              // its patches keep to their limits, LDS among them
+    bool fits_adaptive = false;     // also for a solve of variable step (32 bytes a slot, not 8)
     int32_t patches = 0;
     int32_t max_comm = 0, max_local = 0, max_groups = 0, max_parts = 0;      // as in PatchLayout
 };
@@ -123,9 +124,10 @@ constexpr double kPatchTripUs = 1.76;     // a trip of a word from patch to patc
 
 // The grids (strips) with the fewest patches and with the lowest estimate for one plan, of those
 // whose patches keep to their limits and are at most `most_patches`; 0: there is none.  The same if
-// they have equally many patches.
+// they have equally many patches.  `adaptive`: the one with the lowest estimate that a solve of
+// variable step fits, if neither of these does.
 struct PatchChoice {
-    int32_t fewest = 0, best = 0;
+    int32_t fewest = 0, best = 0, adaptive = 0;
 };
 PatchChoice choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan, int32_t most_patches,
                         int32_t forced, int32_t lanes);

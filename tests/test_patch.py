@@ -738,3 +738,25 @@ def test_a_stream_under_capture_takes_one_patch():
                 assert np.array_equal(splits.cpu().numpy(), r["splits"])
     finally:
         h.close()
+
+
+@pytest.mark.gpu
+def test_a_variable_step_has_a_layout_of_its_own():
+    """A fabric whose fixed-step plans run on one patch that has no room for the weights of a variable
+    step: that one is solved on several."""
+    import oracle
+    t = fabric(5, 6, "xor")
+    d = np.floor(np.random.default_rng(1).pareto(1.1, t.n_comm) * 1e6)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        splits, lam = B.plan(h, d, 0.05, 60)
+        assert h.last_patches == 1
+        ref = oracle.solve(*t.csr(), d, 0.05, 60)
+        assert lam == ref["lam"] and np.array_equal(splits, ref["splits"])
+        got = _adaptive(h, t, d, 0.1, 60, 7)
+        assert h.last_patches > 1
+        ref = oracle.solve_adaptive(*t.csr(), d, 0.1, 60, 7)
+        assert got[1:] == (ref["lam"], ref["iters"], ref["lb"])
+        assert np.array_equal(got[0], ref["splits"])
+    finally:
+        h.close()
