@@ -11,8 +11,8 @@
 //
 // The same with one workgroup (k_alone) waits for nobody.  It follows every solve of several
 // patches (patch_kernel.hpp) in the stream: where that went through, it returns at once (1.3 to
-// 2.8 us); where patches gave up waiting for each other, it solves
-// the plans they left undone, slowly but surely.
+// 4 us); where patches gave up waiting for each other, it solves the plans they left undone, slowly
+// but surely.
 #include "host_topo.hpp"
 #include "kernels.hpp"
 #include "phases.hpp"
