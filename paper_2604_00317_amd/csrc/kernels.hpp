@@ -98,6 +98,7 @@ struct DeviceTopo {
     int32_t E, K, P;
     int64_t nnz;
     int32_t pmax, lmax;
+    int32_t first_direct;      // 1: the first candidate of every commodity is a single link
     bool cost_max;
     // forward CSR
     const int32_t *comm_ptr;   // [K+1]

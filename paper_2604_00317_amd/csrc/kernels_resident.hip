@@ -477,42 +477,64 @@ __global__ __launch_bounds__(1024) void k_resident_coop(
     }
 }
 
-__host__ __device__ inline size_t reg_plan_bytes(int E, int K, int nt, int maxp)
+// LDS of one plan of k_resident_reg: prices of nt links, +0.0 and +inf; loads of nt links, then a
+// place per thread for what is no link; choices; counts.
+__host__ __device__ inline size_t reg_plan_bytes(int K, int nt, int maxp)
 {
-    return sizeof(double) * (E + 2) + align8(K + 1) + sizeof(uint32_t) * maxp * nt;
+    return sizeof(double) * (3 * nt + 2) + align8(K + 1) + sizeof(uint32_t) * maxp * nt;
 }
+
+// What the plans of a workgroup share, behind their own LDS (the first plan starts at LDS address 0,
+// so byte offsets are addresses).
+struct RegShared {
+    double max[16], sum[16], invrho[kMaxPlansPerBlock];
+    int fine[16], inexact;
+};
 
 // Register-resident variant for small dense fabrics (one modeled node): every thread owns one
 // commodity and one link for the whole solve, so what never changes between iterations lives in
-// registers -- the link ids of the commodity's MAXP x MAXL candidate steps, its choice counts,
-// the link's MAXROW reverse pairs with the demands they can add, and the link's length,
-// congestion sum and 1/capacity.  LDS holds only what threads exchange: the prices and the
-// choices.  Short paths are padded with the price slot E (+0.0, neutral for the sum and for the
-// maximum of positive prices), absent candidates start at slot E + 1 (+inf: never below the
-// best), absent pairs have an empty mask.  The additions are those of the generic kernel in the
-// same order (0 + p is p; adding +0.0 changes nothing), so the results are the same bits.
-template <bool MAXC, bool ONEWAVE, int MAXP, int MAXL, int MAXROW>
+// registers -- where the prices of the commodity's MAXP x 2 candidate steps lie, and the link's
+// length, congestion sum and 1/capacity.  LDS holds only what threads exchange.  Short paths are
+// padded with a price of +0.0 (neutral for the sum and for the maximum of positive prices), absent
+// candidates start at +inf (never below the best).  DIRECT: every first candidate is a single link.
+//
+// Loads are summed in one of two ways, chosen per plan from its demands:
+//   scatter  Where the demands lie on a power-of-two grid with a total below 2^52 units (byte
+//            counts), every order of additions gives the same sum, so a commodity adds its demand to
+//            the loads of the links it has chosen by LDS atomics: two per commodity.
+//   gather   Elsewhere a link's thread looks at its MAXROW reverse pairs -- the choice of each pair's
+//            commodity, an 8-bit mask of the candidates that use the link, the demand -- and adds in
+//            the order of the generic kernel.
+// The scatter replaces sixteen choice reads and sixteen additions in a row by two atomics, and
+// the minimum carries the winner's links and its place up the tree, so nothing is looked up after it.
+// What bounds it: one plan, the chain price reads -> sums -> tree -> atomics -> load -> price of one
+// wave; 4096 plans (four waves per SIMD), vector issue and the LDS about equally.  One node of 8 GPUs,
+// 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).
+template <bool MAXC, bool ONEWAVE, int MAXP, bool DIRECT, int MAXROW>
 __global__ __launch_bounds__(1024) void k_resident_reg(
-    int E, int K, int P, int batch, int nt, int plans_per_block, double eps, int iters,
+    int E, int K, int P, int batch, int nt_arg, int plans_per_block, double eps, int iters,
     const int32_t *__restrict__ g_cp, const int32_t *__restrict__ g_lp,
     const int32_t *__restrict__ g_pl, const int32_t *__restrict__ g_rp,
     const uint32_t *__restrict__ g_rev, const double *__restrict__ g_invcap,
     const double *__restrict__ demand_all, double *__restrict__ splits_all,
     double *__restrict__ lambda_all)
 {
-    static_assert(MAXP <= 8, "a choice is a bit of one mask byte; eight 8-bit counters per word");
+    static_assert(MAXP <= 8, "a choice is a bit of one mask byte and three bits of a packed word");
     static_assert(MAXROW % 4 == 0, "four mask bytes per register");
     extern __shared__ __align__(16) unsigned char lds[];
-    __shared__ double red[16];
-    __shared__ double s_invrho[kMaxPlansPerBlock];
 
+    const int nt = ONEWAVE ? kWave : nt_arg;
     const int slot = threadIdx.x / nt;            // plan slot inside the workgroup
     const int t = threadIdx.x - slot * nt;        // thread inside the plan group
     const int plan = blockIdx.x * plans_per_block + slot;
     const bool live = plan < batch;
-    const size_t plan_bytes = reg_plan_bytes(E, K, nt, MAXP);
-    double *price = reinterpret_cast<double *>(lds + plan_bytes * slot);
-    uint8_t *choice = reinterpret_cast<uint8_t *>(price + E + 2);
+    // byte offsets from the start of `lds`
+    const uint32_t plan_bytes = static_cast<uint32_t>(reg_plan_bytes(K, nt, MAXP));
+    RegShared &sh = *reinterpret_cast<RegShared *>(lds + plan_bytes * plans_per_block);
+    const uint32_t price0 = plan_bytes * slot;
+    const uint32_t load0 = price0 + 8u * (nt + 2), spare0 = load0 + 8u * nt;
+    auto f64_at = [&](uint32_t off) { return reinterpret_cast<double *>(lds + off); };
+    uint8_t *choice = lds + spare0 + 8u * nt;
     // choice counts of this thread's commodity, candidate j at [j * nt + t]
     uint32_t *count = reinterpret_cast<uint32_t *>(choice + align8(K + 1)) + t;
     const double *d_in = demand_all + static_cast<size_t>(live ? plan : 0) * K;
@@ -528,43 +550,166 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
         }
     };
 
-    // the commodity of this thread: where the price of every candidate step lives
+    // the commodity of this thread: where the prices of the candidate steps lie, and, per
+    // candidate, where the loads of its links lie (bits 3..15 and 16..28, in units of eight bytes)
+    // and its number (bits 29..31)
     const bool has_k = t < K;
-    const double *pp[MAXP][MAXL];
+    const double d = has_k ? d_in[t] : 0.0;
+    uint32_t step[MAXP][2], links[MAXP];
     int p0 = 0, np = 0;
     if (has_k) {
         p0 = g_cp[t];
         np = g_cp[t + 1] - p0;
     }
+    const uint32_t zero = price0 + 8u * nt, spare = spare0 + 8u * t;
 #pragma unroll
     for (int j = 0; j < MAXP; ++j) {
         count[j * nt] = 0u;
-        int a = 0, b = 0;
+        int a = 0, n = 0;
         if (j < np) {
             a = g_lp[p0 + j];
-            b = g_lp[p0 + j + 1];
+            n = g_lp[p0 + j + 1] - a;
         }
+        uint32_t load_at[2] = {spare, spare};
+        step[j][0] = n > 0 ? zero : zero + 8u;
+        step[j][1] = zero;
 #pragma unroll
-        for (int i = 0; i < MAXL; ++i) {
-            int e = (i == 0 && j >= np) ? E + 1 : E;
-            if (a + i < b) e = g_pl[a + i];
-            pp[j][i] = price + e;
-        }
+        for (int i = 0; i < 2; ++i)
+            if (i < n) {
+                const uint32_t e = 8u * static_cast<uint32_t>(g_pl[a + i]);
+                step[j][i] = price0 + e;
+                load_at[i] = load0 + e;
+            }
+        links[j] = load_at[0] | load_at[1] << 13 | static_cast<uint32_t>(j) << 29;
     }
-    // the link of this thread: for every reverse pair where the commodity's choice lives, the
-    // candidates that use the link, and the demand they add
+    // the link of this thread
     const bool has_e = t < E;
-    const uint8_t *cptr[MAXROW];
-    uint32_t wb4[MAXROW / 4];      // the 8-bit candidate masks of four pairs per register
-    double dm[MAXROW];
     double ic = 0.0, len = 1.0, S = 0.0, reach = 0.0;
+    int r0 = 0, rn = 0;
+    if (has_e) {
+        r0 = g_rp[t];
+        rn = g_rp[t + 1] - r0;
+        ic = g_invcap[t];
+    }
+    // width rho: every commodity that can reach the link counts once
+#pragma unroll 4
+    for (int i = 0; i < rn; ++i) {
+        const uint32_t wa = g_rev[2 * (r0 + i)];
+        const uint32_t k = wa & kCommMask;
+        if (wa & kFirstFlag) reach = reach + d_in[k];
+    }
+    *f64_at(price0 + 8u * t) = MAXC ? 1.0 : ic;
+    *f64_at(load0 + 8u * t) = 0.0;
+    *f64_at(spare) = 0.0;
+    if (t == 0) {
+        *f64_at(zero) = 0.0;
+        *f64_at(zero + 8u) = __builtin_inf();
+        choice[K] = 0u;                            // read (never used) by padding pairs
+        if (slot == 0) sh.inexact = 0;
+    }
+    // per plan, inside its thread group (nt is a multiple of 64): the width, and the total and
+    // the finest grid of the demands
     {
-        int r0 = 0, rn = 0;
-        if (has_e) {
-            r0 = g_rp[t];
-            rn = g_rp[t + 1] - r0;
-            ic = g_invcap[t];
+        const double wm = wave_max(reach * ic);
+        const double ws = wave_sum_f64(fabs(d));
+        const int wf = wave_min_i32(lowest_bit(d));
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+            sh.max[threadIdx.x >> 6] = wm;
+            sh.sum[threadIdx.x >> 6] = ws;
+            sh.fine[threadIdx.x >> 6] = wf;
         }
+        __syncthreads();
+        if (t == 0) {
+            double m = 0.0, total = 0.0;
+            int fine = kNoBit;
+            const int w0 = (slot * nt) >> 6, nw = nt >> 6;
+            for (int w = 0; w < nw; ++w) {
+                m = fmax(m, sh.max[w0 + w]);
+                total = total + sh.sum[w0 + w];
+                fine = min(fine, sh.fine[w0 + w]);
+            }
+            sh.invrho[slot] = (m > 0.0) ? 1.0 / m : 0.0;
+            // (one bit less than a double holds, for the rounding of the total; the grid kept off
+            // the denormals, which atomics need not keep.  Comparisons with a NaN are false.)
+            const bool on_grid = total == 0.0 || (total < __builtin_inf() && fine >= -1022 &&
+                                                  ilogb(total) + 1 - fine <= 52);
+            if (ONEWAVE) sh.fine[w0] = on_grid ? 1 : 0;
+            else if (!on_grid) sh.inexact = 1;
+        }
+        __syncthreads();
+    }
+    const double invrho = sh.invrho[slot];
+    const bool exact = __builtin_amdgcn_readfirstlane(
+                           ONEWAVE ? sh.fine[slot] : 1 - sh.inexact) != 0;
+
+    auto path_costs = [&](double (&c)[MAXP]) {
+        // the prices of four candidates are requested before the first is used
+        constexpr int kBatch = 4;
+#pragma unroll
+        for (int j0 = 0; j0 < MAXP; j0 += kBatch) {
+            double pv[kBatch][2];
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (j0 + j >= MAXP) break;
+                pv[j][0] = *f64_at(step[j0 + j][0]);
+                if (!DIRECT || j0 + j > 0) pv[j][1] = *f64_at(step[j0 + j][1]);
+            }
+#pragma unroll
+            for (int j = 0; j < kBatch; ++j) {
+                if (j0 + j >= MAXP) break;
+                double cj = pv[j][0];                    // 0 + p is p
+                if (!DIRECT || j0 + j > 0) {
+                    if constexpr (MAXC) cj = (pv[j][1] > cj) ? pv[j][1] : cj;
+                    else cj = cj + pv[j][1];
+                }
+                c[j0 + j] = cj;
+            }
+        }
+    };
+    auto step_link = [&](double load) {
+        const double u = load * ic;
+        S = S + u;
+        const double g = u * invrho;
+        const double t1 = eps * g;
+        const double t2 = 1.0 + t1;
+        len = len * t2;
+        *f64_at(price0 + 8u * t) = MAXC ? len : len * ic;
+    };
+    if (exact) {
+        for (int it = 0; it < iters; ++it) {
+            double c[MAXP];
+            uint32_t w[MAXP];
+            path_costs(c);
+#pragma unroll
+            for (int j = 0; j < MAXP; ++j) w[j] = links[j];
+            // the minimum as a tree over neighbours; of equal costs the left, so the lowest,
+            // candidate wins: what the strict `<` scan in candidate order picks (all +inf, a
+            // commodity without traffic-bearing candidates, resolves to candidate 0 either way)
+#pragma unroll
+            for (int s = 1; s < MAXP; s *= 2)
+#pragma unroll
+                for (int j = 0; j + s < MAXP; j += 2 * s) {
+                    w[j] = c[j + s] < c[j] ? w[j + s] : w[j];
+                    c[j] = fast_min_f64(c[j], c[j + s]);
+                }
+            // (what is no link goes to the thread's own spare place)
+            lds_add_f64(f64_at(w[0] & 0xFFF8u), d);
+            lds_add_f64(f64_at((w[0] >> 13) & 0xFFF8u), d);
+            (void)__hip_atomic_fetch_add(count + (w[0] >> 29) * nt, 1u, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+            plan_sync();
+            const unsigned long long taken = __hip_atomic_exchange(
+                reinterpret_cast<unsigned long long *>(f64_at(load0 + 8u * t)), 0ull,
+                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+            step_link(__longlong_as_double(static_cast<long long>(taken)));
+            plan_sync();
+        }
+    } else {
+        // for every reverse pair of the link where the commodity's choice lives, the candidates
+        // that use the link (8-bit masks, four to a register), and the demand they add
+        const uint8_t *cptr[MAXROW];
+        uint32_t wb4[MAXROW / 4];
+        double dm[MAXROW];
 #pragma unroll
         for (int i = 0; i < MAXROW / 4; ++i) wb4[i] = 0u;
 #pragma unroll
@@ -572,111 +717,49 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
             cptr[i] = choice + K;                  // padding: the spare choice, empty mask
             dm[i] = 0.0;
             if (i < rn) {
-                const uint32_t wa = g_rev[2 * (r0 + i)];
-                const uint32_t k = wa & kCommMask;
+                const uint32_t k = g_rev[2 * (r0 + i)] & kCommMask;
                 if (k < static_cast<uint32_t>(K)) {
                     cptr[i] = choice + k;
                     wb4[i / 4] |= (g_rev[2 * (r0 + i) + 1] & 0xFFu) << (8 * (i % 4));
                     dm[i] = d_in[k];
                 }
-                // width rho: every commodity that can reach the link counts once
-                if (wa & kFirstFlag) reach = reach + dm[i];
             }
         }
-    }
-    if (has_e) price[t] = MAXC ? 1.0 : ic;
-    if (t == 0) {
-        price[E] = 0.0;
-        price[E + 1] = __builtin_inf();
-        choice[K] = 0u;                            // read (never used) by padding pairs
-    }
-    // per-plan width: reduce inside the plan group through LDS (nt is a multiple of 64)
-    {
-        const double wm = wave_max(has_e ? reach * ic : 0.0);
-        if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x >> 6] = wm;
-        __syncthreads();
-        if (t == 0) {
-            double m = 0.0;
-            const int w0 = (slot * nt) >> 6, nw = nt >> 6;
-            for (int w = 0; w < nw; ++w) m = fmax(m, red[w0 + w]);
-            s_invrho[slot] = (m > 0.0) ? 1.0 / m : 0.0;
-        }
-        __syncthreads();
-    }
-    const double invrho = s_invrho[slot];
-
-    // eight 8-bit counters in one 64-bit word, emptied into the LDS counts before any can wrap
-    unsigned long long tally = 0ull;
-    auto flush = [&] {
+        for (int it = 0; it < iters; ++it) {
+            if (has_k) {
+                double c[MAXP];
+                path_costs(c);
+                double best = c[0];
 #pragma unroll
-        for (int j = 0; j < MAXP; ++j)
-            count[j * nt] += static_cast<uint32_t>(tally >> (8 * j)) & 0xFFu;
-        tally = 0ull;
-    };
-    for (int it = 0; it < iters; ++it) {
-        if (has_k) {
-            // the prices of four candidates are requested before the first is used
-            constexpr int kBatch = MAXP < 4 ? MAXP : 4;
-            double c[MAXP];
+                for (int j = 1; j < MAXP; ++j) best = fast_min_f64(best, c[j]);
+                int bj = MAXP - 1;
 #pragma unroll
-            for (int j0 = 0; j0 < MAXP; j0 += kBatch) {
-                double pv[kBatch][MAXL];
+                for (int j = MAXP - 2; j >= 0; --j) bj = (c[j] == best) ? j : bj;
+                choice[t] = static_cast<uint8_t>(bj);
+                count[bj * nt] += 1u;
+            }
+            plan_sync();
+            if (has_e) {
+                // the choices of all pairs are requested before the first is used
+                uint32_t ch[MAXROW];
 #pragma unroll
-                for (int j = 0; j < kBatch; ++j)
+                for (int i = 0; i < MAXROW; ++i) ch[i] = *cptr[i];
+                double load = 0.0;
 #pragma unroll
-                    for (int i = 0; i < MAXL; ++i) pv[j][i] = *pp[j0 + j][i];
-#pragma unroll
-                for (int j = 0; j < kBatch; ++j) {
-                    double cj = pv[j][0];                    // 0 + p is p
-#pragma unroll
-                    for (int i = 1; i < MAXL; ++i) {
-                        if constexpr (MAXC) cj = (pv[j][i] > cj) ? pv[j][i] : cj;
-                        else cj = cj + pv[j][i];
-                    }
-                    c[j0 + j] = cj;
+                for (int i = 0; i < MAXROW; ++i) {
+                    // 1 where the commodity's choice uses the link (a choice is below 8, so it
+                    // stays inside its mask byte); fma(d, 1.0, load) rounds like load + d, and
+                    // fma(d, 0.0, load) leaves the sum as it is (demands are finite)
+                    const uint32_t h = ((wb4[i / 4] >> ch[i]) >> (8 * (i % 4))) & 1u;
+                    load = __builtin_fma(dm[i], static_cast<double>(h), load);
                 }
+                step_link(load);
             }
-            // the minimum, then the lowest candidate that holds it: what the strict `<` scan
-            // in candidate order picks (all +inf, a commodity without traffic-bearing
-            // candidates, resolves to candidate 0 either way)
-            double best = c[0];
-#pragma unroll
-            for (int j = 1; j < MAXP; ++j) best = fast_min_f64(best, c[j]);
-            int bj = MAXP - 1;
-#pragma unroll
-            for (int j = MAXP - 2; j >= 0; --j) bj = (c[j] == best) ? j : bj;
-            choice[t] = static_cast<uint8_t>(bj);
-            tally += 1ull << (8 * bj);
-            if ((it & 127) == 127) flush();
+            plan_sync();
         }
-        plan_sync();
-        if (has_e) {
-            // the choices of all pairs are requested before the first is used
-            uint32_t ch[MAXROW];
-#pragma unroll
-            for (int i = 0; i < MAXROW; ++i) ch[i] = *cptr[i];
-            double load = 0.0;
-#pragma unroll
-            for (int i = 0; i < MAXROW; ++i) {
-                // 1 where the commodity's choice uses the link (a choice is below 8, so it
-                // stays inside its mask byte); fma(d, 1.0, load) rounds like load + d, and
-                // fma(d, 0.0, load) leaves the sum as it is (demands are finite)
-                const uint32_t h = ((wb4[i / 4] >> ch[i]) >> (8 * (i % 4))) & 1u;
-                load = __builtin_fma(dm[i], static_cast<double>(h), load);
-            }
-            const double u = load * ic;
-            S = S + u;
-            const double g = u * invrho;
-            const double t1 = eps * g;
-            const double t2 = 1.0 + t1;
-            len = len * t2;
-            price[t] = MAXC ? len : len * ic;
-        }
-        plan_sync();
     }
 
     const double T = static_cast<double>(iters);
-    if (has_k) flush();
     if (live && has_k) {
         double *out = splits_all + static_cast<size_t>(plan) * P + p0;
 #pragma unroll
@@ -685,17 +768,23 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
     }
     const double sm = wave_max(has_e ? S : 0.0);
     __syncthreads();
-    if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x >> 6] = sm;
+    if ((threadIdx.x & (kWave - 1)) == 0) sh.max[threadIdx.x >> 6] = sm;
     __syncthreads();
     if (t == 0 && live) {
         double m = 0.0;
         const int w0 = (slot * nt) >> 6, nw = nt >> 6;
-        for (int w = 0; w < nw; ++w) m = fmax(m, red[w0 + w]);
+        for (int w = 0; w < nw; ++w) m = fmax(m, sh.max[w0 + w]);
         lambda_all[plan] = m / T;
     }
 }
 
 constexpr int kRegMaxPaths = 8, kRegMaxLen = 2, kRegMaxRow = 16;
+
+// candidates the instantiation of k_resident_reg for a fabric has room for
+int reg_paths(const DeviceTopo &t)
+{
+    return t.first_direct ? (t.pmax < 4 ? 4 : t.pmax) : kRegMaxPaths;
+}
 
 struct ResidentPlan {
     int nt, plans_per_block;
@@ -731,7 +820,7 @@ bool plan_resident(const DeviceTopo &t, int batch, ResidentPlan &rp)
     // a plan with more of either than its threads keeps to the LDS kernel, which strides
     rp.in_registers = !t.resident_generic && t.pmax <= kRegMaxPaths && t.lmax <= kRegMaxLen &&
                       t.rev_row_max <= kRegMaxRow && need <= nt;
-    if (rp.in_registers) rp.lds_bytes = reg_plan_bytes(t.E, t.K, nt, kRegMaxPaths) * ppb;
+    if (rp.in_registers) rp.lds_bytes = reg_plan_bytes(t.K, nt, reg_paths(t)) * ppb + sizeof(RegShared);
     // a few plans: all 1024 threads of a workgroup for each, lanes sharing commodities and links
     rp.coop_lanes = 0;
     rp.coop_registers = false;
@@ -843,11 +932,22 @@ hipError_t launch_resident(const DeviceTopo &t, int32_t batch, const double *dem
         }                                                                                      \
     } while (0)
     if (rp.in_registers) {
-#define NIMBLE_REG_LAUNCH(MAXC, ONEW)                                                          \
-    hipLaunchKernelGGL((k_resident_reg<MAXC, ONEW, kRegMaxPaths, kRegMaxLen, kRegMaxRow>),     \
-                       dim3(grid), dim3(block), rp.lds_bytes, s, t.E, t.K, t.P, batch, rp.nt,  \
+#define NIMBLE_REG_LAUNCH_P(MAXC, ONEW, MP, DIR)                                               \
+    hipLaunchKernelGGL((k_resident_reg<MAXC, ONEW, MP, DIR, kRegMaxRow>), dim3(grid),          \
+                       dim3(block), rp.lds_bytes, s, t.E, t.K, t.P, batch, rp.nt,              \
                        rp.plans_per_block, eps, iters, t.comm_ptr, t.path_ptr, t.path_links,   \
                        t.rev_ptr, t.rev_pair, t.invcap, demand, splits, lambda)
+#define NIMBLE_REG_LAUNCH(MAXC, ONEW)                                                          \
+    do {                                                                                       \
+        if (!t.first_direct) NIMBLE_REG_LAUNCH_P(MAXC, ONEW, kRegMaxPaths, false);             \
+        else switch (reg_paths(t)) {                                                           \
+        case 4: NIMBLE_REG_LAUNCH_P(MAXC, ONEW, 4, true); break;                               \
+        case 5: NIMBLE_REG_LAUNCH_P(MAXC, ONEW, 5, true); break;                               \
+        case 6: NIMBLE_REG_LAUNCH_P(MAXC, ONEW, 6, true); break;                               \
+        case 7: NIMBLE_REG_LAUNCH_P(MAXC, ONEW, 7, true); break;                               \
+        default: NIMBLE_REG_LAUNCH_P(MAXC, ONEW, kRegMaxPaths, true); break;                   \
+        }                                                                                      \
+    } while (0)
         const bool one_wave = rp.nt == kWave;
         if (t.cost_max) {
             if (one_wave) NIMBLE_REG_LAUNCH(true, true);
@@ -856,6 +956,7 @@ hipError_t launch_resident(const DeviceTopo &t, int32_t batch, const double *dem
             if (one_wave) NIMBLE_REG_LAUNCH(false, true);
             else NIMBLE_REG_LAUNCH(false, false);
         }
+#undef NIMBLE_REG_LAUNCH_P
 #undef NIMBLE_REG_LAUNCH
         return hipGetLastError();
     }

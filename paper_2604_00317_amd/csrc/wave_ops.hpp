@@ -221,6 +221,45 @@ __device__ __forceinline__ double wave_max(double v)
     return v;
 }
 
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    v = v + partner_f64<1>(v);
+    v = v + partner_f64<2>(v);
+    v = v + partner_f64<4>(v);
+    v = v + partner_f64<8>(v);
+    v = v + partner_f64<16>(v);
+    v = v + partner_f64<32>(v);
+    return v;
+}
+
+__device__ __forceinline__ int wave_min_i32(int v)
+{
+    v = min(v, partner_i32<1>(v));
+    v = min(v, partner_i32<2>(v));
+    v = min(v, partner_i32<4>(v));
+    v = min(v, partner_i32<8>(v));
+    v = min(v, partner_i32<16>(v));
+    v = min(v, partner_i32<32>(v));
+    return v;
+}
+
+// The power of two of the lowest bit set in d: the finest grid d lies on (kNoBit for zeros).
+constexpr int kNoBit = 4096;
+__device__ __forceinline__ int lowest_bit(double d)
+{
+    if (d == 0.0) return kNoBit;
+    const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(d));
+    const int ex = static_cast<int>((b >> 52) & 2047u);
+    const unsigned long long man = (b & ((1ull << 52) - 1ull)) | (ex ? 1ull << 52 : 0ull);
+    return (ex ? ex : 1) - 1075 + __ffsll(static_cast<long long>(man)) - 1;
+}
+
+// Adds v to *p in LDS and returns nothing: one instruction that nobody waits for.
+__device__ __forceinline__ void lds_add_f64(double *p, double v)
+{
+    (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // max(x[first], x[first + STRIDE], ...) over the entries below n (0 when there is none; the
 // entries are not negative): eight loads are requested side by side, so that the count of trips
 // to memory is an eighth of the count of entries.

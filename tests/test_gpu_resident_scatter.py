@@ -1,0 +1,80 @@
+"""Register-resident kernel: loads summed by scatter or by gather, against the oracle bit for bit.
+
+The kernel scatters where the demands of a plan lie on a power-of-two grid with a total below
+2^52 units and gathers, in the oracle's own order, everywhere else: both are the oracle's bits for
+any demands.  Sizes: every instantiation (4 to 8 candidates, first candidate direct or not), plans of
+one wave and of several, one plan and batches that mix both kinds of demands.
+"""
+import numpy as np
+import pytest
+
+from paper_2604_00317_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a visible MI355X; no fallback path exists")
+    from paper_2604_00317_amd import binding
+    binding.load_library(build_if_missing=False)
+    return binding
+
+
+def demands_of(kind, K, rng):
+    d = np.floor(rng.pareto(1.1, K) * 1e6)
+    if kind == "bytes":
+        d[rng.integers(0, K)] = 0.0
+    elif kind == "zero":
+        d[:] = 0.0
+    elif kind == "one":
+        d[:] = 0.0
+        d[K // 2] = 3.0
+    elif kind == "fractional":
+        d = d / 7.0
+    elif kind in ("total_2^51", "total_2^53"):     # either side of the limit of the scatter
+        d = np.floor(rng.random(K) * 64)
+        d[0] = 1.0
+        d[1] = 2.0 ** int(kind[8:]) - 1.0
+    elif kind == "denormal":                       # a grid atomics need not keep
+        d = np.floor(rng.random(K) * 1000) * 2.0 ** -1070
+    elif kind == "huge":
+        d = d * 2.0 ** 900
+    return d
+
+
+KINDS = ["bytes", "zero", "one", "fractional", "total_2^51", "total_2^53", "denormal", "huge"]
+# nodes of 3 to 9 GPUs (2 to 8 candidates, the last with 72 pairs); random topologies of up to 8
+# candidates whose first is not always direct: one wave, two waves, a full workgroup's threads
+FABRICS = [("node", g) for g in (3, 4, 5, 6, 7, 8, 9)] + [
+    ("random", (31, 64, 64, 5)), ("random", (32, 130, 100, 8)), ("random", (33, 1024, 700, 4)),
+    ("random", (34, 1, 2, 1))]
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("fabric", FABRICS, ids=lambda f: f"{f[0]}{f[1]}")
+def test_scatter_and_gather_are_the_oracles_bits(oracle_mod, B, fabric, flags):
+    kind, what = fabric
+    if kind == "node":
+        t = W.build_fabric(1, what)
+    else:
+        seed, E, K, pm = what
+        t = W.random_topology(np.random.default_rng(seed), E, K, pm, min(2, E))
+    rng = np.random.default_rng(7)
+    plans = np.stack([demands_of(k, t.n_comm, rng) for k in KINDS])
+    iters = 40
+    refs = [oracle_mod.solve(*t.csr(), d, 0.07, iters, flags=flags) for d in plans]
+    print(f"{fabric} K={t.n_comm} E={t.n_links} flags={flags}", flush=True)
+    h = B.nimble_topo_create(*t.csr(), flags=flags)
+    try:
+        assert h.resident_in_registers
+        splits, lam = B.plan(h, plans, 0.07, iters)             # side by side in a workgroup
+        for i, r in enumerate(refs):
+            assert np.array_equal(splits[i], r["splits"]) and lam[i] == r["lam"], KINDS[i]
+        for i, r in enumerate(refs):
+            s, l = B.plan(h, plans[i], 0.07, iters)
+            assert np.array_equal(s, r["splits"]) and l == r["lam"], KINDS[i]
+    finally:
+        h.close()
