@@ -16,6 +16,8 @@
 // examples of the algorithm directly (tests/test_gpu_alg1.py), not only against the CPU oracle.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
+
 #include "kernels.hpp"
 #include "wave_ops.hpp"
 
@@ -26,6 +28,7 @@ namespace {
 constexpr int kAlg1Threads = 64;          // most problems per workgroup
 constexpr int kAlg1MinThreads = 8;        // fewest: larger topologies leave less LDS per problem
 constexpr size_t kAlg1LdsBudget = 150 * 1024;
+constexpr size_t kAlg1LdsPlain = 64 * 1024;      // no opt-in needed below this
 
 __global__ __launch_bounds__(kAlg1Threads) void k_alg1(int E, int K, int P, int batch,
                                                         const int32_t *__restrict__ cp,
@@ -114,15 +117,68 @@ __global__ __launch_bounds__(kAlg1Threads) void k_alg1(int E, int K, int P, int 
 // G lanes per problem (G a power of two >= the most candidates of any pair, at most 64), 64 / G
 // problems per wave.  The sweep over the pairs stays sequential -- every routed chunk changes
 // the costs the next pair sees -- but lane j costs candidate j of the pair, the group takes the
-// (cost, index) minimum by DPP (the lowest index among equal costs: the strict `<` of the
-// sequential scan), and the winning lane routes the chunk.  A problem lives inside one wave, so
-// its lanes are ordered by the wave's in-order LDS operations; workgroups never synchronise
-// after the set-up (a workgroup is one wave).  LDS: the candidate table of the topology (per
-// pair and lane, LM link ids padded with E, whose load and 1/capacity are 0) and 1/capacity
-// once per workgroup, then L[E+1], r[K] and the flows f[P] per problem -- nothing in the sweep
-// touches global memory.  All lanes walk all pairs, so a wave sweeps until the last of its
-// problems is done.
-template <int G, int LM>
+// minimum by DPP and the lowest lane that holds it (the strict `<` of the sequential scan) routes
+// the chunk.  A problem lives inside one wave, so its lanes are ordered by the wave's in-order LDS
+// operations; workgroups never synchronise after the set-up (a workgroup is one wave).  LDS: 1/capacity
+// per workgroup; L[E + 2], the remainders r[K], the amounts f[K] of this sweep and the flows (by path;
+// AHEAD: G per pair) per problem.  L[E] (1/capacity 0) stands for a link that is not there, L[E + 1] = +inf (1/capacity 1)
+// for a candidate that is not there.  All lanes walk all pairs, so a wave sweeps until the last
+// of its problems is done (amounts of 0 change nothing).
+//
+// What bounds it is the chain from pair to pair, so everything that does not depend on the pair
+// before is taken out of it.  What a pair routes depends on its own remainder only: the amounts of
+// a sweep (a division each) are worked out before the sweep, side by side.  AHEAD (paths of at most
+// two links, at most 16 candidates) also reads the loads of a pair's links before the pair before
+// it has routed its chunk, and adds that chunk where the candidate it took uses the same link: a
+// table holds, per pair and lane, the links, their 1/capacity and which candidates of the pair
+// before use them.  That leaves decision -> compare -> minimum -> decision, without a trip to LDS;
+// the wave's own instructions (about fifty a pair) then bound it.  Chunks are added by LDS atomics that
+// return nothing (they round like an addition, denormals included); the lanes that do not take the
+// pair add to a spare place.  Longer paths read the loads when they are needed; their links come from
+// memory, asked for ahead in stages.
+// 4096 problems of one node of 8 GPUs (56 pairs, 10 sweeps at most): 222 -> 102 us
+// (one problem 200 -> 86; 7.5 us a sweep).  512 problems of two nodes of 8 (240 pairs of up to 16
+// candidates, on a thread per problem until their lists left the LDS): 12.4 -> 1.24 ms.
+constexpr int kAheadSteps = 2, kAheadLanes = 16;
+constexpr int kAheadPairs = 4;           // steps of the unrolled loop; pairs are padded to them
+
+// a candidate of up to two links: their byte offsets in L (16 bits each), and for each of them the
+// candidates of the pair before that use it
+struct __align__(16) Alg1Entry {
+    uint32_t at, mask0, mask1, unused;
+    double ic0, ic1;
+};
+
+struct Alg1Lds {
+    size_t ic, problem, per_problem, spare, cp, tab, bytes;
+};
+
+__host__ __device__ inline Alg1Lds alg1_lds(int E, int K, int P, int lanes, bool ahead)
+{
+    Alg1Lds l;
+    const int pairs = (K + kAheadPairs - 1) / kAheadPairs * kAheadPairs;
+    size_t o = 0;
+    l.ic = o;       o += sizeof(double) * (E + 2);
+    l.per_problem = sizeof(double) * (static_cast<size_t>(E) + 3 + 2 * static_cast<size_t>(pairs) +
+                                      (ahead ? static_cast<size_t>(pairs) * lanes : P));
+    l.problem = o;  o += l.per_problem * (kWave / lanes);
+    l.spare = o;    o += sizeof(double) * kWave;         // a place per lane for what is not wanted
+    o = (o + 15) & ~size_t(15);
+    l.tab = o;      o += ahead ? sizeof(Alg1Entry) * (static_cast<size_t>(pairs) + 2) * lanes : 0;
+    l.cp = o;       o += sizeof(int32_t) * (K + 1);
+    l.bytes = o;
+    return l;
+}
+
+// the largest of two numbers that are no NaN, or the other one
+__device__ __forceinline__ double max_f64(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+template <int G, int LM, bool AHEAD>
 __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int batch,
                                                       const int32_t *__restrict__ cp,
                                                       const int32_t *__restrict__ lp,
@@ -134,54 +190,161 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
                                                       double *__restrict__ lambda,
                                                       int32_t *__restrict__ sweeps_out)
 {
-    extern __shared__ __align__(16) double s_mem[];
+    static_assert(!AHEAD || (LM == kAheadSteps && G <= kAheadLanes), "masks of 16 bits");
+    extern __shared__ __align__(16) unsigned char s_alg1[];
     constexpr int kPerBlock = kWave / G;                      // problems of this wave
-    const size_t per_problem = size_t(E) + 1 + K + P;
-    double *s_ic = s_mem;                                     // [E + 1]
-    double *s_state = s_ic + (E + 1);                         // per problem: L[E+1], r[K], f[P]
-    int32_t *s_cp = reinterpret_cast<int32_t *>(s_state + kPerBlock * per_problem);   // [K + 1]
-    int32_t *s_tab = s_cp + (K + 1);                          // [K][G][LM]
-    for (int e = threadIdx.x; e <= E; e += kWave) s_ic[e] = e < E ? invcap[e] : 0.0;
-    for (int k = threadIdx.x; k <= K; k += kWave) s_cp[k] = cp[k];
-    for (int idx = threadIdx.x; idx < K * G; idx += kWave) {
-        const int k = idx / G, jj = idx % G;
-        const int p = cp[k] + jj;
-        int la = 0, lb = 0;
-        if (p < cp[k + 1]) {
-            la = lp[p];
-            lb = lp[p + 1];
-        }
-        for (int i = 0; i < LM; ++i) s_tab[size_t(idx) * LM + i] = la + i < lb ? pl[la + i] : E;
-    }
+    const Alg1Lds l = alg1_lds(E, K, P, G, AHEAD);
     const int lane = threadIdx.x;
     const int j = lane % G;
     const int slot = lane / G;
     const int b = blockIdx.x * kPerBlock + slot;
     const bool live = b < batch;
-    double *L = s_state + size_t(slot) * per_problem;
-    double *r = L + (E + 1);
-    double *fl = r + K;
+    double *s_ic = reinterpret_cast<double *>(s_alg1 + l.ic);
+    double *L = reinterpret_cast<double *>(s_alg1 + l.problem + l.per_problem * slot);
+    const int pairs = (K + kAheadPairs - 1) / kAheadPairs * kAheadPairs;
+    double *r = L + (E + 2), *amount = r + pairs, *fl = amount + (pairs + 1);
+    double *spare = reinterpret_cast<double *>(s_alg1 + l.spare) + lane;
+    Alg1Entry *s_tab = reinterpret_cast<Alg1Entry *>(s_alg1 + l.tab);   // [pairs + 2][G]
+    int32_t *s_cp = reinterpret_cast<int32_t *>(s_alg1 + l.cp);
+    for (int e = lane; e < E; e += kWave) s_ic[e] = invcap[e];
+    for (int k = lane; k <= K; k += kWave) s_cp[k] = cp[k];
     for (int e = j; e <= E; e += G) L[e] = 0.0;
-    for (int k = j; k < K; k += G) r[k] = live ? demand[size_t(b) * K + k] : 0.0;
-    for (int p = j; p < P; p += G) fl[p] = 0.0;
+    // (set-up and results in batches of eight, so that the trips to memory overlap)
+    bool some = false;
+    for (int k0 = j; k0 < pairs; k0 += 8 * G) {
+        double d[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = k0 + i * G;
+            d[i] = demand[size_t(live ? b : 0) * K + (k < K ? k : 0)];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int k = k0 + i * G;
+            if (!live || k >= K) d[i] = 0.0;
+            if (k < pairs) r[k] = d[i];
+            some = some || d[i] > 0.0;
+        }
+    }
+    for (int i = j; i < (AHEAD ? pairs * G : P); i += G) fl[i] = 0.0;
+    if (lane == 0) {
+        s_ic[E] = 0.0;
+        s_ic[E + 1] = 1.0;
+    }
+    if (j == 0) L[E + 1] = __builtin_inf();
     __syncthreads();                                 // one wave: orders the set-up
+    auto offset = [](double *p, uint32_t bytes) {
+        return reinterpret_cast<double *>(reinterpret_cast<unsigned char *>(p) + bytes);
+    };
+    auto after = [&](int k) { return k + 1 < K ? k + 1 : 0; };
+    if constexpr (AHEAD) {
+        for (int idx0 = lane; idx0 < (pairs + 2) * G; idx0 += 8 * kWave) {
+            bool there[8];
+            int la[8], two[8], x0[8], x1[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int k = (idx0 + i * kWave) / G, kc = k < K ? k : K - 1;
+                int p = s_cp[kc] + idx0 % G;
+                there[i] = k < K && p < s_cp[kc + 1];
+                p = there[i] ? p : 0;
+                la[i] = lp[p];
+                two[i] = lp[p + 1];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                two[i] = two[i] - la[i] > 1 ? 1 : 0;
+                x0[i] = pl[la[i]];
+                x1[i] = pl[la[i] + two[i]];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int e0 = there[i] ? x0[i] : E + 1, e1 = there[i] && two[i] ? x1[i] : E;
+                Alg1Entry entry = {};
+                entry.at = 8u * (static_cast<uint32_t>(e0) | static_cast<uint32_t>(e1) << 16);
+                entry.ic0 = s_ic[e0];
+                entry.ic1 = s_ic[e1];
+                if (idx0 + i * kWave < (pairs + 2) * G) s_tab[idx0 + i * kWave] = entry;
+            }
+        }
+        __syncthreads();
+        for (int idx = lane; idx < (pairs + 2) * G; idx += kWave) {
+            const int before = idx / G > 0 ? idx / G - 1 : 0;      // (the first pair has none)
+            const uint32_t e0 = s_tab[idx].at & 0xFFFFu, e1 = s_tab[idx].at >> 16;
+            uint32_t m0 = 0u, m1 = 0u;
+#pragma unroll
+            for (int c = 0; c < G; ++c) {
+                const uint32_t o = s_tab[before * G + c].at, o0 = o & 0xFFFFu, o1 = o >> 16;
+                m0 |= (e0 == o0 || e0 == o1 ? 1u : 0u) << c;
+                m1 |= (e1 == o0 || e1 == o1 ? 1u : 0u) << c;
+            }
+            s_tab[idx].mask0 = e0 < 8u * E ? m0 : 0u;
+            s_tab[idx].mask1 = e1 < 8u * E ? m1 : 0u;
+        }
+        __syncthreads();
+    }
     // lanes of this problem inside the wave
-    const unsigned long long gmask = (G == 64 ? ~0ull : ((1ull << G) - 1ull)) << (lane - j);
+    const unsigned long long gmask = (G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull)) << (lane - j);
+    // the one lane of the group that takes the pair, of those whose cost is the least
+    auto takes = [&](double c, double m, uint32_t &low) {
+        const unsigned long long eq = __builtin_amdgcn_ballot_w64(c == m);
+        if constexpr (G <= 32) {
+            const uint32_t half = lane & 32 ? static_cast<uint32_t>(eq >> 32)
+                                            : static_cast<uint32_t>(eq);
+            const uint32_t field = __builtin_amdgcn_ubfe(half, (lane - j) & 31, G & 31);
+            low = G == 32 ? half & (0u - half) : field & (0u - field);
+            return low == 1u << (j & 31);
+        } else {
+            low = 0u;
+            return j == __ffsll(static_cast<long long>(eq)) - 1;
+        }
+    };
+    auto least = [&](double c) {
+        double m = c;
+        if constexpr (G > 1) m = fast_min_f64(m, partner_f64<1>(m));
+        if constexpr (G > 2) m = fast_min_f64(m, partner_f64<2>(m));
+        if constexpr (G > 4) m = fast_min_f64(m, partner_f64<4>(m));
+        if constexpr (G > 8) m = fast_min_f64(m, partner_f64<8>(m));
+        if constexpr (G > 16) m = fast_min_f64(m, partner_f64<16>(m));
+        if constexpr (G > 32) m = fast_min_f64(m, partner_f64<32>(m));
+        return m;
+    };
     int sweeps = 0;
     bool gave_up = false, done = false;
-    // the first pair's share of the topology
-    int n_pa = s_cp[0], n_np = s_cp[1] - s_cp[0];
-    int n_e[LM];
-    double n_ic[LM];
+
+    // not AHEAD: links and 1/capacity of the pair at hand, links of the next, list of the one after
+    // (asked for without branches, so that nobody waits for one request before the next is made)
+    int e_now[LM], e_next[LM], p_now = 0, p_next = 0, p_list = 0, la = 0, lb = 0, k_list = 0;
+    double ic_now[LM];
+    auto ask_list = [&](int k) {
+        p_list = s_cp[k] + j;
+        const bool there = p_list < s_cp[k + 1];
+        p_list = there ? p_list : 0;
+        la = lp[p_list];
+        lb = lp[p_list + 1];
+        lb = there ? lb : la;
+    };
+    auto ask_links = [&](int (&e)[LM]) {
+        const int n = lb - la;
 #pragma unroll
-    for (int i = 0; i < LM; ++i) {
-        n_e[i] = s_tab[size_t(j) * LM + i];
-        n_ic[i] = s_ic[n_e[i]];
+        for (int i = 0; i < LM; ++i) {
+            const int x = pl[la + (i < n ? i : 0)];
+            e[i] = i < n ? x : i == 0 ? E + 1 : E;
+        }
+    };
+    if constexpr (!AHEAD) {
+        ask_list(0);
+        p_now = p_list;
+        ask_links(e_now);
+#pragma unroll
+        for (int i = 0; i < LM; ++i) ic_now[i] = s_ic[e_now[i]];
+        ask_list(after(0));
+        p_next = p_list;
+        ask_links(e_next);
+        k_list = after(after(0));
+        ask_list(k_list);
     }
     for (;;) {
-        bool mine = false;
-        for (int k = j; k < K; k += G) mine = mine || r[k] > 0.0;
-        const bool any = (__ballot(mine) & gmask) != 0ull;
+        const bool any = (__ballot(some) & gmask) != 0ull;
         if (!done) {
             if (!any) done = true;
             else if (sweeps == max_sweeps) {
@@ -190,67 +353,137 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
             } else sweeps += 1;
         }
         if (__all(done)) break;                      // wave-uniform
-        for (int k = 0; k < K; ++k) {                // the same pair in every lane
-            // this pair's share of the topology was requested during the previous pair; the
-            // next pair's (the first pair of the next sweep after the last) is requested now,
-            // so that only the loads L_e -- which the previous pair may have changed -- are
-            // waited for on the way to the argmin
-            const int pa = n_pa, np = n_np;
-            int e[LM];
-            double ice[LM];
+        // what every pair routes in this sweep, and what it leaves for the next
+        some = false;
+        for (int k0 = j; k0 < pairs; k0 += kAheadPairs * G) {
+            double rk[kAheadPairs], f[kAheadPairs];
 #pragma unroll
-            for (int i = 0; i < LM; ++i) {
-                e[i] = n_e[i];
-                ice[i] = n_ic[i];
-            }
-            {
-                const int kn = k + 1 < K ? k + 1 : 0;
-                n_pa = s_cp[kn];
-                n_np = s_cp[kn + 1] - n_pa;
-                const int32_t *tab = s_tab + (size_t(kn) * G + j) * LM;
+            for (int i = 0; i < kAheadPairs; ++i) rk[i] = k0 + i * G < pairs ? r[k0 + i * G] : 0.0;
 #pragma unroll
-                for (int i = 0; i < LM; ++i) n_e[i] = tab[i];
-#pragma unroll
-                for (int i = 0; i < LM; ++i) n_ic[i] = s_ic[n_e[i]];
-            }
-            const double rk = r[k];
-            double Lv[LM];
-#pragma unroll
-            for (int i = 0; i < LM; ++i) Lv[i] = L[e[i]];
-            // the amount depends on the remainder only: every lane works it out while the
-            // loads arrive and the argmin runs (the division is the longest chain of the step)
-            double f = rk;
-            {
-                const double want = rk * phi;
+            for (int i = 0; i < kAheadPairs; ++i) {
+                const double want = rk[i] * phi;
                 const double chunks = floor(want / chi);
                 double fc = chunks * chi;
                 if (!(fc > 0.0)) fc = chi;
-                if (!(rk < chi)) f = fc;
+                f[i] = rk[i];
+                if (!(rk[i] < chi)) f[i] = fc;
+                if (done || !(rk[i] > 0.0)) f[i] = 0.0;
             }
-            double c = 0.0;                          // costs are >= 0: the max starts at 0
 #pragma unroll
-            for (int i = 0; i < LM; ++i) {           // padding steps cost 0 * 0
-                const double ce = Lv[i] * ice[i];
-                if (ce > c) c = ce;
+            for (int i = 0; i < kAheadPairs; ++i) {
+                const double rest = rk[i] - f[i];
+                some = some || rest > 0.0;
+                if (k0 + i * G < pairs) {
+                    amount[k0 + i * G] = f[i];
+                    r[k0 + i * G] = rest;
+                }
             }
-            if (j >= np) c = __builtin_inf();
-            const int bj = group_argmin_two_pass<G>(c, j);
-            if (!done && rk > 0.0 && np > 0 && j == bj) {
-                fl[pa + bj] = fl[pa + bj] + f;
-#pragma unroll
-                for (int i = 0; i < LM; ++i)
-                    if (e[i] < E) L[e[i]] = Lv[i] + f;
-                r[k] = rk - f;
-            }
-            // the next pair sees the loads this one left
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if constexpr (AHEAD) {
+            const Alg1Entry *entry = s_tab + j;
+            const double *next_amount = amount + 1;
+            double *flow = fl + j;
+            // the pair at hand (its loads without the chunk of the pair before) and the next one's
+            // links; what the pair before routed, and which of its lanes took it
+            Alg1Entry now = entry[0], next = entry[G];
+            double *at0 = offset(L, now.at & 0xFFFFu), *at1 = offset(L, now.at >> 16);
+            double L0 = *at0, L1 = *at1, f = amount[0], routed = 0.0;
+            uint32_t took = 0u;
+            for (int k0 = 0; k0 < pairs; k0 += kAheadPairs) {
+#pragma unroll
+                for (int i = 0; i < kAheadPairs; ++i) {
+                    const Alg1Entry after = entry[(i + 2) * G];
+                    const double f_next = next_amount[i];  // (the one past the last is not used)
+                    // (asked for before this pair's own additions: corrected when its turn comes)
+                    double *n_at0 = offset(L, next.at & 0xFFFFu), *n_at1 = offset(L, next.at >> 16);
+                    const double n0 = *n_at0, n1 = *n_at1;
+                    const double a0 = L0 + routed, a1 = L1 + routed;
+                    L0 = (now.mask0 & took) != 0u ? a0 : L0;
+                    L1 = (now.mask1 & took) != 0u ? a1 : L1;
+                    const double c = max_f64(L0 * now.ic0, L1 * now.ic1);
+                    const bool me = takes(c, least(c), took);
+                    lds_add_f64(me ? flow + i * G : spare, f);
+                    lds_add_f64(me ? at0 : spare, f);
+                    lds_add_f64(me ? at1 : spare, f);
+                    routed = f;
+                    f = f_next;
+                    now = next;
+                    next = after;
+                    at0 = n_at0;
+                    at1 = n_at1;
+                    L0 = n0;
+                    L1 = n1;
+                }
+                entry += kAheadPairs * G;
+                next_amount += kAheadPairs;
+                flow += kAheadPairs * G;
+            }
+        } else {
+            double f = amount[0];
+            for (int k = 0; k < K; ++k) {            // the same pair in every lane
+                double Lv[LM];
+#pragma unroll
+                for (int i = 0; i < LM; ++i) Lv[i] = L[e_now[i]];
+                const double f_next = amount[k + 1];
+                const double flow_now = fl[p_now];
+                double ic_next[LM];
+#pragma unroll
+                for (int i = 0; i < LM; ++i) ic_next[i] = s_ic[e_next[i]];
+                int e_after[LM];
+                const int p_after = p_list;
+                ask_links(e_after);
+                k_list = after(k_list);
+                ask_list(k_list);
+                double c = Lv[0] * ic_now[0];
+#pragma unroll
+                for (int i = 1; i < LM; ++i) c = max_f64(c, Lv[i] * ic_now[i]);
+                uint32_t low;
+                if (takes(c, least(c), low)) {
+                    fl[p_now] = flow_now + f;
+#pragma unroll
+                    for (int i = 0; i < LM; ++i)
+                        if (e_now[i] < E) L[e_now[i]] = Lv[i] + f;
+                }
+#pragma unroll
+                for (int i = 0; i < LM; ++i) {
+                    e_now[i] = e_next[i];
+                    ic_now[i] = ic_next[i];
+                    e_next[i] = e_after[i];
+                }
+                p_now = p_next;
+                p_next = p_after;
+                f = f_next;
+                // the next pair sees the loads this one left
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
     if (live) {
         double *out = flows + size_t(b) * P;
-        for (int p = j; p < P; p += G) out[p] = fl[p];
+        if constexpr (!AHEAD)
+            for (int p = j; p < P; p += G) out[p] = fl[p];
+        for (int k0 = 0; AHEAD && k0 < K; k0 += 8) {
+            int p[8], n[8];
+            double v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int k = k0 + i < K ? k0 + i : K - 1;
+                p[i] = s_cp[k];
+                n[i] = s_cp[k + 1] - p[i];
+                v[i] = fl[k * G + j];
+            }
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                if (j < n[i] && k0 + i < K) out[p[i] + j] = v[i];
+        }
     }
     double lam = 0.0;
     for (int e = j; e < E; e += G) {
@@ -269,23 +502,35 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
     }
 }
 
-constexpr size_t kAlg1GroupLds = 64 * 1024;      // no opt-in needed below this
-
-// link ids per candidate in the table of k_alg1_group: 2 or 8
-int alg1_group_steps(const DeviceTopo &t) { return t.lmax <= 2 ? 2 : 8; }
-
 // lanes per problem of k_alg1_group, or 0 if the topology does not fit it
-int alg1_group_lanes(const DeviceTopo &t, size_t &lds)
+int alg1_group_lanes(const DeviceTopo &t, bool &ahead, size_t &lds)
 {
     if (t.alg1_thread_per_problem || t.pmax > kWave || t.pmax < 1 || t.lmax > 8 || t.K < 1)
         return 0;
-    const int G = lanes_per_commodity(t.pmax);
-    const size_t per_block = kWave / G;
-    lds = sizeof(double) * (t.E + 1) +
-          sizeof(double) * per_block * (static_cast<size_t>(t.E) + 1 + t.K + t.P) +
-          sizeof(int32_t) * (t.K + 1) +
-          sizeof(int32_t) * static_cast<size_t>(t.K) * G * alg1_group_steps(t);
-    return lds <= kAlg1GroupLds ? G : 0;
+    // (more lanes than candidates where only fewer problems fit the LDS together)
+    for (int G = lanes_per_commodity(t.pmax); G <= kWave; G *= 2) {
+        ahead = t.lmax <= kAheadSteps && G <= kAheadLanes && 8 * (t.E + 1) <= 0xFFFF;
+        lds = alg1_lds(t.E, t.K, t.P, G, ahead).bytes;
+        if (ahead && lds > kAlg1LdsBudget) {
+            ahead = false;
+            lds = alg1_lds(t.E, t.K, t.P, G, ahead).bytes;
+        }
+        if (lds <= kAlg1LdsBudget) return G;
+    }
+    return 0;
+}
+
+// What is accepted: topologies whose state fits 64 KB with a group of lanes per problem and the
+// candidate lists beside it (2 or 8 links each), or a workgroup of the kernel with a thread per problem.
+bool alg1_small(const DeviceTopo &t)
+{
+    if (t.pmax > kWave || t.pmax < 1 || t.lmax > 8 || t.K < 1) return false;
+    const size_t G = lanes_per_commodity(t.pmax);
+    return sizeof(double) * (t.E + 1) +
+               sizeof(double) * (kWave / G) * (static_cast<size_t>(t.E) + 1 + t.K + t.P) +
+               sizeof(int32_t) * (t.K + 1) +
+               sizeof(int32_t) * static_cast<size_t>(t.K) * G * (t.lmax <= 2 ? 2 : 8) <=
+           kAlg1LdsPlain;
 }
 
 }  // namespace
@@ -306,8 +551,7 @@ size_t alg1_lds_bytes(const DeviceTopo &t)
 
 bool alg1_fits(const DeviceTopo &t)
 {
-    size_t lds = 0;
-    return alg1_group_lanes(t, lds) > 0 || alg1_lds_bytes(t) <= kAlg1LdsBudget;
+    return (!t.alg1_thread_per_problem && alg1_small(t)) || alg1_lds_bytes(t) <= kAlg1LdsBudget;
 }
 
 hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand, double phi,
@@ -315,30 +559,59 @@ hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand,
                        int32_t *sweeps, hipStream_t s)
 {
     size_t glds = 0;
-    const int G = alg1_group_lanes(t, glds);
+    bool ahead = false;
+    int G = alg1_group_lanes(t, ahead, glds);
+    if (G > 0 && !alg1_small(t)) {
+        // A pair takes the group 0.55 us whatever its candidates, a thread about 0.065 us per link of
+        // them (two nodes of 8, 16 or 32 candidates of up to five links: 0.53 against 5.2, 0.56 against
+        // 8.8 us), but a compute unit holds fewer groups than threads.
+        const double groups = 256.0 * (kWave / G) * static_cast<double>(160 * 1024 / glds);
+        const double threads = 256.0 * alg1_threads(t);
+        if (0.55 * std::ceil(batch / groups) >
+            0.065 * static_cast<double>(t.nnz) / t.K * std::ceil(batch / threads))
+            G = 0;
+    }
     if (G > 0) {
         const int per_block = kWave / G;
         const int ggrid = (batch + per_block - 1) / per_block;
-        const bool two = alg1_group_steps(t) == 2;
-#define NIMBLE_ALG1_ARGS                                                                       \
-    dim3(ggrid), dim3(kWave), glds, s, t.E, t.K, t.P, batch, t.comm_ptr, t.path_ptr,           \
-        t.path_links, t.invcap, demand, phi, chi, max_sweeps, flows, lambda, sweeps
-#define NIMBLE_ALG1_LAUNCH(GG)                                                                 \
+#define NIMBLE_ALG1_LAUNCH(GG, LM, AHEAD)                                                      \
+    do {                                                                                       \
+        if (glds > kAlg1LdsPlain) {                                                            \
+            const hipError_t ea = hipFuncSetAttribute(                                         \
+                reinterpret_cast<const void *>(&k_alg1_group<GG, LM, AHEAD>),                  \
+                hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kAlg1LdsBudget)); \
+            if (ea != hipSuccess) return ea;                                                   \
+        }                                                                                      \
+        hipLaunchKernelGGL((k_alg1_group<GG, LM, AHEAD>), dim3(ggrid), dim3(kWave), glds, s,   \
+                           t.E, t.K, t.P, batch, t.comm_ptr, t.path_ptr, t.path_links,         \
+                           t.invcap, demand, phi, chi, max_sweeps, flows, lambda, sweeps);     \
+        return hipGetLastError();                                                              \
+    } while (0)
+#define NIMBLE_ALG1_LONG(GG)                                                                   \
     case GG:                                                                                   \
-        if (two) hipLaunchKernelGGL((k_alg1_group<GG, 2>), NIMBLE_ALG1_ARGS);                  \
-        else hipLaunchKernelGGL((k_alg1_group<GG, 8>), NIMBLE_ALG1_ARGS);                      \
-        return hipGetLastError();
-        switch (G) {
-            NIMBLE_ALG1_LAUNCH(1)
-            NIMBLE_ALG1_LAUNCH(2)
-            NIMBLE_ALG1_LAUNCH(4)
-            NIMBLE_ALG1_LAUNCH(8)
-            NIMBLE_ALG1_LAUNCH(16)
-            NIMBLE_ALG1_LAUNCH(32)
-            NIMBLE_ALG1_LAUNCH(64)
+        if (t.lmax <= 5) NIMBLE_ALG1_LAUNCH(GG, 5, false);                                     \
+        NIMBLE_ALG1_LAUNCH(GG, 8, false)
+#define NIMBLE_ALG1_AHEAD(GG)                                                                  \
+    case GG: NIMBLE_ALG1_LAUNCH(GG, kAheadSteps, true)
+        if (ahead) switch (G) {
+            NIMBLE_ALG1_AHEAD(1);
+            NIMBLE_ALG1_AHEAD(2);
+            NIMBLE_ALG1_AHEAD(4);
+            NIMBLE_ALG1_AHEAD(8);
+            NIMBLE_ALG1_AHEAD(16);
         }
+        switch (G) {
+            NIMBLE_ALG1_LONG(1);
+            NIMBLE_ALG1_LONG(2);
+            NIMBLE_ALG1_LONG(4);
+            NIMBLE_ALG1_LONG(8);
+            NIMBLE_ALG1_LONG(16);
+            NIMBLE_ALG1_LONG(32);
+            NIMBLE_ALG1_LONG(64);
+        }
+#undef NIMBLE_ALG1_AHEAD
+#undef NIMBLE_ALG1_LONG
 #undef NIMBLE_ALG1_LAUNCH
-#undef NIMBLE_ALG1_ARGS
     }
     const size_t lds = alg1_lds_bytes(t);
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_alg1),

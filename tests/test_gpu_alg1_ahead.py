@@ -1,0 +1,71 @@
+"""Algorithm 1 with the loads of a pair read before the pair before it has routed: bit for bit the
+oracle's where consecutive pairs fight for the same links, and at the edges of the padded pair loop."""
+import numpy as np
+import pytest
+
+from paper_2604_00317_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2604_00317_amd import binding
+    binding.load_library(build_if_missing=False)
+    return binding
+
+
+def check(oracle_mod, B, t, demands, phi, chi):
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        flows, lam, sweeps = B.plan_alg1(h, demands, phi, chi)
+    finally:
+        h.close()
+    for b in range(demands.shape[0]):
+        ref = oracle_mod.alg1(*t.csr(), demands[b], phi, chi)
+        assert np.array_equal(flows[b], ref["flows"]), f"problem {b}"
+        assert lam[b] == ref["lam"] and sweeps[b] == ref["sweeps"], f"problem {b}"
+
+
+# (links, pairs, most candidates, most links of a path): two to nine links for all pairs, so that
+# most pairs want what the pair before has just loaded; 1 to 16 candidates, pairs around multiples
+# of four; then groups of more lanes than the ahead form has, and longer paths
+SHAPES = [(2, 1, 2, 2), (2, 2, 2, 1), (3, 3, 1, 2), (3, 4, 3, 2), (4, 5, 4, 2), (9, 56, 7, 2),
+          (9, 57, 8, 2), (6, 59, 16, 2), (20, 61, 9, 2), (9, 30, 17, 2), (9, 30, 6, 3), (9, 31, 20, 7)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_consecutive_pairs_on_the_same_links(oracle_mod, B, shape):
+    E, K, pm, lm = shape
+    rng = np.random.default_rng(E * 100 + K)
+    t = W.random_topology(rng, E, K, pm, lm)
+    d = np.floor(rng.pareto(1.1, (21, K)) * 1e6)
+    d[1] = 0.0
+    d[2, ::2] = 0.0
+    d[3] = d[3] / 7.0
+    d[4] = np.floor(rng.random(K) * 1000) * 2.0 ** -1070          # denormal bytes, one chunk each
+    print(f"[alg1] {shape}", flush=True)
+    check(oracle_mod, B, t, d, 0.5, 65536.0)
+
+
+@pytest.mark.parametrize("gpus,rails", [(8, "own"), (5, "own"), (8, "pair")])
+def test_two_nodes(oracle_mod, B, gpus, rails):
+    """Long paths on a group of lanes; a NIC per GPU takes more lanes than a pair has candidates."""
+    t = W.build_fabric(2, gpus, gpus, [[r] for r in range(gpus)]) if rails == "own" else \
+        W.build_fabric(2, gpus, gpus // 2, W.pair_access(gpus // 2))
+    rng = np.random.default_rng(gpus)
+    d = np.floor(rng.pareto(1.1, (9, t.n_comm)) * 1e6)
+    check(oracle_mod, B, t, d, 0.5, float(1 << 20))
+
+
+def test_topologies_beyond_the_limits_are_refused(B):
+    t = W.random_topology(np.random.default_rng(1), 8000, 10, 2, 2)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        with pytest.raises(B.NimbleError) as e:
+            B.plan_alg1(h, np.ones((1, 10)), 0.5, 1.0)
+        assert e.value.status == B.NIMBLE_ERR_RANGE
+    finally:
+        h.close()
