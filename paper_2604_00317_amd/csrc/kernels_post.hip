@@ -21,6 +21,7 @@ namespace nimble {
 namespace {
 
 constexpr int kPostBlock = 256;
+constexpr int kPairsAtOnce = 2;          // of a group of lanes, where there are many pairs
 
 __global__ __launch_bounds__(kPostBlock) void k_quantize(int K, const int32_t *__restrict__ cp,
                                                          const double *__restrict__ demand,
@@ -74,6 +75,22 @@ __global__ __launch_bounds__(kPostBlock) void k_quantize(int K, const int32_t *_
     }
 }
 
+// The values of v in both rows of a pair of rows (of both halves of the wave): own and other, in an
+// order that is the same in all of them.  One vector instruction, where a shuffle goes through the LDS.
+struct TwoI32 {
+    int a, b;
+};
+__device__ __forceinline__ TwoI32 both_rows(int v)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return {static_cast<int>(r[0]), static_cast<int>(r[1])};
+}
+__device__ __forceinline__ TwoI32 both_halves(int v)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return {static_cast<int>(r[0]), static_cast<int>(r[1])};
+}
+
 template <int L>
 __device__ __forceinline__ int group_sum_i32(int v)
 {
@@ -81,8 +98,14 @@ __device__ __forceinline__ int group_sum_i32(int v)
     if constexpr (L > 2) v += partner_i32<2>(v);
     if constexpr (L > 4) v += partner_i32<4>(v);
     if constexpr (L > 8) v += partner_i32<8>(v);
-    if constexpr (L > 16) v += partner_i32<16>(v);
-    if constexpr (L > 32) v += partner_i32<32>(v);
+    if constexpr (L > 16) {
+        const TwoI32 r = both_rows(v);
+        v = r.a + r.b;
+    }
+    if constexpr (L > 32) {
+        const TwoI32 h = both_halves(v);
+        v = h.a + h.b;
+    }
     return v;
 }
 
@@ -93,8 +116,14 @@ __device__ __forceinline__ int group_max_i32(int v)
     if constexpr (L > 2) v = max(v, partner_i32<2>(v));
     if constexpr (L > 4) v = max(v, partner_i32<4>(v));
     if constexpr (L > 8) v = max(v, partner_i32<8>(v));
-    if constexpr (L > 16) v = max(v, partner_i32<16>(v));
-    if constexpr (L > 32) v = max(v, partner_i32<32>(v));
+    if constexpr (L > 16) {
+        const TwoI32 r = both_rows(v);
+        v = max(r.a, r.b);
+    }
+    if constexpr (L > 32) {
+        const TwoI32 h = both_halves(v);
+        v = max(h.a, h.b);
+    }
     return v;
 }
 
@@ -171,143 +200,159 @@ __device__ __forceinline__ int group_rank(KEY key, int lane)
 }
 
 // The rank counted as above, for 32-bit keys of groups that fill whole DPP rows, without a
-// carry from one comparison to the next.  Keys lie in [-1, 2^30), so the sign of key - ko says whether ko is ahead; the
+// carry from one comparison to the next.  Keys lie in [-1, 2^30) and those of candidates differ, so the
+// sign of ko - key says whether ko is behind, and all but the own one are ahead or behind; the
 // signs are shifted into a word (32 comparisons at most per word) and counted at the end.
+// (Not key - ko: the compiler makes that v_subrev_u32 with the move across lanes inside, which was
+// seen to return ko - key here.)
 template <int S>
 __device__ __forceinline__ void collect_signs(int v, int key, unsigned &signs)
 {
-    signs = __builtin_amdgcn_alignbit(signs, static_cast<unsigned>(key - dpp_i32<0x120 + S>(v)), 31);
+    signs = __builtin_amdgcn_alignbit(signs, static_cast<unsigned>(dpp_i32<0x120 + S>(v) - key), 31);
     if constexpr (S > 1) collect_signs<S - 1>(v, key, signs);
 }
-// all sixteen lanes of the row 16, 32 or 48 lanes away, S of them rotated
-__device__ __forceinline__ int row_ahead(int v, int key)
+// how many of the sixteen lanes of a row are behind
+__device__ __forceinline__ int row_behind(int v, int key)
 {
-    unsigned signs = static_cast<unsigned>(key - v) >> 31;
+    unsigned signs = static_cast<unsigned>(v - key) >> 31;
     collect_signs<15>(v, key, signs);
     return __popc(signs);
 }
 template <int L>
 __device__ __forceinline__ int group_rank_narrow(int key)
 {
-    int rank = row_ahead(key, key);              // (a key is not ahead of itself)
-    if constexpr (L > 16) rank += row_ahead(__shfl_xor(key, 16, kWave), key);
-    if constexpr (L > 32) {
-        rank += row_ahead(__shfl_xor(key, 32, kWave), key);
-        rank += row_ahead(__shfl_xor(key, 48, kWave), key);
-    }
-    return rank;
+    if constexpr (L <= 16) return L - 1 - row_behind(key, key);   // (nobody is behind oneself)
+    const TwoI32 r = both_rows(key);
+    if constexpr (L <= 32) return L - 1 - row_behind(r.a, key) - row_behind(r.b, key);
+    const TwoI32 a = both_halves(r.a), b = both_halves(r.b);
+    return L - 1 - row_behind(a.a, key) - row_behind(a.b, key) - row_behind(b.a, key) -
+           row_behind(b.b, key);
 }
 
 // L lanes per pair (L a power of two, every pair has at most L candidates); the lanes of a
 // group take the same branches, so the cross-lane steps are reached by whole groups.
-// Vector issue bounds it: a wave needs several hundred instructions for 64 candidates of 16 bytes.
-// NARROW (iters < 2^24) therefore keeps all whole numbers but the flows in 32 bits: remainders are
-// below iters, so the low halves of N * c and q * iters give them, and the product with 1 / iters
-// is as good for the quotient as the division.  Measured on 261 632 pairs of 32 candidates: 59.0 us
-// with 64-bit whole numbers throughout, 50.1 us (2.7 TB/s) like this.
-template <int L, bool NARROW>
+// The two trips to memory a wave makes one after the other (list, then fractions) bound it: a group
+// takes U pairs, whose lists are asked for together.  NARROW (iters < 2^24) keeps all whole numbers but
+// the flows in 32 bits: remainders are below iters, so the low halves of N * c and q * iters give them,
+// and the product with 1 / iters is as good for the quotient as the division.  Measured on 261 632
+// pairs of 32 candidates: 59.0 us with 64-bit whole numbers throughout, 49.6 us (2.8 TB/s) in 32 bits,
+// 52.0 us with a third fewer instructions (reciprocals passed in, subtractions in the moves across
+// lanes), 43.7 us with those and two pairs at a time.
+template <int L, bool NARROW, int U>
 __global__ __launch_bounds__(kPostBlock) void k_quantize_group(int K,
                                                                const int32_t *__restrict__ cp,
                                                                const double *__restrict__ demand,
                                                                const double *__restrict__ splits,
-                                                               int iters, long long chi,
-                                                               double theta,
+                                                               int iters, double inv_iters,
+                                                               long long chi, int chi_is_pow2,
+                                                               double inv_chi, double theta,
                                                                double *__restrict__ flows)
 {
-    const long long tid = static_cast<long long>(blockIdx.x) * kPostBlock + threadIdx.x;
-    const long long kk = tid / L;
-    const int j = static_cast<int>(tid % L);
-    const int k = kk < K ? static_cast<int>(kk) : K;
+    const int j = static_cast<int>(threadIdx.x % L);
     const int lane = threadIdx.x & (kWave - 1);
-    const bool pair_ok = k < K;
-    int a = 0, n = 0;
-    double dk = 0.0;
-    if (pair_ok) {
-        a = cp[k];
-        n = cp[k + 1] - a;
-        dk = demand[k];
+    // the lists of all pairs are asked for together, then their fractions
+    int at[U], count[U];
+    double demand_of[U], split_of[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const long long kk = (static_cast<long long>(blockIdx.x) * U + u) * (kPostBlock / L) +
+                             threadIdx.x / L;
+        const int k = kk < K ? static_cast<int>(kk) : K - 1;
+        at[u] = cp[k];
+        count[u] = kk < K ? cp[k + 1] : 0;
+        demand_of[u] = demand[k];
     }
-    const bool mine = j < n;
-    const double chi_d = static_cast<double>(chi);
-    const double whole = floor(dk / chi_d);
-    const bool small = dk <= theta;
-    const bool wide = !(whole < 2147483648.0);           // N * c_j would leave 64 bits
-    const double Nd = (small || wide) ? 0.0 : whole;
-    const double res = dk - Nd * chi_d;                  // (chi <= 2^40: the product is N * chi)
-    int c = -1, q = 0, rem = -1;                         // absent candidates rank behind all
-    if (mine) {
-        const double T = static_cast<double>(iters);
-        // floor(N * c / T): the quotient is below 2^31, so the quotient in double (N * c / T, or
-        // N * c times 1 / T, three roundings of 2^-53 each) is within one of it and one exact
-        // correction step either way settles it
-        if constexpr (NARROW) {
-            const double cd = rint(splits[a + j] * T);
-            c = static_cast<int>(cd);
-            q = static_cast<int>((Nd * cd) * (1.0 / T));
-            rem = static_cast<int>(static_cast<unsigned>(static_cast<int>(Nd)) *
-                                       static_cast<unsigned>(c) -
-                                   static_cast<unsigned>(q) * static_cast<unsigned>(iters));
-            if (rem < 0) {
-                q -= 1;
-                rem += iters;
-            } else if (rem >= iters) {
-                q += 1;
-                rem -= iters;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        count[u] -= at[u];                               // (not positive: no pair)
+        split_of[u] = splits[at[u] + (j < count[u] ? j : 0)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int a = at[u];
+        const double dk = demand_of[u], split = split_of[u];
+        const bool mine = j < count[u];
+        const double chi_d = static_cast<double>(chi);
+        // (a product with an exact reciprocal rounds like the quotient)
+        const double whole = floor(chi_is_pow2 ? dk * inv_chi : dk / chi_d);
+        const bool small = dk <= theta;
+        const bool wide = !(whole < 2147483648.0);           // N * c_j would leave 64 bits
+        const double Nd = (small || wide) ? 0.0 : whole;
+        const double res = dk - Nd * chi_d;                  // (chi <= 2^40: the product is N * chi)
+        int c = -1, q = 0, rem = -1;                         // absent candidates rank behind all
+        if (mine) {
+            const double T = static_cast<double>(iters);
+            // floor(N * c / T): the quotient is below 2^31, so the quotient in double (N * c / T, or
+            // N * c times 1 / T, three roundings of 2^-53 each) is within one of it and one exact
+            // correction step either way settles it
+            if constexpr (NARROW) {
+                const double cd = rint(splits[a + j] * T);
+                c = static_cast<int>(cd);
+                q = static_cast<int>((Nd * cd) * inv_iters);
+                rem = static_cast<int>(static_cast<unsigned>(static_cast<int>(Nd)) *
+                                           static_cast<unsigned>(c) -
+                                       static_cast<unsigned>(q) * static_cast<unsigned>(iters));
+                const int low = rem < 0 ? 1 : 0, high = rem >= iters ? 1 : 0;
+                q += high - low;
+                rem += low ? iters : high ? -iters : 0;
+            } else {
+                const long long N = static_cast<long long>(Nd);
+                const long long cl = llrint(splits[a + j] * T);
+                const long long nc = N * cl;
+                long long ql = static_cast<long long>(static_cast<double>(nc) / T);
+                long long r = nc - ql * iters;
+                if (r < 0) {
+                    ql -= 1;
+                    r += iters;
+                } else if (r >= iters) {
+                    ql += 1;
+                    r -= iters;
+                }
+                c = static_cast<int>(cl);                    // c <= iters < 2^31
+                q = static_cast<int>(ql);
+                rem = static_cast<int>(r);
             }
-        } else {
-            const long long N = static_cast<long long>(Nd);
-            const long long cl = llrint(splits[a + j] * T);
-            const long long nc = N * cl;
-            long long ql = static_cast<long long>(static_cast<double>(nc) / T);
-            long long r = nc - ql * iters;
-            if (r < 0) {
-                ql -= 1;
-                r += iters;
-            } else if (r >= iters) {
-                ql += 1;
-                r -= iters;
-            }
-            c = static_cast<int>(cl);                    // c <= iters < 2^31
-            q = static_cast<int>(ql);
-            rem = static_cast<int>(r);
         }
+        // left-over chunks of the pair: fewer than n (every quota is below 2^31, and so is the sum)
+        const int R = static_cast<int>(Nd) - group_sum_i32<L>(q);
+        // the candidate with the largest count, the lowest index among equals; then the candidates
+        // ahead of j for a left-over chunk
+        bool most;
+        int rank;
+        if constexpr (NARROW) {
+            const int claim = mine ? ((c << 6) | (63 - lane)) : -1;
+            most = group_max_i32<L>(claim) == claim;
+            const int key = mine ? ((rem << 6) | (63 - lane)) : -1;
+            if constexpr (L >= 16) rank = group_rank_narrow<L>(key);
+            else rank = group_rank<L, int>(key, lane);
+            // (wanted by some lanes only, but moved to where they alone are active the subtractions
+            // part from the moves across lanes, which have to stay here: an instruction more for each)
+            asm volatile("" : "+v"(rank));
+        } else {
+            const int c_max = group_max_i32<L>(c);
+            int j_max = (c == c_max) ? j : 0x7FFFFFFF;
+            if constexpr (L > 1) j_max = min(j_max, partner_i32<1>(j_max));
+            if constexpr (L > 2) j_max = min(j_max, partner_i32<2>(j_max));
+            if constexpr (L > 4) j_max = min(j_max, partner_i32<4>(j_max));
+            if constexpr (L > 8) j_max = min(j_max, partner_i32<8>(j_max));
+            if constexpr (L > 16) j_max = min(j_max, partner_i32<16>(j_max));
+            if constexpr (L > 32) j_max = min(j_max, partner_i32<32>(j_max));
+            most = j == j_max;
+            const long long key = mine ? ((static_cast<long long>(rem) << 6) | (63 - lane)) : -1;
+            rank = group_rank<L, long long>(key, lane);
+        }
+        if (!mine) continue;
+        double f;
+        if (small) f = (j == 0) ? dk : 0.0;                  // small message: first candidate only
+        else if (wide) f = __builtin_nan("");
+        else {
+            // (the product of two whole numbers that doubles hold is rounded once, like the conversion
+            // of the exact product)
+            f = chi_d * static_cast<double>(q + (rank < R ? 1 : 0));
+            if (most) f = f + res;
+        }
+        flows[a + j] = f;
     }
-    // left-over chunks of the pair: fewer than n (every quota is below 2^31, and so is the sum)
-    const int R = static_cast<int>(Nd) - group_sum_i32<L>(q);
-    // the candidate with the largest count, the lowest index among equals; then the candidates
-    // ahead of j for a left-over chunk
-    bool most;
-    int rank;
-    if constexpr (NARROW) {
-        const int claim = mine ? ((c << 6) | (63 - lane)) : -1;
-        most = group_max_i32<L>(claim) == claim;
-        const int key = mine ? ((rem << 6) | (63 - lane)) : -1;
-        if constexpr (L >= 16) rank = group_rank_narrow<L>(key);
-        else rank = group_rank<L, int>(key, lane);
-    } else {
-        const int c_max = group_max_i32<L>(c);
-        int j_max = (c == c_max) ? j : 0x7FFFFFFF;
-        if constexpr (L > 1) j_max = min(j_max, partner_i32<1>(j_max));
-        if constexpr (L > 2) j_max = min(j_max, partner_i32<2>(j_max));
-        if constexpr (L > 4) j_max = min(j_max, partner_i32<4>(j_max));
-        if constexpr (L > 8) j_max = min(j_max, partner_i32<8>(j_max));
-        if constexpr (L > 16) j_max = min(j_max, partner_i32<16>(j_max));
-        if constexpr (L > 32) j_max = min(j_max, partner_i32<32>(j_max));
-        most = j == j_max;
-        const long long key = mine ? ((static_cast<long long>(rem) << 6) | (63 - lane)) : -1;
-        rank = group_rank<L, long long>(key, lane);
-    }
-    if (!mine) return;
-    double f;
-    if (small) f = (j == 0) ? dk : 0.0;                  // small message: first candidate only
-    else if (wide) f = __builtin_nan("");
-    else {
-        // (the product of two whole numbers that doubles hold is rounded once, like the conversion
-        // of the exact product)
-        f = chi_d * static_cast<double>(q + (rank < R ? 1 : 0));
-        if (most) f = f + res;
-    }
-    flows[a + j] = f;
 }
 
 }  // namespace
@@ -319,17 +364,23 @@ hipError_t launch_quantize(const DeviceTopo &t, const double *demand, const doub
     if (t.pmax <= kWave) {
         const int L = lanes_per_commodity(t.pmax);
         const int64_t threads = static_cast<int64_t>(t.K) * L;
-        const int g = static_cast<int>((threads + kPostBlock - 1) / kPostBlock);
+        // (more than one pair at a time only where the lanes fill the chip's 256 compute units of 2048
+        // several times over)
+        const bool many = iters < (1 << 24) && threads >= (1 << 20);
+        const int64_t per_block = many ? kPostBlock * kPairsAtOnce : kPostBlock;
+        const int g = static_cast<int>((threads + per_block - 1) / per_block);
+        const double inv_iters = 1.0 / static_cast<double>(iters);
+        const double inv_chi = 1.0 / static_cast<double>(chi);
+        const int chi_is_pow2 = (chi & (chi - 1)) == 0 ? 1 : 0;
+#define NIMBLE_QUANT_ARGS                                                                      \
+    dim3(g), dim3(kPostBlock), 0, s, t.K, t.comm_ptr, demand, splits, iters, inv_iters,        \
+        static_cast<long long>(chi), chi_is_pow2, inv_chi, theta, flows
 #define NIMBLE_QUANT_LAUNCH(LL)                                                                \
     case LL:                                                                                   \
-        if (iters < (1 << 24))   /* counts and remainders above a 6-bit index fit 30 bits */    \
-            hipLaunchKernelGGL((k_quantize_group<LL, true>), dim3(g), dim3(kPostBlock), 0, s,  \
-                               t.K, t.comm_ptr, demand, splits, iters,                         \
-                               static_cast<long long>(chi), theta, flows);                     \
-        else                                                                                   \
-            hipLaunchKernelGGL((k_quantize_group<LL, false>), dim3(g), dim3(kPostBlock), 0, s, \
-                               t.K, t.comm_ptr, demand, splits, iters,                         \
-                               static_cast<long long>(chi), theta, flows);                     \
+        if (many) hipLaunchKernelGGL((k_quantize_group<LL, true, kPairsAtOnce>), NIMBLE_QUANT_ARGS); \
+        else if (iters < (1 << 24))   /* counts and remainders above a 6-bit index fit 30 bits */ \
+            hipLaunchKernelGGL((k_quantize_group<LL, true, 1>), NIMBLE_QUANT_ARGS);            \
+        else hipLaunchKernelGGL((k_quantize_group<LL, false, 1>), NIMBLE_QUANT_ARGS);          \
         return hipGetLastError();
         switch (L) {
             NIMBLE_QUANT_LAUNCH(1)
@@ -341,6 +392,7 @@ hipError_t launch_quantize(const DeviceTopo &t, const double *demand, const doub
             NIMBLE_QUANT_LAUNCH(64)
         }
 #undef NIMBLE_QUANT_LAUNCH
+#undef NIMBLE_QUANT_ARGS
     }
     const int grid = (t.K + kPostBlock - 1) / kPostBlock;
     hipLaunchKernelGGL(k_quantize, dim3(grid), dim3(kPostBlock), 0, s, t.K, t.comm_ptr, demand,

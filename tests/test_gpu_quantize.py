@@ -139,3 +139,19 @@ def test_too_many_chunks_is_flagged_and_bad_arguments_are_refused(B):
             assert ei.value.status == B.NIMBLE_ERR_INVALID
     finally:
         h.close()
+
+
+def test_more_pairs_than_the_chip_holds_at_once(oracle_mod, B):
+    """From 2^20 lanes on a group of lanes takes two pairs; an odd number of blocks' worth of them."""
+    gpus = 8
+    t = W.build_fabric(23, gpus, gpus, W.xor_access(gpus))
+    rng = np.random.default_rng(23)
+    iters = 977
+    cp = t.comm_path_ptr
+    c = rng.integers(0, iters // 64, t.n_paths)
+    c[cp[:-1]] = 0
+    c[cp[:-1]] = iters - np.add.reduceat(c, cp[:-1])
+    d = np.floor(rng.pareto(1.1, t.n_comm) * 1e7)
+    for chi in (1 << 20, 1000):
+        ref = oracle_mod.quantize(cp, d, c / iters, iters, chi, 1e5)
+        assert np.array_equal(gpu_quantize(B, t, d, c / iters, iters, chi, 1e5), ref), chi
