@@ -21,7 +21,7 @@ namespace nimble {
 namespace {
 
 constexpr int kPostBlock = 256;
-constexpr int kPairsAtOnce = 2;          // of a group of lanes, where there are many pairs
+constexpr int kPairsAtOnce = 4;          // of a group of lanes, where there are many pairs
 
 __global__ __launch_bounds__(kPostBlock) void k_quantize(int K, const int32_t *__restrict__ cp,
                                                          const double *__restrict__ demand,
@@ -232,12 +232,13 @@ __device__ __forceinline__ int group_rank_narrow(int key)
 // L lanes per pair (L a power of two, every pair has at most L candidates); the lanes of a
 // group take the same branches, so the cross-lane steps are reached by whole groups.
 // The two trips to memory a wave makes one after the other (list, then fractions) bound it: a group
-// takes U pairs, whose lists are asked for together.  NARROW (iters < 2^24) keeps all whole numbers but
+// takes U pairs, whose lists and fractions are asked for together.  NARROW (iters < 2^24) keeps all whole numbers but
 // the flows in 32 bits: remainders are below iters, so the low halves of N * c and q * iters give them,
 // and the product with 1 / iters is as good for the quotient as the division.  Measured on 261 632
 // pairs of 32 candidates: 59.0 us with 64-bit whole numbers throughout, 49.6 us (2.8 TB/s) in 32 bits,
 // 52.0 us with a third fewer instructions (reciprocals passed in, subtractions in the moves across
-// lanes), 43.7 us with those and two pairs at a time.
+// lanes), 43.7 us with those and two pairs at a time, 36.2 us (3.8 TB/s) with four whose fractions are
+// asked for together too.
 template <int L, bool NARROW, int U>
 __global__ __launch_bounds__(kPostBlock) void k_quantize_group(int K,
                                                                const int32_t *__restrict__ cp,
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(kPostBlock) void k_quantize_group(int K,
             // N * c times 1 / T, three roundings of 2^-53 each) is within one of it and one exact
             // correction step either way settles it
             if constexpr (NARROW) {
-                const double cd = rint(splits[a + j] * T);
+                const double cd = rint(split * T);
                 c = static_cast<int>(cd);
                 q = static_cast<int>((Nd * cd) * inv_iters);
                 rem = static_cast<int>(static_cast<unsigned>(static_cast<int>(Nd)) *
@@ -297,7 +298,7 @@ __global__ __launch_bounds__(kPostBlock) void k_quantize_group(int K,
                 rem += low ? iters : high ? -iters : 0;
             } else {
                 const long long N = static_cast<long long>(Nd);
-                const long long cl = llrint(splits[a + j] * T);
+                const long long cl = llrint(split * T);
                 const long long nc = N * cl;
                 long long ql = static_cast<long long>(static_cast<double>(nc) / T);
                 long long r = nc - ql * iters;

@@ -142,7 +142,7 @@ def test_too_many_chunks_is_flagged_and_bad_arguments_are_refused(B):
 
 
 def test_more_pairs_than_the_chip_holds_at_once(oracle_mod, B):
-    """From 2^20 lanes on a group of lanes takes two pairs; an odd number of blocks' worth of them."""
+    """From 2^20 lanes on a group of lanes takes four pairs; the last block has fewer."""
     gpus = 8
     t = W.build_fabric(23, gpus, gpus, W.xor_access(gpus))
     rng = np.random.default_rng(23)
