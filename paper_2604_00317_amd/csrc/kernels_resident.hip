@@ -509,7 +509,9 @@ struct RegShared {
 // the minimum carries the winner's links and its place up the tree, so nothing is looked up after it.
 // What bounds it: one plan, the chain price reads -> sums -> tree -> atomics -> load -> price of one
 // wave; 4096 plans (four waves per SIMD), vector issue and the LDS about equally.  One node of 8 GPUs,
-// 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).
+// 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).  What
+// stays with the gather pays for the choice between them: 81.4 us as the only way, 83.3 with a count in
+// LDS per iteration and its pairs read one by one, 76.9 as it is (9 GPUs, 512 plans: 145.0, 158.0, 148.8).
 template <bool MAXC, bool ONEWAVE, int MAXP, bool DIRECT, int MAXROW>
 __global__ __launch_bounds__(1024) void k_resident_reg(
     int E, int K, int P, int batch, int nt_arg, int plans_per_block, double eps, int iters,
@@ -706,7 +708,10 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
         }
     } else {
         // for every reverse pair of the link where the commodity's choice lives, the candidates
-        // that use the link (8-bit masks, four to a register), and the demand they add
+        // that use the link (8-bit masks, four to a register), and the demand they add; eight
+        // pairs are asked for together
+        constexpr int kRows = 8;
+        static_assert(MAXROW % kRows == 0, "whole requests");
         const uint8_t *cptr[MAXROW];
         uint32_t wb4[MAXROW / 4];
         double dm[MAXROW];
@@ -716,15 +721,40 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
         for (int i = 0; i < MAXROW; ++i) {
             cptr[i] = choice + K;                  // padding: the spare choice, empty mask
             dm[i] = 0.0;
-            if (i < rn) {
-                const uint32_t k = g_rev[2 * (r0 + i)] & kCommMask;
-                if (k < static_cast<uint32_t>(K)) {
-                    cptr[i] = choice + k;
-                    wb4[i / 4] |= (g_rev[2 * (r0 + i) + 1] & 0xFFu) << (8 * (i % 4));
-                    dm[i] = d_in[k];
-                }
+        }
+#pragma unroll
+        for (int i0 = 0; i0 < MAXROW; i0 += kRows) {
+            if (i0 >= rn) continue;
+            uint32_t k[kRows], wb[kRows];
+            double dk[kRows];
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+                const int r = 2 * (r0 + (i0 + q < rn ? i0 + q : i0));
+                k[q] = g_rev[r] & kCommMask;
+                wb[q] = g_rev[r + 1];
+            }
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+                if (i0 + q >= rn || k[q] >= static_cast<uint32_t>(K)) k[q] = K;
+                dk[q] = d_in[k[q] < static_cast<uint32_t>(K) ? k[q] : 0u];
+            }
+#pragma unroll
+            for (int q = 0; q < kRows; ++q) {
+                const bool there = k[q] < static_cast<uint32_t>(K);
+                cptr[i0 + q] = choice + k[q];
+                wb4[(i0 + q) / 4] |= (there ? wb[q] & 0xFFu : 0u) << (8 * ((i0 + q) % 4));
+                dm[i0 + q] = there ? dk[q] : 0.0;
             }
         }
+        // eight 8-bit counters in one 64-bit word, emptied into the LDS counts before any can
+        // wrap: a count in LDS on every iteration is a read, a wait and a write in the chain
+        unsigned long long tally = 0ull;
+        auto flush = [&] {
+#pragma unroll
+            for (int j = 0; j < MAXP; ++j)
+                count[j * nt] += static_cast<uint32_t>(tally >> (8 * j)) & 0xFFu;
+            tally = 0ull;
+        };
         for (int it = 0; it < iters; ++it) {
             if (has_k) {
                 double c[MAXP];
@@ -736,7 +766,8 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
 #pragma unroll
                 for (int j = MAXP - 2; j >= 0; --j) bj = (c[j] == best) ? j : bj;
                 choice[t] = static_cast<uint8_t>(bj);
-                count[bj * nt] += 1u;
+                tally += 1ull << (8 * bj);
+                if ((it & 127) == 127) flush();
             }
             plan_sync();
             if (has_e) {
@@ -757,6 +788,7 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
             }
             plan_sync();
         }
+        if (has_k) flush();
     }
 
     const double T = static_cast<double>(iters);

@@ -78,3 +78,24 @@ def test_scatter_and_gather_are_the_oracles_bits(oracle_mod, B, fabric, flags):
             assert np.array_equal(s, r["splits"]) and l == r["lam"], KINDS[i]
     finally:
         h.close()
+
+
+@pytest.mark.parametrize("iters", [127, 128, 129, 255, 256, 600])
+def test_gathered_plans_count_every_iteration(oracle_mod, B, iters):
+    """The gather counts choices eight bits at a time: either side of every emptying, and a commodity
+    that takes the same candidate on all iterations (a direct link costs half of a detour)."""
+    t = W.build_fabric(1, 9)
+    rng = np.random.default_rng(iters)
+    d = np.stack([demands_of("fractional", t.n_comm, rng) for _ in range(3)])
+    d[1, 1:] = 0.0
+    d[2] = 1.0 / 3.0
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        splits, lam = B.plan(h, d, 1e-6, iters)        # tiny steps: choices stay for many iterations
+        for i in range(3):
+            r = oracle_mod.solve(*t.csr(), d[i], 1e-6, iters)
+            assert np.array_equal(splits[i], r["splits"]) and lam[i] == r["lam"], i
+            sums = np.add.reduceat(splits[i], t.comm_path_ptr[:-1])
+            assert np.allclose(sums, 1.0, rtol=0, atol=1e-12)
+    finally:
+        h.close()
