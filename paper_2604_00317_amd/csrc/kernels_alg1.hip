@@ -134,11 +134,15 @@ __global__ __launch_bounds__(kAlg1Threads) void k_alg1(int E, int K, int P, int 
 // before use them.  That leaves decision -> compare -> minimum -> decision, without a trip to LDS;
 // the wave's own instructions (about fifty a pair) then bound it.  Chunks are added by LDS atomics that
 // return nothing (they round like an addition, denormals included); the lanes that do not take the
-// pair add to a spare place.  Longer paths read the loads when they are needed; their links come from
-// memory, asked for ahead in stages.
+// pair add to a spare place.  The other forms read the loads when they are needed and pass over pairs
+// that have nothing left in any problem of the wave (a problem routes most of its pairs in its first
+// sweeps, so one problem on its own skips more than eight that share a wave).  TABLE: the links of all
+// candidates lie in LDS; without it they come from memory, asked for ahead in stages.
 // 4096 problems of one node of 8 GPUs (56 pairs, 10 sweeps at most): 222 -> 102 us
 // (one problem 200 -> 86; 7.5 us a sweep).  512 problems of two nodes of 8 (240 pairs of up to 16
-// candidates, on a thread per problem until their lists left the LDS): 12.4 -> 1.24 ms.
+// candidates, a thread per problem where their lists do not fit the LDS): 8.2 -> 0.79 ms.  Two nodes of
+// 4 GPUs (56 pairs, up to 5 links): one problem 176 us with a table but without passing over, 207
+// without either, 110 with both; 4096 problems 233, 209, 173.
 constexpr int kAheadSteps = 2, kAheadLanes = 16;
 constexpr int kAheadPairs = 4;           // steps of the unrolled loop; pairs are padded to them
 
@@ -153,7 +157,11 @@ struct Alg1Lds {
     size_t ic, problem, per_problem, spare, cp, tab, bytes;
 };
 
-__host__ __device__ inline Alg1Lds alg1_lds(int E, int K, int P, int lanes, bool ahead)
+// link numbers per candidate in the table of the form that is not AHEAD
+__host__ __device__ constexpr int alg1_table_steps(int lm) { return lm <= 2 ? 2 : 8; }
+
+// `steps`: alg1_table_steps where the form that is not AHEAD has its table, 0 otherwise
+__host__ __device__ inline Alg1Lds alg1_lds(int E, int K, int P, int lanes, bool ahead, int steps)
 {
     Alg1Lds l;
     const int pairs = (K + kAheadPairs - 1) / kAheadPairs * kAheadPairs;
@@ -164,7 +172,8 @@ __host__ __device__ inline Alg1Lds alg1_lds(int E, int K, int P, int lanes, bool
     l.problem = o;  o += l.per_problem * (kWave / lanes);
     l.spare = o;    o += sizeof(double) * kWave;         // a place per lane for what is not wanted
     o = (o + 15) & ~size_t(15);
-    l.tab = o;      o += ahead ? sizeof(Alg1Entry) * (static_cast<size_t>(pairs) + 2) * lanes : 0;
+    l.tab = o;      o += ahead ? sizeof(Alg1Entry) * (static_cast<size_t>(pairs) + 2) * lanes
+                               : sizeof(uint16_t) * static_cast<size_t>(K) * lanes * steps;
     l.cp = o;       o += sizeof(int32_t) * (K + 1);
     l.bytes = o;
     return l;
@@ -178,7 +187,7 @@ __device__ __forceinline__ double max_f64(double a, double b)
     return r;
 }
 
-template <int G, int LM, bool AHEAD>
+template <int G, int LM, bool AHEAD, bool TABLE>
 __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int batch,
                                                       const int32_t *__restrict__ cp,
                                                       const int32_t *__restrict__ lp,
@@ -193,7 +202,8 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
     static_assert(!AHEAD || (LM == kAheadSteps && G <= kAheadLanes), "masks of 16 bits");
     extern __shared__ __align__(16) unsigned char s_alg1[];
     constexpr int kPerBlock = kWave / G;                      // problems of this wave
-    const Alg1Lds l = alg1_lds(E, K, P, G, AHEAD);
+    constexpr int kSteps = TABLE ? alg1_table_steps(LM) : 0;
+    const Alg1Lds l = alg1_lds(E, K, P, G, AHEAD, kSteps);
     const int lane = threadIdx.x;
     const int j = lane % G;
     const int slot = lane / G;
@@ -205,6 +215,7 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
     double *r = L + (E + 2), *amount = r + pairs, *fl = amount + (pairs + 1);
     double *spare = reinterpret_cast<double *>(s_alg1 + l.spare) + lane;
     Alg1Entry *s_tab = reinterpret_cast<Alg1Entry *>(s_alg1 + l.tab);   // [pairs + 2][G]
+    uint16_t *s_links = reinterpret_cast<uint16_t *>(s_alg1 + l.tab);   // [K][G][kSteps]
     int32_t *s_cp = reinterpret_cast<int32_t *>(s_alg1 + l.cp);
     for (int e = lane; e < E; e += kWave) s_ic[e] = invcap[e];
     for (int k = lane; k <= K; k += kWave) s_cp[k] = cp[k];
@@ -282,6 +293,20 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
         }
         __syncthreads();
     }
+    if constexpr (TABLE) {
+        for (int idx = lane; idx < K * G; idx += kWave) {
+            const int k = idx / G;
+            int p = s_cp[k] + idx % G;
+            const bool there = p < s_cp[k + 1];
+            p = there ? p : 0;
+            const int la = lp[p], n = there ? lp[p + 1] - la : 0;
+#pragma unroll
+            for (int i = 0; i < LM; ++i)
+                s_links[idx * kSteps + i] =
+                    static_cast<uint16_t>(i < n ? pl[la + i] : i == 0 ? E + 1 : E);
+        }
+        __syncthreads();
+    }
     // lanes of this problem inside the wave
     const unsigned long long gmask = (G == 64 ? ~0ull : ((1ull << (G & 63)) - 1ull)) << (lane - j);
     // the one lane of the group that takes the pair, of those whose cost is the least
@@ -319,11 +344,28 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
         p_list = s_cp[k] + j;
         const bool there = p_list < s_cp[k + 1];
         p_list = there ? p_list : 0;
-        la = lp[p_list];
-        lb = lp[p_list + 1];
-        lb = there ? lb : la;
+        if constexpr (!TABLE) {
+            la = lp[p_list];
+            lb = lp[p_list + 1];
+            lb = there ? lb : la;
+        }
     };
     auto ask_links = [&](int (&e)[LM]) {
+        if constexpr (TABLE) {
+            const uint16_t *from = s_links + (k_list * G + j) * kSteps;
+            if constexpr (kSteps == 2) {
+                const uint32_t w = *reinterpret_cast<const uint32_t *>(from);
+                e[0] = static_cast<int>(w & 0xFFFFu);
+                e[1] = static_cast<int>(w >> 16);
+            } else {
+                const uint4 w = *reinterpret_cast<const uint4 *>(from);
+                const uint32_t of[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int i = 0; i < LM; ++i)
+                    e[i] = static_cast<int>(i % 2 ? of[i / 2] >> 16 : of[i / 2] & 0xFFFFu);
+            }
+            return;
+        }
         const int n = lb - la;
 #pragma unroll
         for (int i = 0; i < LM; ++i) {
@@ -337,7 +379,8 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
         ask_links(e_now);
 #pragma unroll
         for (int i = 0; i < LM; ++i) ic_now[i] = s_ic[e_now[i]];
-        ask_list(after(0));
+        k_list = after(0);
+        ask_list(k_list);
         p_next = p_list;
         ask_links(e_next);
         k_list = after(after(0));
@@ -437,15 +480,18 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
                 ask_links(e_after);
                 k_list = after(k_list);
                 ask_list(k_list);
-                double c = Lv[0] * ic_now[0];
+                // (late in a solve most pairs have nothing left in any problem of the wave)
+                if (__builtin_amdgcn_ballot_w64(f > 0.0) != 0ull) {
+                    double c = Lv[0] * ic_now[0];
 #pragma unroll
-                for (int i = 1; i < LM; ++i) c = max_f64(c, Lv[i] * ic_now[i]);
-                uint32_t low;
-                if (takes(c, least(c), low)) {
-                    fl[p_now] = flow_now + f;
+                    for (int i = 1; i < LM; ++i) c = max_f64(c, Lv[i] * ic_now[i]);
+                    uint32_t low;
+                    if (takes(c, least(c), low)) {
+                        fl[p_now] = flow_now + f;
 #pragma unroll
-                    for (int i = 0; i < LM; ++i)
-                        if (e_now[i] < E) L[e_now[i]] = Lv[i] + f;
+                        for (int i = 0; i < LM; ++i)
+                            if (e_now[i] < E) L[e_now[i]] = Lv[i] + f;
+                    }
                 }
 #pragma unroll
                 for (int i = 0; i < LM; ++i) {
@@ -502,26 +548,9 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
     }
 }
 
-// lanes per problem of k_alg1_group, or 0 if the topology does not fit it
-int alg1_group_lanes(const DeviceTopo &t, bool &ahead, size_t &lds)
-{
-    if (t.alg1_thread_per_problem || t.pmax > kWave || t.pmax < 1 || t.lmax > 8 || t.K < 1)
-        return 0;
-    // (more lanes than candidates where only fewer problems fit the LDS together)
-    for (int G = lanes_per_commodity(t.pmax); G <= kWave; G *= 2) {
-        ahead = t.lmax <= kAheadSteps && G <= kAheadLanes && 8 * (t.E + 1) <= 0xFFFF;
-        lds = alg1_lds(t.E, t.K, t.P, G, ahead).bytes;
-        if (ahead && lds > kAlg1LdsBudget) {
-            ahead = false;
-            lds = alg1_lds(t.E, t.K, t.P, G, ahead).bytes;
-        }
-        if (lds <= kAlg1LdsBudget) return G;
-    }
-    return 0;
-}
-
 // What is accepted: topologies whose state fits 64 KB with a group of lanes per problem and the
 // candidate lists beside it (2 or 8 links each), or a workgroup of the kernel with a thread per problem.
+// The former are also those whose lists are kept in LDS.
 bool alg1_small(const DeviceTopo &t)
 {
     if (t.pmax > kWave || t.pmax < 1 || t.lmax > 8 || t.K < 1) return false;
@@ -531,6 +560,32 @@ bool alg1_small(const DeviceTopo &t)
                sizeof(int32_t) * (t.K + 1) +
                sizeof(int32_t) * static_cast<size_t>(t.K) * G * (t.lmax <= 2 ? 2 : 8) <=
            kAlg1LdsPlain;
+}
+
+// the form of k_alg1_group for a topology; lanes: of a problem, 0 if the topology does not fit it
+struct Alg1Group {
+    int lanes;
+    bool ahead, table;
+    size_t lds;
+};
+Alg1Group alg1_group(const DeviceTopo &t)
+{
+    if (t.alg1_thread_per_problem || t.pmax > kWave || t.pmax < 1 || t.lmax > 8 || t.K < 1)
+        return {};
+    // (more lanes than candidates where only fewer problems fit the LDS together)
+    for (int G = lanes_per_commodity(t.pmax); G <= kWave; G *= 2) {
+        const Alg1Group forms[] = {
+            {G, true, false, alg1_lds(t.E, t.K, t.P, G, true, 0).bytes},
+            {G, false, true, alg1_lds(t.E, t.K, t.P, G, false, alg1_table_steps(t.lmax)).bytes},
+            {G, false, false, alg1_lds(t.E, t.K, t.P, G, false, 0).bytes}};
+        for (const Alg1Group &g : forms) {
+            if (g.ahead && !(t.lmax <= kAheadSteps && G <= kAheadLanes && 8 * (t.E + 1) <= 0xFFFF))
+                continue;
+            if (g.table && !alg1_small(t)) continue;
+            if (g.lds <= kAlg1LdsBudget) return g;
+        }
+    }
+    return {};
 }
 
 }  // namespace
@@ -558,9 +613,9 @@ hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand,
                        double chi, int32_t max_sweeps, double *flows, double *lambda,
                        int32_t *sweeps, hipStream_t s)
 {
-    size_t glds = 0;
-    bool ahead = false;
-    int G = alg1_group_lanes(t, ahead, glds);
+    const Alg1Group group = alg1_group(t);
+    int G = group.lanes;
+    const size_t glds = group.lds;
     if (G > 0 && !alg1_small(t)) {
         // A pair takes the group 0.55 us whatever its candidates, a thread about 0.065 us per link of
         // them (two nodes of 8, 16 or 32 candidates of up to five links: 0.53 against 5.2, 0.56 against
@@ -574,43 +629,44 @@ hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand,
     if (G > 0) {
         const int per_block = kWave / G;
         const int ggrid = (batch + per_block - 1) / per_block;
-#define NIMBLE_ALG1_LAUNCH(GG, LM, AHEAD)                                                      \
+#define NIMBLE_ALG1_LAUNCH(GG, LM, AHEAD, TABLE)                                               \
     do {                                                                                       \
         if (glds > kAlg1LdsPlain) {                                                            \
             const hipError_t ea = hipFuncSetAttribute(                                         \
-                reinterpret_cast<const void *>(&k_alg1_group<GG, LM, AHEAD>),                  \
+                reinterpret_cast<const void *>(&k_alg1_group<GG, LM, AHEAD, TABLE>),           \
                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kAlg1LdsBudget)); \
             if (ea != hipSuccess) return ea;                                                   \
         }                                                                                      \
-        hipLaunchKernelGGL((k_alg1_group<GG, LM, AHEAD>), dim3(ggrid), dim3(kWave), glds, s,   \
-                           t.E, t.K, t.P, batch, t.comm_ptr, t.path_ptr, t.path_links,         \
-                           t.invcap, demand, phi, chi, max_sweeps, flows, lambda, sweeps);     \
+        hipLaunchKernelGGL((k_alg1_group<GG, LM, AHEAD, TABLE>), dim3(ggrid), dim3(kWave),     \
+                           glds, s, t.E, t.K, t.P, batch, t.comm_ptr, t.path_ptr,              \
+                           t.path_links, t.invcap, demand, phi, chi, max_sweeps, flows,        \
+                           lambda, sweeps);                                                    \
         return hipGetLastError();                                                              \
     } while (0)
-#define NIMBLE_ALG1_LONG(GG)                                                                   \
+#define NIMBLE_ALG1_FORM(GG, LM)                                                               \
+    if (t.lmax <= LM) {                                                                        \
+        if (group.table) NIMBLE_ALG1_LAUNCH(GG, LM, false, true);                              \
+        NIMBLE_ALG1_LAUNCH(GG, LM, false, false);                                              \
+    }
+#define NIMBLE_ALG1_LANES(GG)                                                                  \
     case GG:                                                                                   \
-        if (t.lmax <= 5) NIMBLE_ALG1_LAUNCH(GG, 5, false);                                     \
-        NIMBLE_ALG1_LAUNCH(GG, 8, false)
-#define NIMBLE_ALG1_AHEAD(GG)                                                                  \
-    case GG: NIMBLE_ALG1_LAUNCH(GG, kAheadSteps, true)
-        if (ahead) switch (G) {
-            NIMBLE_ALG1_AHEAD(1);
-            NIMBLE_ALG1_AHEAD(2);
-            NIMBLE_ALG1_AHEAD(4);
-            NIMBLE_ALG1_AHEAD(8);
-            NIMBLE_ALG1_AHEAD(16);
-        }
+        if constexpr (GG <= kAheadLanes)                                                       \
+            if (group.ahead) NIMBLE_ALG1_LAUNCH(GG, kAheadSteps, true, false);                 \
+        NIMBLE_ALG1_FORM(GG, 2)                                                                \
+        NIMBLE_ALG1_FORM(GG, 5)                                                                \
+        NIMBLE_ALG1_FORM(GG, 8)                                                                \
+        break;
         switch (G) {
-            NIMBLE_ALG1_LONG(1);
-            NIMBLE_ALG1_LONG(2);
-            NIMBLE_ALG1_LONG(4);
-            NIMBLE_ALG1_LONG(8);
-            NIMBLE_ALG1_LONG(16);
-            NIMBLE_ALG1_LONG(32);
-            NIMBLE_ALG1_LONG(64);
+            NIMBLE_ALG1_LANES(1)
+            NIMBLE_ALG1_LANES(2)
+            NIMBLE_ALG1_LANES(4)
+            NIMBLE_ALG1_LANES(8)
+            NIMBLE_ALG1_LANES(16)
+            NIMBLE_ALG1_LANES(32)
+            NIMBLE_ALG1_LANES(64)
         }
-#undef NIMBLE_ALG1_AHEAD
-#undef NIMBLE_ALG1_LONG
+#undef NIMBLE_ALG1_LANES
+#undef NIMBLE_ALG1_FORM
 #undef NIMBLE_ALG1_LAUNCH
     }
     const size_t lds = alg1_lds_bytes(t);

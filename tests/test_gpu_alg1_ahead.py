@@ -60,6 +60,51 @@ def test_two_nodes(oracle_mod, B, gpus, rails):
     check(oracle_mod, B, t, d, 0.5, float(1 << 20))
 
 
+def fabric(what):
+    if isinstance(what, str):
+        nodes, gpus, rails = what.split()
+        nodes, gpus = int(nodes), int(gpus)
+        if rails == "none":
+            return W.build_fabric(nodes, gpus)
+        access = W.xor_access(gpus) if rails == "xor" else [[r] for r in range(gpus)]
+        return W.build_fabric(nodes, gpus, gpus, access)
+    return W.random_topology(np.random.default_rng(5), *what)
+
+
+# every kind of group, at 2, 5 and 8 links of a path and up to 64 candidates; one problem, whose finished
+# pairs are passed over, and problems that share waves
+FORMS = [
+    ("1 4 none", 21), ("1 10 none", 21), ("1 12 none", 21), ("1 13 none", 21), ("1 16 none", 21),
+    ("2 4 own", 1), ("2 4 own", 21), ("2 4 xor", 21), ("3 4 own", 21),
+    ((100, 30, 33, 2), 21), ((200, 60, 8, 8), 21), ((60, 200, 4, 8), 21), ((30, 50, 33, 8), 21),
+    ((30, 20, 64, 5), 21), ((60, 200, 2, 2), 21), ((60, 400, 1, 2), 21), ((20, 60, 4, 5), 21),
+]
+
+
+@pytest.mark.parametrize("what,batch", FORMS, ids=str)
+def test_every_form_is_the_oracles_bits(oracle_mod, B, what, batch):
+    t = fabric(what)
+    rng = np.random.default_rng(batch)
+    n = min(batch, 21)
+    d = np.minimum(np.floor(rng.pareto(1.1, (n, t.n_comm)) * 1e6), 2e7)
+    d[-1] = d[-1] / 7.0
+    if n > 3:
+        d[1] = 0.0                               # nothing to do beside problems that have
+        d[2, ::2] = 0.0
+        d[3] = np.where(np.arange(t.n_comm) == t.n_comm // 2, 1e8, 0.0)   # one pair, many sweeps
+    rows = np.arange(batch) % n
+    print(f"[alg1] {what} x {batch}", flush=True)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        flows, lam, sweeps = B.plan_alg1(h, d[rows], 0.5, float(1 << 20))
+    finally:
+        h.close()
+    for i in range(n):
+        ref = oracle_mod.alg1(*t.csr(), d[i], 0.5, float(1 << 20))
+        assert (flows[rows == i] == ref["flows"]).all(), f"problem {i}"
+        assert (lam[rows == i] == ref["lam"]).all() and (sweeps[rows == i] == ref["sweeps"]).all()
+
+
 def test_topologies_beyond_the_limits_are_refused(B):
     t = W.random_topology(np.random.default_rng(1), 8000, 10, 2, 2)
     h = B.nimble_topo_create(*t.csr())
