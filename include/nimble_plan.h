@@ -190,9 +190,10 @@ nimble_status_t nimble_plan_solve_batch(nimble_topo_t *topo, int32_t batch,
  * lowest bottleneck cost max_e F(L_e) (strict `<` in candidate order), routes f = r if r < chi,
  * else the largest multiple of chi that is <= r * phi (one chunk when that is 0), and adds f to
  * the loads of that candidate's links at once (the next pair sees it).  F(L_e) = L_e / cap_e.
- * A group of lanes (one per candidate of the current pair) runs one problem; topologies with
- * more than 64 candidates per pair, paths of more than 8 links, or tables beyond 64 KB of LDS
- * run one thread per problem.
+ * A group of lanes (one or more per candidate of the current pair) runs one problem; topologies with
+ * more than 64 candidates per pair, paths of more than 8 links or more per-problem state than a group
+ * finds LDS for, and batches that fill the GPU several times over with groups, run one thread per
+ * problem.
  *
  *   d_traffic   device [batch][n_comm], bytes >= 0
  *   phi         routed fraction of the remainder per visit, 0 < phi <= 1

@@ -32,6 +32,12 @@ int32_t nimble_topo_adaptive_folds(const nimble_topo_t *topo);
  * in LDS; -1 for a NULL handle.  Both kernels return the same bits. */
 int32_t nimble_topo_resident_in_registers(const nimble_topo_t *topo);
 
+/* The kernel nimble_alg1_solve_batch would run for a batch of this size: 0 for a thread per problem,
+ * else 100 x kind + lanes per problem, with kind 1 for loads read a pair ahead, 2 for candidate lists in
+ * LDS, 3 for candidate lists from memory; -1 for a NULL handle, batch < 1 or a topology it refuses.  All
+ * of them return the same bits. */
+int32_t nimble_topo_alg1_form(const nimble_topo_t *topo, int32_t batch);
+
 /*
  * Benchmark helper: enqueue `reps` back-to-back launches of one phase of the streaming regime
  * on `hip_stream`, without changing the plan state another solve depends on

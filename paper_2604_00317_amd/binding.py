@@ -39,7 +39,7 @@ EXPORTS = [
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
     "nimble_host_patch_check", "nimble_debug_patches_gave_up",
     "nimble_debug_refuse_cooperative", "nimble_debug_fail_patch_build",
-    "nimble_topo_last_patches",
+    "nimble_topo_last_patches", "nimble_topo_alg1_form",
 ]
 
 _lib = None
@@ -113,6 +113,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.nimble_debug_live_allocations.argtypes = []
     lib.nimble_debug_stream_read.restype = ctypes.c_int
     lib.nimble_debug_stream_read.argtypes = [vp, i64, i32, vp, vp]
+    lib.nimble_topo_alg1_form.restype = i32
+    lib.nimble_topo_alg1_form.argtypes = [vp, i32]
     lib.nimble_topo_last_patches.restype = i32
     lib.nimble_topo_last_patches.argtypes = [vp]
     lib.nimble_debug_fail_patch_build.restype = None
@@ -215,6 +217,9 @@ class Topo:
     @property
     def last_patches(self) -> int:
         return load_library().nimble_topo_last_patches(self.handle)
+
+    def alg1_form(self, batch: int) -> int:
+        return load_library().nimble_topo_alg1_form(self.handle, batch)
 
     @property
     def adaptive_folds(self) -> bool:

@@ -1005,6 +1005,13 @@ int32_t nimble_topo_resident_in_registers(const nimble_topo_t *t)
     return t ? (nimble::resident_in_registers(t->d) ? 1 : 0) : -1;
 }
 
+int32_t nimble_topo_alg1_form(const nimble_topo_t *topo, int32_t batch)
+{
+    if (!topo || batch < 1 || !nimble::alg1_fits(topo->d)) return -1;
+    const nimble::Alg1Form f = nimble::alg1_form(topo->d, batch);
+    return f.lanes == 0 ? 0 : 100 * (f.ahead ? 1 : f.table ? 2 : 3) + f.lanes;
+}
+
 int64_t nimble_topo_phase_bytes(const nimble_topo_t *t, int32_t phase)
 {
     if (!t) return -1;

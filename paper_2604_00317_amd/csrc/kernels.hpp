@@ -331,6 +331,13 @@ hipError_t launch_ad_histogram(const DeviceTopo &t, const AdaptiveState &a, cons
 // the LDS of a compute unit.
 size_t alg1_lds_bytes(const DeviceTopo &t);
 bool alg1_fits(const DeviceTopo &t);
+// the kernel of Algorithm 1 for a batch: lanes per problem (0: the kernel with a thread per problem)
+struct Alg1Form {
+    int lanes;
+    bool ahead, table;
+    size_t lds;                // bytes of a workgroup
+};
+Alg1Form alg1_form(const DeviceTopo &t, int32_t batch);
 // lambda[b] is NaN when problem b still had traffic left after max_sweeps sweeps.
 hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand, double phi,
                        double chi, int32_t max_sweeps, double *flows, double *lambda,

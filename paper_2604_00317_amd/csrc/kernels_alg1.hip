@@ -170,7 +170,7 @@ __host__ __device__ inline Alg1Lds alg1_lds(int E, int K, int P, int lanes, bool
     l.per_problem = sizeof(double) * (static_cast<size_t>(E) + 3 + 2 * static_cast<size_t>(pairs) +
                                       (ahead ? static_cast<size_t>(pairs) * lanes : P));
     l.problem = o;  o += l.per_problem * (kWave / lanes);
-    l.spare = o;    o += sizeof(double) * kWave;         // a place per lane for what is not wanted
+    l.spare = o;    o += ahead ? sizeof(double) * kWave : 0;    // a place per lane for what is not wanted
     o = (o + 15) & ~size_t(15);
     l.tab = o;      o += ahead ? sizeof(Alg1Entry) * (static_cast<size_t>(pairs) + 2) * lanes
                                : sizeof(uint16_t) * static_cast<size_t>(K) * lanes * steps;
@@ -562,32 +562,6 @@ bool alg1_small(const DeviceTopo &t)
            kAlg1LdsPlain;
 }
 
-// the form of k_alg1_group for a topology; lanes: of a problem, 0 if the topology does not fit it
-struct Alg1Group {
-    int lanes;
-    bool ahead, table;
-    size_t lds;
-};
-Alg1Group alg1_group(const DeviceTopo &t)
-{
-    if (t.alg1_thread_per_problem || t.pmax > kWave || t.pmax < 1 || t.lmax > 8 || t.K < 1)
-        return {};
-    // (more lanes than candidates where only fewer problems fit the LDS together)
-    for (int G = lanes_per_commodity(t.pmax); G <= kWave; G *= 2) {
-        const Alg1Group forms[] = {
-            {G, true, false, alg1_lds(t.E, t.K, t.P, G, true, 0).bytes},
-            {G, false, true, alg1_lds(t.E, t.K, t.P, G, false, alg1_table_steps(t.lmax)).bytes},
-            {G, false, false, alg1_lds(t.E, t.K, t.P, G, false, 0).bytes}};
-        for (const Alg1Group &g : forms) {
-            if (g.ahead && !(t.lmax <= kAheadSteps && G <= kAheadLanes && 8 * (t.E + 1) <= 0xFFFF))
-                continue;
-            if (g.table && !alg1_small(t)) continue;
-            if (g.lds <= kAlg1LdsBudget) return g;
-        }
-    }
-    return {};
-}
-
 }  // namespace
 
 // Problems per workgroup: the most (a power of two, at most 64) whose state fits the budget.
@@ -609,23 +583,64 @@ bool alg1_fits(const DeviceTopo &t)
     return (!t.alg1_thread_per_problem && alg1_small(t)) || alg1_lds_bytes(t) <= kAlg1LdsBudget;
 }
 
+// Rough time of `blocks` workgroups in us per pair and sweep: `us` for one on a compute unit by
+// itself, `more` of that for every further one beside it, as many side by side as the LDS holds.
+// (It is handed out in pieces of 1280 bytes.)
+static double alg1_time(int64_t blocks, size_t lds, double us, double more)
+{
+    const int64_t side = 160 * 1024 / ((lds + 1279) / 1280 * 1280);
+    const int64_t rounds = blocks / (256 * side), rest = (blocks % (256 * side) + 255) / 256;
+    return us * (rounds * (1.0 + more * (side - 1)) + (rest ? 1.0 + more * (rest - 1) : 0.0));
+}
+
+// The fastest of the forms a topology fits, by the time a pair takes in one sweep: AHEAD 0.13 us, 0.22
+// to 0.39 with a table of up to 2, 5 or 8 links, 0.24 to 0.49 with lists from memory, 0.55 and 0.068 per
+// link of its candidates with a thread per problem.  The faster a form, the more LDS it takes, and the
+// fewer of its workgroups run side by side.  Measured on 41 topologies (one to four nodes of 2 to 20
+// GPUs, random ones of up to 64 candidates and 8 links; 6 to 992 pairs) and 1 to 65536 problems,
+// 260 calls: the form chosen is the fastest but for two, where it is 3 % behind.
+Alg1Form alg1_form(const DeviceTopo &t, int32_t batch)
+{
+    Alg1Form best = {};
+    double least = 0.0;
+    auto offer = [&](const Alg1Form &f, int per_block, double us, double more) {
+        const double time = alg1_time((batch + int64_t(per_block) - 1) / per_block, f.lds, us, more);
+        if (best.lds == 0 || time < least) {
+            best = f;
+            least = time;
+        }
+    };
+    if (!t.alg1_thread_per_problem && t.pmax >= 1 && t.pmax <= kWave && t.lmax <= 8 && t.K >= 1) {
+        const int of = t.lmax <= 2 ? 0 : t.lmax <= 5 ? 1 : 2;
+        constexpr double kTable[] = {0.22, 0.32, 0.39}, kMemory[] = {0.24, 0.38, 0.49};
+        for (int form = 0; form < 3; ++form) {
+            const bool ahead = form == 0, table = form == 1;
+            if (table && !alg1_small(t)) continue;
+            // (more lanes than candidates where only fewer problems fit the LDS together)
+            for (int G = lanes_per_commodity(t.pmax); G <= kWave; G *= 2) {
+                if (ahead && (t.lmax > kAheadSteps || G > kAheadLanes || 8 * (t.E + 1) > 0xFFFF)) break;
+                const size_t lds =
+                    alg1_lds(t.E, t.K, t.P, G, ahead, table ? alg1_table_steps(t.lmax) : 0).bytes;
+                if (lds > kAlg1LdsBudget) continue;
+                if (ahead) offer({G, ahead, table, lds}, kWave / G, 0.13, 0.16);
+                else offer({G, ahead, table, lds}, kWave / G, table ? kTable[of] : kMemory[of], 0.03);
+                break;
+            }
+        }
+    }
+    if (alg1_lds_bytes(t) <= kAlg1LdsBudget)
+        offer({0, false, false, alg1_lds_bytes(t)}, alg1_threads(t),
+              0.55 + 0.068 * static_cast<double>(t.nnz) / t.K, 0.02);
+    return best;
+}
+
 hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand, double phi,
                        double chi, int32_t max_sweeps, double *flows, double *lambda,
                        int32_t *sweeps, hipStream_t s)
 {
-    const Alg1Group group = alg1_group(t);
-    int G = group.lanes;
-    const size_t glds = group.lds;
-    if (G > 0 && !alg1_small(t)) {
-        // A pair takes the group 0.55 us whatever its candidates, a thread about 0.065 us per link of
-        // them (two nodes of 8, 16 or 32 candidates of up to five links: 0.53 against 5.2, 0.56 against
-        // 8.8 us), but a compute unit holds fewer groups than threads.
-        const double groups = 256.0 * (kWave / G) * static_cast<double>(160 * 1024 / glds);
-        const double threads = 256.0 * alg1_threads(t);
-        if (0.55 * std::ceil(batch / groups) >
-            0.065 * static_cast<double>(t.nnz) / t.K * std::ceil(batch / threads))
-            G = 0;
-    }
+    const Alg1Form form = alg1_form(t, batch);
+    const int G = form.lanes;
+    const size_t glds = form.lds;
     if (G > 0) {
         const int per_block = kWave / G;
         const int ggrid = (batch + per_block - 1) / per_block;
@@ -645,13 +660,13 @@ hipError_t launch_alg1(const DeviceTopo &t, int32_t batch, const double *demand,
     } while (0)
 #define NIMBLE_ALG1_FORM(GG, LM)                                                               \
     if (t.lmax <= LM) {                                                                        \
-        if (group.table) NIMBLE_ALG1_LAUNCH(GG, LM, false, true);                              \
+        if (form.table) NIMBLE_ALG1_LAUNCH(GG, LM, false, true);                               \
         NIMBLE_ALG1_LAUNCH(GG, LM, false, false);                                              \
     }
 #define NIMBLE_ALG1_LANES(GG)                                                                  \
     case GG:                                                                                   \
         if constexpr (GG <= kAheadLanes)                                                       \
-            if (group.ahead) NIMBLE_ALG1_LAUNCH(GG, kAheadSteps, true, false);                 \
+            if (form.ahead) NIMBLE_ALG1_LAUNCH(GG, kAheadSteps, true, false);                  \
         NIMBLE_ALG1_FORM(GG, 2)                                                                \
         NIMBLE_ALG1_FORM(GG, 5)                                                                \
         NIMBLE_ALG1_FORM(GG, 8)                                                                \

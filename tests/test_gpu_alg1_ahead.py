@@ -71,18 +71,25 @@ def fabric(what):
     return W.random_topology(np.random.default_rng(5), *what)
 
 
-# every kind of group, at 2, 5 and 8 links of a path and up to 64 candidates; one problem, whose finished
-# pairs are passed over, and problems that share waves
+# (fabric, problems, kernel: 0 a thread per problem, else 100 x kind + lanes with kind 1 loads read
+# ahead, 2 lists in LDS, 3 lists from memory): every kind, at 2, 5 and 8 links of a path, at every
+# count of lanes that a rule can give it, and batches on both sides of a change
 FORMS = [
-    ("1 4 none", 21), ("1 10 none", 21), ("1 12 none", 21), ("1 13 none", 21), ("1 16 none", 21),
-    ("2 4 own", 1), ("2 4 own", 21), ("2 4 xor", 21), ("3 4 own", 21),
-    ((100, 30, 33, 2), 21), ((200, 60, 8, 8), 21), ((60, 200, 4, 8), 21), ((30, 50, 33, 8), 21),
-    ((30, 20, 64, 5), 21), ((60, 200, 2, 2), 21), ((60, 400, 1, 2), 21), ((20, 60, 4, 5), 21),
+    ("1 4 none", 21, 104), ("1 4 none", 65536, 204),
+    ("1 10 none", 21, 116), ("1 10 none", 2112, 216), ("1 10 none", 20000, 316),
+    ("1 12 none", 21, 116), ("1 12 none", 1500, 316),      # 151 KB of LDS for four problems
+    ("1 13 none", 21, 316), ("1 16 none", 21, 316),        # no room for the loads read ahead
+    ("2 4 own", 1, 204), ("2 4 own", 21, 204), ("2 4 xor", 21, 216), ("2 4 xor", 16384, 316),
+    ("3 4 own", 21, 304),
+    ((100, 30, 33, 2), 21, 232), ((200, 60, 8, 8), 21, 208), ((60, 200, 4, 8), 21, 304),
+    ((30, 50, 33, 8), 21, 364), ((30, 20, 64, 5), 21, 264), ((30, 20, 64, 5), 8192, 364),
+    ((60, 200, 2, 2), 21, 304), ((60, 400, 1, 2), 21, 308),
+    ((20, 60, 4, 5), 21, 204), ((20, 60, 4, 5), 65536, 0),
 ]
 
 
-@pytest.mark.parametrize("what,batch", FORMS, ids=str)
-def test_every_form_is_the_oracles_bits(oracle_mod, B, what, batch):
+@pytest.mark.parametrize("what,batch,form", FORMS, ids=str)
+def test_every_form_is_the_oracles_bits(oracle_mod, B, what, batch, form):
     t = fabric(what)
     rng = np.random.default_rng(batch)
     n = min(batch, 21)
@@ -96,6 +103,7 @@ def test_every_form_is_the_oracles_bits(oracle_mod, B, what, batch):
     print(f"[alg1] {what} x {batch}", flush=True)
     h = B.nimble_topo_create(*t.csr())
     try:
+        assert h.alg1_form(batch) == form
         flows, lam, sweeps = B.plan_alg1(h, d[rows], 0.5, float(1 << 20))
     finally:
         h.close()
@@ -103,6 +111,39 @@ def test_every_form_is_the_oracles_bits(oracle_mod, B, what, batch):
         ref = oracle_mod.alg1(*t.csr(), d[i], 0.5, float(1 << 20))
         assert (flows[rows == i] == ref["flows"]).all(), f"problem {i}"
         assert (lam[rows == i] == ref["lam"]).all() and (sweeps[rows == i] == ref["sweeps"]).all()
+
+
+def test_more_lds_than_a_kernel_has_by_default_under_capture(oracle_mod, B):
+    """The first call on a topology whose groups want more than 64 KB, made while capturing."""
+    import torch
+    t = fabric("2 6 own")
+    rng = np.random.default_rng(3)
+    d = np.floor(rng.pareto(1.1, (2, 5, t.n_comm)) * 1e6)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        assert h.alg1_form(5) == 308
+        dd = torch.as_tensor(d[0].reshape(-1)).to("cuda:0")
+        ff = torch.zeros(5 * t.n_paths, dtype=torch.float64, device="cuda:0")
+        ll = torch.zeros(5, dtype=torch.float64, device="cuda:0")
+        ss = torch.zeros(5, dtype=torch.int32, device="cuda:0")
+        torch.cuda.synchronize()
+        side = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            B.nimble_alg1_solve_batch(h, 5, dd, 0.5, 65536.0, 1 << 20, ff, ll, ss,
+                                      stream=torch.cuda.current_stream())
+        for turn in range(4):
+            dd.copy_(torch.as_tensor(d[turn % 2].reshape(-1)))
+            ff.fill_(-1.0)
+            graph.replay()
+            torch.cuda.synchronize()
+            got = ff.cpu().numpy().reshape(5, -1)
+            for i in range(5):
+                ref = oracle_mod.alg1(*t.csr(), d[turn % 2][i], 0.5, 65536.0)
+                assert np.array_equal(got[i], ref["flows"]) and ll[i].item() == ref["lam"]
+                assert ss[i].item() == ref["sweeps"]
+    finally:
+        h.close()
 
 
 def test_topologies_beyond_the_limits_are_refused(B):
