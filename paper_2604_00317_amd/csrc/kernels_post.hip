@@ -203,12 +203,10 @@ __device__ __forceinline__ int group_rank(KEY key, int lane)
 // carry from one comparison to the next.  Keys lie in [-1, 2^30) and those of candidates differ, so the
 // sign of ko - key says whether ko is behind, and all but the own one are ahead or behind; the
 // signs are shifted into a word (32 comparisons at most per word) and counted at the end.
-// (Not key - ko: the compiler makes that v_subrev_u32 with the move across lanes inside, which was
-// seen to return ko - key here.)
 template <int S>
 __device__ __forceinline__ void collect_signs(int v, int key, unsigned &signs)
 {
-    signs = __builtin_amdgcn_alignbit(signs, static_cast<unsigned>(dpp_i32<0x120 + S>(v) - key), 31);
+    signs = __builtin_amdgcn_alignbit(signs, static_cast<unsigned>(dpp_less_i32<0x120 + S>(v, key)), 31);
     if constexpr (S > 1) collect_signs<S - 1>(v, key, signs);
 }
 // how many of the sixteen lanes of a row are behind

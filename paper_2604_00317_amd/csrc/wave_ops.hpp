@@ -15,11 +15,23 @@ constexpr int kDppHalfMirror = 0x141;
 constexpr int kDppMirror = 0x140;
 
 // (every lane has a source, so nothing has to be kept for lanes without one: without that the compiler
-// copies v first, two instructions more per step of a 64-bit reduction)
+// copies v first, two instructions more per step of a 64-bit reduction.  Fifteen solves by the patch
+// kernels took 0.98 to 1.01 of the time they take with the copy.)
+// A lane that is switched off is read as 0.  The compiler puts the move into the instruction that uses
+// it where it can, and one kind of those is not what it takes it for: this GPU runs
+// v_subrev_u32_dpp d, a, b as moved(b) - a, not as b - moved(a) (seen in all lanes, clang 22 of ROCm
+// 7.2).  So never subtract the result from something: dpp_less_i32 has the move in front.
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v)
 {
     return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+}
+
+// The value of v in the lane that CTRL names, less x.
+template <int CTRL>
+__device__ __forceinline__ int dpp_less_i32(int v, int x)
+{
+    return dpp_i32<CTRL>(v) - x;
 }
 
 template <int CTRL>

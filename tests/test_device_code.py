@@ -1,0 +1,67 @@
+"""What the compiler made of the kernels: instructions this GPU does not run as the compiler means them.
+
+`v_subrev_u32_dpp d, a, b` is meant as b - moved(a).  The GPU returns moved(b) - a: the move across lanes
+goes to the operand that a reversed instruction takes first.  The compiler makes it from any x - moved(y).
+"""
+import os
+import re
+import struct
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LLVM = "/opt/rocm/llvm/bin"
+REVERSED_MOVE = re.compile(r"\bv_\w*rev_\w*_dpp\b")
+
+
+def device_objects(fatbin: bytes):
+    """The gfx950 code objects of a .hip_fatbin section: offload bundles one behind the other."""
+    magic = b"__CLANG_OFFLOAD_BUNDLE__"
+    at = fatbin.find(magic)
+    while at >= 0:
+        (count,) = struct.unpack_from("<Q", fatbin, at + len(magic))
+        p = at + len(magic) + 8
+        for _ in range(count):
+            offset, size, n = struct.unpack_from("<QQQ", fatbin, p)
+            name = fatbin[p + 24:p + 24 + n].decode()
+            p += 24 + n
+            if name.endswith("gfx950") and size:
+                yield fatbin[at + offset:at + offset + size]
+        at = fatbin.find(magic, at + len(magic))
+
+
+def disassembled(elf: str, tmp) -> str:
+    section = str(tmp / "fatbin")
+    subprocess.run([f"{LLVM}/llvm-objcopy", f"--dump-section=.hip_fatbin={section}", elf,
+                    str(tmp / "rest")], check=True, capture_output=True)
+    text = []
+    for i, code in enumerate(device_objects(open(section, "rb").read())):
+        obj = tmp / f"code{i}.o"
+        obj.write_bytes(code)
+        text.append(subprocess.run([f"{LLVM}/llvm-objdump", "-d", "--no-show-raw-insn", str(obj)],
+                                   check=True, capture_output=True, text=True).stdout)
+    return "\n".join(text)
+
+
+def test_no_lane_move_inside_a_reversed_instruction(tmp_path):
+    from paper_2604_00317_amd import binding as B
+    B.load_library()
+    text = disassembled(B.LIB_PATH, tmp_path)
+    assert text.count("s_endpgm") > 100 and "v_sub_u32_dpp" in text      # the kernels are there
+    assert REVERSED_MOVE.findall(text) == []
+
+
+@pytest.mark.parametrize("expr,bad", [("nimble::dpp_less_i32<0x121>(v, x)", False),
+                                      ("x - nimble::dpp_i32<0x121>(v)", True)])
+def test_the_subtraction_helper_keeps_the_move_in_front(tmp_path, expr, bad):
+    """The helper's form, and the one that the check above is there to find."""
+    from paper_2604_00317_amd import build
+    src = tmp_path / "probe.hip"
+    src.write_text('#include "wave_ops.hpp"\n'
+                   "__global__ void k(int *o) { int v = o[threadIdx.x], x = o[64 + threadIdx.x];\n"
+                   f"  o[threadIdx.x] = {expr}; }}\n")
+    r = subprocess.run(["/opt/rocm/bin/hipcc", *build.FLAGS, f"-I{build.CSRC}", "-S",
+                        "--cuda-device-only", "-o", "-", str(src)], check=True,
+                       capture_output=True, text=True)
+    assert bool(REVERSED_MOVE.search(r.stdout)) == bad
