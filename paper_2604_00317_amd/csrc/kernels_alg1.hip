@@ -131,12 +131,13 @@ __global__ __launch_bounds__(kAlg1Threads) void k_alg1(int E, int K, int P, int 
 // two links, at most 16 candidates) also reads the loads of a pair's links before the pair before
 // it has routed its chunk, and adds that chunk where the candidate it took uses the same link: a
 // table holds, per pair and lane, the links, their 1/capacity and which candidates of the pair
-// before use them.  That leaves decision -> compare -> minimum -> decision, without a trip to LDS;
-// the wave's own instructions (about fifty a pair) then bound it.  Chunks are added by LDS atomics that
-// return nothing (they round like an addition, denormals included); the lanes that do not take the
-// pair add to a spare place.  The other forms read the loads when they are needed and pass over pairs
-// that have nothing left in any problem of the wave (a problem routes most of its pairs in its first
-// sweeps, so one problem on its own skips more than eight that share a wave).  TABLE: the links of all
+// before use them.  What a decision depends on is then the one before it, without a trip to LDS.
+// (The compiled loop forms the sums of the next pair's loads with the chunk beforehand and so still
+// waits for them ahead of the decision: 320 cycles a pair, of which the wave's own fifty or so
+// instructions are about 200.)  Chunks are added by LDS atomics that return nothing; the lanes that do
+// not take the pair add to a spare place.  The other forms read the loads when they are needed and pass
+// over pairs that have nothing left in any problem of the wave (a problem routes most of its pairs in
+// its first sweeps, so one problem on its own skips more than eight that share a wave).  TABLE: the links of all
 // candidates lie in LDS; without it they come from memory, asked for ahead in stages.
 // 4096 problems of one node of 8 GPUs (56 pairs, 10 sweeps at most): 222 -> 102 us
 // (one problem 200 -> 86; 7.5 us a sweep).  512 problems of two nodes of 8 (240 pairs of up to 16

@@ -236,7 +236,8 @@ __device__ __forceinline__ int group_rank_narrow(int key)
 // pairs of 32 candidates: 59.0 us with 64-bit whole numbers throughout, 49.6 us (2.8 TB/s) in 32 bits,
 // 52.0 us with a third fewer instructions (reciprocals passed in, subtractions in the moves across
 // lanes), 43.7 us with those and two pairs at a time, 36.2 us (3.8 TB/s) with four whose fractions are
-// asked for together too.
+// asked for together too.  These are calls that find their 136 MB in the cache: from memory 59.7 us
+// before and 41.6 now.
 template <int L, bool NARROW, int U>
 __global__ __launch_bounds__(kPostBlock) void k_quantize_group(int K,
                                                                const int32_t *__restrict__ cp,
@@ -363,8 +364,10 @@ hipError_t launch_quantize(const DeviceTopo &t, const double *demand, const doub
     if (t.pmax <= kWave) {
         const int L = lanes_per_commodity(t.pmax);
         const int64_t threads = static_cast<int64_t>(t.K) * L;
-        // (more than one pair at a time only where the lanes fill the chip's 256 compute units of 2048
-        // several times over)
+        // (Four pairs at a time pay where that many lanes are more than the chip's 256 compute units
+        // hold anyway, 2048 each.  One pair against four, buffers from memory, 8 lanes a pair: 2^19
+        // lanes 7.8 and 8.4 us, 2^20 11.6 and 10.9, 2^21 18.5 and 14.9, 2^23 61 and 39; 64 lanes: 9.1
+        // and 10.1, 13.9 and 14.0, 22.2 and 20.3, 74 and 56.  Widths between them cross there too.)
         const bool many = iters < (1 << 24) && threads >= (1 << 20);
         const int64_t per_block = many ? kPostBlock * kPairsAtOnce : kPostBlock;
         const int g = static_cast<int>((threads + per_block - 1) / per_block);

@@ -631,8 +631,9 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
                 fine = min(fine, sh.fine[w0 + w]);
             }
             sh.invrho[slot] = (m > 0.0) ? 1.0 / m : 0.0;
-            // (one bit less than a double holds, for the rounding of the total; the grid kept off
-            // the denormals, which atomics need not keep.  Comparisons with a NaN are false.)
+            // (One bit less than a double holds, for the rounding of the total.  Denormal grids stay
+            // with the gather: the reciprocal of their width can be infinite, and the two pick
+            // differently among lengths that are no numbers.  Comparisons with a NaN are false.)
             const bool on_grid = total == 0.0 || (total < __builtin_inf() && fine >= -1022 &&
                                                   ilogb(total) + 1 - fine <= 52);
             if (ONEWAVE) sh.fine[w0] = on_grid ? 1 : 0;

@@ -268,7 +268,8 @@ __device__ __forceinline__ int lowest_bit(double d)
     return (ex ? ex : 1) - 1075 + __ffsll(static_cast<long long>(man)) - 1;
 }
 
-// Adds v to *p in LDS and returns nothing: one instruction that nobody waits for.
+// Adds v to *p in LDS and returns nothing: one instruction that nobody waits for.  It rounds like an
+// addition and keeps denormals (chunks of denormal bytes are the CPU definition's bits).
 __device__ __forceinline__ void lds_add_f64(double *p, double v)
 {
     (void)__hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);

@@ -155,3 +155,51 @@ def test_more_pairs_than_the_chip_holds_at_once(oracle_mod, B):
     for chi in (1 << 20, 1000):
         ref = oracle_mod.quantize(cp, d, c / iters, iters, chi, 1e5)
         assert np.array_equal(gpu_quantize(B, t, d, c / iters, iters, chi, 1e5), ref), chi
+
+
+@pytest.mark.parametrize("lanes", [1, 2, 4, 8, 16, 32, 64])
+def test_every_width_with_several_pairs_to_a_group(oracle_mod, B, lanes):
+    """From 2^20 lanes on, at every count of lanes to a pair: a last block with few pairs, ragged lists,
+    counts with many ties and the largest anywhere.  (The same 1021 pairs over and over: what a pair gets
+    does not depend on the others.)"""
+    import torch
+    rng = np.random.default_rng(lanes)
+    M, iters, theta = 1021, 977, 2e5
+    K = (1 << 20) // lanes + 3
+    n = rng.integers(lanes // 2 + 1, lanes + 1, M) if lanes > 1 else np.ones(M, dtype=np.int64)
+    n[0] = lanes
+    lists, demand = [], np.floor(rng.pareto(1.1, M) * 1e6)
+    for k in range(M):
+        if k % 3 == 0:                                   # all as equal as they can be
+            c = np.full(n[k], iters // n[k])
+            c[:iters - c.sum()] += 1
+        elif k % 3 == 1:                                 # two that share the most, the rest few or none
+            c = rng.integers(0, 3, n[k]) * (iters // (8 * lanes))
+            c[:2] = 0
+            c[:2] = (iters - c.sum()) // min(2, n[k])
+            c[-1] += iters - c.sum()
+        else:
+            c = rng.multinomial(iters, rng.dirichlet(np.ones(n[k]) * 0.5))
+        lists.append(rng.permutation(c))
+    cp1 = np.r_[0, np.cumsum(n)].astype(np.int32)
+    x1 = np.concatenate(lists) / iters
+    which = np.arange(K) % M
+    cp = np.r_[0, np.cumsum(n[which])].astype(np.int32)
+    whole, rest = divmod(K, M)
+    splits = np.r_[np.tile(x1, whole), x1[:cp1[rest]]]
+    P = int(cp[-1])
+    E = 64
+    h = B.nimble_topo_create(E, np.ones(E), K, cp, P, np.arange(P + 1, dtype=np.int32),
+                             (np.arange(P, dtype=np.int64) * 7 % E).astype(np.int32))
+    try:
+        x = torch.as_tensor(splits).to("cuda:0")
+        d = torch.as_tensor(demand[which]).to("cuda:0")
+        for chi in (1 << 16, 1000):
+            print(f"[quantize] {lanes} lanes, {K} pairs, chi={chi}", flush=True)
+            ref = oracle_mod.quantize(cp1, demand, x1, iters, chi, theta)
+            f = torch.full((P,), float("nan"), dtype=torch.float64, device="cuda:0")
+            B.nimble_plan_quantize(h, d, x, iters, chi, theta, f)
+            got = f.cpu().numpy()
+            assert np.array_equal(got, np.r_[np.tile(ref, whole), ref[:cp1[rest]]]), chi
+    finally:
+        h.close()

@@ -2,8 +2,8 @@
 
 The kernel scatters where the demands of a plan lie on a power-of-two grid with a total below
 2^52 units and gathers, in the oracle's own order, everywhere else: both are the oracle's bits for
-any demands.  Sizes: every instantiation (4 to 8 candidates, first candidate direct or not), plans of
-one wave and of several, one plan and batches that mix both kinds of demands.
+any demands.  Sizes: every instantiation (4 to 8 candidates with a direct first one, 8 with any; each for
+plans of one wave and of several), one plan and batches that mix both kinds of demands.
 """
 import numpy as np
 import pytest
@@ -38,19 +38,47 @@ def demands_of(kind, K, rng):
         d = np.floor(rng.random(K) * 64)
         d[0] = 1.0
         d[1] = 2.0 ** int(kind[8:]) - 1.0
-    elif kind == "denormal":                       # a grid atomics need not keep
+    elif kind == "denormal":                       # a grid and loads that are denormal
         d = np.floor(rng.random(K) * 1000) * 2.0 ** -1070
+    elif kind == "denormal_grid":                  # some demands denormal, a width that is not
+        d = np.floor(rng.random(K) * 2.0 ** 44) * 2.0 ** -1030
+        d[::3] = np.floor(rng.random(d[::3].size) * 128) * 2.0 ** -1030
+    elif kind == "denormal_spread":                # a denormal grid with too large a total
+        d = np.floor(rng.random(K) * 1000) * 2.0 ** -1070
+        d[0] = 2.0 ** -900
     elif kind == "huge":
         d = d * 2.0 ** 900
     return d
 
 
-KINDS = ["bytes", "zero", "one", "fractional", "total_2^51", "total_2^53", "denormal", "huge"]
+KINDS = ["bytes", "zero", "one", "fractional", "total_2^51", "total_2^53", "denormal", "denormal_grid",
+         "denormal_spread", "huge"]
 # nodes of 3 to 9 GPUs (2 to 8 candidates, the last with 72 pairs); random topologies of up to 8
-# candidates whose first is not always direct: one wave, two waves, a full workgroup's threads
+# candidates whose first is not always direct: one wave, two waves, a full workgroup's threads; several
+# waves with a direct first candidate: meshes (2 candidates), circulant lists of 5 to 8 (of 8 in one too)
 FABRICS = [("node", g) for g in (3, 4, 5, 6, 7, 8, 9)] + [
     ("random", (31, 64, 64, 5)), ("random", (32, 130, 100, 8)), ("random", (33, 1024, 700, 4)),
-    ("random", (34, 1, 2, 1))]
+    ("random", (34, 1, 2, 1)), ("mesh", 11), ("mesh", 31), ("circulant", (90, 5)),
+    ("circulant", (90, 6)), ("circulant", (90, 7)), ("circulant", (400, 7)), ("circulant", (90, 8)), ("circulant", (60, 8))]
+
+
+def circulant(n, most):
+    """n pairs and links; pair k has its own link, and up to `most` - 1 ways over links k + 2j - 1 and
+    k + 2j, so that a link has at most 2 `most` - 1 pairs."""
+    cp, lp, pl = [0], [0], []
+    for k in range(n):
+        pl += [k]
+        lp.append(len(pl))
+        for j in range(1, most - k % 3 if k else most):
+            pl += [(k + 2 * j - 1) % n, (k + 2 * j) % n]
+            lp.append(len(pl))
+        cp.append(len(lp) - 1)
+    cap = np.random.default_rng(n).choice([25.0, 50.0, 100.0], size=n) * 1e9
+    zeros = np.zeros(n, dtype=np.int32)
+    return W.Topology(n_links=n, cap=cap, n_comm=n, comm_path_ptr=np.asarray(cp, dtype=np.int32),
+                      n_paths=len(lp) - 1, path_link_ptr=np.asarray(lp, dtype=np.int32),
+                      path_links=np.asarray(pl, dtype=np.int32), src=zeros, dst=zeros,
+                      meta=dict(kind="circulant"))
 
 
 @pytest.mark.parametrize("flags", [0, 1])
@@ -59,6 +87,10 @@ def test_scatter_and_gather_are_the_oracles_bits(oracle_mod, B, fabric, flags):
     kind, what = fabric
     if kind == "node":
         t = W.build_fabric(1, what)
+    elif kind == "mesh":
+        t = W.two_candidate_mesh(what)
+    elif kind == "circulant":
+        t = circulant(*what)
     else:
         seed, E, K, pm = what
         t = W.random_topology(np.random.default_rng(seed), E, K, pm, min(2, E))
