@@ -1,7 +1,8 @@
 // The sequential planner of Algorithm 1 ("Link Load Balancing w. Iterative Approximation"),
 // batched, all problems on the same topology.  Two kernels compute the same numbers: a group of
 // G lanes per problem whose lanes cost the candidates of a pair side by side (k_alg1_group, up
-// to 64 candidates per pair), and one thread per problem (k_alg1) for anything else.
+// to 64 candidates per pair), and one thread per problem (k_alg1) for anything else and for batches
+// that fill the chip several times over with groups.
 //
 // The algorithm is a Gauss-Seidel sweep -- every routed chunk changes the link costs the next
 // pair sees -- so one problem offers no parallelism beyond its candidate scan; a batch of
@@ -121,9 +122,9 @@ __global__ __launch_bounds__(kAlg1Threads) void k_alg1(int E, int K, int P, int 
 // the chunk.  A problem lives inside one wave, so its lanes are ordered by the wave's in-order LDS
 // operations; workgroups never synchronise after the set-up (a workgroup is one wave).  LDS: 1/capacity
 // per workgroup; L[E + 2], the remainders r[K], the amounts f[K] of this sweep and the flows (by path;
-// AHEAD: G per pair) per problem.  L[E] (1/capacity 0) stands for a link that is not there, L[E + 1] = +inf (1/capacity 1)
-// for a candidate that is not there.  All lanes walk all pairs, so a wave sweeps until the last
-// of its problems is done (amounts of 0 change nothing).
+// AHEAD: G per pair) per problem.  L[E] (1/capacity 0) stands for a link that is not there, L[E + 1] =
+// +inf (1/capacity 1) for a candidate that is not there.  All lanes walk all pairs, so a wave sweeps
+// until the last of its problems is done (amounts of 0 change nothing).
 //
 // What bounds it is the chain from pair to pair, so everything that does not depend on the pair
 // before is taken out of it.  What a pair routes depends on its own remainder only: the amounts of
@@ -137,8 +138,8 @@ __global__ __launch_bounds__(kAlg1Threads) void k_alg1(int E, int K, int P, int 
 // instructions are about 200.)  Chunks are added by LDS atomics that return nothing; the lanes that do
 // not take the pair add to a spare place.  The other forms read the loads when they are needed and pass
 // over pairs that have nothing left in any problem of the wave (a problem routes most of its pairs in
-// its first sweeps, so one problem on its own skips more than eight that share a wave).  TABLE: the links of all
-// candidates lie in LDS; without it they come from memory, asked for ahead in stages.
+// its first sweeps, so one problem on its own skips more than eight that share a wave).  TABLE: the links
+// of all candidates lie in LDS; without it they come from memory, asked for ahead in stages.
 // 4096 problems of one node of 8 GPUs (56 pairs, 10 sweeps at most): 222 -> 102 us
 // (one problem 200 -> 86; 7.5 us a sweep).  512 problems of two nodes of 8 (240 pairs of up to 16
 // candidates, a thread per problem where their lists do not fit the LDS): 8.2 -> 0.79 ms.  Two nodes of

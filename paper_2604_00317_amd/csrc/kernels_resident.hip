@@ -508,7 +508,8 @@ struct RegShared {
 // The scatter replaces sixteen choice reads and sixteen additions in a row by two atomics, and
 // the minimum carries the winner's links and its place up the tree, so nothing is looked up after it.
 // What bounds it: one plan, the chain price reads -> sums -> tree -> atomics -> load -> price of one
-// wave; 4096 plans (four waves per SIMD), vector issue and the LDS about equally.  One node of 8 GPUs,
+// wave (590 cycles an iteration, 310 of them waited); 4096 plans (four waves per SIMD), the LDS, busy
+// for 185 of the 205 thousand cycles a wave is there, then vector issue (131).  One node of 8 GPUs,
 // 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).  What
 // stays with the gather pays for the choice between them: 81.4 us as the only way, 83.3 with a count in
 // LDS per iteration and its pairs read one by one, 76.9 as it is (9 GPUs, 512 plans: 145.0, 158.0, 148.8).
