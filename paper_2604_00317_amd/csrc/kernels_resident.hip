@@ -732,11 +732,12 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
 #pragma unroll
             for (int q = 0; q < kRows; ++q) {
                 const int r = 2 * (r0 + (i0 + q < rn ? i0 + q : i0));
-                k[q] = g_rev[r] & kCommMask;
+                k[q] = g_rev[r];
                 wb[q] = g_rev[r + 1];
             }
 #pragma unroll
             for (int q = 0; q < kRows; ++q) {
+                k[q] &= kCommMask;
                 if (i0 + q >= rn || k[q] >= static_cast<uint32_t>(K)) k[q] = K;
                 dk[q] = d_in[k[q] < static_cast<uint32_t>(K) ? k[q] : 0u];
             }
