@@ -181,14 +181,6 @@ __host__ __device__ inline Alg1Lds alg1_lds(int E, int K, int P, int lanes, bool
     return l;
 }
 
-// the largest of two numbers that are no NaN, or the other one
-__device__ __forceinline__ double max_f64(double a, double b)
-{
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
 template <int G, int LM, bool AHEAD, bool TABLE>
 __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int batch,
                                                       const int32_t *__restrict__ cp,
@@ -448,7 +440,7 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
                     const double a0 = L0 + routed, a1 = L1 + routed;
                     L0 = (now.mask0 & took) != 0u ? a0 : L0;
                     L1 = (now.mask1 & took) != 0u ? a1 : L1;
-                    const double c = max_f64(L0 * now.ic0, L1 * now.ic1);
+                    const double c = fast_max_f64(L0 * now.ic0, L1 * now.ic1);
                     const bool me = takes(c, least(c), took);
                     lds_add_f64(me ? flow + i * G : spare, f);
                     lds_add_f64(me ? at0 : spare, f);
@@ -486,7 +478,7 @@ __global__ __launch_bounds__(kWave) void k_alg1_group(int E, int K, int P, int b
                 if (__builtin_amdgcn_ballot_w64(f > 0.0) != 0ull) {
                     double c = Lv[0] * ic_now[0];
 #pragma unroll
-                    for (int i = 1; i < LM; ++i) c = max_f64(c, Lv[i] * ic_now[i]);
+                    for (int i = 1; i < LM; ++i) c = fast_max_f64(c, Lv[i] * ic_now[i]);
                     uint32_t low;
                     if (takes(c, least(c), low)) {
                         fl[p_now] = flow_now + f;

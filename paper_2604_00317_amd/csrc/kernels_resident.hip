@@ -16,6 +16,8 @@
 // row (pairs l, l + 16, ... each, the 16 partial sums added by a fixed butterfly).  Path costs
 // are the same sums as before; link loads are added in that fixed tree instead of the
 // sequential order, which is the same number for demands on a power-of-two grid (byte counts).
+#include <type_traits>
+
 #include "host_topo.hpp"
 #include "kernels.hpp"
 #include "wave_ops.hpp"
@@ -512,7 +514,7 @@ struct RegShared {
 // for 185 of the 205 thousand cycles a wave is there, then vector issue (131).  One node of 8 GPUs,
 // 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).  What
 // stays with the gather pays for the choice between them: 81.4 us as the only way, 83.3 with a count in
-// LDS per iteration and its pairs read one by one, 76.9 as it is (9 GPUs, 512 plans: 145.0, 158.0, 148.8).
+// LDS per iteration and its pairs read one by one, 76.8 as it is (9 GPUs, 512 plans: 145.1, 158.0, 148.9).
 template <bool MAXC, bool ONEWAVE, int MAXP, bool DIRECT, int MAXROW>
 __global__ __launch_bounds__(1024) void k_resident_reg(
     int E, int K, int P, int batch, int nt_arg, int plans_per_block, double eps, int iters,
@@ -632,10 +634,11 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
                 fine = min(fine, sh.fine[w0 + w]);
             }
             sh.invrho[slot] = (m > 0.0) ? 1.0 / m : 0.0;
-            // (One bit less than a double holds, for the rounding of the total.  Denormal grids stay
-            // with the gather: the reciprocal of their width can be infinite, and the two pick
-            // differently among lengths that are no numbers.  Comparisons with a NaN are false.)
-            const bool on_grid = total == 0.0 || (total < __builtin_inf() && fine >= -1022 &&
+            // (One bit less than a double holds, for the rounding of the total.  Grids next to the
+            // denormals stay with the gather: the reciprocal of the width can be infinite there, and
+            // among lengths that are no numbers the tree of the scatter does not pick as the scan.
+            // Comparisons with a NaN are false.)
+            const bool on_grid = total == 0.0 || (total < __builtin_inf() && fine >= -900 &&
                                                   ilogb(total) + 1 - fine <= 52);
             if (ONEWAVE) sh.fine[w0] = on_grid ? 1 : 0;
             else if (!on_grid) sh.inexact = 1;
@@ -646,7 +649,8 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
     const bool exact = __builtin_amdgcn_readfirstlane(
                            ONEWAVE ? sh.fine[slot] : 1 - sh.inexact) != 0;
 
-    auto path_costs = [&](double (&c)[MAXP]) {
+    // (`numbers`: prices are numbers; a maximum without that starts at 0 like the scan's)
+    auto path_costs = [&](double (&c)[MAXP], auto numbers) {
         // the prices of four candidates are requested before the first is used
         constexpr int kBatch = 4;
 #pragma unroll
@@ -662,8 +666,10 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
             for (int j = 0; j < kBatch; ++j) {
                 if (j0 + j >= MAXP) break;
                 double cj = pv[j][0];                    // 0 + p is p
+                if constexpr (MAXC && !numbers) cj = fast_max_f64(cj, 0.0);
                 if (!DIRECT || j0 + j > 0) {
-                    if constexpr (MAXC) cj = (pv[j][1] > cj) ? pv[j][1] : cj;
+                    if constexpr (MAXC && !numbers) cj = fast_max_f64(cj, pv[j][1]);
+                    else if constexpr (MAXC) cj = (pv[j][1] > cj) ? pv[j][1] : cj;
                     else cj = cj + pv[j][1];
                 }
                 c[j0 + j] = cj;
@@ -683,7 +689,7 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
         for (int it = 0; it < iters; ++it) {
             double c[MAXP];
             uint32_t w[MAXP];
-            path_costs(c);
+            path_costs(c, std::true_type());
 #pragma unroll
             for (int j = 0; j < MAXP; ++j) w[j] = links[j];
             // the minimum as a tree over neighbours; of equal costs the left, so the lowest,
@@ -761,13 +767,16 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
         for (int it = 0; it < iters; ++it) {
             if (has_k) {
                 double c[MAXP];
-                path_costs(c);
+                path_costs(c, std::false_type());
                 double best = c[0];
 #pragma unroll
                 for (int j = 1; j < MAXP; ++j) best = fast_min_f64(best, c[j]);
                 int bj = MAXP - 1;
 #pragma unroll
-                for (int j = MAXP - 2; j >= 0; --j) bj = (c[j] == best) ? j : bj;
+                for (int j = MAXP - 2; j >= 1; --j) bj = (c[j] == best) ? j : bj;
+                // (also where the first cost is no number: a width without a finite reciprocal makes
+                // all lengths infinite or no numbers at once, and the scan then keeps the first)
+                bj = !(c[0] > best) ? 0 : bj;
                 choice[t] = static_cast<uint8_t>(bj);
                 tally += 1ull << (8 * bj);
                 if ((it & 127) == 127) flush();

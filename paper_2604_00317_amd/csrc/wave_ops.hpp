@@ -98,6 +98,14 @@ __device__ __forceinline__ double fast_min_f64(double a, double b)
     return r;
 }
 
+// The larger of two numbers, or the one that is no NaN.
+__device__ __forceinline__ double fast_max_f64(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
 // Argmin over aligned groups of L lanes, every lane holding its own best (cost, index) with
 // index = 0x7FFFFFFF when it has no candidate: the costs are min-reduced, then the indices of
 // the lanes whose cost equals the minimum are min-reduced, which is the tie rule "lowest

@@ -46,13 +46,21 @@ def demands_of(kind, K, rng):
     elif kind == "denormal_spread":                # a denormal grid with too large a total
         d = np.floor(rng.random(K) * 1000) * 2.0 ** -1070
         d[0] = 2.0 ** -900
+    elif kind == "tiny":                           # a width whose reciprocal is infinite
+        d = np.floor(rng.random(K) * 2.0 ** 40) * 2.0 ** -1060
+    elif kind == "tiny_spread":
+        d = np.floor(rng.random(K) * 1000) * 2.0 ** -1070
+        d[0] = 2.0 ** -1000
+    elif kind == "tiny_one":                       # the same on a grid that doubles hold
+        d[:] = 0.0
+        d[K // 2] = 2.0 ** -1020
     elif kind == "huge":
         d = d * 2.0 ** 900
     return d
 
 
 KINDS = ["bytes", "zero", "one", "fractional", "total_2^51", "total_2^53", "denormal", "denormal_grid",
-         "denormal_spread", "huge"]
+         "denormal_spread", "tiny", "tiny_spread", "tiny_one", "huge"]
 # nodes of 3 to 9 GPUs (2 to 8 candidates, the last with 72 pairs); random topologies of up to 8
 # candidates whose first is not always direct: one wave, two waves, a full workgroup's threads; several
 # waves with a direct first candidate: meshes (2 candidates), circulant lists of 5 to 8 (of 8 in one too)
