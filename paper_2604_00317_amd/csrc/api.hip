@@ -306,6 +306,14 @@ hipError_t ensure_state_plans(nimble_topo *t, int32_t plans)
 
 // ---- patch layouts --------------------------------------------------------------------------
 
+// How many teams of `patches` patches are resident at once, a patch per compute unit.
+void count_teams(const nimble_topo *t, nimble::DevicePatches &p, int32_t patches)
+{
+    p.xcds = std::max(1, t->n_cu / nimble::kCusOfXcd);
+    p.max_teams = t->n_cu / patches;
+    p.near_teams = p.xcds * (t->n_cu / p.xcds / patches);
+}
+
 hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::DevicePatches &p)
 {
     p.shape = l.shape;
@@ -328,10 +336,10 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     if (e == hipSuccess) e = upload(t, l.words.data(), l.words.size(), &p.words);
     if (e == hipSuccess) e = upload(t, l.first.data(), l.first.size(), &p.first);
     if (e == hipSuccess && l.n_patches > 1) {
-        p.max_teams = t->n_cu / l.n_patches;
+        count_teams(t, p, l.n_patches);
         e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_parts, &p.parts);
         if (e == hipSuccess)
-            e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * nimble::kPatchCopies * l.n_patches,
+            e = allocate(t, static_cast<size_t>(p.max_teams) * nimble::kPatchMeetings * l.n_patches,
                          &p.maxima);
         if (e == hipSuccess) e = allocate(t, static_cast<size_t>(t->d.E), &p.len_start);
         if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
@@ -399,7 +407,7 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
             continue;
         nimble::DevicePatches p;
         p.n_patches = built.n_patches;
-        p.max_teams = t->n_cu / built.n_patches;
+        count_teams(t, p, built.n_patches);
         p.iteration_us = nimble::patch_iteration_us(shape, built.n_patches, built.max_groups,
                                                     built.max_parts);
         p.list_bytes = 0;

@@ -39,6 +39,8 @@ constexpr int32_t kPatchMaxLocal = 2900;      // local links whose state fits th
 constexpr int32_t kPatchExport = 1 << 30;     // in loc_link: this patch writes the link's results
 constexpr int32_t kPatchDescInts = 8;
 constexpr int32_t kPatchCopies = 8;           // of the list of maxima the patches meet over
+constexpr int32_t kPatchMeetings = 2 * kPatchCopies + 1;   // words of a patch: those lists, two of
+                                              // each, and the XCD it runs on
 constexpr int32_t kPatchWordsProduct = 5;
 constexpr int32_t kPatchWordsPlain = 11;
 

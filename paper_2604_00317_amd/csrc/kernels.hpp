@@ -8,6 +8,8 @@
 
 namespace nimble {
 
+constexpr int32_t kCusOfXcd = 32;
+
 // One patch layout on the device (host_patch.hpp) with the exchange buffers of its teams, and
 // the arguments of a launch of the patch kernels (patch_kernel.hpp).
 struct DevicePatches {
@@ -16,10 +18,12 @@ struct DevicePatches {
     int32_t max_comm, max_local, max_groups, max_parts;
     int64_t n_parts;
     int32_t max_teams;           // plans whose patches are resident at once
+    int32_t xcds;                // XCDs of the device
+    int32_t near_teams;          // the same if every team keeps to one XCD (0: it does not fit one)
     const int32_t *desc, *loc_link, *comm, *group;
     const uint32_t *words, *first;
     double *parts;               // [max_teams][2][n_parts]
-    double *maxima;              // [max_teams][2][kPatchCopies][n_patches]
+    double *maxima;              // [max_teams][kPatchMeetings][n_patches]
     double *len_start;           // [E] lengths a warm solve starts from, whatever becomes of it
     uint32_t *abort_word;
     double iteration_us;         // estimate of one iteration of max_teams plans
@@ -55,6 +59,7 @@ struct PatchArgs {
     uint32_t *abort_word;
     int64_t n_parts;
     int32_t K, P, E, n_patches, plans, teams, iters;
+    int32_t near_xcds;           // XCDs the teams are dealt to, each within one; 1: they keep to none
     uint32_t spin_limit;
     double eps;
     double *terms;               // see PatchAdaptive

@@ -704,6 +704,29 @@ def test_teams_that_solve_several_plans(monkeypatch, iters, flags):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("strips,patches", [(2, 4), (3, 9), (5, 25), (6, 36)])
+def test_teams_of_one_xcd_and_of_several(monkeypatch, strips, patches):
+    """Patches that fit the compute units of one XCD (32) exchange their loads inside it, one team per
+    XCD or several; 36 do not.  One plan, as many as fill some XCDs, and more than there are teams."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    t = fabric(6, 6, "pair")
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        d = np.floor(np.random.default_rng(6).pareto(1.1, (70, t.n_comm)) * 1e6)
+        ref = [oracle.solve(*t.csr(), x, 0.05, 9) for x in d]
+        for n in (1, 11, 70):
+            splits, lam = B.plan(h, d[:n], 0.05, 9)
+            assert h.last_patches == patches
+            assert not B.nimble_debug_patches_gave_up(h)
+            for b in range(n):
+                assert np.atleast_1d(lam)[b] == ref[b]["lam"], (n, b)
+                assert np.array_equal(splits.reshape(n, -1)[b], ref[b]["splits"]), (n, b)
+    finally:
+        h.close()
+
+
+@pytest.mark.gpu
 def test_a_stream_under_capture_takes_one_patch():
     """Of a fabric with a layout of one patch and a faster one of several (4 nodes, a NIC per GPU
     reachable from two), an eager plan takes the several, a captured one the single patch."""
