@@ -223,6 +223,14 @@ nimble_status_t nimble_host_patch_check(int32_t n_links, int32_t n_comm,
                                         const int32_t *path_link_ptr, const int32_t *path_links,
                                         int32_t strips, int32_t lanes, int64_t *out);
 
+/* The same for a grid of strips_x x strips_y patches, with `blocks` other than 0 for its layout in
+ * blocks.  out[16]: as above, then most places for commodities of a patch, most users (summed over
+ * its groups), most head blocks, most tails, most links that no other patch uses. */
+nimble_status_t nimble_host_grid_check(int32_t n_links, int32_t n_comm,
+                                       const int32_t *comm_path_ptr, int32_t n_paths,
+                                       const int32_t *path_link_ptr, const int32_t *path_links,
+                                       int32_t strips_x, int32_t strips_y, int32_t blocks, int64_t *out);
+
 #ifdef __cplusplus
 }
 #endif

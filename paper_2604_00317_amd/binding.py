@@ -37,7 +37,7 @@ EXPORTS = [
     "nimble_plan_solve_static", "nimble_static_scratch_bytes", "nimble_debug_barrier_probe",
     "nimble_topo_reserve_batch", "nimble_debug_fail_allocation",
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
-    "nimble_host_patch_check", "nimble_debug_patches_gave_up",
+    "nimble_host_patch_check", "nimble_host_grid_check", "nimble_debug_patches_gave_up",
     "nimble_debug_refuse_cooperative", "nimble_debug_fail_patch_build",
     "nimble_topo_last_patches", "nimble_topo_alg1_form",
 ]
@@ -137,6 +137,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
                                                vp]
     lib.nimble_plan_quantize.restype = ctypes.c_int
     lib.nimble_plan_quantize.argtypes = [vp, vp, vp, i32, ctypes.c_int64, ctypes.c_double, vp, vp]
+    lib.nimble_host_grid_check.restype = ctypes.c_int
+    lib.nimble_host_grid_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, i32, vp]
     lib.nimble_host_patch_check.restype = ctypes.c_int
     lib.nimble_host_patch_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, vp]
     lib.nimble_host_layout_stats.restype = ctypes.c_int
@@ -468,6 +470,25 @@ def nimble_host_patch_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_p
         raise NimbleError(st, "invalid CSR")
     keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "threads",
             "max_local", "max_groups", "max_users", "max_parts", "parts"]
+    return dict(zip(keys, (int(v) for v in out)))
+
+
+def nimble_host_grid_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_ptr, path_links,
+                           strips_x, strips_y, blocks):
+    """Host-only: builds and checks the layout of a strips_x x strips_y grid, in slots or in blocks;
+    dict of its sizes (see include/nimble_plan_debug.h), `failed` is the number of the check that
+    failed."""
+    cp = _host(comm_path_ptr, np.int32)
+    lp = _host(path_link_ptr, np.int32)
+    pl = _host(path_links, np.int32)
+    out = np.zeros(16, dtype=np.int64)
+    st = load_library().nimble_host_grid_check(n_links, n_comm, _hp(cp), n_paths, _hp(lp), _hp(pl),
+                                               strips_x, strips_y, int(blocks), _hp(out))
+    if st != NIMBLE_OK:
+        raise NimbleError(st, "invalid CSR")
+    keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "threads",
+            "max_local", "max_groups", "max_users", "max_parts", "parts", "max_comm", "max_at",
+            "max_heads", "max_tails", "max_private"]
     return dict(zip(keys, (int(v) for v in out)))
 
 

@@ -10,7 +10,7 @@ LIB = os.path.join(_HERE, "libnimble_plan.so")
 SOURCES = ["api.hip", "kernels_stream.hip", "kernels_resident.hip",
            "kernels_persistent.hip", "kernels_alg1.hip", "kernels_post.hip", "kernels_adaptive.hip", "kernels_probe.hip",
            "kernels_patch_single.hip", "kernels_patch_sum.hip", "kernels_patch_max.hip",
-           "kernels_patch_adaptive.hip",
+           "kernels_patch_adaptive.hip", "kernels_blocks_sum.hip", "kernels_blocks_max.hip",
            "host_topo.cpp", "host_patch.cpp"]
 # -ffp-contract=off: one IEEE operation per statement on host and device (no FMA contraction).
 # packed-fp32-ops is switched off for every device compile of this build.

@@ -306,10 +306,12 @@ hipError_t ensure_state_plans(nimble_topo *t, int32_t plans)
 
 // ---- patch layouts --------------------------------------------------------------------------
 
+int32_t xcds_of(const nimble_topo *t) { return std::max(1, t->n_cu / nimble::kCusOfXcd); }
+
 // How many teams of `patches` patches are resident at once, a patch per compute unit.
 void count_teams(const nimble_topo *t, nimble::DevicePatches &p, int32_t patches)
 {
-    p.xcds = std::max(1, t->n_cu / nimble::kCusOfXcd);
+    p.xcds = xcds_of(t);
     p.max_teams = t->n_cu / patches;
     p.near_teams = p.xcds * (t->n_cu / p.xcds / patches);
 }
@@ -327,19 +329,27 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     p.maxima = nullptr;
     p.len_start = nullptr;
     p.abort_word = nullptr;
-    p.iteration_us = nimble::patch_iteration_us(l.shape, l.n_patches, l.max_groups, l.max_parts);
-    p.list_bytes = 4 * static_cast<int64_t>(l.words.size() + l.first.size());
+    p.max_heads = l.max_heads;
+    p.max_tails = l.max_tails;
+    p.heads = p.tails = nullptr;
+    p.row = l.row;
+    p.max_users = l.max_users;
+    p.max_at = l.max_at;
+    p.list_bytes = 4 * static_cast<int64_t>(l.words.size() + l.first.size() + l.heads.size());
     hipError_t e = upload(t, l.desc.data(), l.desc.size(), &p.desc);
     if (e == hipSuccess) e = upload(t, l.loc_link.data(), l.loc_link.size(), &p.loc_link);
     if (e == hipSuccess) e = upload(t, l.comm.data(), l.comm.size(), &p.comm);
     if (e == hipSuccess) e = upload(t, l.group.data(), l.group.size(), &p.group);
     if (e == hipSuccess) e = upload(t, l.words.data(), l.words.size(), &p.words);
     if (e == hipSuccess) e = upload(t, l.first.data(), l.first.size(), &p.first);
+    if (e == hipSuccess && l.shape.blocks) e = upload(t, l.heads.data(), l.heads.size(), &p.heads);
+    if (e == hipSuccess && l.shape.blocks) e = upload(t, l.tails.data(), l.tails.size(), &p.tails);
+    if (e == hipSuccess) e = upload(t, l.at.data(), l.at.size(), &p.at);
     if (e == hipSuccess && l.n_patches > 1) {
         count_teams(t, p, l.n_patches);
         e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_parts, &p.parts);
         if (e == hipSuccess)
-            e = allocate(t, static_cast<size_t>(p.max_teams) * nimble::kPatchMeetings * l.n_patches,
+            e = allocate(t, static_cast<size_t>(p.max_teams) * nimble::patch_meeting_words(l.n_patches),
                          &p.maxima);
         if (e == hipSuccess) e = allocate(t, static_cast<size_t>(t->d.E), &p.len_start);
         if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
@@ -363,16 +373,16 @@ double general_iteration_us(const nimble_topo *t, int32_t plans, bool streamed)
 }
 
 // How many microseconds `plans` plans of `iters` iterations take less on the layout than without
-// patches, by the estimates.  A solve of several patches has some 14 us more before its first
-// iteration (words of the exchange to clear, a cooperative launch) and loads the lists at about
-// 1 TB/s: one iteration of the 16-node fabric takes 41 us against 31 streamed, of the 64-node
-// fabric 130 against 83, and 16 iterations 83 against 140 and 256 against 358.
+// patches, by the estimates.  A solve of several patches has more before its first iteration than one
+// of one patch (words of the exchange to clear, a cooperative launch, the kernel that completes what
+// patches give up: 36 to 45 us in all against 10 to 17, calls one at a time; the larger difference is
+// taken, since one patch leaves the other compute units free) and loads the lists at about 1 TB/s.
 double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int32_t plans,
                        int32_t iters, bool streamed)
 {
     const int32_t at_once = p.n_patches > 1 ? p.max_teams : t->n_cu;
     const double us = p.iteration_us * ((plans + at_once - 1) / at_once);
-    const double before = p.n_patches > 1 ? 14.0 + 0.9e-6 * static_cast<double>(p.list_bytes) : 0.0;
+    const double before = p.n_patches > 1 ? 36.0 + 0.9e-6 * static_cast<double>(p.list_bytes) : 0.0;
     return iters * (general_iteration_us(t, plans, streamed) - us) - before;
 }
 
@@ -383,33 +393,39 @@ double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int
 hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, const int32_t *pl)
 {
     const nimble::DeviceTopo &d = t->d;
+    // "n": n x n patches, "nxm": n x m
     const char *env = std::getenv("NIMBLE_TUNE_PATCH_STRIPS");
     const char *env_lanes = std::getenv("NIMBLE_TUNE_PATCH_LANES");
-    const int32_t forced = env ? std::atoi(env) : -1, lanes = env_lanes ? std::atoi(env_lanes) : 0;
-    t->patches_forced = forced > 0;
-    if (forced == 0 || d.resident_generic ||
+    const char *env_blocks = std::getenv("NIMBLE_TUNE_PATCH_BLOCKS");
+    nimble::PatchForced forced;
+    int32_t strips = -1;
+    if (env) {
+        const char *by = std::strchr(env, 'x');
+        strips = std::atoi(env);
+        forced.grid = nimble::PatchGrid{strips, by ? std::atoi(by + 1) : strips};
+    }
+    if (env_lanes) forced.lanes = std::atoi(env_lanes);
+    if (env_blocks) forced.blocks = std::atoi(env_blocks);
+    t->patches_forced = strips > 0;
+    if (strips == 0 || d.resident_generic ||
         d.K > static_cast<int64_t>(t->n_cu) * nimble::kPatchThreads)
         return hipSuccess;
     nimble::PatchScan scan;
     nimble::scan_patches(d.E, d.K, cp, lp, pl, scan);
     if (!scan.fits) return hipSuccess;
-    const nimble::PatchChoice c = nimble::choose_cuts(d.E, d.K, scan, t->n_cu, forced, lanes);
-    if (c.best == 0) return hipSuccess;
-    for (int32_t i = 0; i < 3; ++i) {
-        const int32_t strips = i == 0 ? c.best : i == 1 ? c.fewest : c.adaptive;
-        if ((i == 1 && strips == c.best) || strips == 0 || (i == 2 && d.cost_max)) continue;
+    const std::vector<nimble::PatchOption> options = nimble::choose_cuts(
+        d.E, d.K, scan, t->n_cu, xcds_of(t), forced);
+    for (const nimble::PatchOption &o : options) {
+        if (d.cost_max && &o == &options.back() && options.size() == 3) continue;
         nimble::PatchCut cut;
-        nimble::PatchShape shape;
         nimble::PatchLayout built;
-        nimble::cut_patches(d.K, scan, strips, cut);
-        if (!nimble::patch_shape(scan, cut.most, lanes, shape) ||
-            !nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, shape, built))
-            continue;
+        nimble::cut_patches(d.K, scan, o.grid, cut);
+        if (!nimble::build_patches(d.E, d.K, cp, lp, pl, scan, cut, o.shape, built)) continue;
         nimble::DevicePatches p;
+        p.shape = o.shape;
         p.n_patches = built.n_patches;
         count_teams(t, p, built.n_patches);
-        p.iteration_us = nimble::patch_iteration_us(shape, built.n_patches, built.max_groups,
-                                                    built.max_parts);
+        p.iteration_us = o.us;
         p.list_bytes = 0;
         if (!t->patches_forced && patches_gain_us(t, p, 1, 1000, true) <= 0.0 &&
             patches_gain_us(t, p, 1, 1000, false) <= 0.0 &&

@@ -15,15 +15,17 @@ constexpr int32_t kCusOfXcd = 32;
 struct DevicePatches {
     PatchShape shape;
     int32_t n_patches = 0;       // 0: no such layout
-    int32_t max_comm, max_local, max_groups, max_parts;
+    int32_t max_comm, max_local, max_groups, max_parts, max_heads, max_tails;
     int64_t n_parts;
     int32_t max_teams;           // plans whose patches are resident at once
     int32_t xcds;                // XCDs of the device
     int32_t near_teams;          // the same if every team keeps to one XCD (0: it does not fit one)
     const int32_t *desc, *loc_link, *comm, *group;
-    const uint32_t *words, *first;
+    const uint16_t *at;
+    int32_t row, max_users, max_at;
+    const uint32_t *words, *first, *heads, *tails;
     double *parts;               // [max_teams][2][n_parts]
-    double *maxima;              // [max_teams][kPatchMeetings][n_patches]
+    double *maxima;              // [max_teams][patch_meeting_words(n_patches)]
     double *len_start;           // [E] lengths a warm solve starts from, whatever becomes of it
     uint32_t *abort_word;
     double iteration_us;         // estimate of one iteration of max_teams plans
@@ -48,7 +50,7 @@ inline int64_t patch_adaptive_words(int64_t K, int64_t E)
 
 struct PatchArgs {
     const int32_t *desc, *loc_link, *comm, *group;
-    const uint32_t *words, *first;
+    const uint32_t *words, *first, *heads, *tails;
     const int32_t *comm_ptr;
     const double *invcap;        // by link id
     const double *demand;        // [plans * K]
@@ -60,6 +62,9 @@ struct PatchArgs {
     int64_t n_parts;
     int32_t K, P, E, n_patches, plans, teams, iters;
     int32_t near_xcds;           // XCDs the teams are dealt to, each within one; 1: they keep to none
+    int32_t by_xcd;              // a team that is spread has its patch p on XCD p modulo kPatchXcds
+    int32_t row, max_users;      // see PatchLayout
+    const uint16_t *at;
     uint32_t spin_limit;
     double eps;
     double *terms;               // see PatchAdaptive

@@ -10,6 +10,8 @@ namespace patch {
 PatchKernel multi_kernel_sum(const PatchShape &s);
 PatchKernel multi_kernel_max(const PatchShape &s);
 PatchKernel adaptive_kernel(const PatchShape &s, bool multi);
+PatchKernel block_kernel_sum(const PatchShape &s);
+PatchKernel block_kernel_max(const PatchShape &s);
 
 namespace {
 
@@ -37,6 +39,10 @@ __global__ __launch_bounds__(256) void k_patch_clear(unsigned long long *parts, 
 
 PatchKernel kernel_of(const DevicePatches &p, bool cost_max, bool adaptive)
 {
+    if (p.shape.blocks) {
+        if (adaptive || p.n_patches == 1) return nullptr;
+        return cost_max ? block_kernel_max(p.shape) : block_kernel_sum(p.shape);
+    }
     if (adaptive) return cost_max ? nullptr : adaptive_kernel(p.shape, p.n_patches > 1);
     if (p.n_patches > 1) return cost_max ? multi_kernel_max(p.shape) : multi_kernel_sum(p.shape);
     return cost_max ? kernel_for<true, false, false>(p.shape)
@@ -47,11 +53,12 @@ PatchKernel kernel_of(const DevicePatches &p, bool cost_max, bool adaptive)
 
 }  // namespace patch
 
-constexpr size_t kLdsBytes = 160 * 1024;         // of a compute unit
-
 size_t patch_lds_bytes(const DevicePatches &p, bool adaptive)
 {
-    return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups, p.max_comm,
+    if (p.shape.blocks)
+        return static_cast<size_t>(block_lds(p.max_local, p.max_heads, p.max_tails, p.max_comm, p.max_at,
+                                             p.shape, adaptive ? 32 : 8).bytes);
+    return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups, p.max_at, p.max_comm,
                                                  p.shape.lanes * p.shape.quads, adaptive ? 32 : 8)
                                    .bytes);
 }
@@ -60,13 +67,13 @@ int patch_blocks_per_cu(const DevicePatches &p, bool cost_max, bool adaptive)
 {
     const patch::PatchKernel k = patch::kernel_of(p, cost_max, adaptive);
     const size_t lds = patch_lds_bytes(p, adaptive);
-    if (k == nullptr || lds > kLdsBytes) return 0;
+    if (k == nullptr || lds > kPatchLdsBytes) return 0;
     const void *f = reinterpret_cast<const void *>(k);
     int n = 0;
     // (the limit belongs to the kernel, which topologies with patches of other sizes share: it is
     // always set to all there is)
     if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            static_cast<int>(kLdsBytes)) != hipSuccess ||
+                            kPatchLdsBytes) != hipSuccess ||
         hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, p.shape.threads, lds) != hipSuccess) {
         (void)hipGetLastError();
         return 0;
@@ -88,6 +95,8 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     a.group = p.group;
     a.words = p.words;
     a.first = p.first;
+    a.heads = p.heads;
+    a.tails = p.tails;
     a.comm_ptr = t.comm_ptr;
     a.invcap = t.invcap;
     a.demand = demand;
@@ -115,6 +124,11 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     const bool near = p.near_teams > 0 && (plans + p.near_teams - 1) / p.near_teams <= rounds;
     a.teams = std::min(plans, near ? p.near_teams : p.max_teams);
     a.near_xcds = near ? p.xcds : 1;
+    a.by_xcd = a.teams == 1 && p.xcds == kPatchXcds && p.n_patches >= kPatchXcds &&
+               p.n_patches <= kPatchXcds * kPatchXcdPatches;
+    a.row = p.row;
+    a.max_users = p.max_users;
+    a.at = p.at;
     const int32_t blocks = a.near_xcds * p.n_patches * ((a.teams + a.near_xcds - 1) / a.near_xcds);
     a.iters = iters;
     a.spin_limit = spin_limit;
@@ -137,7 +151,7 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
         return hipLaunchKernel(f, dim3(plans), dim3(p.shape.threads), args, lds, s);
     const int64_t words = p.n_patches > 1 ? a.teams * 2 * p.n_parts : 0;
     const int64_t maxima =
-        p.n_patches > 1 ? static_cast<int64_t>(a.teams) * kPatchMeetings * p.n_patches
+        p.n_patches > 1 ? static_cast<int64_t>(a.teams) * patch_meeting_words(p.n_patches)
                          : 0;
     // (patches that share no link have no parts, but maxima, an abort word and a lambda all the same)
     int64_t grid = (std::max({words, maxima, n_terms, static_cast<int64_t>(plans),

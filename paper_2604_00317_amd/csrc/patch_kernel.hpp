@@ -17,7 +17,12 @@
 // exchange it belongs to -- loads are never negative.  Exchange n uses buffer n & 1 and the sign
 // (n >> 1) & 1; all words start with the sign set.  A patch overwrites its part of exchange n
 // with that of n + 2 only after it has read all parts of n + 1 of the groups it shares, which
-// their writers published after reading n: nobody misses a word.  Every wait is bounded; when one
+// their writers published after reading n: nobody misses a word.  The words of a patch lie side by
+// side, so that it writes whole cache lines: 256 patches that exchange 72 groups of 8 links with 15
+// others each and do nothing else take 7820 cycles per exchange where every part of a group is half a
+// line of its own, 5900 to 6400 this way; with 16 groups 4860 and 3700.  (Accumulators on the memory side that all users
+// add to, a patch per group that adds up the parts for the others, and one per XCD took 8400 to 13200.)
+// Every wait is bounded; when one
 // expires the team gives up, lambda becomes NaN, and whatever follows in the stream (launch_alone;
 // the host, after a solve of variable step) solves the plan without patches.  A limit of zero
 // means that nobody waits at all.
@@ -32,12 +37,12 @@
 // them as binary64 numbers one after the other, in code of its own (solve_wide: a branch in the
 // ordinary loop cost plans of one patch 4 to 15 %); several patches mark the plan as given up.
 //
-// What bounds it and what it measured, us per iteration against two launches per iteration (and,
-// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 2.64 -> 0.91 (one
-// patch: the chain scan, barrier, scatter, update; the LDS is busy for half of it), 7 nodes of 6
-// 7.1 -> 2.4 and 16 nodes 7.3 -> 2.8 (the trip of a word from patch to patch and the fixed steps take
-// 1.8), 64 nodes 18.5 -> 7.9 (the LDS is busy for 7200 of 19000 cycles, half of them bank conflicts;
-// then the parts of 31 users).
+// What bounds it and what it measured, us per iteration (in brackets: two launches per iteration and,
+// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 0.91 (2.64): one
+// patch, the chain scan, barrier, scatter, update; the LDS is busy for half of it; 7 nodes of 6 1.7 to
+// 2.0 (7.1) and 16 nodes 2.25 (7.3): the trip of a word from patch to patch, some 3000 cycles with
+// the reading of the words; 64 nodes 7.5 (18.5), 6.8 in blocks (patch_blocks.hpp): the words of up to
+// 31 users of every shared link, 131 KB per patch and iteration, then vector issue and LDS of the scan.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -63,18 +68,19 @@ struct LinkState {
     double len, S, invcap;
 };
 struct Lds {
-    int link, red, group, count, bytes;
+    int link, red, group, at, count, bytes;
 };
 
-__host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int n_comm, int slots,
+__host__ __device__ inline Lds lds_layout(int n_local, int n_groups, int n_at, int n_comm, int slots,
                                           int slot_bytes)
 {
     Lds l;
     int o = 8 * (n_local + 2);                  // [n_local] +0.0, [n_local + 1] +inf
     l.link = o;    o += static_cast<int>(sizeof(LinkState)) * n_local;
     l.red = o;     o += 8 * 40;
+    l.group = o;   o += 4 * (n_groups + 1);
+    l.at = o;      o += 2 * n_at;
     o = (o + 15) & ~15;
-    l.group = o;   o += 16 * n_groups;
     l.count = o;   o += slot_bytes * n_comm * slots;
     l.bytes = o;
     return l;
@@ -117,6 +123,7 @@ __device__ __forceinline__ uint32_t select(bool c, uint32_t a, uint32_t b)
 // the iterations (they never change) it would fill more registers than there are.
 __device__ __forceinline__ void keep_in_loop(uint32_t &v) { asm volatile("" : "+v"(v)); }
 __device__ __forceinline__ void keep_in_loop(double &v) { asm volatile("" : "+v"(v)); }
+__device__ __forceinline__ void keep_uniform(int &v) { asm volatile("" : "+s"(v)); }
 
 // How the loads of a patch are summed: as whole numbers of units of 2^unit, and where the demands
 // are no such whole numbers also of 2^(unit - kLowBits).  (That not even those hold them is noted
@@ -129,6 +136,7 @@ struct Demand {
     unsigned long long units, low;
 };
 
+template <int LOW = kLowBits>
 __device__ __forceinline__ Demand on_grid(double d, const Grid &gr)
 {
     const double h = trunc(ldexp(d, -gr.unit));
@@ -136,7 +144,7 @@ __device__ __forceinline__ Demand on_grid(double d, const Grid &gr)
     Demand n;
     n.units = static_cast<unsigned long long>(static_cast<long long>(h));
     n.low = static_cast<unsigned long long>(
-        static_cast<long long>(trunc(ldexp(r, kLowBits - gr.unit))));
+        static_cast<long long>(trunc(ldexp(r, LOW - gr.unit))));
     return n;
 }
 
@@ -162,15 +170,37 @@ __device__ __forceinline__ void add_loads(LinkState *links, uint32_t pad, const 
         if (off[x] < pad) lds_add(&reinterpret_cast<LinkState *>(base + off[x] * 5u)->low, d.low);
 }
 
+// the same where the loads of the links lie side by side
+template <int N>
+__device__ __forceinline__ void add_loads(unsigned long long *load, unsigned long long *low, uint32_t pad,
+                                          const uint32_t (&off)[N], const Grid &gr, const Demand &d)
+{
+    unsigned char *base = reinterpret_cast<unsigned char *>(load);
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        if (off[x] < pad) lds_add(reinterpret_cast<unsigned long long *>(base + off[x]), d.units);
+    if (gr.exact) return;                                               // wave-uniform
+    base = reinterpret_cast<unsigned char *>(low);
+#pragma unroll
+    for (int x = 0; x < N; ++x)
+        if (off[x] < pad) lds_add(reinterpret_cast<unsigned long long *>(base + off[x]), d.low);
+}
+
 // the load of a link, which starts at zero again
+template <int LOW = kLowBits>
+__device__ __forceinline__ double take_load(unsigned long long &load, unsigned long long &low,
+                                            const Grid &gr)
+{
+    const double hi = ldexp(static_cast<double>(static_cast<long long>(load)), gr.unit);
+    load = 0ull;
+    if (gr.exact) return hi;
+    const double lo = ldexp(static_cast<double>(static_cast<long long>(low)), gr.unit - LOW);
+    low = 0ull;
+    return hi + lo;
+}
 __device__ __forceinline__ double take_load(LinkState &s, const Grid &gr)
 {
-    const double hi = ldexp(static_cast<double>(static_cast<long long>(s.load)), gr.unit);
-    s.load = 0ull;
-    if (gr.exact) return hi;
-    const double lo = ldexp(static_cast<double>(static_cast<long long>(s.low)), gr.unit - kLowBits);
-    s.low = 0ull;
-    return hi + lo;
+    return take_load(s.load, s.low, gr);
 }
 
 // `near`: all who read the word run on this XCD and find it in its L2; the store need not go on to
@@ -222,59 +252,42 @@ __device__ __forceinline__ double add_across32(double v)
     return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
 
-// Loads of shared links, kGroupsAtOnce groups side by side: for every group lane 8j + i adds the
-// parts j, j + 8, ... of link i in order, then the eight partial sums are added in a fixed tree.
-// All words are asked for together and those that have not arrived asked for again, so that the
-// trips to memory of all groups overlap.  (The parts of a group are padded to a multiple of eight;
-// its users write the padding too, as zeros.)  Lane 8q + i returns the load of link i of group q
-// (q < kGroupsAtOnce).  `at` and `users`: first part and users of the groups (0 users: none).
-constexpr int kGroupsAtOnce = 4;
-constexpr int kPartsAtOnce = 4;
-// first part and parts of some groups, the same in all lanes (0 parts: no group)
-struct Bundle {
-    int at[kGroupsAtOnce], parts[kGroupsAtOnce];
-};
-__device__ __forceinline__ double group_loads(const double *parts, const Bundle &bu, unsigned phase,
-                                              unsigned limit, unsigned *abort_word, int &dead,
-                                              int lane)
+// Loads of shared links.  Every link has `lanes` lanes (1, 2 or 4, the same in all patches: as many as
+// there are threads for): lane `sub` of them adds up the parts of users sub, sub + lanes, ... in order,
+// then the partial sums are added in a fixed tree, so that all patches get the same bits.  NX words of a
+// lane are asked for together, and again as long as some have not arrived.  `at`: LDS address of where
+// the users of the link's group have their words; `link`: the link's place in its group; `most`: the
+// largest number of users.
+template <int NX>
+__device__ __forceinline__ double parts_of_link(const double *words, uint32_t at, int users, int most,
+                                                int sub, int lanes, uint32_t link, unsigned phase,
+                                                unsigned limit, unsigned *abort_word, int &dead)
 {
-    double sum[kGroupsAtOnce];
-    int most = 0;
-#pragma unroll
-    for (int q = 0; q < kGroupsAtOnce; ++q) {
-        sum[q] = 0.0;
-        most = most > bu.parts[q] ? most : bu.parts[q];
-    }
-    for (int c0 = 0; c0 < most; c0 += 8 * kPartsAtOnce) {           // wave-uniform, as all below
-        unsigned long long v[kGroupsAtOnce][kPartsAtOnce];
+    double sum = 0.0;
+    // (what follows from these is worked out here: kept over the iterations it would fill more
+    // registers than there are)
+    uint32_t n = static_cast<uint32_t>(users > sub ? users - sub : 0);     // of the users from `sub` on
+    keep_in_loop(n);
+    keep_in_loop(at);
+    keep_uniform(lanes);
+    at += 2 * static_cast<uint32_t>(n > 0 ? sub : 0);
+    for (int c = 0; c < most; c += NX * lanes) {                    // wave-uniform, as all below
+        unsigned long long v[NX];
         unsigned polls = 0;
         for (;;) {
             unsigned any = 0u, all = ~0u;
 #pragma unroll
-            for (int q = 0; q < kGroupsAtOnce; ++q) {
-                const double *src = parts + (bu.at[q] + c0 * kPatchGroup);
-                const int n = bu.parts[q] - c0;
-#pragma unroll
-                for (int x = 0; x < kPartsAtOnce; ++x)
-                    v[q][x] = static_cast<unsigned long long>(phase) << 63;
-                if (n > 0) {
-                    v[q][0] = get_word(src + static_cast<unsigned>(lane));
-                    if (n > 8) {
-                        v[q][1] = get_word(src + static_cast<unsigned>(lane) + 64);
-                        if (n > 16) {
-                            v[q][2] = get_word(src + static_cast<unsigned>(lane) + 128);
-                            if (n > 24) v[q][3] = get_word(src + static_cast<unsigned>(lane) + 192);
-                        }
-                    }
-                }
+            for (int x = 0; x < NX; ++x) {
+                const uint32_t u = c + x * lanes;        // (users there are not: the first one again)
+                const uint32_t unit = *reinterpret_cast<const uint16_t *>(s_lds + at + 2 * (u < n ? u : 0u));
+                v[x] = get_word(reinterpret_cast<const double *>(
+                    reinterpret_cast<const unsigned char *>(words) + (unit * (8u * kPatchGroup) + 8u * link)));
             }
 #pragma unroll
-            for (int q = 0; q < kGroupsAtOnce; ++q)
-#pragma unroll
-                for (int x = 0; x < kPartsAtOnce; ++x) {
-                    any |= static_cast<unsigned>(v[q][x] >> 32);
-                    all &= static_cast<unsigned>(v[q][x] >> 32);
-                }
+            for (int x = 0; x < NX; ++x) {
+                any |= static_cast<unsigned>(v[x] >> 32);
+                all &= static_cast<unsigned>(v[x] >> 32);
+            }
             const unsigned long long wrong =
                 phase ? __builtin_amdgcn_ballot_w64((all >> 31) == 0u)
                       : __builtin_amdgcn_ballot_w64((any >> 31) != 0u);
@@ -289,19 +302,23 @@ __device__ __forceinline__ double group_loads(const double *parts, const Bundle 
             }
         }
 #pragma unroll
-        for (int q = 0; q < kGroupsAtOnce; ++q)
-#pragma unroll
-            for (int x = 0; x < kPartsAtOnce; ++x) sum[q] = sum[q] + word_value(v[q][x]);
+        for (int x = 0; x < NX; ++x)
+            sum = sum + (static_cast<uint32_t>(c + x * lanes) < n ? word_value(v[x]) : 0.0);
     }
-    double mine = 0.0;
-#pragma unroll
-    for (int q = 0; q < kGroupsAtOnce; ++q) {
-        double t = sum[q] + dpp_f64<0x128>(sum[q]);     // row_ror:8, lane ^ 8
-        t = add_across16(t);
-        t = add_across32(t);
-        mine = (lane >> 3) == q ? t : mine;
-    }
-    return mine;
+    if (lanes > 1) sum = add_across32(sum);
+    if (lanes > 2) sum = add_across16(sum);
+    return sum;
+}
+// (the words of four, eight or sixteen users at a time)
+__device__ __forceinline__ double load_of_link(const double *words, uint32_t at, int users, int most,
+                                               int sub, int lanes, int link, unsigned phase,
+                                               unsigned limit, unsigned *abort_word, int &dead)
+{
+    if (most <= 4 * lanes)
+        return parts_of_link<4>(words, at, users, most, sub, lanes, link, phase, limit, abort_word, dead);
+    if (most <= 8 * lanes)
+        return parts_of_link<8>(words, at, users, most, sub, lanes, link, phase, limit, abort_word, dead);
+    return parts_of_link<16>(words, at, users, most, sub, lanes, link, phase, limit, abort_word, dead);
 }
 
 __device__ __forceinline__ double wave_sum(double v)
@@ -366,6 +383,129 @@ __device__ __forceinline__ double sum_in_order(const double *x, int n, unsigned 
         }
     }
     return s;
+}
+
+// How the demands of a patch are summed: d is this thread's (0: none).  Noted beside: they lie on no
+// grid.  (Called by all threads; ends with a barrier behind it to come.)
+__device__ __forceinline__ Grid find_grid(double d, double *red, int *s_wide, int n_waves, int wave,
+                                          int lane)
+{
+    // total and finest grid of the patch's demands
+    double sum = d;
+    int fine = 4096;
+    if (d != 0.0) {
+        const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(d));
+        const int ex = static_cast<int>((b >> 52) & 2047u);
+        const unsigned long long man = (b & ((1ull << 52) - 1ull)) | (ex ? 1ull << 52 : 0ull);
+        fine = (ex ? ex : 1) - 1075 + __ffsll(static_cast<long long>(man)) - 1;
+    }
+    sum = wave_sum(sum);
+    for (int o = 32; o > 0; o >>= 1) fine = min(fine, __shfl_xor(fine, o, kWave));
+    if (lane == 0) {
+        red[wave] = sum;
+        reinterpret_cast<int *>(red + 16)[wave] = fine;
+    }
+    __syncthreads();
+    double total = 0.0;
+    for (int q = 0; q < n_waves; ++q) {
+        total = total + red[q];
+        fine = min(fine, reinterpret_cast<const int *>(red + 16)[q]);
+    }
+    const bool some = total > 0.0 && total < __builtin_inf();
+    const int top = some ? ilogb(total) + 1 : 0;            // the total is below 2^top
+    Grid gr;
+    gr.exact = __builtin_amdgcn_readfirstlane(!some || top - fine <= 53 ? 1 : 0) != 0;
+    gr.unit = __builtin_amdgcn_readfirstlane(!some ? 0 : gr.exact ? fine : top - kSumBits);
+    if (threadIdx.x == 0)
+        *s_wide = total == __builtin_inf() || (some && top - fine > kSumBits + kLowBits);
+    return gr;
+}
+
+// Whether the patches p, p + every, p - every ... of the team are on this XCD.
+__device__ __forceinline__ bool on_one_xcd(double *maxima, const PatchArgs &a, int p, int every, double *red,
+                                           int &dead)
+{
+    double *ids = maxima + (kPatchMeetings - 1) * a.n_patches;
+    int *all = reinterpret_cast<int *>(red + 38);
+    const int id = __builtin_amdgcn_s_getreg(kXccId) & 15;
+    if (threadIdx.x == 0) {
+        *all = 1;
+        put_word(ids + p, static_cast<double>(id), 0u);
+    }
+    bool other = false;
+    for (int b = threadIdx.x; b < a.n_patches; b += blockDim.x) {
+        unsigned polls = 0;
+        unsigned long long v;
+        for (;;) {
+            v = get_word(ids + b);
+            if ((v >> 63) == 0ull || dead) break;
+            if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
+        }
+        other = other || dead || (b % every == p % every && word_value(v) != static_cast<double>(id));
+    }
+    dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
+    __syncthreads();
+    if (other) *all = 0;
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(*all) != 0;
+}
+
+// The largest v of all patches of the team (v: the patch's, in all threads).
+__device__ __forceinline__ double max_of_team(double v, double *maxima, unsigned &meeting,
+                                              const PatchArgs &a, int p, bool near, double *red,
+                                              int *s_flag, int &dead, int n_waves, int wave, int lane)
+{
+    double *mx = maxima + (meeting & 1u) * (kPatchCopies * a.n_patches);
+    const unsigned phase = (meeting >> 1) & 1u;
+    if (threadIdx.x == 0) put_word(mx + p, v, phase, near);
+    for (int b = threadIdx.x; b < a.n_patches; b += blockDim.x) {
+        unsigned polls = 0;
+        unsigned long long x;
+        for (;;) {
+            x = get_word(mx + b);
+            if (static_cast<unsigned>(x >> 63) == phase || dead) break;
+            if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
+        }
+        v = fmax(v, word_value(x));
+    }
+    meeting += 1u;
+    dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
+    v = wave_max(v);
+    __syncthreads();
+    if (lane == 0) red[wave] = v;
+    if (dead) *s_flag = 1;
+    __syncthreads();
+    for (int q = 0; q < n_waves; ++q) v = fmax(v, red[q]);
+    return v;
+}
+
+// By one thread of a patch: lambda as this patch has it.
+template <bool MULTI, bool ADAPT>
+__device__ __forceinline__ void report_lambda(double lam, const PatchArgs &a, int plan, const int *s_flag,
+                                              const int *s_wide)
+{
+    if constexpr (MULTI) {
+        // (the largest of non-negative numbers is the largest of their bit patterns, and a quiet NaN is
+        // above them all)
+        if ((*s_flag & 1) || *s_wide != 0) lam = __longlong_as_double(0x7FF8000000000000ll);
+        if (!ADAPT && *s_wide != 0)
+            __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        (void)__hip_atomic_fetch_max(reinterpret_cast<unsigned long long *>(a.lambda + plan),
+                                     static_cast<unsigned long long>(__double_as_longlong(lam)),
+                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        a.lambda[plan] = lam;
+    }
+}
+
+// a team that gave up leaves its other plans undone
+__device__ __forceinline__ void give_up_rest(const PatchArgs &a, int plan, int t)
+{
+    if (t == 0)
+        for (int rest = plan + a.teams; rest < a.plans; rest += a.teams)
+            (void)__hip_atomic_fetch_max(reinterpret_cast<unsigned long long *>(a.lambda + rest),
+                                         0x7FF8000000000000ull, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // One plan of a fabric of one patch whose demands no grid holds: the thread of a commodity scans
@@ -532,15 +672,16 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
     const int32_t *dsc = a.desc + kPatchDescInts * p;
     const int n_local = dsc[1], n_shared = MULTI ? dsc[2] : 0, n_groups = MULTI ? dsc[4] : 0;
     const int n_comm = dsc[6];
+    const int n_at = MULTI ? a.group[dsc[3] + n_groups] : 0;
     const int32_t *comm = a.comm + dsc[5];
     const int32_t *loc_link = a.loc_link + dsc[0];
     constexpr int kSlotBytes = ADAPT ? 32 : 8;
-    const Lds l = lds_layout(n_local, n_groups, n_comm, L * QL, kSlotBytes);
+    const Lds l = lds_layout(n_local, n_groups, n_at, n_comm, L * QL, kSlotBytes);
     const uint32_t pad = 8u * static_cast<uint32_t>(n_local);
     double *price = lds_ptr(0), *red = lds_ptr(l.red);
     LinkState *links = reinterpret_cast<LinkState *>(lds_ptr(l.link));
     int *s_flag = reinterpret_cast<int *>(red + 39), *s_wide = s_flag + 1;
-    int4 *groups = reinterpret_cast<int4 *>(s_lds + l.group);
+    int *groups = reinterpret_cast<int *>(s_lds + l.group);          // users of group q: from groups[q] on
 
     // this lane's share of the lists, for the whole solve
     const int j = t % L, g = t / L;
@@ -552,8 +693,11 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             w[q][x] = a.words[((static_cast<size_t>(p) * QL + q) * NW + x) * NT + t];
     const bool busy = (wave * kWave) / L < n_comm;         // this wave has commodities
     if constexpr (MULTI)
-        for (int q = t; q < n_groups; q += NT)
-            groups[q] = reinterpret_cast<const int4 *>(a.group)[dsc[3] + q];
+    {
+        for (int q = t; q <= n_groups; q += NT) groups[q] = a.group[dsc[3] + q];
+        for (int q = t; q < n_at; q += NT)
+            reinterpret_cast<uint16_t *>(s_lds + l.at)[q] = a.at[dsc[7] + q];
+    }
 
     unsigned exchange = 0u;          // exchanges made so far, the same in all patches of a team
     unsigned meeting = 0u;           // maxima folded over all patches so far
@@ -561,34 +705,16 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
     double *parts_of_team = nullptr, *maxima_of_team = nullptr;
     if constexpr (MULTI) {
         parts_of_team = a.parts + static_cast<size_t>(team) * 2 * a.n_parts;
-        maxima_of_team = a.maxima + static_cast<size_t>(team) * kPatchMeetings * a.n_patches;
+        maxima_of_team = a.maxima + static_cast<size_t>(team) * patch_meeting_words(a.n_patches);
     }
     bool near = false;               // the whole team is on this XCD
     if constexpr (MULTI)
-        if (a.near_xcds > 1) {
-            double *ids = maxima_of_team + (kPatchMeetings - 1) * a.n_patches;
-            const int id = __builtin_amdgcn_s_getreg(kXccId) & 15;
-            if (t == 0) {
-                *reinterpret_cast<int *>(red + 38) = 1;
-                put_word(ids + p, static_cast<double>(id), 0u);
-            }
-            bool other = false;
-            for (int b = t; b < a.n_patches; b += NT) {
-                unsigned polls = 0;
-                unsigned long long v;
-                for (;;) {
-                    v = get_word(ids + b);
-                    if ((v >> 63) == 0ull || dead) break;
-                    if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
-                }
-                other = other || dead || word_value(v) != static_cast<double>(id);
-            }
-            dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
-            __syncthreads();
-            if (other) *reinterpret_cast<int *>(red + 38) = 0;
-            __syncthreads();
-            near = __builtin_amdgcn_readfirstlane(*reinterpret_cast<int *>(red + 38)) != 0;
-        }
+        if (a.near_xcds > 1) near = on_one_xcd(maxima_of_team, a, p, 1, red, dead);
+    // ADAPT, a team that is spread: patches meet XCD by XCD
+    const bool by_xcd = MULTI && ADAPT && a.near_xcds == 1 && a.by_xcd != 0;
+    bool by_xcd_near = false;
+    if constexpr (MULTI && ADAPT)
+        if (by_xcd) by_xcd_near = on_one_xcd(maxima_of_team, a, p, kPatchXcds, red, dead);
 
     for (int plan = team; plan < a.plans; plan += MULTI ? a.teams : a.plans) {
         const double *demand = a.demand + static_cast<size_t>(plan) * a.K;
@@ -612,39 +738,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             price[n_local + 1] = __builtin_inf();
             *s_flag = 0;
         }
-        // total and finest grid of the patch's demands
-        Grid gr;
-        {
-            double sum = j == 0 ? d : 0.0;
-            int fine = 4096;
-            if (d != 0.0) {
-                const unsigned long long b =
-                    static_cast<unsigned long long>(__double_as_longlong(d));
-                const int ex = static_cast<int>((b >> 52) & 2047u);
-                const unsigned long long man =
-                    (b & ((1ull << 52) - 1ull)) | (ex ? 1ull << 52 : 0ull);
-                fine = (ex ? ex : 1) - 1075 + __ffsll(static_cast<long long>(man)) - 1;
-            }
-            sum = wave_sum(sum);
-            for (int o = 32; o > 0; o >>= 1) fine = min(fine, __shfl_xor(fine, o, kWave));
-            if (lane == 0) {
-                red[wave] = sum;
-                reinterpret_cast<int *>(red + 16)[wave] = fine;
-            }
-            __syncthreads();
-            double total = 0.0;
-            for (int q = 0; q < n_waves; ++q) {
-                total = total + red[q];
-                fine = min(fine, reinterpret_cast<const int *>(red + 16)[q]);
-            }
-            const bool some = total > 0.0 && total < __builtin_inf();
-            const int top = some ? ilogb(total) + 1 : 0;            // the total is below 2^top
-            gr.exact = __builtin_amdgcn_readfirstlane(!some || top - fine <= 53 ? 1 : 0) != 0;
-            gr.unit = __builtin_amdgcn_readfirstlane(
-                !some ? 0 : gr.exact ? fine : top - kSumBits);
-            if (t == 0)
-                *s_wide = total == __builtin_inf() || (some && top - fine > kSumBits + kLowBits);
-        }
+        const Grid gr = find_grid(j == 0 ? d : 0.0, red, s_wide, n_waves, wave, lane);
         const Demand units = on_grid(d, gr);
         // width rho: every commodity that can reach a link counts once
         if constexpr (!ADAPT) {
@@ -675,10 +769,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             }
         double wmax = 0.0;
         auto publish = [&](double v, int i) {
-            const int4 gd = groups[i / kPatchGroup];       // first part, parts, own part, users
-            double *dst = parts_of_team + (exchange & 1u) * a.n_parts + gd.x + i % kPatchGroup;
-            for (int c = gd.z; c < gd.y; c += gd.w)
-                put_word(dst + c * kPatchGroup, c == gd.z ? v : 0.0, (exchange >> 1) & 1u, near);
+            put_word(parts_of_team + (exchange & 1u) * a.n_parts + p * a.row * kPatchGroup + i, v,
+                     (exchange >> 1) & 1u, near);
         };
         if constexpr (!ADAPT)
             for (int i = t; i < n_local; i += NT) {
@@ -686,26 +778,18 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 if (MULTI && i < n_shared) publish(reach, i);
                 else wmax = fmax(wmax, reach * links[i].invcap);
             }
-        // f(local link, load) for the shared links, a lane each; the groups of a patch are dealt
-        // to its waves in bundles
-        auto bundle_of = [&](int q0) {
-            Bundle bu;
-#pragma unroll
-            for (int q = 0; q < kGroupsAtOnce; ++q) {
-                const int4 gd = groups[q0 + q < n_groups ? q0 + q : 0];
-                bu.at[q] = __builtin_amdgcn_readfirstlane(gd.x);
-                bu.parts[q] = q0 + q < n_groups ? __builtin_amdgcn_readfirstlane(gd.y) : 0;
-            }
-            return bu;
-        };
+        // f(local link, load) for the shared links
+        const int lanes = MULTI ? patch_link_lanes(NT, a.row) : 1;
+        const int per_wave = kWave / lanes;
         auto for_shared = [&](auto f) {
-            for (int q0 = wave * kGroupsAtOnce; q0 < n_groups; q0 += n_waves * kGroupsAtOnce) {
-                const Bundle bu = bundle_of(q0);
-                const double load =
-                    group_loads(parts_of_team + (exchange & 1u) * a.n_parts, bu,
-                                (exchange >> 1) & 1u, a.spin_limit, a.abort_word, dead, lane);
-                if (lane < kGroupsAtOnce * kPatchGroup && q0 + (lane >> 3) < n_groups)
-                    f(q0 * kPatchGroup + lane, load);
+            for (int i0 = wave * per_wave; i0 < n_shared; i0 += n_waves * per_wave) {
+                const int i = i0 + (lane & (per_wave - 1));
+                const int q = i < n_shared ? i / kPatchGroup : 0, from = groups[q];
+                const double load = load_of_link(
+                    parts_of_team + (exchange & 1u) * a.n_parts, l.at + 2 * from, groups[q + 1] - from,
+                    a.max_users, lane / per_wave, lanes, i & (kPatchGroup - 1), (exchange >> 1) & 1u,
+                    a.spin_limit, a.abort_word, dead);
+                if (lane < per_wave && i < n_shared) f(i, load);
             }
         };
         if constexpr (MULTI && !ADAPT) {
@@ -719,28 +803,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             __syncthreads();
             for (int q = 0; q < n_waves; ++q) wmax = fmax(wmax, red[q]);
             if constexpr (MULTI) {
-                // the maximum over all patches of the team
-                double *mx = maxima_of_team + (meeting & 1u) * (kPatchCopies * a.n_patches);
-                const unsigned phase = (meeting >> 1) & 1u;
-                if (t == 0) put_word(mx + p, wmax, phase, near);
-                for (int b = t; b < a.n_patches; b += NT) {
-                    unsigned polls = 0;
-                    unsigned long long v;
-                    for (;;) {
-                        v = get_word(mx + b);
-                        if (static_cast<unsigned>(v >> 63) == phase || dead) break;
-                        if (!keep_waiting(polls, a.spin_limit, a.abort_word)) dead = 1;
-                    }
-                    wmax = fmax(wmax, word_value(v));
-                }
-                meeting += 1u;
-                dead = __builtin_amdgcn_ballot_w64(dead != 0) != 0ull ? 1 : 0;
-                wmax = wave_max(wmax);
-                __syncthreads();
-                if (lane == 0) red[wave] = wmax;
-                if (dead) *s_flag = 1;
-                __syncthreads();
-                for (int q = 0; q < n_waves; ++q) wmax = fmax(wmax, red[q]);
+                wmax = max_of_team(wmax, maxima_of_team, meeting, a, p, near, red, s_flag, dead, n_waves,
+                                   wave, lane);
             }
         }
         const double invrho = wmax > 0.0 ? 1.0 / wmax : 0.0;
@@ -891,7 +955,38 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 if (MULTI ? wave == 0 : true)
                     for (int q = 0; q < n_waves; ++q) v = fmax(v, r[q]);
                 if constexpr (MULTI) {
-                    if (wave == 0) {
+                    if (wave == 0 && by_xcd) {
+                        // through the leader of the XCD (its first patch), so that every list is
+                        // read on one XCD or has eight words
+                        const unsigned phase = (meeting >> 1) & 1u;
+                        const int x = p % kPatchXcds;
+                        double *here = maxima_of_team + kPatchMeetings * a.n_patches +
+                                       (meeting & 1u) * kPatchTree / 2;
+                        double *all = here + kPatchXcds * kPatchXcdPatches;
+                        here += x * kPatchXcdPatches;
+                        if (lane == 0) put_word(here + p / kPatchXcds, v, phase, by_xcd_near);
+                        auto await_max = [&](const double *w, bool mine) {
+                            unsigned polls = 0;
+                            unsigned long long b = static_cast<unsigned long long>(phase) << 63;
+                            for (;;) {
+                                if (mine) b = get_word(w);
+                                if (__builtin_amdgcn_ballot_w64(static_cast<unsigned>(b >> 63) != phase) == 0ull ||
+                                    dead)
+                                    break;
+                                const int late = keep_waiting(polls, a.spin_limit, a.abort_word) ? 0 : 1;
+                                dead = __builtin_amdgcn_readfirstlane(late);
+                            }
+                            return word_value(b);
+                        };
+                        if (p < kPatchXcds) {
+                            const double m = wave_max(await_max(
+                                here + lane, lane < (a.n_patches - p + kPatchXcds - 1) / kPatchXcds));
+                            if (lane == 0) put_word(all + x * kPatchLine, m, phase);
+                        }
+                        v = await_max(all + lane * kPatchLine, lane < kPatchXcds);
+                        v = wave_max(v);
+                        if (lane == 0) r[0] = v;
+                    } else if (wave == 0) {
                         double *mx = maxima_of_team + (meeting & 1u) * (kPatchCopies * a.n_patches);
                         const unsigned phase = (meeting >> 1) & 1u;
                         if (lane < kPatchCopies)
@@ -1025,8 +1120,9 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 for (int i = t; i < n_local; i += NT) update(i, take_load(links[i], gr));
             }
             __syncthreads();
+            // (looked at now and then only: whoever has given up waits no more)
             if constexpr (MULTI)
-                if (__builtin_amdgcn_readfirstlane(*s_flag) != 0) break;     // workgroup-uniform
+                if ((it & 31) == 31 && __builtin_amdgcn_readfirstlane(*s_flag) != 0) break;    // uniform
         }
         const double T = ADAPT ? W : static_cast<double>(a.iters);
         if (g < n_comm) {
@@ -1068,32 +1164,13 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         __syncthreads();
         if (t == 0) {
             for (int q = 0; q < n_waves; ++q) smax = fmax(smax, red[q]);
-            double lam = ADAPT && !(T > 0.0) ? 0.0 : smax / T;
-            if constexpr (MULTI) {
-                // (the largest of non-negative numbers is the largest of their bit patterns, and
-                // a quiet NaN is above them all)
-                if ((*s_flag & 1) || *s_wide != 0) lam = __longlong_as_double(0x7FF8000000000000ll);
-                if (!ADAPT && *s_wide != 0)
-                    __hip_atomic_store(a.abort_word, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                (void)__hip_atomic_fetch_max(
-                    reinterpret_cast<unsigned long long *>(a.lambda + plan),
-                    static_cast<unsigned long long>(__double_as_longlong(lam)), __ATOMIC_RELAXED,
-                    __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                a.lambda[plan] = lam;
-            }
+            report_lambda<MULTI, ADAPT>(ADAPT && !(T > 0.0) ? 0.0 : smax / T, a, plan, s_flag, s_wide);
         }
-        if constexpr (MULTI) {
+        if constexpr (MULTI)
             if (!ADAPT && *s_flag != 0) {
-                // a team that gave up leaves its other plans undone
-                if (t == 0)
-                    for (int rest = plan + a.teams; rest < a.plans; rest += a.teams)
-                        (void)__hip_atomic_fetch_max(
-                            reinterpret_cast<unsigned long long *>(a.lambda + rest),
-                            0x7FF8000000000000ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                give_up_rest(a, plan, t);
                 break;
             }
-        }
     }
 }
 
