@@ -38,7 +38,7 @@
 // ordinary loop cost plans of one patch 4 to 15 %); several patches mark the plan as given up.
 //
 // What bounds it and what it measured, us per iteration (in brackets: two launches per iteration and,
-// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 0.91 (2.64): one
+// on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 0.84 (2.64): one
 // patch, the chain scan, barrier, scatter, update; the LDS is busy for half of it; 7 nodes of 6 1.7 to
 // 2.0 (7.1) and 16 nodes 2.25 (7.3): the trip of a word from patch to patch, some 3000 cycles with
 // the reading of the words; 64 nodes 7.5 (18.5), 6.8 in blocks (patch_blocks.hpp): the words of up to
@@ -825,6 +825,14 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         // candidate's weight (0: not this lane's to keep), and where `terms` is given the
         // commodity's term of the bound, demand times cheapest cost, is published there.
         auto pass = [&](double *terms, unsigned term_phase, uint32_t &mark) {
+            // Two slots a lane: every slot's candidates one by one.  That spares the second look at the
+            // best slot's prices, one trip to the LDS of the five in the chain of an iteration (2 nodes
+            // of 8 0.902 -> 0.835 us, with two NICs in reach 1.355 -> 1.230, 8 such nodes 2.27 -> 2.06).
+            // With one slot the prices are at hand anyway; it is the shorter code for the largest price
+            // (7 nodes of 6 2.01 -> 1.97) and for a variable step (16 nodes 5.54 -> 5.48), not for the sum
+            // (16 nodes 2.217 -> 2.229).  From three slots on the additions cost more than the trip (one
+            // patch of 24 GPUs 1.454 -> 1.492 with four, of 30 2.44 -> 2.60 with six).
+            constexpr bool kEach = PRODUCT && (QL == 2 || (QL == 1 && (MAXC || ADAPT)));
             double best = 0.0;
             uint32_t wb[NW];             // the slot that holds the best candidate so far
             int sb = 0, pos = 0;
@@ -837,15 +845,28 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                 double m;
                 int at = 0;
                 if constexpr (PRODUCT) {
-                    // Of the two ways to reach the middle link the cheaper one is the cheaper
-                    // one for every way on: rounded additions keep the order.  (Which of equally
-                    // cheap candidates comes first is settled below.)
                     const double mid = lds_lo(ws[2]);
                     const double t0 = join<MAXC>(join<MAXC>(lds_lo(ws[0]), lds_lo(ws[1])), mid);
                     const double t2 = join<MAXC>(join<MAXC>(lds_hi(ws[0]), lds_hi(ws[1])), mid);
-                    const double tm = fast_min_f64(t0, t2);
-                    m = fast_min_f64(join<MAXC>(join<MAXC>(tm, lds_lo(ws[3])), lds_lo(ws[4])),
-                                     join<MAXC>(join<MAXC>(tm, lds_hi(ws[3])), lds_hi(ws[4])));
+                    if constexpr (kEach) {
+                        const double d0 = lds_lo(ws[3]), d1 = lds_hi(ws[3]);
+                        const double e0 = lds_lo(ws[4]), e1 = lds_hi(ws[4]);
+                        const double c0 = join<MAXC>(join<MAXC>(t0, d0), e0);
+                        const double c1 = join<MAXC>(join<MAXC>(t0, d1), e1);
+                        const double c2 = join<MAXC>(join<MAXC>(t2, d0), e0);
+                        m = fast_min_f64(fast_min_f64(c0, c1),
+                                         fast_min_f64(c2, join<MAXC>(join<MAXC>(t2, d1), e1)));
+                        at = select(c2 == m, 2, 3);
+                        at = select(c1 == m, 1, at);
+                        at = select(c0 == m, 0, at);
+                    } else {
+                        // Of the two ways to reach the middle link the cheaper one is the cheaper
+                        // one for every way on: rounded additions keep the order.  (Which of equally
+                        // cheap candidates comes first is settled below.)
+                        const double tm = fast_min_f64(t0, t2);
+                        m = fast_min_f64(join<MAXC>(join<MAXC>(tm, lds_lo(ws[3])), lds_lo(ws[4])),
+                                         join<MAXC>(join<MAXC>(tm, lds_hi(ws[3])), lds_hi(ws[4])));
+                    }
                 } else {
                     double c[4];
 #pragma unroll
@@ -872,12 +893,12 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                     const bool better = m < best;
                     best = fast_min_f64(best, m);
                     sb = select(better, q, sb);
-                    if constexpr (!PRODUCT) pos = select(better, at, pos);
+                    if constexpr (!PRODUCT || kEach) pos = select(better, at, pos);
                     take_words<NW>(wb, w[q], better);
                 }
             }
             uint32_t off[5];
-            if constexpr (PRODUCT) {
+            if constexpr (PRODUCT && !kEach) {
                 // the candidates of the best slot, exactly: the first that costs `best`
                 const double mid = lds_lo(wb[2]);
                 const double t0 = join<MAXC>(join<MAXC>(lds_lo(wb[0]), lds_lo(wb[1])), mid);
