@@ -388,7 +388,7 @@ double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int
 
 // Builds the patch layouts of a fabric: the one with the fewest patches, which solves the most
 // plans side by side, the one whose estimate is lowest for a single plan, if that is another, and
-// one for solves of variable step if they fit neither.
+// the one for solves of variable step if that is a third.
 // (Layouts that would never be faster than what runs without them are not made.)
 hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, const int32_t *pl)
 {
@@ -416,7 +416,7 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
     const std::vector<nimble::PatchOption> options = nimble::choose_cuts(
         d.E, d.K, scan, t->n_cu, xcds_of(t), forced);
     for (const nimble::PatchOption &o : options) {
-        if (d.cost_max && &o == &options.back() && options.size() == 3) continue;
+        if (d.cost_max && o.variable_only) continue;         // (there is none of that cost)
         nimble::PatchCut cut;
         nimble::PatchLayout built;
         nimble::cut_patches(d.K, scan, o.grid, cut);
@@ -641,8 +641,8 @@ static const nimble::DevicePatches *adaptive_patches(const nimble_topo_t *t, int
         t->forced_regime != NIMBLE_REGIME_AUTO)
         return nullptr;
     // A step of variable size takes longer than one of fixed size: 0.9 us with one patch (2 nodes: 1.8
-    // against 0.9), 3.2 with several (16 nodes: 6.0 against 2.8; 24: 7.6 against 4.6), and about as
-    // much kernel by kernel (24 nodes: 13.9 against 10.7).
+    // against 0.9), 3.2 with several (16 nodes: 5.3 against 2.2), and about as much kernel by kernel
+    // (24 nodes: 13.9 against 10.7).
     constexpr double kOnePatch = 0.9, kMore = 3.2;
     const nimble::DevicePatches *best = nullptr;
     double best_us = t->patches_forced ? 1e30 : general_iteration_us(t, 1, true) + kMore;

@@ -838,8 +838,10 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
     if (best == nullptr) return out;
     out.push_back(*best);
     if (most != best) out.push_back(*most);
-    if (adaptive != nullptr && !best->sizes.fits_adaptive && !most->sizes.fits_adaptive)
+    if (adaptive != nullptr && adaptive != best && adaptive != most) {
         out.push_back(*adaptive);
+        out.back().variable_only = true;
+    }
     return out;
 }
 

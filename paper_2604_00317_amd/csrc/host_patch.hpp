@@ -247,12 +247,13 @@ struct PatchOption {
     PatchShape shape;
     PatchSizes sizes;
     double us = 0.0;             // estimate of an iteration of one plan
+    bool variable_only = false;  // made for solves of variable step alone
 };
 
 // The cut that solves the most plans in a time (by the estimates, `cus` compute units in `xcds`
 // XCDs) and the one with the lowest estimate for one plan, of those whose patches keep to their limits;
-// one of the two if they are the same.  If a solve of variable step fits neither, also the one with
-// the lowest estimate that it fits.
+// one of the two if they are the same.  If neither has the lowest estimate of those that a solve of
+// variable step fits (layouts of blocks have no such kernels), that one as well.
 std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan,
                                      int32_t cus, int32_t xcds, const PatchForced &forced);
 
