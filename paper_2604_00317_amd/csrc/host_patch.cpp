@@ -718,15 +718,23 @@ bool measure_blocks(const PatchScan &scan, const PatchCut &cut, PatchSizes &m, P
 {
     const int32_t L = scan.block_lanes;
     if (L == 0 || m.max_local > kPatchMaxLocal || m.max_groups == 0) return false;
-    PatchBlocks pb;
-    size_t comm = 0, heads = 0, tails = 0;
-    for (const std::vector<int32_t> &members : cut.members) {
-        find_blocks(scan, members, pb);
-        comm = std::max(comm, pb.comm.size());
-        heads = std::max(heads, pb.head_at.size());
-        tails = std::max(tails, pb.tail_at.size());
-        if (comm > static_cast<size_t>(kPatchThreads)) return false;
-    }
+    std::atomic<size_t> most_comm{0}, most_heads{0}, most_tails{0};
+    auto raise = [](std::atomic<size_t> &m, size_t v) {
+        size_t old = m.load();
+        while (old < v && !m.compare_exchange_weak(old, v)) {
+        }
+    };
+    parallel_ranges(static_cast<int64_t>(cut.members.size()), [&](int64_t b0, int64_t b1) {
+        PatchBlocks pb;
+        for (int64_t b = b0; b < b1 && most_comm.load() <= static_cast<size_t>(kPatchThreads); ++b) {
+            find_blocks(scan, cut.members[static_cast<size_t>(b)], pb);
+            raise(most_comm, pb.comm.size());
+            raise(most_heads, pb.head_at.size());
+            raise(most_tails, pb.tail_at.size());
+        }
+    }, std::max<int64_t>(1, 4096 / std::max<int64_t>(1, cut.most)));
+    const size_t comm = most_comm.load(), heads = most_heads.load(), tails = most_tails.load();
+    if (comm > static_cast<size_t>(kPatchThreads)) return false;
     shape = PatchShape();
     shape.blocks = 1;
     shape.product = scan.block_product;
@@ -786,27 +794,31 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
         const int32_t teams = n <= cus_of_xcd ? xcds * (cus_of_xcd / n) : cus / n;
         return o.us / std::max(1, teams);
     };
-    double best_us = 1e30, best_shared = 1e30;               // of the slots
-    auto try_blocks = [&](size_t i) {
-        PatchOption &o = tried[2 * i + 1];
-        o.grid = grids[i];
-        // (what the blocks of a cut come to at best is known without looking for them)
-        PatchOption least = o;
+    double best_us = 1e30, best_shared = 1e30;
+    // what the blocks of a cut come to at best is known without looking for them
+    auto least_of = [&](size_t i) {
+        PatchOption least = tried[2 * i + 1];
         least.sizes.max_comm = static_cast<int32_t>(cuts[i].most);
         least.shape.blocks = 1;
         least.shape.lanes = scan.block_lanes;
         least.shape.product = scan.block_product;
         least.shape.threads = std::max(64, (std::max(least.sizes.max_comm,
-                                                     kPatchGroup * o.sizes.max_groups) + 63) / 64 * 64);
+                                                     kPatchGroup * least.sizes.max_groups) + 63) / 64 * 64);
         least.us = patch_iteration_us(least.shape, least.sizes);
-        if (o.sizes.patches < 2 || scan.block_lanes == 0 ||
-            (forced.blocks < 0 && least.us >= best_us && shared_us(least) >= best_shared) ||
+        return least;
+    };
+    auto try_blocks = [&](size_t i, const PatchOption &least) {
+        PatchOption &o = tried[2 * i + 1];
+        o.grid = grids[i];
+        if ((forced.blocks < 0 && least.us >= best_us && shared_us(least) >= best_shared) ||
             !measure_blocks(scan, cuts[i], o.sizes, o.shape)) {
             o.sizes.fits = false;
             return;
         }
         o.sizes.fits_adaptive = false;                       // (there are no such kernels)
         o.us = patch_iteration_us(o.shape, o.sizes);
+        best_us = std::min(best_us, o.us);
+        best_shared = std::min(best_shared, shared_us(o));
     };
     // one patch that is done before words could go from patch to patch needs no comparison
     size_t from = 0;
@@ -823,10 +835,16 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
             best_us = std::min(best_us, o.us);
             best_shared = std::min(best_shared, shared_us(o));
         }
-    if (forced.blocks != 0 && (forced.lanes == 0 || forced.blocks > 0))
-        parallel_ranges(rest, [&](int64_t g0, int64_t g1) {
-            for (int64_t g = g0; g < g1; ++g) try_blocks(from + static_cast<size_t>(g));
-        }, grain);
+    if (scan.block_lanes > 0 && forced.blocks != 0 && (forced.lanes == 0 || forced.blocks > 0)) {
+        // the most promising first: most of the others need no look then
+        std::vector<std::pair<size_t, PatchOption>> least;
+        for (size_t i = from; i < grids.size(); ++i)
+            if (tried[2 * i + 1].sizes.patches > 1) least.emplace_back(i, least_of(i));
+        std::sort(least.begin(), least.end(), [](const auto &a, const auto &b) {
+            return a.second.us != b.second.us ? a.second.us < b.second.us : a.first < b.first;
+        });
+        for (const auto &c : least) try_blocks(c.first, c.second);
+    }
     const PatchOption *best = nullptr, *most = nullptr, *adaptive = nullptr;
     for (const PatchOption &o : tried) {
         if (!o.sizes.fits) continue;
