@@ -291,7 +291,7 @@ def main() -> int:
         total = plan_bytes(topo, r["patches"], bytes_, w.iters) * batch
         name = REGIME_NAMES.get(regime, "auto")
         if r["patches"] > 0:
-            name = f"k_patch, {r['patches']} workgroups per plan"
+            name = f"patch kernel, {r['patches']} workgroups per plan"
         roofline = dict(bound="hbm", kernel=name, achieved=total / sec / 1e9, peak=HBM_PEAK_GBS,
                         unit="GB/s", frac=total / sec / 1e9 / HBM_PEAK_GBS,
                         us_per_iteration=sec * 1e6 / w.iters, traffic=None)

@@ -8,8 +8,8 @@
 //   choose   the L lanes exchange costs so that lane j ends with the cheapest slot of commodity j:
 //            L - 1 exchanges for L commodities, most of them v_permlane swaps of whole half-waves;
 //   scatter  lane j finds the candidate within that slot and adds its demand to the loads of its links;
-//   update   as in patch_kernel.hpp, a link's length, price and congestion in registers of the lane
-//            that sums up its parts.
+//   update   as in patch_kernel.hpp, but length and congestion of a link in registers of the lane that
+//            sums up its parts.
 // What bounds it: the exchange (60 % of an iteration of the 64-node fabric), then the LDS in scan and
 // scatter (5200 of 16400 cycles, half of them bank conflicts of atomics and of gathers) and vector issue
 // (some 200 instructions of a wave outside the exchange, 400 with slots).  Against slots, us per
