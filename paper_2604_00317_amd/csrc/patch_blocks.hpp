@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_blocks(PatchArgs a)
             s.invcap = e >= 0 ? a.invcap[e & ~kPatchExport] : 0.0;
             s.len = a.len_in && e >= 0 ? a.len_in[e & ~kPatchExport] : 1.0;
             s.S = 0.0;
-            price[i] = MAXC ? s.len : s.len * s.invcap;
+            price[i] = link_price<MAXC>(s.len, s.invcap);
         };
         start(shared, s_link);
         start(mine, p_link);
@@ -318,7 +318,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_blocks(PatchArgs a)
             const double t1 = a.eps * gn;
             const double t2 = 1.0 + t1;
             s.len = s.len * t2;
-            price[i] = MAXC ? s.len : s.len * s.invcap;
+            price[i] = link_price<MAXC>(s.len, s.invcap);
         };
 
         // (the first round finds the width)

@@ -625,7 +625,7 @@ __device__ __forceinline__ void solve_wide(const PatchArgs &a, int plan, int n_c
             const double t2 = 1.0 + t1;
             const double ln = s.len * t2;
             s.len = ln;
-            price[i] = MAXC ? ln : ln * s.invcap;
+            price[i] = link_price<MAXC>(ln, s.invcap);
         }
         __syncthreads();
     }
@@ -730,7 +730,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             links[i].len = l0;
             links[i].S = 0.0;
             links[i].invcap = ic;
-            price[i] = MAXC ? l0 : l0 * ic;
+            price[i] = link_price<MAXC>(l0, ic);
         }
         for (int i = t; i < n_comm * L * QL * (kSlotBytes / 8); i += NT) lds_ptr(l.count)[i] = 0.0;
         if (t == 0) {
@@ -819,7 +819,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             const double t2 = 1.0 + t1;
             const double ln = s.len * t2;
             s.len = ln;
-            price[i] = MAXC ? ln : ln * ic;
+            price[i] = link_price<MAXC>(ln, ic);
         };
         // Scan and scatter of an iteration.  ADAPT: `mark` receives the LDS offset of the chosen
         // candidate's weight (0: not this lane's to keep), and where `terms` is given the
@@ -1081,7 +1081,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
                         const double t2 = 1.0 + t1;
                         const double ln = s.len * t2;
                         s.len = ln;
-                        price[i] = MAXC ? ln : ln * s.invcap;
+                        price[i] = link_price<MAXC>(ln, s.invcap);
                     }
                     if (mark != 0u) *lds_ptr(mark) = *lds_ptr(mark) + sigma;
                     done += 1;
