@@ -201,7 +201,7 @@ __global__ __launch_bounds__(1024) void k_resident(
                     const double t2 = 1.0 + t1;
                     const double ln = len[e] * t2;
                     len[e] = ln;
-                    price[e] = MAXC ? ln : ln * ic;
+                    price[e] = link_price<MAXC>(ln, ic);
                 }
             }
             __syncthreads();
@@ -248,7 +248,7 @@ __global__ __launch_bounds__(1024) void k_resident(
             const double t2 = 1.0 + t1;
             const double l = len[e] * t2;
             len[e] = l;
-            price[e] = MAXC ? l : l * ic;
+            price[e] = link_price<MAXC>(l, ic);
         }
         __syncthreads();
     }
@@ -457,7 +457,7 @@ __global__ __launch_bounds__(1024) void k_resident_coop(
                 const double t2 = 1.0 + t1;
                 const double ln = len[e] * t2;
                 len[e] = ln;
-                price[e] = MAXC ? ln : ln * ic;
+                price[e] = link_price<MAXC>(ln, ic);
             }
         }
         __syncthreads();
@@ -514,7 +514,9 @@ struct RegShared {
 // for 185 of the 205 thousand cycles a wave is there, then vector issue (131).  One node of 8 GPUs,
 // 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).  What
 // stays with the gather pays for the choice between them: 81.4 us as the only way, 83.3 with a count in
-// LDS per iteration and its pairs read one by one, 76.8 as it is (9 GPUs, 512 plans: 145.1, 158.0, 148.9).
+// LDS per iteration and its pairs read one by one, 79.3 as it is (9 GPUs, 512 plans: 145.1, 158.0, 151.4),
+// of which 1.7 (2.1) for prices that are numbers whatever the width (link_price).  A maximum is one
+// instruction, v_max_f64, in both: bottleneck cost, one plan 58.4 -> 47.6 us, 9 GPUs, 512 plans 161 -> 115.
 template <bool MAXC, bool ONEWAVE, int MAXP, bool DIRECT, int MAXROW>
 __global__ __launch_bounds__(1024) void k_resident_reg(
     int E, int K, int P, int batch, int nt_arg, int plans_per_block, double eps, int iters,
@@ -616,7 +618,9 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
     // the finest grid of the demands
     {
         const double wm = wave_max(reach * ic);
-        const double ws = wave_sum_f64(fabs(d));
+        // (a capacity without a finite reciprocal stands for a total that is none)
+        const double ws = __builtin_amdgcn_ballot_w64(ic == __builtin_inf()) != 0ull
+                              ? __builtin_inf() : wave_sum_f64(fabs(d));
         const int wf = wave_min_i32(lowest_bit(d));
         if ((threadIdx.x & (kWave - 1)) == 0) {
             sh.max[threadIdx.x >> 6] = wm;
@@ -634,12 +638,13 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
                 fine = min(fine, sh.fine[w0 + w]);
             }
             sh.invrho[slot] = (m > 0.0) ? 1.0 / m : 0.0;
-            // (One bit less than a double holds, for the rounding of the total.  Grids next to the
-            // denormals stay with the gather: the reciprocal of the width can be infinite there, and
-            // among lengths that are no numbers the tree of the scatter does not pick as the scan.
-            // Comparisons with a NaN are false.)
+            // (One bit less than a double holds, for the rounding of the total.  A width or a
+            // reciprocal of it that is infinite makes lengths that are no numbers: such plans stay with
+            // the gather, whose prices are numbers all the same; here that would be one operation
+            // more in the chain of an iteration.  Grids next to the denormals stay with it as well.)
             const bool on_grid = total == 0.0 || (total < __builtin_inf() && fine >= -900 &&
-                                                  ilogb(total) + 1 - fine <= 52);
+                                                  ilogb(total) + 1 - fine <= 52 &&
+                                                  m < __builtin_inf() && sh.invrho[slot] < __builtin_inf());
             if (ONEWAVE) sh.fine[w0] = on_grid ? 1 : 0;
             else if (!on_grid) sh.inexact = 1;
         }
@@ -649,8 +654,7 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
     const bool exact = __builtin_amdgcn_readfirstlane(
                            ONEWAVE ? sh.fine[slot] : 1 - sh.inexact) != 0;
 
-    // (`numbers`: prices are numbers; a maximum without that starts at 0 like the scan's)
-    auto path_costs = [&](double (&c)[MAXP], auto numbers) {
+    auto path_costs = [&](double (&c)[MAXP]) {
         // the prices of four candidates are requested before the first is used
         constexpr int kBatch = 4;
 #pragma unroll
@@ -666,30 +670,30 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
             for (int j = 0; j < kBatch; ++j) {
                 if (j0 + j >= MAXP) break;
                 double cj = pv[j][0];                    // 0 + p is p
-                if constexpr (MAXC && !numbers) cj = fast_max_f64(cj, 0.0);
                 if (!DIRECT || j0 + j > 0) {
-                    if constexpr (MAXC && !numbers) cj = fast_max_f64(cj, pv[j][1]);
-                    else if constexpr (MAXC) cj = (pv[j][1] > cj) ? pv[j][1] : cj;
+                    if constexpr (MAXC) cj = fast_max_f64(cj, pv[j][1]);
                     else cj = cj + pv[j][1];
                 }
                 c[j0 + j] = cj;
             }
         }
     };
-    auto step_link = [&](double load) {
+    // (`numbers`: every length is one)
+    auto step_link = [&](double load, auto numbers) {
         const double u = load * ic;
         S = S + u;
         const double g = u * invrho;
         const double t1 = eps * g;
         const double t2 = 1.0 + t1;
         len = len * t2;
-        *f64_at(price0 + 8u * t) = MAXC ? len : len * ic;
+        if constexpr (numbers) *f64_at(price0 + 8u * t) = MAXC ? len : len * ic;
+        else *f64_at(price0 + 8u * t) = link_price<MAXC>(len, ic);
     };
     if (exact) {
         for (int it = 0; it < iters; ++it) {
             double c[MAXP];
             uint32_t w[MAXP];
-            path_costs(c, std::true_type());
+            path_costs(c);
 #pragma unroll
             for (int j = 0; j < MAXP; ++j) w[j] = links[j];
             // the minimum as a tree over neighbours; of equal costs the left, so the lowest,
@@ -711,7 +715,7 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
             const unsigned long long taken = __hip_atomic_exchange(
                 reinterpret_cast<unsigned long long *>(f64_at(load0 + 8u * t)), 0ull,
                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-            step_link(__longlong_as_double(static_cast<long long>(taken)));
+            step_link(__longlong_as_double(static_cast<long long>(taken)), std::true_type());
             plan_sync();
         }
     } else {
@@ -767,16 +771,13 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
         for (int it = 0; it < iters; ++it) {
             if (has_k) {
                 double c[MAXP];
-                path_costs(c, std::false_type());
+                path_costs(c);
                 double best = c[0];
 #pragma unroll
                 for (int j = 1; j < MAXP; ++j) best = fast_min_f64(best, c[j]);
                 int bj = MAXP - 1;
 #pragma unroll
-                for (int j = MAXP - 2; j >= 1; --j) bj = (c[j] == best) ? j : bj;
-                // (also where the first cost is no number: a width without a finite reciprocal makes
-                // all lengths infinite or no numbers at once, and the scan then keeps the first)
-                bj = !(c[0] > best) ? 0 : bj;
+                for (int j = MAXP - 2; j >= 0; --j) bj = (c[j] == best) ? j : bj;
                 choice[t] = static_cast<uint8_t>(bj);
                 tally += 1ull << (8 * bj);
                 if ((it & 127) == 127) flush();
@@ -796,7 +797,7 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
                     const uint32_t h = ((wb4[i / 4] >> ch[i]) >> (8 * (i % 4))) & 1u;
                     load = __builtin_fma(dm[i], static_cast<double>(h), load);
                 }
-                step_link(load);
+                step_link(load, std::false_type());
             }
             plan_sync();
         }

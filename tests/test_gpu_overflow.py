@@ -7,6 +7,8 @@ import numpy as np
 import pytest
 
 from paper_2604_00317_amd import binding as B
+from paper_2604_00317_amd import workloads as W
+from test_gpu_resident_scatter import FABRICS, circulant
 from test_patch import _random, fabric
 from test_patch_blocks import SHAPES
 
@@ -35,12 +37,13 @@ def _overflowing(t, seed, plans):
     return csr, d
 
 
-def _check(oracle_mod, csr, d, iters, flags, patches=None):
+def _check(oracle_mod, csr, d, iters, flags, patches=None, regime=0, layout=0):
     n_links = csr[0]
     refs = [oracle_mod.solve(*csr, x, 0.05, iters, flags=flags, len0=np.ones(n_links)) for x in d]
     assert any(np.isnan(r["len"]).any() and np.isfinite(r["len"]).any() for r in refs)
-    h = B.nimble_topo_create(*csr, flags=flags)
+    h = B.nimble_topo_create(*csr, flags=flags | layout)
     try:
+        B.nimble_topo_set_regime(h, regime)
         splits, lam = B.plan(h, d, 0.05, iters)
         used = h.last_patches
         for b, ref in enumerate(refs):
@@ -124,3 +127,49 @@ def test_demands_no_grid_holds(oracle_mod, monkeypatch):
     d[0, 100] = 2.0 ** -100
     print("[overflow] one patch, no grid", flush=True)
     _check(oracle_mod, csr, d, 60, 0, patches=1)
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("where", FABRICS, ids=lambda f: f"{f[0]}{f[1]}")
+def test_one_commodity_and_link_per_thread(oracle_mod, where, flags):
+    """k_resident_reg, whole bytes and fractions; and capacities without a finite reciprocal on links that
+    carry nothing, so that the width is an ordinary number and 0 * inf is the load over a capacity."""
+    kind, what = where
+    if kind == "node":
+        t = W.build_fabric(1, what)
+    elif kind == "mesh":
+        t = W.two_candidate_mesh(what)
+    elif kind == "circulant":
+        t = circulant(*what)
+    else:
+        t = W.random_topology(np.random.default_rng(what[0]), what[1], what[2], what[3], min(2, what[1]))
+    print(f"[overflow registers] {where} flags={flags}", flush=True)
+    if t.n_links > 1:
+        csr, d = _overflowing(t, 8, 3)
+        d[2] /= 7.0
+        _check(oracle_mod, csr, d, 40, flags)
+    rng = np.random.default_rng(9)
+    d = np.where(rng.random((2, t.n_comm)) < 0.1, np.floor(rng.random((2, t.n_comm)) * 1e6) + 1.0, 0.0)
+    path_comm = np.repeat(np.arange(t.n_comm), np.diff(t.comm_path_ptr))
+    reach = np.zeros(t.n_links)
+    np.maximum.at(reach, t.path_links, np.repeat(d.max(axis=0)[path_comm], np.diff(t.path_link_ptr)))
+    csr = list(t.csr())
+    csr[1] = np.where((reach == 0) & (np.arange(t.n_links) % 2 == 0), 1e-310, t.cap)
+    if (reach == 0).sum() > 2 and d.any(axis=1).all():
+        _check(oracle_mod, csr, d, 40, flags)
+
+
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("generic", [False, True])
+def test_resident(oracle_mod, monkeypatch, generic, flags):
+    """One workgroup per plan: lanes that share commodities, with lists in registers or not, and a thread
+    per commodity."""
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", "0")
+    if generic:
+        monkeypatch.setenv("NIMBLE_TUNE_RESIDENT_GENERIC", "1")
+    for name in ((1, 8, "none"), (2, 8, "pair"), (3, 4, "xor"), (13, 200, 150, 20, 4), (5, 500, 900, 12, 2),
+                 (20, 100, 90, 20, 5), (18, 60, 80, 3, 4)):
+        t = _random(*name) if len(name) > 3 else fabric(*name)
+        print(f"[overflow resident] {name} generic={generic} flags={flags}", flush=True)
+        csr, d = _overflowing(t, 11, 2)
+        _check(oracle_mod, csr, d, 40, flags, regime=B.NIMBLE_REGIME_RESIDENT)
