@@ -154,7 +154,7 @@ __device__ __forceinline__ void solve_plan(const PersistentArgs &a, unsigned int
         const int e = a.pos_link[i];             // lengths and sums by position, prices by link id
         const double l0 = a.len_in != nullptr ? a.len_in[e] : 1.0;
         a.len[i] = l0;
-        a.price[e] = MAXC ? l0 : l0 * a.invcap[e];
+        a.price[e] = link_price<MAXC>(l0, a.invcap[e]);
         a.S[i] = 0.0;
     }
     for (int p = tid; p < a.P; p += n_threads) a.count[p] = 0u;

@@ -59,7 +59,7 @@ __global__ __launch_bounds__(kBlock) void k_init(int E, int K, int P, bool cost_
     // are kept by position in the flat order of the rows, the price by link id
     for (int e = tid; e < E; e += stride) {
         const double l_e = len_in ? len_in[e] : 1.0;
-        price[e] = cost_max ? l_e : l_e * invcap[e];
+        price[e] = cost_max ? link_price<true>(l_e, 1.0) : link_price<false>(l_e, invcap[e]);
         len[e] = len_in ? len_in[pos_link[e]] : 1.0;      // here e is a position
         S[e] = 0.0;
     }
@@ -378,8 +378,8 @@ struct PriceTerms<true, MAXC> {
         const double t1 = eps * su;
         const double t2 = 1.0 + t1;
         const double ln = v[q] * t2;
-        if constexpr (MAXC) return ln;
-        else return ln * c[q];
+        if constexpr (MAXC) return link_price<true>(ln, 1.0);
+        else return link_price<false>(ln, c[q]);
     }
 };
 
@@ -899,7 +899,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_update(FusedArgs a)
                 const double t2 = 1.0 + t1;
                 const double ln = st.l * t2;
                 a.len[i] = ln;
-                a.price[st.e] = MAXC ? ln : ln * st.ic;
+                a.price[st.e] = link_price<MAXC>(ln, st.ic);
                 smax = fmax(smax, s_new);
             }
         }
@@ -1039,7 +1039,7 @@ __global__ __launch_bounds__(1024) void k_group_reduce_update(GroupArgs a)
                 const double t2e = 1.0 + t1e;
                 const double ln = st.l * t2e;
                 a.len[i] = ln;
-                a.price[st.e] = MAXC ? ln : ln * st.ic;
+                a.price[st.e] = link_price<MAXC>(ln, st.ic);
                 smax = fmax(smax, s_new);
             }
         }
@@ -1153,7 +1153,7 @@ __global__ __launch_bounds__(kBlock) void k_reduce_update_multi(FusedArgs a)
                 const double t2 = 1.0 + t1;
                 const double ln = l_old[u] * t2;
                 len[u][i] = ln;
-                price[u][e] = MAXC ? ln : ln * ic;
+                price[u][e] = link_price<MAXC>(ln, ic);
                 smax[u] = fmax(smax[u], s_new);
             }
         }

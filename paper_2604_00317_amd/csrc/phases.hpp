@@ -672,7 +672,7 @@ __device__ __forceinline__ double update_phase(int E, double eps, double invrho,
             const double t2 = 1.0 + t1;
             const double ln = l_old * t2;
             len[i] = ln;
-            price[e] = MAXC ? ln : ln * ic;
+            price[e] = link_price<MAXC>(ln, ic);
             smax = fmax(smax, s_new);
         }
     }
@@ -741,7 +741,7 @@ __device__ __forceinline__ void ad_apply_block(const AdApplyArgs &a, int block, 
         const double ln = l_old * t2;
         a.len[i] = ln;
         a.len_id_new[e_i] = ln;
-        a.price[e_i] = MAXC ? ln : ln * cap_i;
+        a.price[e_i] = link_price<MAXC>(ln, cap_i);
     }
     __syncthreads();
     const double sm = block_max(s_new, red);

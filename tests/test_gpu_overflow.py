@@ -160,6 +160,21 @@ def test_one_commodity_and_link_per_thread(oracle_mod, where, flags):
 
 
 @pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("layout", [0, 2])
+@pytest.mark.parametrize("regime", [B.NIMBLE_REGIME_STREAM, B.NIMBLE_REGIME_PERSISTENT])
+def test_streamed(oracle_mod, regime, layout, flags):
+    """Record kernels and the reduce kernels of every layout, one plan and three; several waves of a row."""
+    for name in ((2, 8, "pair"), (7, 6, "pair"), (3, 8, "xor"), (8, 4, "own"), (5, 500, 900, 12, 2),
+                 (13, 200, 150, 20, 4), (16, 300, 700, 40, 7)):
+        t = _random(*name) if len(name) > 3 else fabric(*name)
+        print(f"[overflow streamed] {name} regime={regime} layout={layout} flags={flags}", flush=True)
+        csr, d = _overflowing(t, 10, 3)
+        if regime == B.NIMBLE_REGIME_STREAM:
+            _check(oracle_mod, csr, d, 30, flags, regime=regime, layout=layout)
+        _check(oracle_mod, csr, d[:1], 30, flags, regime=regime, layout=layout)
+
+
+@pytest.mark.parametrize("flags", [0, 1])
 @pytest.mark.parametrize("generic", [False, True])
 def test_resident(oracle_mod, monkeypatch, generic, flags):
     """One workgroup per plan: lanes that share commodities, with lists in registers or not, and a thread
