@@ -196,7 +196,8 @@ __global__ __launch_bounds__(kAdBlock) void k_ad_lambda(int n_s_blocks,
     const double smax = block_max(m, red);            // (its barriers also publish s_sum)
     if (threadIdx.x != 0) return;
     const double W = ascal[0];
-    const double lam = W > 0.0 ? smax / W : 0.0;
+    // (steps of zero, where the largest load over a capacity is infinite: 0 / 0, no number)
+    const double lam = flags[1] > 0 ? smax / W : 0.0;
     ascal[3] = lam;
     if (check) {
         const double lb = s_sum[0] / s_sum[1];

@@ -950,7 +950,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             }
         };
 
-        double W = 0.0;                  // ADAPT: sum of the steps
+        double W = 0.0;                  // ADAPT: sum of the steps, their number
+        int done = 0;
         if constexpr (ADAPT) {
             // Iteration t steps by sigma = 1 / (largest normalised load of any link), so all
             // patches meet once more per iteration.  Every check_every iterations the bound
@@ -962,7 +963,7 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             const int64_t n_words = static_cast<int64_t>(a.K) + a.E + n_alpha + n_d;
             const double gap = (1.0 + a.eps) * (1.0 + a.eps);
             double lb_best = 0.0;
-            int done = 0, until_check = a.check_every;
+            int until_check = a.check_every;
             unsigned checks = 0u;
             // The largest v of all patches; `row` alternates between calls.  The first wave leaves
             // its patch's maximum in every copy of the list and waits for the others' in its own
@@ -1185,7 +1186,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
         __syncthreads();
         if (t == 0) {
             for (int q = 0; q < n_waves; ++q) smax = fmax(smax, red[q]);
-            report_lambda<MULTI, ADAPT>(ADAPT && !(T > 0.0) ? 0.0 : smax / T, a, plan, s_flag, s_wide);
+            // (ADAPT, steps of zero where the largest load over a capacity is infinite: 0 / 0, no number)
+            report_lambda<MULTI, ADAPT>(ADAPT && done == 0 ? 0.0 : smax / T, a, plan, s_flag, s_wide);
         }
         if constexpr (MULTI)
             if (!ADAPT && *s_flag != 0) {

@@ -9,7 +9,7 @@ import pytest
 from paper_2604_00317_amd import binding as B
 from paper_2604_00317_amd import workloads as W
 from test_gpu_resident_scatter import FABRICS, circulant
-from test_patch import _random, fabric
+from test_patch import _adaptive, _random, fabric
 from test_patch_blocks import SHAPES
 
 pytestmark = pytest.mark.gpu
@@ -188,3 +188,29 @@ def test_resident(oracle_mod, monkeypatch, generic, flags):
         print(f"[overflow resident] {name} generic={generic} flags={flags}", flush=True)
         csr, d = _overflowing(t, 11, 2)
         _check(oracle_mod, csr, d, 40, flags, regime=B.NIMBLE_REGIME_RESIDENT)
+
+
+@pytest.mark.parametrize("strips", [0, 1, 3])
+@pytest.mark.parametrize("kind", ["all", "few", "capacities"])
+def test_variable_step(oracle_mod, monkeypatch, kind, strips):
+    """Steps of zero (the largest load over a capacity is infinite): splits stay on the first candidates,
+    lambda is 0 / 0, no number, and never below a bound; loads just below the largest double; and
+    capacities without a finite reciprocal."""
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    for name in ((2, 8, "pair"), (3, 4, "xor"), (7, 6, "pair")):
+        t = fabric(*name)
+        csr, d = _overflowing(t, 3, 1)
+        if kind == "few":
+            csr[1] = csr[1] * 30.0
+        elif kind == "capacities":
+            csr[1] = np.where(np.arange(t.n_links) % 5 == 0, 1e-310, t.cap)
+        print(f"[overflow adaptive] {name} {kind} strips={strips}", flush=True)
+        ref = oracle_mod.solve_adaptive(*csr, d[0], 0.05, 40, 7)
+        h = B.nimble_topo_create(*csr)
+        try:
+            splits, lam, done, lb = _adaptive(h, t, d[0], 0.05, 40, 7)
+            assert (done, lb) == (ref["iters"], ref["lb"])
+            assert np.array_equal([lam], [ref["lam"]], equal_nan=True)
+            assert np.array_equal(splits, ref["splits"])
+        finally:
+            h.close()
