@@ -231,6 +231,17 @@ nimble_status_t nimble_host_grid_check(int32_t n_links, int32_t n_comm,
                                        const int32_t *path_link_ptr, const int32_t *path_links,
                                        int32_t strips_x, int32_t strips_y, int32_t blocks, int64_t *out);
 
+/* The patch layouts nimble_topo_create would choose on a device of `cus` compute units in `xcds` XCDs, and
+ * whether they can be built.  strips_x, strips_y, lanes, blocks: what the switches ask for
+ * (0, 0, 0, -1: nothing).  out[8 * i ...]: strips of layout i in either direction, patches, most groups of
+ * a patch, 1 for blocks, lanes, 1 when it is there for solves of variable step alone, and 0 or the number
+ * of the check its build failed (-1: it was refused).  n_out: how many there are, at most 3. */
+nimble_status_t nimble_host_patch_choice(int32_t n_links, int32_t n_comm,
+                                         const int32_t *comm_path_ptr, int32_t n_paths,
+                                         const int32_t *path_link_ptr, const int32_t *path_links,
+                                         int32_t cus, int32_t xcds, int32_t strips_x, int32_t strips_y,
+                                         int32_t lanes, int32_t blocks, int64_t out[24], int32_t *n_out);
+
 #ifdef __cplusplus
 }
 #endif

@@ -37,7 +37,8 @@ EXPORTS = [
     "nimble_plan_solve_static", "nimble_static_scratch_bytes", "nimble_debug_barrier_probe",
     "nimble_topo_reserve_batch", "nimble_debug_fail_allocation",
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
-    "nimble_host_patch_check", "nimble_host_grid_check", "nimble_debug_patches_gave_up",
+    "nimble_host_patch_check", "nimble_host_grid_check", "nimble_host_patch_choice",
+    "nimble_debug_patches_gave_up",
     "nimble_debug_refuse_cooperative", "nimble_debug_fail_patch_build",
     "nimble_topo_last_patches", "nimble_topo_alg1_form",
 ]
@@ -139,6 +140,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.nimble_plan_quantize.argtypes = [vp, vp, vp, i32, ctypes.c_int64, ctypes.c_double, vp, vp]
     lib.nimble_host_grid_check.restype = ctypes.c_int
     lib.nimble_host_grid_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, i32, vp]
+    lib.nimble_host_patch_choice.restype = ctypes.c_int
+    lib.nimble_host_patch_choice.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, i32, i32, i32, i32, vp, vp]
     lib.nimble_host_patch_check.restype = ctypes.c_int
     lib.nimble_host_patch_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, vp]
     lib.nimble_host_layout_stats.restype = ctypes.c_int
@@ -490,6 +493,23 @@ def nimble_host_grid_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_pt
             "max_local", "max_groups", "max_users", "max_parts", "parts", "max_comm", "max_at",
             "max_heads", "max_tails", "max_private"]
     return dict(zip(keys, (int(v) for v in out)))
+
+
+def nimble_host_patch_choice(n_links, n_comm, comm_path_ptr, n_paths, path_link_ptr, path_links, cus=256,
+                             xcds=8, strips=(0, 0), lanes=0, blocks=-1):
+    """Host-only: the patch layouts nimble_topo_create would choose, a list of dicts (see
+    include/nimble_plan_debug.h); `failed` is 0 for a layout that can be built and reads back."""
+    cp = _host(comm_path_ptr, np.int32)
+    lp = _host(path_link_ptr, np.int32)
+    pl = _host(path_links, np.int32)
+    out = np.zeros((3, 8), dtype=np.int64)
+    n = np.zeros(1, dtype=np.int32)
+    st = load_library().nimble_host_patch_choice(n_links, n_comm, _hp(cp), n_paths, _hp(lp), _hp(pl), cus,
+                                                 xcds, strips[0], strips[1], lanes, blocks, _hp(out), _hp(n))
+    if st != NIMBLE_OK:
+        raise NimbleError(st, "invalid CSR")
+    keys = ["x", "y", "patches", "max_groups", "blocks", "lanes", "variable_only", "failed"]
+    return [dict(zip(keys, (int(v) for v in row))) for row in out[:int(n[0])]]
 
 
 def plan(topo: Topo, traffic, eps: float, iters: int, device: str = "cuda:0"):

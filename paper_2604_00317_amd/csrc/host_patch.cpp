@@ -590,7 +590,7 @@ double patch_iteration_us(const PatchShape &s, const PatchSizes &m)
     // a patch publishes; the words it reads; then what the commodities take.
     const bool near = m.patches <= kPatchXcdPatches;
     const double waves = s.threads / 64.0;
-    const int32_t lanes = patch_link_lanes(s.threads, (m.max_groups + 1) / 2 * 2);
+    const int32_t lanes = patch_link_lanes(s.threads, patch_row(m.max_groups));
     const int32_t per_round = s.threads / lanes;
     const double rounds = (m.max_groups * kPatchGroup + per_round - 1) / per_round;
     const int32_t words = (m.max_users + lanes - 1) / lanes;
@@ -709,7 +709,8 @@ PatchSizes measure_cut(int32_t n_links, const PatchScan &scan, const PatchCut &c
     // (prices, link states, groups and counts: lds_layout in patch_kernel.hpp)
     const int64_t links_lds = 48ll * m.max_local + 2ll * m.max_at + 4ll * m.max_groups + 512;
     const int64_t slots = static_cast<int64_t>(m.max_comm) * shape.lanes * shape.quads;
-    m.fits = m.max_local <= kPatchMaxLocal && links_lds + 8 * slots <= kPatchLdsBytes;
+    m.fits = m.max_local <= kPatchMaxLocal && links_lds + 8 * slots <= kPatchLdsBytes &&
+             static_cast<int64_t>(B) * patch_row(m.max_groups) <= kPatchMaxUnits;
     m.fits_adaptive = m.fits && links_lds + 32 * slots <= kPatchLdsBytes;
     return m;
 }
@@ -717,7 +718,9 @@ PatchSizes measure_cut(int32_t n_links, const PatchScan &scan, const PatchCut &c
 bool measure_blocks(const PatchScan &scan, const PatchCut &cut, PatchSizes &m, PatchShape &shape)
 {
     const int32_t L = scan.block_lanes;
-    if (L == 0 || m.max_local > kPatchMaxLocal || m.max_groups == 0) return false;
+    if (L == 0 || m.max_local > kPatchMaxLocal || m.max_groups == 0 ||
+        static_cast<int64_t>(m.patches) * patch_row(m.max_groups) > kPatchMaxUnits)
+        return false;
     std::atomic<size_t> most_comm{0}, most_heads{0}, most_tails{0};
     auto raise = [](std::atomic<size_t> &m, size_t v) {
         size_t old = m.load();
@@ -991,9 +994,8 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
         }
         out.max_comm = std::max(out.max_comm, d[6]);
     }
-    // (an even number of units: rows begin with a cache line)
-    out.row = (out.max_groups + 1) / 2 * 2;
-    if (static_cast<int64_t>(B) * out.row > 65536) return false;
+    out.row = patch_row(out.max_groups);
+    if (static_cast<int64_t>(B) * out.row > kPatchMaxUnits) return false;
     out.n_parts = static_cast<int64_t>(B) * out.row * kPatchGroup;
     out.loc_link.assign(first_local[B], -1);
     for (int32_t b = 0; b < B; ++b) {
@@ -1433,6 +1435,52 @@ nimble_status_t host_check(int32_t n_links, int32_t n_comm, const int32_t *cp, c
 }  // namespace
 
 }  // namespace nimble
+
+extern "C" nimble_status_t nimble_host_patch_choice(int32_t n_links, int32_t n_comm,
+                                                     const int32_t *comm_path_ptr, int32_t n_paths,
+                                                     const int32_t *path_link_ptr,
+                                                     const int32_t *path_links, int32_t cus, int32_t xcds,
+                                                     int32_t strips_x, int32_t strips_y, int32_t lanes,
+                                                     int32_t blocks, int64_t *out, int32_t *n_out)
+{
+    try {
+        std::string why;
+        const nimble_status_t st = nimble::validate_csr(n_links, nullptr, n_comm, comm_path_ptr, n_paths,
+                                                        path_link_ptr, path_links, why);
+        if (st != NIMBLE_OK) return st;
+        if (!out || !n_out || cus < 1 || xcds < 1 || lanes < 0) return NIMBLE_ERR_INVALID;
+        nimble::PatchForced forced;
+        forced.grid = nimble::PatchGrid{strips_x, strips_y};
+        forced.lanes = lanes;
+        forced.blocks = blocks;
+        *n_out = 0;
+        nimble::PatchScan scan;
+        nimble::scan_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links, scan);
+        if (!scan.fits) return NIMBLE_OK;
+        for (const nimble::PatchOption &o :
+             nimble::choose_cuts(n_links, n_comm, scan, cus, xcds, forced)) {
+            nimble::PatchCut cut;
+            nimble::PatchLayout built;
+            nimble::cut_patches(n_comm, scan, o.grid, cut);
+            int64_t *row = out + 8 * (*n_out)++;
+            row[0] = o.grid.x;
+            row[1] = o.grid.y;
+            row[2] = o.sizes.patches;
+            row[3] = o.sizes.max_groups;
+            row[4] = o.shape.blocks;
+            row[5] = o.shape.lanes;
+            row[6] = o.variable_only ? 1 : 0;
+            row[7] = -1;
+            if (nimble::build_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links, scan, cut,
+                                      o.shape, built))
+                row[7] = nimble::check_patches(n_links, n_comm, comm_path_ptr, path_link_ptr, path_links,
+                                               built);
+        }
+        return NIMBLE_OK;
+    } catch (const std::exception &) {
+        return NIMBLE_ERR_ALLOC;
+    }
+}
 
 extern "C" void nimble_debug_fail_patch_build(int32_t where) { nimble::g_fault.store(where); }
 

@@ -45,6 +45,7 @@ namespace nimble {
 constexpr int32_t kPatchGroup = 8;
 constexpr int32_t kPatchThreads = 1024;
 constexpr int32_t kPatchMaxLocal = 2900;      // local links whose state fits the LDS
+constexpr int32_t kPatchMaxUnits = 65536;     // groups' places in an exchange buffer, numbered in 16 bits
 constexpr int32_t kPatchExport = 1 << 30;     // in loc_link: this patch writes the link's results
 constexpr int32_t kPatchDescInts = 12;
 constexpr int32_t kPatchCopies = 8;           // of the list of maxima the patches meet over
@@ -159,6 +160,8 @@ struct PatchLayout {
     std::vector<uint16_t> at;
     int32_t row = 0;                // of units per patch
 };
+// (an even number of units: rows begin with a cache line)
+constexpr int32_t patch_row(int32_t max_groups) { return (max_groups + 1) / 2 * 2; }
 
 // What a fabric's commodities need, found once and used for every grid that is tried.
 struct PatchScan {

@@ -726,6 +726,44 @@ def test_teams_of_one_xcd_and_of_several(monkeypatch, strips, patches):
         h.close()
 
 
+def part_of(t, seed, pairs, paths):
+    """A fabric of which a share `pairs` of the commodities is planned for, with a share `paths` of their
+    candidates (at least one)."""
+    rng = np.random.default_rng(seed)
+    comm = np.repeat(np.arange(t.n_comm), np.diff(t.comm_path_ptr))
+    on = rng.random(t.n_comm) < pairs
+    keep = rng.random(t.n_paths) < paths
+    some = np.zeros(t.n_comm, dtype=bool)
+    some[comm[keep]] = True
+    keep[t.comm_path_ptr[:-1][~some]] = True
+    keep &= on[comm]
+    lens = np.diff(t.path_link_ptr)
+    k = int(on.sum())
+    zeros = np.zeros(k, dtype=np.int32)
+    return W.Topology(n_links=t.n_links, cap=t.cap, n_comm=k,
+                      comm_path_ptr=np.concatenate([[0], np.cumsum(np.bincount(
+                          comm[keep], minlength=t.n_comm)[on])]).astype(np.int32),
+                      n_paths=int(keep.sum()),
+                      path_link_ptr=np.concatenate([[0], np.cumsum(lens[keep])]).astype(np.int32),
+                      path_links=t.path_links[np.repeat(keep, lens)], src=zeros, dst=zeros,
+                      meta=dict(kind="part"))
+
+
+# (the first three: 274 groups in each of 16 x 16 patches, 310 and 292 in each of 15 x 15, more places than
+# 16 bits number)
+@pytest.mark.parametrize("what", [(64, 8, "own", 0.05, 0.1), (56, 8, "own", 0.05, 0.4),
+                                  (48, 8, "pair", 0.05, 0.3), (48, 8, "xor", 0.2, 0.2),
+                                  (16, 8, "pair", 1.0, 1.0), (24, 8, "xor", 1.0, 1.0),
+                                  (6, 6, "pair", 1.0, 1.0), (9, 5, "own", 0.7, 0.7)])
+@pytest.mark.parametrize("cus", [256, 64])
+def test_what_is_chosen_can_be_built(what, cus):
+    t = part_of(fabric(*what[:3]), 1, *what[3:])
+    chosen = B.nimble_host_patch_choice(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths, t.path_link_ptr,
+                                        t.path_links, cus, cus // 32)
+    assert all(c["failed"] == 0 and c["patches"] <= cus for c in chosen), chosen
+    assert chosen or cus < 256
+
+
 @pytest.mark.gpu
 def test_a_stream_under_capture_takes_one_patch():
     """Of a fabric with a layout of one patch and a faster one of several (4 nodes, a NIC per GPU
