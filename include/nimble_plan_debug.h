@@ -242,6 +242,14 @@ nimble_status_t nimble_host_patch_choice(int32_t n_links, int32_t n_comm,
                                          int32_t cus, int32_t xcds, int32_t strips_x, int32_t strips_y,
                                          int32_t lanes, int32_t blocks, int64_t out[24], int32_t *n_out);
 
+/* How `plans` plans of `patches` patches each would run on a device of `cus` compute units in `xcds` XCDs:
+ * near 1 when every team of patches keeps to one XCD, teams that many side by side, and us the
+ * microseconds of one iteration of all plans that the choice of a layout counts with, from those of one
+ * iteration of a near and of a spread team. */
+nimble_status_t nimble_host_patch_teams(int32_t patches, int32_t cus, int32_t xcds, int32_t plans,
+                                        double near_us, double spread_us, int32_t *near, int32_t *teams,
+                                        double *us);
+
 #ifdef __cplusplus
 }
 #endif

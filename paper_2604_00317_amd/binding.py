@@ -37,7 +37,7 @@ EXPORTS = [
     "nimble_plan_solve_static", "nimble_static_scratch_bytes", "nimble_debug_barrier_probe",
     "nimble_topo_reserve_batch", "nimble_debug_fail_allocation",
     "nimble_debug_fail_host_allocation", "nimble_debug_live_allocations",
-    "nimble_host_patch_check", "nimble_host_grid_check", "nimble_host_patch_choice",
+    "nimble_host_patch_check", "nimble_host_grid_check", "nimble_host_patch_choice", "nimble_host_patch_teams",
     "nimble_debug_patches_gave_up",
     "nimble_debug_refuse_cooperative", "nimble_debug_fail_patch_build",
     "nimble_topo_last_patches", "nimble_topo_alg1_form",
@@ -142,6 +142,8 @@ def load_library(build_if_missing: bool = True) -> ctypes.CDLL:
     lib.nimble_host_grid_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, i32, vp]
     lib.nimble_host_patch_choice.restype = ctypes.c_int
     lib.nimble_host_patch_choice.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, i32, i32, i32, i32, vp, vp]
+    lib.nimble_host_patch_teams.restype = ctypes.c_int
+    lib.nimble_host_patch_teams.argtypes = [i32, i32, i32, i32, ctypes.c_double, ctypes.c_double, vp, vp, vp]
     lib.nimble_host_patch_check.restype = ctypes.c_int
     lib.nimble_host_patch_check.argtypes = [i32, i32, vp, i32, vp, vp, i32, i32, vp]
     lib.nimble_host_layout_stats.restype = ctypes.c_int
@@ -510,6 +512,18 @@ def nimble_host_patch_choice(n_links, n_comm, comm_path_ptr, n_paths, path_link_
         raise NimbleError(st, "invalid CSR")
     keys = ["x", "y", "patches", "max_groups", "blocks", "lanes", "variable_only", "failed"]
     return [dict(zip(keys, (int(v) for v in row))) for row in out[:int(n[0])]]
+
+
+def nimble_host_patch_teams(patches, plans, near_us, spread_us, cus=256, xcds=8):
+    """Host-only: (teams keep to one XCD each, how many side by side, microseconds of an iteration of all
+    plans) as the choice of a layout and the launch have it."""
+    near, teams = ctypes.c_int32(), ctypes.c_int32()
+    us = ctypes.c_double()
+    st = load_library().nimble_host_patch_teams(patches, cus, xcds, plans, near_us, spread_us,
+                                                ctypes.byref(near), ctypes.byref(teams), ctypes.byref(us))
+    if st != NIMBLE_OK:
+        raise NimbleError(st, "invalid sizes")
+    return bool(near.value), teams.value, us.value
 
 
 def plan(topo: Topo, traffic, eps: float, iters: int, device: str = "cuda:0"):

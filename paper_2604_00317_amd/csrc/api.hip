@@ -308,14 +308,6 @@ hipError_t ensure_state_plans(nimble_topo *t, int32_t plans)
 
 int32_t xcds_of(const nimble_topo *t) { return std::max(1, t->n_cu / nimble::kCusOfXcd); }
 
-// How many teams of `patches` patches are resident at once, a patch per compute unit.
-void count_teams(const nimble_topo *t, nimble::DevicePatches &p, int32_t patches)
-{
-    p.xcds = xcds_of(t);
-    p.max_teams = t->n_cu / patches;
-    p.near_teams = p.xcds * (t->n_cu / p.xcds / patches);
-}
-
 hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::DevicePatches &p)
 {
     p.shape = l.shape;
@@ -324,7 +316,6 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     p.max_groups = l.max_groups;
     p.max_parts = l.max_parts;
     p.n_parts = l.n_parts;
-    p.max_teams = 1 << 30;
     p.parts = nullptr;
     p.maxima = nullptr;
     p.len_start = nullptr;
@@ -346,10 +337,9 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     if (e == hipSuccess && l.shape.blocks) e = upload(t, l.tails.data(), l.tails.size(), &p.tails);
     if (e == hipSuccess) e = upload(t, l.at.data(), l.at.size(), &p.at);
     if (e == hipSuccess && l.n_patches > 1) {
-        count_teams(t, p, l.n_patches);
-        e = allocate(t, static_cast<size_t>(p.max_teams) * 2 * l.n_parts, &p.parts);
+        e = allocate(t, static_cast<size_t>(p.teams.spread) * 2 * l.n_parts, &p.parts);
         if (e == hipSuccess)
-            e = allocate(t, static_cast<size_t>(p.max_teams) * nimble::patch_meeting_words(l.n_patches),
+            e = allocate(t, static_cast<size_t>(p.teams.spread) * nimble::patch_meeting_words(l.n_patches),
                          &p.maxima);
         if (e == hipSuccess) e = allocate(t, static_cast<size_t>(t->d.E), &p.len_start);
         if (e == hipSuccess) e = allocate(t, 1, &p.abort_word);
@@ -380,8 +370,7 @@ double general_iteration_us(const nimble_topo *t, int32_t plans, bool streamed)
 double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int32_t plans,
                        int32_t iters, bool streamed)
 {
-    const int32_t at_once = p.n_patches > 1 ? p.max_teams : t->n_cu;
-    const double us = p.iteration_us * ((plans + at_once - 1) / at_once);
+    const double us = nimble::plans_iteration_us(p.teams, plans, p.iteration_us, p.spread_us);
     const double before = p.n_patches > 1 ? 36.0 + 0.9e-6 * static_cast<double>(p.list_bytes) : 0.0;
     return iters * (general_iteration_us(t, plans, streamed) - us) - before;
 }
@@ -424,12 +413,14 @@ hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, co
         nimble::DevicePatches p;
         p.shape = o.shape;
         p.n_patches = built.n_patches;
-        count_teams(t, p, built.n_patches);
+        p.xcds = xcds_of(t);
+        p.teams = nimble::patch_teams(built.n_patches, t->n_cu, p.xcds);
         p.iteration_us = o.us;
+        p.spread_us = o.spread_us;
         p.list_bytes = 0;
         if (!t->patches_forced && patches_gain_us(t, p, 1, 1000, true) <= 0.0 &&
             patches_gain_us(t, p, 1, 1000, false) <= 0.0 &&
-            patches_gain_us(t, p, p.max_teams, 1000, false) <= 0.0)
+            patches_gain_us(t, p, p.teams.spread, 1000, false) <= 0.0)
             continue;
         const hipError_t e = upload_patches(t, built, p);
         if (e != hipSuccess) return e;

@@ -579,7 +579,7 @@ double patch_scan_us(const PatchShape &s)
     return 0.88 * (0.3 + 0.06 * s.quads + std::max(lds, valu) / 2400.0);
 }
 
-double patch_iteration_us(const PatchShape &s, const PatchSizes &m)
+double patch_iteration_us(const PatchShape &s, const PatchSizes &m, bool near)
 {
     if (m.patches < 2 || m.max_groups == 0) return patch_scan_us(s);
     // Fitted to 2352 measured layouts: 51 fabrics of 2 to 64 nodes in every square grid and in those
@@ -588,7 +588,6 @@ double patch_iteration_us(const PatchShape &s, const PatchSizes &m)
     // than the fastest on average (the worst, 8 x 8 for 8 nodes of 8, 19 %).  Terms: the words of a
     // link's users, asked for four, eight or sixteen at a time, round after round of links; the links
     // a patch publishes; the words it reads; then what the commodities take.
-    const bool near = m.patches <= kPatchXcdPatches;
     const double waves = s.threads / 64.0;
     const int32_t lanes = patch_link_lanes(s.threads, patch_row(m.max_groups));
     const int32_t per_round = s.threads / lanes;
@@ -761,7 +760,12 @@ bool measure_blocks(const PatchScan &scan, const PatchCut &cut, PatchSizes &m, P
 std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan,
                                      int32_t cus, int32_t xcds, const PatchForced &forced)
 {
-    const int32_t cus_of_xcd = cus / std::max(1, xcds);
+    xcds = std::max(1, xcds);
+    const int32_t cus_of_xcd = cus / xcds;
+    auto estimate = [&](PatchOption &o) {
+        o.spread_us = patch_iteration_us(o.shape, o.sizes, false);
+        o.us = o.sizes.patches <= cus_of_xcd ? patch_iteration_us(o.shape, o.sizes, true) : o.spread_us;
+    };
     std::vector<PatchGrid> grids;
     if (forced.grid.x > 0) {
         grids.push_back(forced.grid);
@@ -789,13 +793,15 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
         tried[2 * i + 1].sizes = o.sizes;
         tried[2 * i + 1].sizes.fits = tried[2 * i + 1].sizes.fits_adaptive = false;
         if (!fits || forced.blocks == 1) o.sizes.fits = o.sizes.fits_adaptive = false;
-        if (o.sizes.fits) o.us = patch_iteration_us(o.shape, o.sizes);
+        if (o.sizes.fits) estimate(o);
     };
-    // microseconds of an iteration of as many plans as there is room for, per plan
+    // microseconds of an iteration of as many plans as there is room for, per plan; near teams where they
+    // fit an XCD (rated by the spread ones where more of those fit, layouts of 25 patches took the place of
+    // 28 to 32 on 13 of 275 fabrics: 1.4 to 1.7 times as fast for 9 and 10 plans, 0.86 to 0.98 for 2
+    // to 8, 12, 16, 24, 32 and 64)
     auto shared_us = [&](const PatchOption &o) {
-        const int32_t n = o.sizes.patches;
-        const int32_t teams = n <= cus_of_xcd ? xcds * (cus_of_xcd / n) : cus / n;
-        return o.us / std::max(1, teams);
+        const PatchTeams t = patch_teams(o.sizes.patches, cus, xcds);
+        return t.near > 0 ? o.us / t.near : o.spread_us / t.spread;
     };
     double best_us = 1e30, best_shared = 1e30;
     // what the blocks of a cut come to at best is known without looking for them
@@ -807,7 +813,7 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
         least.shape.product = scan.block_product;
         least.shape.threads = std::max(64, (std::max(least.sizes.max_comm,
                                                      kPatchGroup * least.sizes.max_groups) + 63) / 64 * 64);
-        least.us = patch_iteration_us(least.shape, least.sizes);
+        estimate(least);
         return least;
     };
     auto try_blocks = [&](size_t i, const PatchOption &least) {
@@ -819,7 +825,7 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
             return;
         }
         o.sizes.fits_adaptive = false;                       // (there are no such kernels)
-        o.us = patch_iteration_us(o.shape, o.sizes);
+        estimate(o);
         best_us = std::min(best_us, o.us);
         best_shared = std::min(best_shared, shared_us(o));
     };
@@ -1480,6 +1486,19 @@ extern "C" nimble_status_t nimble_host_patch_choice(int32_t n_links, int32_t n_c
     } catch (const std::exception &) {
         return NIMBLE_ERR_ALLOC;
     }
+}
+
+extern "C" nimble_status_t nimble_host_patch_teams(int32_t patches, int32_t cus, int32_t xcds,
+                                                    int32_t plans, double near_us, double spread_us,
+                                                    int32_t *near, int32_t *teams, double *us)
+{
+    if (!near || !teams || !us || patches < 1 || xcds < 1 || cus < patches || plans < 1)
+        return NIMBLE_ERR_INVALID;
+    const nimble::PatchTeams t = nimble::patch_teams(patches, cus, xcds);
+    *near = nimble::teams_keep_near(t, plans) ? 1 : 0;
+    *teams = std::min(plans, *near ? t.near : t.spread);
+    *us = nimble::plans_iteration_us(t, plans, near_us, spread_us);
+    return NIMBLE_OK;
 }
 
 extern "C" void nimble_debug_fail_patch_build(int32_t where) { nimble::g_fault.store(where); }

@@ -229,9 +229,32 @@ bool measure_blocks(const PatchScan &scan, const PatchCut &cut, PatchSizes &m, P
 
 // Estimated times in microseconds of an iteration: the scan, scatter and update of one patch, and
 // the same with the exchange between several.
+// (`near`: a team within one XCD).
 double patch_scan_us(const PatchShape &s);
-double patch_iteration_us(const PatchShape &s, const PatchSizes &m);
+double patch_iteration_us(const PatchShape &s, const PatchSizes &m, bool near);
 constexpr double kPatchTripUs = 1.3;      // no iteration of several patches is shorter
+// Teams of patches that are resident at once, a patch per compute unit.
+struct PatchTeams {
+    int32_t spread = 0;          // each over all XCDs
+    int32_t near = 0;            // each within one (0: they do not fit one)
+};
+constexpr PatchTeams patch_teams(int32_t patches, int32_t cus, int32_t xcds)
+{
+    return PatchTeams{cus / patches, xcds * (cus / xcds / patches)};
+}
+// Teams keep to one XCD where they fit one and `plans` plans take no more rounds that way: an iteration is
+// 4 to 25 % shorter then, and a round more costs more than that (teams of 12, 20, 28 and 30 patches, 1 to 32
+// plans: 20 patches of 10 nodes, 12 plans in one round of spread teams 1071 us, in two of near ones 1687;
+// 32 plans in three and four 3073 and 3339; 16 plans, two rounds either way, 2027 and 1703).
+constexpr bool teams_keep_near(const PatchTeams &t, int32_t plans)
+{
+    return t.near > 0 && (plans + t.near - 1) / t.near <= (plans + t.spread - 1) / t.spread;
+}
+// Microseconds of an iteration of `plans` plans, from those of one of a near and of a spread team.
+constexpr double plans_iteration_us(const PatchTeams &t, int32_t plans, double near_us, double spread_us)
+{
+    return (teams_keep_near(t, plans) ? near_us : spread_us) * ((plans + t.spread - 1) / t.spread);
+}
 // Lanes that add up the parts of a shared link: as many as there are threads for.
 constexpr int32_t patch_link_lanes(int32_t threads, int32_t row)
 {
@@ -250,6 +273,7 @@ struct PatchOption {
     PatchShape shape;
     PatchSizes sizes;
     double us = 0.0;             // estimate of an iteration of one plan
+    double spread_us = 0.0;      // the same with its patches spread over the XCDs
     bool variable_only = false;  // made for solves of variable step alone
 };
 

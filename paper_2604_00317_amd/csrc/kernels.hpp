@@ -17,18 +17,18 @@ struct DevicePatches {
     int32_t n_patches = 0;       // 0: no such layout
     int32_t max_comm, max_local, max_groups, max_parts, max_heads, max_tails;
     int64_t n_parts;
-    int32_t max_teams;           // plans whose patches are resident at once
+    PatchTeams teams;            // plans whose patches are resident at once
     int32_t xcds;                // XCDs of the device
-    int32_t near_teams;          // the same if every team keeps to one XCD (0: it does not fit one)
     const int32_t *desc, *loc_link, *comm, *group;
     const uint16_t *at;
     int32_t row, max_users, max_at;
     const uint32_t *words, *first, *heads, *tails;
-    double *parts;               // [max_teams][2][n_parts]
-    double *maxima;              // [max_teams][patch_meeting_words(n_patches)]
+    double *parts;               // [teams.spread][2][n_parts]
+    double *maxima;              // [teams.spread][patch_meeting_words(n_patches)]
     double *len_start;           // [E] lengths a warm solve starts from, whatever becomes of it
     uint32_t *abort_word;
-    double iteration_us;         // estimate of one iteration of max_teams plans
+    double iteration_us;         // estimate of an iteration of one plan
+    double spread_us;            // the same with its patches spread over the XCDs
     int64_t list_bytes;          // candidate lists a solve loads
     bool adaptive;               // the kernel of variable step runs on it
 };

@@ -116,13 +116,12 @@ hipError_t launch_patches(const DeviceTopo &t, const DevicePatches &p, int32_t p
     a.E = t.E;
     a.n_patches = p.n_patches;
     a.plans = plans;
-    // A team keeps to one XCD where it fits one and no more rounds of teams come of it: its words
-    // then go from patch to patch through that XCD's L2 (sixteen plans of the 16-node fabric, 16
-    // patches each: 4.56 -> 3.87 ms; patches of a team spread over the XCDs, neighbours side by side
-    // on one, were slower than dealt out in turn: 16 nodes, variable step 5.9 -> 7.5 ms).
-    const int32_t rounds = (plans + p.max_teams - 1) / p.max_teams;
-    const bool near = p.near_teams > 0 && (plans + p.near_teams - 1) / p.near_teams <= rounds;
-    a.teams = std::min(plans, near ? p.near_teams : p.max_teams);
+    // The words of a team that keeps to one XCD go from patch to patch through that XCD's L2 (sixteen
+    // plans of the 16-node fabric, 16 patches each: 4.56 -> 3.87 ms; patches of a team spread over the
+    // XCDs, neighbours side by side on one, were slower than dealt out in turn: 16 nodes, variable step
+    // 5.9 -> 7.5 ms).
+    const bool near = teams_keep_near(p.teams, plans);
+    a.teams = std::min(plans, near ? p.teams.near : p.teams.spread);
     a.near_xcds = near ? p.xcds : 1;
     a.by_xcd = a.teams == 1 && p.xcds == kPatchXcds && p.n_patches >= kPatchXcds &&
                p.n_patches <= kPatchXcds * kPatchXcdPatches;

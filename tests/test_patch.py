@@ -764,6 +764,17 @@ def test_what_is_chosen_can_be_built(what, cus):
     assert chosen or cus < 256
 
 
+@pytest.mark.parametrize("patches,plans,near,teams,us", [
+    (1, 1, True, 1, 2.0), (1, 257, True, 256, 4.0), (16, 16, True, 16, 2.0), (16, 17, True, 16, 4.0),
+    (20, 1, True, 1, 2.0), (20, 8, True, 8, 2.0), (20, 9, False, 9, 3.0), (20, 12, False, 12, 3.0),
+    (20, 13, True, 8, 4.0), (20, 16, True, 8, 4.0), (20, 17, False, 12, 6.0), (32, 9, True, 8, 4.0),
+    (33, 1, False, 1, 3.0), (33, 8, False, 7, 6.0), (256, 1, False, 1, 3.0), (256, 3, False, 1, 9.0)])
+def test_plans_are_rated_as_they_run(patches, plans, near, teams, us):
+    """Teams within one XCD (2 us an iteration) while that takes no more rounds than teams that are spread
+    (3 us): the layout is chosen by the microseconds of the teams that the launch then makes."""
+    assert B.nimble_host_patch_teams(patches, plans, 2.0, 3.0) == (near, teams, us)
+
+
 @pytest.mark.gpu
 def test_a_stream_under_capture_takes_one_patch():
     """Of a fabric with a layout of one patch and a faster one of several (4 nodes, a NIC per GPU
