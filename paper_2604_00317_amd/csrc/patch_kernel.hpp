@@ -12,9 +12,10 @@
 // update: a patch publishes its part of a link's load and sums the parts of all users, in the
 // same order in every patch, so that all hold the same length and price.
 //
-// Exchange without barriers or fences: a part is one 8-byte word, stored and loaded at agent
-// scope (past the caches that are not coherent between the XCDs), whose sign bit says which
-// exchange it belongs to -- loads are never negative.  Exchange n uses buffer n & 1 and the sign
+// Exchange without barriers or fences: a part is one 8-byte word, loaded at agent scope (past the
+// L1 caches) and stored at agent scope (past the L2 caches, which are not coherent between the XCDs)
+// or, where all its readers are on the writer's XCD, into that XCD's L2 alone (put_word).  Its sign bit
+// says which exchange it belongs to -- loads are never negative.  Exchange n uses buffer n & 1 and the sign
 // (n >> 1) & 1; all words start with the sign set.  A patch overwrites its part of exchange n
 // with that of n + 2 only after it has read all parts of n + 1 of the groups it shares, which
 // their writers published after reading n: nobody misses a word.  The words of a patch lie side by
@@ -206,6 +207,14 @@ __device__ __forceinline__ double take_load(LinkState &s, const Grid &gr)
 // `near`: all who read the word run on this XCD and find it in its L2; the store need not go on to
 // the memory side.  A word is with its reader 255 ns after the store, 412 ns if it goes on all the
 // same, 570 to 640 ns on another XCD (two waves that answer each other).  `near` is wave-uniform.
+// Such a word is stored at workgroup scope though other workgroups read it, which the language does not
+// allow for: it holds because of what this target makes of it.  The L1 of a compute unit is written through,
+// so the store (sc0) goes to the L2 all compute units of the XCD share, where the readers' agent-scope
+// loads (sc1) look; and atomic stores are neither dropped nor combined.  (Should a word not arrive all
+// the same, the wait for it ends and the plan is solved without patches.)
+#if defined(__HIP_DEVICE_COMPILE__) && !defined(__gfx950__)
+#error "words stored at workgroup scope are in the L2 of the XCD on gfx950; look again for another target"
+#endif
 __device__ __forceinline__ void put_word(double *p, double v, unsigned phase, bool near = false)
 {
     const unsigned long long b = (static_cast<unsigned long long>(__double_as_longlong(v)) & ~kSign) |

@@ -52,6 +52,30 @@ def test_no_lane_move_inside_a_reversed_instruction(tmp_path):
     assert REVERSED_MOVE.findall(text) == []
 
 
+def test_words_between_patches_reach_the_l2_or_pass_it(tmp_path):
+    """What is stored for readers on the same XCD is written through to its L2 (sc0), what others read goes
+    past it (sc1), loads go past the L1 (sc1); a second store to a place leaves the first one alone."""
+    from paper_2604_00317_amd import build
+    src = tmp_path / "probe.hip"
+    src.write_text('#include "patch_kernel.hpp"\n'
+                   "using namespace nimble::patch;\n"
+                   "__global__ void near_words(double *o, double a, double b) "
+                   "{ put_word(o, a, 0u, true); put_word(o, b, 1u, true); }\n"
+                   "__global__ void far_words(double *o, double a, double b) "
+                   "{ put_word(o, a, 0u); put_word(o, b, 1u); }\n"
+                   "__global__ void reads(double *o, unsigned long long *r) { *r = get_word(o); }\n")
+    r = subprocess.run(["/opt/rocm/bin/hipcc", *build.FLAGS, f"-I{build.CSRC}", "-S",
+                        "--cuda-device-only", "-o", "-", str(src)], check=True,
+                       capture_output=True, text=True)
+    code = {}
+    for name in ("near_words", "far_words", "reads"):
+        body = re.search(rf"^_Z\d+{name}\w*:(.*?)s_endpgm", r.stdout, re.M | re.S).group(1)
+        code[name] = [line.split() for line in body.splitlines() if "global_" in line]
+    assert [(c[0], c[-1]) for c in code["near_words"]] == [("global_store_dwordx2", "sc0")] * 2
+    assert [(c[0], c[-1]) for c in code["far_words"]] == [("global_store_dwordx2", "sc1")] * 2
+    assert (code["reads"][0][0], code["reads"][0][-1]) == ("global_load_dwordx2", "sc1")
+
+
 @pytest.mark.parametrize("expr,bad", [("nimble::dpp_less_i32<0x121>(v, x)", False),
                                       ("x - nimble::dpp_i32<0x121>(v)", True)])
 def test_the_subtraction_helper_keeps_the_move_in_front(tmp_path, expr, bad):
