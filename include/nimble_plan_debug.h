@@ -215,8 +215,8 @@ nimble_status_t nimble_host_resident_kernel(int32_t n_links, int32_t n_comm,
  * link in use one patch that reports it, and its sizes are those found without building it.
  * out[11]: patches (0: the fabric or the grid does not suit the patch kernels), the number of
  * the check that failed (0: none), 1 for product slots, lanes per commodity, slots per lane,
- * threads, most local links of a patch, most groups, most users of a group, most parts (eight
- * doubles each) a patch reads, doubles of one exchange buffer.
+ * threads, most local links of a patch, most groups, most users of a group, most users (summed
+ * over its groups) of a patch, which reads eight doubles of each, doubles of one exchange buffer.
  */
 nimble_status_t nimble_host_patch_check(int32_t n_links, int32_t n_comm,
                                         const int32_t *comm_path_ptr, int32_t n_paths,
@@ -224,8 +224,8 @@ nimble_status_t nimble_host_patch_check(int32_t n_links, int32_t n_comm,
                                         int32_t strips, int32_t lanes, int64_t *out);
 
 /* The same for a grid of strips_x x strips_y patches, with `blocks` other than 0 for its layout in
- * blocks.  out[16]: as above, then most places for commodities of a patch, most users (summed over
- * its groups), most head blocks, most tails, most links that no other patch uses. */
+ * blocks.  out[15]: as above, then most places for commodities of a patch, most head blocks, most tails,
+ * most links that no other patch uses. */
 nimble_status_t nimble_host_grid_check(int32_t n_links, int32_t n_comm,
                                        const int32_t *comm_path_ptr, int32_t n_paths,
                                        const int32_t *path_link_ptr, const int32_t *path_links,

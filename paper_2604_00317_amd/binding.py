@@ -474,7 +474,7 @@ def nimble_host_patch_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_p
     if st != NIMBLE_OK:
         raise NimbleError(st, "invalid CSR")
     keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "threads",
-            "max_local", "max_groups", "max_users", "max_parts", "parts"]
+            "max_local", "max_groups", "max_users", "max_at", "parts"]
     return dict(zip(keys, (int(v) for v in out)))
 
 
@@ -486,13 +486,13 @@ def nimble_host_grid_check(n_links, n_comm, comm_path_ptr, n_paths, path_link_pt
     cp = _host(comm_path_ptr, np.int32)
     lp = _host(path_link_ptr, np.int32)
     pl = _host(path_links, np.int32)
-    out = np.zeros(16, dtype=np.int64)
+    out = np.zeros(15, dtype=np.int64)
     st = load_library().nimble_host_grid_check(n_links, n_comm, _hp(cp), n_paths, _hp(lp), _hp(pl),
                                                strips_x, strips_y, int(blocks), _hp(out))
     if st != NIMBLE_OK:
         raise NimbleError(st, "invalid CSR")
     keys = ["patches", "failed", "product", "lanes", "slots_per_lane", "threads",
-            "max_local", "max_groups", "max_users", "max_parts", "parts", "max_comm", "max_at",
+            "max_local", "max_groups", "max_users", "max_at", "parts", "max_comm",
             "max_heads", "max_tails", "max_private"]
     return dict(zip(keys, (int(v) for v in out)))
 

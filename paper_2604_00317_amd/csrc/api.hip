@@ -314,7 +314,6 @@ hipError_t upload_patches(nimble_topo *t, const nimble::PatchLayout &l, nimble::
     p.max_comm = l.max_comm;
     p.max_local = l.max_local;
     p.max_groups = l.max_groups;
-    p.max_parts = l.max_parts;
     p.n_parts = l.n_parts;
     p.parts = nullptr;
     p.maxima = nullptr;
@@ -375,9 +374,9 @@ double patches_gain_us(const nimble_topo *t, const nimble::DevicePatches &p, int
     return iters * (general_iteration_us(t, plans, streamed) - us) - before;
 }
 
-// Builds the patch layouts of a fabric: the one with the fewest patches, which solves the most
-// plans side by side, the one whose estimate is lowest for a single plan, if that is another, and
-// the one for solves of variable step if that is a third.
+// Builds the patch layouts of a fabric: the one whose estimate is lowest for a single plan, the one that
+// solves the most plans in a time, if that is another, and the one for solves of variable step if that is
+// a third.
 // (Layouts that would never be faster than what runs without them are not made.)
 hipError_t make_patches(nimble_topo *t, const int32_t *cp, const int32_t *lp, const int32_t *pl)
 {

@@ -183,9 +183,6 @@ int32_t slots_of(int32_t n_cand, int32_t p0, const int32_t *path_link_ptr,
     return n;
 }
 
-// the parts of a group are read eight users at a time
-int32_t padded_parts(int32_t users) { return (users + 7) / 8 * 8; }
-
 // Test hook: 1 the next range of a calling thread, 2 of a worker runs out of memory, 3 no worker
 // can be started.
 std::atomic<int32_t> g_fault{0};
@@ -689,16 +686,14 @@ PatchSizes measure_cut(int32_t n_links, const PatchScan &scan, const PatchCut &c
     for (const auto &s : sets)
         groups_of_first[s.second.first] = (s.second.second + kPatchGroup - 1) / kPatchGroup;
     for (int32_t b = 0; b < B; ++b) {
-        int32_t groups = 0, parts = 0, own = 0, at = 0;
+        int32_t groups = 0, own = 0, at = 0;
         for (int32_t e : links[b]) {
             own += users[e] == 1 ? 1 : 0;
             m.max_users = std::max(m.max_users, users[e]);
             groups += groups_of_first[e];
-            parts += groups_of_first[e] * padded_parts(users[e]);
             at += groups_of_first[e] * users[e];
         }
         m.max_groups = std::max(m.max_groups, groups);
-        m.max_parts = std::max(m.max_parts, parts);
         m.max_at = std::max(m.max_at, at);
         m.max_private = std::max(m.max_private, own);
         m.max_local = std::max(m.max_local, groups * kPatchGroup + own);
@@ -753,7 +748,7 @@ bool measure_blocks(const PatchScan &scan, const PatchCut &cut, PatchSizes &m, P
     const int64_t fixed = block_lds(m.max_local, m.max_heads, m.max_tails, 0, m.max_at, shape, 0).bytes;
     const int64_t slots = static_cast<int64_t>(m.max_comm) * L;
     m.fits = fixed + 8 * slots <= kPatchLdsBytes;
-    m.fits_adaptive = fixed + 32 * slots <= kPatchLdsBytes;
+    m.fits_adaptive = false;                                 // (there are no such kernels)
     return m.fits;
 }
 
@@ -824,7 +819,6 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
             o.sizes.fits = false;
             return;
         }
-        o.sizes.fits_adaptive = false;                       // (there are no such kernels)
         estimate(o);
         best_us = std::min(best_us, o.us);
         best_shared = std::min(best_shared, shared_us(o));
@@ -963,12 +957,9 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
     std::vector<int32_t> first_local(B + 1, 0), first_group(B + 1, 0);
     std::vector<int32_t> first_comm(B + 1, 0), first_head(B + 1, 0), first_tail(B + 1, 0);
     for (int32_t b = 0; b < B; ++b) {
-        int32_t n_private = 0, parts = 0, n_at = 0;
+        int32_t n_private = 0, n_at = 0;
         for (int32_t e : links[b]) n_private += users[e].size() == 1 ? 1 : 0;
-        for (int32_t g : groups_of[b]) {
-            parts += padded_parts(static_cast<int32_t>(groups[g].users->size()));
-            n_at += static_cast<int32_t>(groups[g].users->size());
-        }
+        for (int32_t g : groups_of[b]) n_at += static_cast<int32_t>(groups[g].users->size());
         const int32_t ng = static_cast<int32_t>(groups_of[b].size());
         const int32_t n_local = ng * kPatchGroup + n_private;
         if (n_local > kPatchMaxLocal) return false;
@@ -976,7 +967,6 @@ bool build_patches(int32_t n_links, int32_t n_comm, const int32_t *cp, const int
         first_group[b + 1] = first_group[b] + ng;
         out.max_local = std::max(out.max_local, n_local);
         out.max_groups = std::max(out.max_groups, ng);
-        out.max_parts = std::max(out.max_parts, parts);
         out.max_at = std::max(out.max_at, n_at);
         int32_t *d = &out.desc[static_cast<size_t>(kPatchDescInts) * b];
         d[0] = first_local[b];
@@ -1416,7 +1406,7 @@ nimble_status_t host_check(int32_t n_links, int32_t n_comm, const int32_t *cp, c
     // what is found without building a layout is what it has
     if (t.n_patches > 0 && out[1] == 0 &&
         (m.patches != t.n_patches || m.max_comm != t.max_comm || m.max_local != t.max_local ||
-         m.max_groups != t.max_groups || m.max_parts != t.max_parts || m.max_heads != t.max_heads ||
+         m.max_groups != t.max_groups || m.max_heads != t.max_heads ||
          m.max_tails != t.max_tails || m.max_at != t.max_at))
         out[1] = 19;
     out[2] = t.shape.product;
@@ -1426,14 +1416,13 @@ nimble_status_t host_check(int32_t n_links, int32_t n_comm, const int32_t *cp, c
     out[6] = t.max_local;
     out[7] = t.max_groups;
     out[8] = t.max_users;
-    out[9] = t.max_parts;
+    out[9] = t.max_at;
     out[10] = t.n_parts;
     if (more) {
         out[11] = t.max_comm;
-        out[12] = t.max_at;
-        out[13] = t.max_heads;
-        out[14] = t.max_tails;
-        out[15] = m.max_private;
+        out[12] = t.max_heads;
+        out[13] = t.max_tails;
+        out[14] = m.max_private;
     }
     return NIMBLE_OK;
 }

@@ -132,7 +132,6 @@ struct PatchLayout {
     int32_t max_local = 0;       // most local links (groups padded) of a patch
     int32_t max_groups = 0;      // most groups of a patch
     int32_t max_users = 0;       // most users of a group
-    int32_t max_parts = 0;       // most parts (users of its groups, in eights) of a patch
     int32_t max_at = 0;          // most users (summed over its groups) of a patch
     int32_t max_heads = 0;       // blocks: most head blocks of a patch
     int32_t max_tails = 0;       // blocks: most tails of a patch
@@ -155,8 +154,8 @@ struct PatchLayout {
     std::vector<int32_t> group;     // [groups] start of its users in `at`
     // Users of the groups of a patch, group after group: where the group's words lie in the exchange
     // buffer, in units of kPatchGroup words.  The words of patch b are `row` of them from b * row on,
-    // its groups in their local order.  A patch's run of `at` starts at desc[7] and has one entry
-    // more than users, so that group q has those from group[q] to group[q + 1].
+    // its groups in their local order.  A patch's run of `at` starts at desc[7]; its run of `group` has one
+    // entry more than groups, so that group q has the users from group[q] to group[q + 1].
     std::vector<uint16_t> at;
     int32_t row = 0;                // of units per patch
 };
@@ -216,7 +215,7 @@ struct PatchSizes {
     bool fits = false;              // its patches keep to their limits, LDS among them
     bool fits_adaptive = false;     // also for a solve of variable step (32 bytes a slot, not 8)
     int32_t patches = 0;
-    int32_t max_comm = 0, max_local = 0, max_groups = 0, max_parts = 0;      // as in PatchLayout
+    int32_t max_comm = 0, max_local = 0, max_groups = 0;      // as in PatchLayout
     int32_t max_heads = 0, max_tails = 0, max_at = 0;
     int32_t max_private = 0;        // most links of a patch that no other patch uses
     int32_t max_users = 0;          // most patches that share a link

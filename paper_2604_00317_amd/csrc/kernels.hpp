@@ -15,7 +15,7 @@ constexpr int32_t kCusOfXcd = 32;
 struct DevicePatches {
     PatchShape shape;
     int32_t n_patches = 0;       // 0: no such layout
-    int32_t max_comm, max_local, max_groups, max_parts, max_heads, max_tails;
+    int32_t max_comm, max_local, max_groups, max_heads, max_tails;
     int64_t n_parts;
     PatchTeams teams;            // plans whose patches are resident at once
     int32_t xcds;                // XCDs of the device

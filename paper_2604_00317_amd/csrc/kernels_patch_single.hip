@@ -57,7 +57,7 @@ size_t patch_lds_bytes(const DevicePatches &p, bool adaptive)
 {
     if (p.shape.blocks)
         return static_cast<size_t>(block_lds(p.max_local, p.max_heads, p.max_tails, p.max_comm, p.max_at,
-                                             p.shape, adaptive ? 32 : 8).bytes);
+                                             p.shape, 8).bytes);
     return static_cast<size_t>(patch::lds_layout(p.max_local, p.max_groups, p.max_at, p.max_comm,
                                                  p.shape.lanes * p.shape.quads, adaptive ? 32 : 8)
                                    .bytes);
