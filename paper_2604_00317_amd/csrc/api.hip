@@ -630,14 +630,13 @@ static const nimble::DevicePatches *adaptive_patches(const nimble_topo_t *t, int
     if (t->d.cost_max || t->ad_fold_forced || max_iters > 1 << 20 ||
         t->forced_regime != NIMBLE_REGIME_AUTO)
         return nullptr;
-    // A step of variable size takes longer than one of fixed size: 0.9 us with one patch (2 nodes: 1.8
-    // against 0.9), 3.2 with several (16 nodes: 5.3 against 2.2), and about as much kernel by kernel
-    // (24 nodes: 13.9 against 10.7).
-    constexpr double kOnePatch = 0.9, kMore = 3.2;
+    // (kernel by kernel a step of variable size takes about as much more as with several patches: 24 nodes
+    // 13.9 against 10.7)
     const nimble::DevicePatches *best = nullptr;
-    double best_us = t->patches_forced ? 1e30 : general_iteration_us(t, 1, true) + kMore;
+    double best_us =
+        t->patches_forced ? 1e30 : general_iteration_us(t, 1, true) + nimble::kVariableMoreUs;
     for (const nimble::DevicePatches &p : t->patches) {
-        const double us = p.iteration_us + (p.n_patches > 1 ? kMore : kOnePatch);
+        const double us = nimble::variable_step_us(p.n_patches, p.iteration_us);
         if (p.adaptive && us < best_us) {
             best = &p;
             best_us = us;

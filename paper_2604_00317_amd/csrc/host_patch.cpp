@@ -853,7 +853,10 @@ std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const Patc
         if (!o.sizes.fits) continue;
         if (best == nullptr || o.us < best->us) best = &o;
         if (most == nullptr || shared_us(o) < shared_us(*most)) most = &o;
-        if (o.sizes.fits_adaptive && (adaptive == nullptr || o.us < adaptive->us)) adaptive = &o;
+        if (o.sizes.fits_adaptive &&
+            (adaptive == nullptr || variable_step_us(o.sizes.patches, o.us) <
+                                        variable_step_us(adaptive->sizes.patches, adaptive->us)))
+            adaptive = &o;
     }
     std::vector<PatchOption> out;
     if (best == nullptr) return out;

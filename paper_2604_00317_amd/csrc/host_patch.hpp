@@ -254,6 +254,13 @@ constexpr double plans_iteration_us(const PatchTeams &t, int32_t plans, double n
 {
     return (teams_keep_near(t, plans) ? near_us : spread_us) * ((plans + t.spread - 1) / t.spread);
 }
+// What a step of variable size takes longer than one of fixed size: 0.9 us with one patch (2 nodes: 1.8
+// against 0.9), 3.2 with several (16 nodes: 5.3 against 2.2).
+constexpr double kVariableOneUs = 0.9, kVariableMoreUs = 3.2;
+constexpr double variable_step_us(int32_t patches, double us)
+{
+    return us + (patches > 1 ? kVariableMoreUs : kVariableOneUs);
+}
 // Lanes that add up the parts of a shared link: as many as there are threads for.
 constexpr int32_t patch_link_lanes(int32_t threads, int32_t row)
 {
@@ -278,8 +285,8 @@ struct PatchOption {
 
 // The cut that solves the most plans in a time (by the estimates, `cus` compute units in `xcds`
 // XCDs) and the one with the lowest estimate for one plan, of those whose patches keep to their limits;
-// one of the two if they are the same.  If neither has the lowest estimate of those that a solve of
-// variable step fits (layouts of blocks have no such kernels), that one as well.
+// one of the two if they are the same.  If neither has the lowest estimate of a variable step of those
+// that fit one (layouts of blocks have no such kernels), that one as well.
 std::vector<PatchOption> choose_cuts(int32_t n_links, int32_t n_comm, const PatchScan &scan,
                                      int32_t cus, int32_t xcds, const PatchForced &forced);
 

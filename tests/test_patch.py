@@ -832,3 +832,31 @@ def test_a_variable_step_has_a_layout_of_its_own():
         assert np.array_equal(got[0], ref["splits"])
     finally:
         h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("what,third", [((6, 6, "pair"), True), ((13, 8, "xor"), True),
+                                        ((4, 8, "own"), False), ((3, 8, "xor"), False)])
+def test_a_third_layout_for_the_variable_step(what, third):
+    """Fabrics whose layout for one plan is in blocks, which have no variable step: that one is solved on
+    the layout kept for it alone, or on one patch, which needs no other layout."""
+    import oracle
+    t = fabric(*what)
+    chosen = B.nimble_host_patch_choice(t.n_links, t.n_comm, t.comm_path_ptr, t.n_paths, t.path_link_ptr,
+                                        t.path_links)
+    assert chosen[0]["blocks"] == 1 and chosen[-1]["variable_only"] == third
+    d = np.floor(np.random.default_rng(1).pareto(1.1, t.n_comm) * 1e6)
+    print(f"[patch adaptive] third layout of {what}", flush=True)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        splits, lam = B.plan(h, d, 0.05, 300)
+        assert h.last_patches in (c["patches"] for c in chosen)
+        ref = oracle.solve(*t.csr(), d, 0.05, 300)
+        assert lam == ref["lam"] and np.array_equal(splits, ref["splits"])
+        got = _adaptive(h, t, d, 0.1, 60, 7)
+        assert h.last_patches == (chosen[-1]["patches"] if third else 1)
+        ref = oracle.solve_adaptive(*t.csr(), d, 0.1, 60, 7)
+        assert got[1:] == (ref["lam"], ref["iters"], ref["lb"])
+        assert np.array_equal(got[0], ref["splits"])
+    finally:
+        h.close()
