@@ -4,8 +4,8 @@
 // Reads a topology from four binary files in a directory (cap.bin float64, cp.bin / lp.bin /
 // pl.bin int32), runs every host-only helper of the library on it and checks the round trips:
 // the streaming layout decodes to the plain reverse CSR, every incidence reads back through
-// the forward records, and patch layouts of several grids read back to the CSR, also after a build
-// that ran out of memory.  Exit status 0 and a line "OK ..." on success.
+// the forward records, and patch layouts of several grids, in slots and in blocks, and those that are
+// chosen read back to the CSR, also after a build that ran out of memory.  Exit status 0 and a line "OK ..." on success.
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -86,14 +86,54 @@ int main(int argc, char **argv)
                 return 9;
             }
         }
-    for (int32_t fault : {1, 2, 3, 0}) {
-        if (!with_patches) break;
-        nimble_debug_fail_patch_build(fault);
-        const nimble_status_t st = nimble_host_patch_check(E, K, cp.data(), P, lp.data(), pl.data(), 3,
-                                                           0, patch);
-        // (few commodities need no worker that could fail)
-        if (st != NIMBLE_OK && !(st == NIMBLE_ERR_ALLOC && (fault == 1 || fault == 2))) return 10;
-    }
+    const int32_t grids[][2] = {{2, 2}, {3, 2}, {1, 5}, {4, 8}, {16, 16}};
+    for (const auto &g : grids)
+        for (int32_t blocks : {0, 1}) {
+            int64_t grid[15] = {0};
+            if (!with_patches) continue;
+            if (nimble_host_grid_check(E, K, cp.data(), P, lp.data(), pl.data(), g[0], g[1], blocks,
+                                       grid) != NIMBLE_OK ||
+                grid[1] != 0) {
+                std::fprintf(stderr, "grid %d x %d, blocks %d: check %lld\n", g[0], g[1], blocks,
+                             static_cast<long long>(grid[1]));
+                return 11;
+            }
+        }
+    // what is chosen, with nothing asked for (compute units, XCDs) and with a grid, some of them none
+    const int32_t asked[][4] = {{256, 8, 0, 0}, {64, 2, 0, 0}, {20, 1, 0, 0}, {256, 8, 3, 5},
+                                {256, 8, 3, 0}, {256, 8, 3, -1}, {256, 8, 1, 300}};
+    for (const auto &w : asked)
+        for (int32_t blocks : {-1, 1}) {
+            int64_t chosen[24] = {0};
+            int32_t n = -1;
+            if (!with_patches) continue;
+            if (nimble_host_patch_choice(E, K, cp.data(), P, lp.data(), pl.data(), w[0], w[1], w[2], w[3], 0,
+                                         blocks, chosen, &n) != NIMBLE_OK ||
+                n < 0 || n > 3)
+                return 12;
+            for (int32_t i = 0; i < n; ++i)
+                if (chosen[8 * i + 7] != 0 || chosen[8 * i + 2] > w[0]) {
+                    std::fprintf(stderr, "choice %d of %d x %d on %d: check %lld\n", i, w[2], w[3], w[0],
+                                 static_cast<long long>(chosen[8 * i + 7]));
+                    return 13;
+                }
+        }
+    for (int32_t fault : {1, 2, 3, 0})
+        for (int32_t what : {0, 1, 2}) {
+            if (!with_patches) break;
+            int64_t grid[24] = {0};
+            int32_t n = 0;
+            nimble_debug_fail_patch_build(fault);
+            const nimble_status_t st =
+                what == 0 ? nimble_host_patch_check(E, K, cp.data(), P, lp.data(), pl.data(), 3, 0, patch)
+                : what == 1
+                    ? nimble_host_grid_check(E, K, cp.data(), P, lp.data(), pl.data(), 4, 5, 1, grid)
+                    : nimble_host_patch_choice(E, K, cp.data(), P, lp.data(), pl.data(), 256, 8, 0, 0, 0, -1,
+                                               grid, &n);
+            // (few commodities need no worker that could fail)
+            if (st != NIMBLE_OK && !(st == NIMBLE_ERR_ALLOC && (fault == 1 || fault == 2))) return 10;
+        }
+    nimble_debug_fail_patch_build(0);
     std::printf("OK records %d pairs %lld octets %lld pieces %lld blocks %lld bodies %lld groups %lld\n", n_rec,
                 static_cast<long long>(stats[0]), static_cast<long long>(stats[1]),
                 static_cast<long long>(stats[10]), static_cast<long long>(stats[8]),

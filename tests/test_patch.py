@@ -835,6 +835,29 @@ def test_a_variable_step_has_a_layout_of_its_own():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("every", [1, 7])
+@pytest.mark.parametrize("strips", [6, 7, 9, 14])
+def test_a_variable_step_between_xcds_with_lists_of_any_length(monkeypatch, strips, every):
+    """Teams of more than 32 patches meet through a leader per XCD: 36, 49, 81 and 196 patches, so that the
+    eight leaders have 4 and 5, 6 and 7, 10 and 11, 24 and 25 of them."""
+    import oracle
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", str(strips))
+    t = fabric(7, 6, "pair")
+    d = np.floor(np.random.default_rng(strips).pareto(1.1, t.n_comm) * 1e6)
+    print(f"[patch adaptive] {strips} x {strips} patches, a check every {every}", flush=True)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        for iters in (1, 41):
+            got = _adaptive(h, t, d, 0.1, iters, every)
+            assert h.last_patches == strips * strips
+            ref = oracle.solve_adaptive(*t.csr(), d, 0.1, iters, every)
+            assert got[1:] == (ref["lam"], ref["iters"], ref["lb"])
+            assert np.array_equal(got[0], ref["splits"])
+    finally:
+        h.close()
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("what,third", [((6, 6, "pair"), True), ((13, 8, "xor"), True),
                                         ((4, 8, "own"), False), ((3, 8, "xor"), False)])
 def test_a_third_layout_for_the_variable_step(what, third):
@@ -858,5 +881,40 @@ def test_a_third_layout_for_the_variable_step(what, third):
         ref = oracle.solve_adaptive(*t.csr(), d, 0.1, 60, 7)
         assert got[1:] == (ref["lam"], ref["iters"], ref["lb"])
         assert np.array_equal(got[0], ref["splits"])
+    finally:
+        h.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("blocks", [0, 1])
+@pytest.mark.parametrize("grid,patches", [("2", 4), ("4x5", 20), ("6", 36), ("14", 196)])
+def test_fractional_loads_of_every_link(monkeypatch, grid, patches, blocks):
+    """One iteration from unit lengths on demands that lie on no common grid: choices do not depend on
+    loads yet, so the length of every link shows its load.  The oracle adds up to K demands one after the
+    other and the patches round each part twice and add up to 31: with the width rounded alike and u =
+    2^-53, length - 1 = eps * load / cap / rho differs by at most 2 (K + 31 + 8) u relative, and the
+    length itself by a rounding, 2 u."""
+    import oracle
+    import torch
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_STRIPS", grid)
+    monkeypatch.setenv("NIMBLE_TUNE_PATCH_BLOCKS", str(blocks))
+    t = fabric(7, 6, "pair")
+    rng = np.random.default_rng(12)
+    print(f"[patch] fractional loads, grid {grid}, blocks {blocks}", flush=True)
+    h = B.nimble_topo_create(*t.csr())
+    try:
+        for _ in range(3):
+            d = rng.pareto(1.1, t.n_comm) * 1e6 * (1.0 + rng.random(t.n_comm))
+            length = torch.ones(t.n_links, dtype=torch.float64, device="cuda:0")
+            splits = torch.empty(t.n_paths, dtype=torch.float64, device="cuda:0")
+            lam = torch.empty(1, dtype=torch.float64, device="cuda:0")
+            B.nimble_plan_solve_warm(h, torch.as_tensor(d).to("cuda:0"), 0.5, 1, length, splits, lam)
+            assert h.last_patches == patches and not B.nimble_debug_patches_gave_up(h)
+            ref = oracle.solve(*t.csr(), d, 0.5, 1, len0=np.ones(t.n_links))
+            u, rel = 2.0 ** -53, 2.0 * (t.n_comm + 39) * 2.0 ** -53
+            assert np.array_equal(splits.cpu().numpy(), ref["splits"])
+            assert np.all(np.abs(length.cpu().numpy() - ref["len"]) <= rel * (ref["len"] - 1.0) + 2 * u)
+            assert (ref["len"] > 1.0).mean() > 0.5
+            assert abs(float(lam.item()) - ref["lam"]) <= rel * ref["lam"]
     finally:
         h.close()
