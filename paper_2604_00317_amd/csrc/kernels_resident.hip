@@ -514,9 +514,9 @@ struct RegShared {
 // for 185 of the 205 thousand cycles a wave is there, then vector issue (131).  One node of 8 GPUs,
 // 200 iterations: one plan 81.4 -> 49.3 us, 4096 plans 193.5 -> 112.1 us (gather -> scatter).  What
 // stays with the gather pays for the choice between them: 81.4 us as the only way, 83.3 with a count in
-// LDS per iteration and its pairs read one by one, 79.3 as it is (9 GPUs, 512 plans: 145.1, 158.0, 151.4),
-// of which 1.7 (2.1) for prices that are numbers whatever the width (link_price).  A maximum is one
-// instruction, v_max_f64, in both: bottleneck cost, one plan 58.4 -> 47.6 us, 9 GPUs, 512 plans 161 -> 115.
+// LDS per iteration and its pairs read one by one, 80.5 as it is (9 GPUs, 512 plans: 145.1, 158.0, 150.4),
+// of which 3.4 (1.6) for prices that are numbers whatever the width (link_price).  A maximum is one
+// instruction, v_max_f64, in both: bottleneck cost, one plan 58.0 -> 46.7 us, 9 GPUs, 512 plans 161 -> 117.
 template <bool MAXC, bool ONEWAVE, int MAXP, bool DIRECT, int MAXROW>
 __global__ __launch_bounds__(1024) void k_resident_reg(
     int E, int K, int P, int batch, int nt_arg, int plans_per_block, double eps, int iters,
@@ -619,8 +619,7 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
     {
         const double wm = wave_max(reach * ic);
         // (a capacity without a finite reciprocal stands for a total that is none)
-        const double ws = __builtin_amdgcn_ballot_w64(ic == __builtin_inf()) != 0ull
-                              ? __builtin_inf() : wave_sum_f64(fabs(d));
+        const double ws = wave_sum_f64(ic == __builtin_inf() ? ic : fabs(d));
         const int wf = wave_min_i32(lowest_bit(d));
         if ((threadIdx.x & (kWave - 1)) == 0) {
             sh.max[threadIdx.x >> 6] = wm;
@@ -637,14 +636,15 @@ __global__ __launch_bounds__(1024) void k_resident_reg(
                 total = total + sh.sum[w0 + w];
                 fine = min(fine, sh.fine[w0 + w]);
             }
-            sh.invrho[slot] = (m > 0.0) ? 1.0 / m : 0.0;
+            const double inv = (m > 0.0) ? 1.0 / m : 0.0;
+            sh.invrho[slot] = inv;
             // (One bit less than a double holds, for the rounding of the total.  A width or a
             // reciprocal of it that is infinite makes lengths that are no numbers: such plans stay with
             // the gather, whose prices are numbers all the same; here that would be one operation
             // more in the chain of an iteration.  Grids next to the denormals stay with it as well.)
             const bool on_grid = total == 0.0 || (total < __builtin_inf() && fine >= -900 &&
                                                   ilogb(total) + 1 - fine <= 52 &&
-                                                  m < __builtin_inf() && sh.invrho[slot] < __builtin_inf());
+                                                  m < __builtin_inf() && inv < __builtin_inf());
             if (ONEWAVE) sh.fine[w0] = on_grid ? 1 : 0;
             else if (!on_grid) sh.inexact = 1;
         }
