@@ -250,7 +250,8 @@ nimble_status_t nimble_plan_solve_warm(nimble_topo_t *topo, const double *d_traf
  *
  *   max_iters    >= 1, max_iters * log1p(eps) <= 700
  *   check_every  >= 1
- *   d_splits, d_lambda   device outputs as for nimble_plan_solve
+ *   d_splits, d_lambda   device outputs as for nimble_plan_solve (lambda is 0 / 0, no number, where a
+ *                load over a capacity overflows, so that all steps are zero)
  *   iters_done   host out: iterations made (0 for all-zero traffic: every pair then stays on
  *                its first candidate)
  *   lower_bound  host out: best LB seen (0 if no check was made)

@@ -11,9 +11,9 @@
 //   update   as in patch_kernel.hpp, but length and congestion of a link in registers of the lane that
 //            sums up its parts.
 // What bounds it: the exchange (60 % of an iteration of the 64-node fabric), then the LDS in scan and
-// scatter (5200 of 16400 cycles, half of them bank conflicts of atomics and of gathers) and vector issue
+// scatter (5200 of 16500 cycles, half of them bank conflicts of atomics and of gathers) and vector issue
 // (some 200 instructions of a wave outside the exchange, 400 with slots).  Against slots, us per
-// iteration: 64 nodes of 8, eight slots a commodity, 7.5 -> 6.8, 32 nodes 4.2 -> 3.8, 24 nodes 4.1 -> 3.7;
+// iteration: 64 nodes of 8, eight slots a commodity, 7.5 -> 6.9, 32 nodes 4.2 -> 3.8, 24 nodes 4.1 -> 3.7;
 // with four slots and fewer, or few commodities in a patch, slots are the faster form (16 nodes 2.7
 // against 2.25): the fold is one more trip through the LDS with a barrier behind it.
 #pragma once
@@ -355,6 +355,8 @@ __global__ __launch_bounds__(kPatchThreads) void k_blocks(PatchArgs a)
             }
             __syncthreads();
         }
+        // (a team that has given up goes through its remaining iterations, in which nobody waits any more:
+        // little beside what the one workgroup that solves the plan after it takes)
         if (dead) *s_flag = 1;
         __syncthreads();
         const double T = static_cast<double>(a.iters);

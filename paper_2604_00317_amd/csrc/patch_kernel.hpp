@@ -42,8 +42,8 @@
 // on 2 nodes, a gather over the reverse rows in one workgroup): 2 nodes of 8 GPUs 0.84 (2.64): one
 // patch, the chain scan, barrier, scatter, update; the LDS is busy for half of it; 7 nodes of 6 1.7 to
 // 2.0 (7.1) and 16 nodes 2.25 (7.3): the trip of a word from patch to patch, some 3000 cycles with
-// the reading of the words; 64 nodes 7.5 (18.5), 6.8 in blocks (patch_blocks.hpp): the words of up to
-// 31 users of every shared link, 131 KB per patch and iteration, then vector issue and LDS of the scan.
+// the reading of the words; 64 nodes 7.5 (18.5), 6.9 in blocks (patch_blocks.hpp): the words of up to
+// 31 users of every shared link, 127 KB per patch and iteration, then vector issue and LDS of the scan.
 #pragma once
 #include <hip/hip_runtime.h>
 

@@ -112,7 +112,7 @@ __device__ __forceinline__ double fast_max_f64(double a, double b)
 // not there.  It looks for the largest price with `>` from zero on, which passes over it: 0.  With prices
 // that are numbers, minima of costs in whatever order are the scan's.  (The constants in vector registers:
 // +inf in scalar ones, of which k_blocks has none left, cost 64 nodes 6 %, a comparison and a selection
-// 1.5 %, this 0.5 %; 7 nodes of 6, largest price, 0.6 to 1 %; elsewhere -1 to 1.4 %.)
+// 1.5 %, this 0.5 %; 7 nodes of 6, largest price, 0.6 to 1 %; elsewhere -1 to 1.5 %.)
 template <bool MAXC>
 __device__ __forceinline__ double link_price(double len, double ic)
 {
