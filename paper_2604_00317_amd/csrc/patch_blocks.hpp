@@ -11,7 +11,7 @@
 //   update   as in patch_kernel.hpp, but length and congestion of a link in registers of the lane that
 //            sums up its parts.
 // What bounds it: the exchange (60 % of an iteration of the 64-node fabric), then the LDS in scan and
-// scatter (5200 of 16500 cycles, half of them bank conflicts of atomics and of gathers) and vector issue
+// scatter (5200 of 16400 cycles, half of them bank conflicts of atomics and of gathers) and vector issue
 // (some 200 instructions of a wave outside the exchange, 400 with slots).  Against slots, us per
 // iteration: 64 nodes of 8, eight slots a commodity, 7.5 -> 6.9, 32 nodes 4.2 -> 3.8, 24 nodes 4.1 -> 3.7;
 // with four slots and fewer, or few commodities in a patch, slots are the faster form (16 nodes 2.7

@@ -840,11 +840,12 @@ __global__ __launch_bounds__(kPatchThreads) void k_patch(PatchArgs a)
             // Two slots a lane: every slot's candidates one by one.  That spares the second look at the
             // best slot's prices, one trip to the LDS of the five in the chain of an iteration (2 nodes
             // of 8 0.902 -> 0.835 us, with two NICs in reach 1.355 -> 1.230, 8 such nodes 2.27 -> 2.06).
-            // With one slot the prices are at hand anyway; it is the shorter code for the largest price
-            // (7 nodes of 6 2.01 -> 1.97) and for a variable step (16 nodes 5.54 -> 5.48), not for the sum
-            // (16 nodes 2.217 -> 2.229).  From three slots on the additions cost more than the trip (one
+            // The largest price gains as well (2 nodes of 8 482 -> 462 us for 500 iterations, 20 nodes 1836 ->
+            // 1664).  With one slot the prices are at hand anyway: a variable step is 1 % faster this way (16
+            // nodes 5.54 -> 5.48), the largest price neither way (eleven fabrics, -0.7 to 0.5 %), the sum 0.5 %
+            // slower (16 nodes 2.217 -> 2.229).  From three slots on the additions cost more than the trip (one
             // patch of 24 GPUs 1.454 -> 1.492 with four, of 30 2.44 -> 2.60 with six).
-            constexpr bool kEach = PRODUCT && (QL == 2 || (QL == 1 && (MAXC || ADAPT)));
+            constexpr bool kEach = PRODUCT && (QL == 2 || (QL == 1 && ADAPT));
             double best = 0.0;
             uint32_t wb[NW];             // the slot that holds the best candidate so far
             int sb = 0, pos = 0;
